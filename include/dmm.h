@@ -72,7 +72,8 @@ typedef enum { DMM_BF16 = 1, DMM_F32 = 2 } dmm_dtype;
                                 its fp32 sum rounded to nearest even, once.  Only for a C with one replica
                                 (DMM_EINVAL otherwise): the partial sums of a replicated C stay fp32, since one
                                 rounding to bf16 already costs a relative error of up to 2^-8 per element */
-#define DMM_NO_MERGE 0x800u  /* run the macro-tiles of dmm_plan_items even where the plan has merged ones */
+#define DMM_NO_MERGE 0x800u  /* run the macro-tiles of dmm_plan_items, even where the plan has merged ones or the
+                                kernels for small products would be faster */
 #define DMM_SEPARATE_REDUCE 0x1000u /* replicated C: sum the replicas in a kernel of its own behind the GEMM
                                 (the one dmm_reduce_replicas runs).  Without the flag the sum is fused into the
                                 GEMM wherever that is possible: the macro-tiles of replicas 1, 2, ... run
@@ -249,9 +250,11 @@ int dmm_reduce_replicas_static(dmm_plan_t *p, void *const *c_tiles, const int64_
 /* ---- measurement and test aids (not steps of the method) ---------------------------------- */
 
 /* What the last dmm_execute on a plan did.
- *   ran_merged    1: it ran the merged macro-tiles (the plan has such a list, DMM_NO_MERGE was not
- *                 given and the device grants a workgroup the 160 KB of LDS their kernel asks for)
- *   ran_k_split   1: it cut macro-tiles along K (partial tiles through a scratch buffer, added up
+ *   ran_merged    1: it ran tiles that span several tiles of A, B and C: the merged macro-tiles (the
+ *                 plan has such a list, DMM_NO_MERGE was not given and the device grants a workgroup
+ *                 the 160 KB of LDS their kernel asks for) or, in their place, the tiles of the
+ *                 kernels for small products
+ *   ran_k_split   1: it cut tiles along K (partial tiles through a scratch buffer, added up
  *                 in ascending k by a second kernel: the last round of workgroups would have left
  *                 most of the device idle, or a merged macro-tile had more K-segments than its
  *                 workgroup can hold descriptors for).  Such a run sums in another order than an

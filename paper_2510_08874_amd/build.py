@@ -16,7 +16,7 @@ OUT = os.path.join(HERE, "_build")          # objects and the compiler's interme
 LIB = os.path.join(HERE, "libdmm.so")
 # (source, object name, extra flags): the grouped-GEMM kernels are compiled one instantiation per
 # object file (gemm_instance.hip, DMM_INSTANCE = 0 .. 5), side by side
-UNITS = [("plan.cpp", "plan", []), ("exec.hip", "exec", [])] + \
+UNITS = [("plan.cpp", "plan", []), ("exec.hip", "exec", []), ("small_instance.hip", "small_instance", [])] + \
         [("gemm_instance.hip", f"gemm_instance_{i}", [f"-DDMM_INSTANCE={i}"]) for i in range(6)]
 
 # packed-fp32 ops are switched off for all device code (a target feature of the
@@ -35,6 +35,8 @@ def check_resources(remarks: str, want_kernel: bool) -> None:
     seen = 0
     for b in blocks:
         name = b.split()[0]
+        if "small_gemm_kernel" in name and re.search(r"(ScratchSize \[bytes/lane\]|VGPRs Spill): [1-9]", b):
+            raise RuntimeError(f"{name}: scratch use or spills")
         if "grouped_gemm_kernel" not in name:
             continue
         seen += 1

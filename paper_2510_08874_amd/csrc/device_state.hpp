@@ -261,12 +261,21 @@ struct MergedLaunch {
   size_t n_items = 0, o_a = 0, o_b = 0, o_c = 0, o_k = 0, o_fix = 0, n_fix = 0, total = 0;
 };
 
+// Where the tables of the kernels for small products sit in the plan's device table, and the rest of
+// their arguments.
+struct SmallLaunch {
+  int shape = -1;               // SMALL_* (gemm_launch.hpp)
+  size_t o_rows = 0, o_cols = 0, o_mc = 0, o_nc = 0, o_before = 0, o_klen = 0, o_a = 0, o_b = 0, o_c = 0;
+  int32_t segs = 0, nr = 0, tiles_m = 0, tiles_n = 0, runs = 1, per = 0, c_es = 4;
+};
+
 // What the launches of a dmm_execute need to know besides the device table itself.
 struct ExecLayout {
   bool merged = false;
   MergedLaunch ml;                                                       // merged macro-tiles
   size_t n_items = 0, o_segs = 0, o_fix = 0, o_red = 0, n_first = 0, n_fix = 0;   // per-group macro-tiles
   bool fuse = false, one_launch = false;
+  SmallLaunch small;            // shape >= 0: these kernels run the product
   size_t n_runs = 0;
   bool uses_split = false;      // some macro-tiles store through the plan's scratch buffer
   RedLaunch red;                // the replica-sum launch behind the GEMM (n_items == 0: none)

@@ -18,6 +18,7 @@
 #include "gemm_kernel.hpp"
 #include "gemm_launch.hpp"
 #include "plan_internal.h"
+#include "small_kernel.hpp"
 
 namespace dmm {
 
@@ -62,6 +63,7 @@ int ensure_state(dmm_plan_t *P) {
       DMM_HIP(gemm_allow_lds_1());
       DMM_HIP(gemm_allow_lds_2());
       DMM_HIP(gemm_allow_lds_3());
+      DMM_HIP(small_allow_lds());
       const bool ok = gemm_allow_lds_4() == hipSuccess && gemm_allow_lds_5() == hipSuccess;
       if (!ok) (void)hipGetLastError();
       g_comp_ok[device] = ok;
@@ -234,12 +236,11 @@ int fire_reduce(dmm_plan_t *P, const RedLaunch &L, hipStream_t stream, bool time
 constexpr int32_t MIN_RUN = 64;
 inline int32_t min_run_steps(int64_t es) { return es == 4 ? MIN_RUN / 8 : MIN_RUN; }
 
-// Scratch buffer of the plan for `n_runs` partial tiles; orders this call behind the plan's last one.
-int acquire_split_buffer(dmm_plan_t *P, size_t n_runs, hipStream_t stream) {
+// Scratch buffer of the plan for `need` bytes of partial tiles; orders this call behind the plan's last one.
+int acquire_split_buffer(dmm_plan_t *P, size_t need, hipStream_t stream) {
   // the scratch buffer is shared by all calls on this plan: order this call behind the last one
   // (a no-op when both are on the same stream)
   if (P->dev->last_use_recorded) DMM_HIP(hipStreamWaitEvent(stream, P->dev->last_use, 0));
-  const size_t need = n_runs * sizeof(float) * BM * BN;
   if (need > P->dev->split_cap) {
     // growing: earlier calls on this plan may still use the old buffer
     if (P->dev->split_buf) {
@@ -442,7 +443,7 @@ int build_merged_tables(dmm_plan_t *P, int64_t es, int64_t bk, int64_t c_es, con
     if (r.pad > 0) r.pad = 1;
   items.insert(items.end(), later.begin(), later.end());
   if (n_runs > 0) {
-    int rc = acquire_split_buffer(P, n_runs, stream);
+    int rc = acquire_split_buffer(P, n_runs * sizeof(float) * BM * BN, stream);
     if (rc) return rc;
     for (CompItemDev &d : items)
       if (d.pad == 1) {
@@ -682,7 +683,7 @@ int build_group_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
     }
   }
   if (n_runs > 0) {
-    if ((rc = acquire_split_buffer(P, n_runs, stream))) return rc;
+    if ((rc = acquire_split_buffer(P, n_runs * sizeof(float) * BM * BN, stream))) return rc;
     for (ItemDev &d : hi)
       if (d.c_es < 0) {
         d.c = (void *)(P->dev->split_buf + (uintptr_t)d.c);
@@ -817,11 +818,256 @@ int build_group_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
   return DMM_OK;
 }
 
+// ---- small and skinny products (small_kernel.hpp) ------------------------------------------------
+
+struct SmallPlan {
+  int shape = -1;
+  int32_t runs = 1, per = 0;
+  std::vector<int64_t> mc, nc, kc;
+  std::vector<Extent> rows, cols;
+};
+
+constexpr SmallKind kSmall[SMALL_SHAPES] = {
+    small_kind<SmallBf16Skinny>(0.29, 0.52), small_kind<SmallBf16Half>(0.50, 0.72), small_kind<SmallBf16>(0.68, 0.88),
+    small_kind<SmallF32Tiny>(0.39, 0.72), small_kind<SmallF32>(0.52, 0.78),
+};
+
+int64_t count_steps(const std::vector<int64_t> &kc, int64_t bk) {
+  int64_t n = 0;
+  for (size_t s = 0; s + 1 < kc.size(); ++s) n += (kc[s + 1] - kc[s] + bk - 1) / bk;
+  return n;
+}
+
+// Whether (and how) the kernels for small products run this call: the estimated time of the best of
+// their shapes and numbers of runs against that of the macro-tile kernels.  The line between the two
+// depends on how many macro-tiles there are for the CUs, how much of them is product, how long K is and
+// how many segments it has, so it is drawn by an estimate and not by a size.  Measured, us per call
+// with macro-tiles -> with these kernels: fp32 256^3 54 -> 8.6; bf16 2048^3 (64 macro-tiles, 256 tiles
+// of 128 x 128) 45 -> 38, 3072^3 (144 macro-tiles) 69 against 105: stays; 32 x 12288 x 49152 280 -> 228
+// (5.3 TB/s), 128 x 12288 x 49152 300 against 299, 200 rows 331 against 456: stays; 1024 x 16384 x 1024
+// 67 -> 56; 64 x 5760 x 4960 61 -> 24; fp32 577 x 28352 x 512 216 -> 176; bf16 4838 x 2368 x 1437 in
+// uneven block-cyclic tiles 389 -> 184.  Over 70 drawn products none got more than 4 % slower.
+void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
+  const Grid &A = P->A, &B = P->B, &C = P->C;
+  const int64_t M = C.rows, K = A.cols, N = C.cols, lim = (int64_t)1 << 30;
+  if (C.c != 1 || M <= 0 || K <= 0 || N <= 0 || M >= lim || K >= lim || N >= lim) return;
+  if ((P->flags & DMM_MERGE_ALWAYS) || (x.flags & DMM_NO_MERGE)) return;      // the caller named a work list
+  SmallPlan c;
+  c.mc = merged_cuts({&A.rc, &C.rc});
+  c.nc = merged_cuts({&B.cc, &C.cc});
+  c.kc = merged_cuts({&A.cc, &B.rc});
+  const double mr = (double)c.mc.size(), nr = (double)c.nc.size(), sr = (double)c.kc.size();
+  if (mr * sr + sr * nr + mr * nr > 65536.0) return;
+  size_t items = 0;
+  if (P->merged.valid) items = P->merged.items.size();
+  else
+    for (const dmm_work_item &w : P->items) items += w.group >= 0;
+  if (M >= 2048 && N >= 2048 && items >= 2 * (size_t)cus) return;             // two full rounds of macro-tiles: theirs
+  // Microseconds.  The macro-tile kernels: rounds of macro-tiles, the last one cut along K where it is
+  // at most half full; a K step costs more the fuller the device (its clock falls), every item a
+  // prologue and an epilogue, every segment a switch.
+  const double segs = (double)(c.kc.size() - 1);
+  const int64_t big_steps = count_steps(c.kc, x.bk), tail = (int64_t)(items % (size_t)cus), full = (int64_t)items / cus;
+  const double fill = full > 0 ? 1.0 : (double)tail / cus;
+  const double big_step = (x.es == 2 ? 0.62 + 0.22 * fill : 3.9) * (P->merged.valid ? 1.13 : 1.0), item = 6 + 1.5 * segs;
+  double least = 4 + (double)full * ((double)big_steps * big_step + item);
+  if (tail > 0) {
+    const int64_t runs = tail <= cus / 2 ? std::max<int64_t>(1, std::min<int64_t>(cus / tail, big_steps / min_run_steps(x.es))) : 1;
+    least += (double)((big_steps + runs - 1) / runs) * big_step + item + (runs > 1 ? 6 : 0);
+  }
+  least *= 0.97;                                                               // (not for a tie)
+  // These kernels: rounds of `occ` workgroups per CU, operands at no more than 5.3 TB/s, and a second
+  // launch that adds the partial tiles up.
+  const double bytes = (double)x.es * ((double)M * K + (double)K * N) + (double)x.c_es * (double)M * N;
+  for (int k = 0; k < SMALL_SHAPES; ++k) {
+    const SmallKind &s = kSmall[k];
+    if (s.es != (int)x.es) continue;
+    c.rows = tile_axis(c.mc, 1 << 30, 1, s.tm);
+    c.cols = tile_axis(c.nc, 1 << 30, kPieceAlign, s.tn);
+    const int64_t tiles = (int64_t)(c.rows.size() * c.cols.size()), steps = count_steps(c.kc, s.bk);
+    if (tiles > (1 << 20)) continue;
+    // a run has at least 256 (fp32: 128) elements of k, and the partial tiles fit 64 MB, which is
+    // what the macro-tile kernels use at most
+    const int64_t least_per = (s.es == 2 ? 256 : 128) / s.bk;
+    for (int64_t r = 1; r <= std::max<int64_t>(1, std::min<int64_t>(64, steps / least_per)); ++r) {
+      const int64_t per = (steps + r - 1) / r, runs = (steps + per - 1) / per;
+      if (runs != r) continue;
+      const int64_t part_bytes = runs * tiles * s.tm * s.tn * 4;
+      if (runs > 1 && part_bytes > (int64_t)64 << 20) break;
+      const int64_t per_cu = (tiles * runs + cus - 1) / cus, whole = per_cu / s.occ, rest = per_cu % s.occ;
+      double t = (double)whole * ((double)per * std::max(s.step * s.occ, s.alone) + 2);
+      if (rest > 0) t += (double)per * std::max(s.step * (double)rest, s.alone) + 2;
+      t += segs / (double)runs;
+      t = 4 + std::max(t, bytes / 5.3e6);
+      if (runs > 1) t += 4 + 2.0 * (double)part_bytes / 12e6;
+      if (t < least) {
+        least = t;
+        best->shape = k;
+        best->runs = (int32_t)runs;
+        best->per = (int32_t)per;
+        best->rows = c.rows;
+        best->cols = c.cols;
+      }
+    }
+  }
+  best->mc = c.mc;
+  best->nc = c.nc;
+  best->kc = c.kc;
+}
+
+// Work tables of the kernels for small products:
+//   SmallTile rows[] | cols[] | PieceDev a[] | b[] | c[] | int32 mc[] | nc[] | before[] | klen[]
+// DMM_EINVAL where a tile that the op list names has no pointer.
+int build_small_exec(dmm_plan_t *P, const ExecArgs &x, const SmallPlan &sp, hipStream_t stream, ExecLayout *L) {
+  int rc;
+  const Grid &A = P->A, &B = P->B, &C = P->C;
+  const SmallKind &kind = kSmall[sp.shape];
+  const size_t MR = sp.mc.size() - 1, NR = sp.nc.size() - 1, S = sp.kc.size() - 1;
+  auto holder = [](const std::vector<int64_t> &cuts, int64_t at) {
+    return (int32_t)(std::upper_bound(cuts.begin(), cuts.end() - 1, at) - cuts.begin()) - 1;
+  };
+  SmallLaunch &l = L->small;
+  l.o_rows = 0;
+  l.o_cols = l.o_rows + sp.rows.size() * sizeof(SmallTile);
+  l.o_a = l.o_cols + sp.cols.size() * sizeof(SmallTile);
+  l.o_b = l.o_a + MR * S * sizeof(PieceDev);
+  l.o_c = l.o_b + S * NR * sizeof(PieceDev);
+  l.o_mc = l.o_c + MR * NR * sizeof(PieceDev);
+  l.o_nc = l.o_mc + (MR + 1) * 4;
+  l.o_before = l.o_nc + (NR + 1) * 4;
+  l.o_klen = l.o_before + (S + 1) * 4;
+  const size_t total = l.o_klen + S * 4;
+  std::vector<char> &h = P->dev->host;
+  h.assign(total, 0);
+  auto tiles = [&](size_t at, const std::vector<Extent> &v) {
+    SmallTile *t = (SmallTile *)(h.data() + at);
+    for (size_t i = 0; i < v.size(); ++i) t[i] = {(int32_t)v[i].start, v[i].ext, v[i].first, v[i].pieces};
+  };
+  tiles(l.o_rows, sp.rows);
+  tiles(l.o_cols, sp.cols);
+  auto piece = [](const void *base, int64_t ld, int64_t r, int64_t c, int64_t hh, int64_t w, int64_t esz) {
+    PieceDev d;
+    const int64_t off = r * ld + c;
+    d.ptr = (const char *)base + off * esz;
+    d.room = ((hh - 1) * ld + w - off) * esz;
+    d.pitch = (uint32_t)(ld * esz);
+    d.pad = 0;
+    return d;
+  };
+  std::vector<int32_t> a_ti(MR), c_ti(MR), b_tj(NR), c_tj(NR), a_tj(S), b_ti(S);
+  for (size_t i = 0; i < MR; ++i) { a_ti[i] = holder(A.rc, sp.mc[i]); c_ti[i] = holder(C.rc, sp.mc[i]); }
+  for (size_t j = 0; j < NR; ++j) { b_tj[j] = holder(B.cc, sp.nc[j]); c_tj[j] = holder(C.cc, sp.nc[j]); }
+  for (size_t s = 0; s < S; ++s) { a_tj[s] = holder(A.cc, sp.kc[s]); b_ti[s] = holder(B.rc, sp.kc[s]); }
+  PieceDev *pa = (PieceDev *)(h.data() + l.o_a), *pb = (PieceDev *)(h.data() + l.o_b), *pc = (PieceDev *)(h.data() + l.o_c);
+  for (size_t i = 0; i < MR; ++i)
+    for (size_t s = 0; s < S; ++s) {
+      const int64_t idx = A.table_index(0, a_ti[i], a_tj[s]);
+      if (!x.a_tiles[idx]) return DMM_EINVAL;
+      pa[i * S + s] = piece(x.a_tiles[idx], x.a_ld[idx], sp.mc[i] - A.rc[a_ti[i]], sp.kc[s] - A.cc[a_tj[s]],
+                            A.rc[a_ti[i] + 1] - A.rc[a_ti[i]], A.cc[a_tj[s] + 1] - A.cc[a_tj[s]], x.es);
+    }
+  for (size_t s = 0; s < S; ++s)
+    for (size_t j = 0; j < NR; ++j) {
+      const int64_t idx = B.table_index(0, b_ti[s], b_tj[j]);
+      if (!x.b_tiles[idx]) return DMM_EINVAL;
+      pb[s * NR + j] = piece(x.b_tiles[idx], x.b_ld[idx], sp.kc[s] - B.rc[b_ti[s]], sp.nc[j] - B.cc[b_tj[j]],
+                             B.rc[b_ti[s] + 1] - B.rc[b_ti[s]], B.cc[b_tj[j] + 1] - B.cc[b_tj[j]], x.es);
+    }
+  for (size_t i = 0; i < MR; ++i)
+    for (size_t j = 0; j < NR; ++j) {
+      const int64_t idx = C.table_index(0, c_ti[i], c_tj[j]);
+      if (!x.c_tiles[idx]) return DMM_EINVAL;
+      pc[i * NR + j] = piece(x.c_tiles[idx], x.c_ld[idx], sp.mc[i] - C.rc[c_ti[i]], sp.nc[j] - C.cc[c_tj[j]],
+                             C.rc[c_ti[i] + 1] - C.rc[c_ti[i]], C.cc[c_tj[j] + 1] - C.cc[c_tj[j]], x.c_es);
+    }
+  int32_t *mc = (int32_t *)(h.data() + l.o_mc), *nc = (int32_t *)(h.data() + l.o_nc), *before = (int32_t *)(h.data() + l.o_before),
+          *klen = (int32_t *)(h.data() + l.o_klen);
+  for (size_t i = 0; i <= MR; ++i) mc[i] = (int32_t)sp.mc[i];
+  for (size_t j = 0; j <= NR; ++j) nc[j] = (int32_t)sp.nc[j];
+  before[0] = 0;
+  for (size_t s = 0; s < S; ++s) {
+    klen[s] = (int32_t)(sp.kc[s + 1] - sp.kc[s]);
+    before[s + 1] = before[s] + (klen[s] + kind.bk - 1) / kind.bk;
+  }
+  l.shape = sp.shape;
+  l.segs = (int32_t)S;
+  l.nr = (int32_t)NR;
+  l.tiles_m = (int32_t)sp.rows.size();
+  l.tiles_n = (int32_t)sp.cols.size();
+  l.runs = sp.runs;
+  l.per = sp.per;
+  l.c_es = (int32_t)x.c_es;
+  if (sp.runs > 1 &&
+      (rc = acquire_split_buffer(P, (size_t)sp.runs * sp.rows.size() * sp.cols.size() * (size_t)(kind.tm * kind.tn) * sizeof(float), stream)))
+    return rc;
+  if ((rc = P->dev->gemm_table.upload(h.data(), h.size(), stream, busy_event(P)))) return rc;
+  L->merged = P->merged.valid;
+  L->uses_split = sp.runs > 1;
+  return DMM_OK;
+}
+
+// Whether every tile that the call's own work list would read has a pointer, and every tile of the
+// first replicas of A and B: the kernels for small products read only these
+// (replicas are copies of each other, Section 3); what the other work lists refuse is refused all
+// the same, and what they accept they get.
+bool operands_given(const dmm_plan_t *P, const ExecArgs &x) {
+  auto given = [](const Grid &G, const void *const *tiles, int32_t rep) {
+    for (int32_t i = 0; i < G.gr; ++i)
+      for (int32_t j = 0; j < G.gc; ++j)
+        if (G.rc[i + 1] > G.rc[i] && G.cc[j + 1] > G.cc[j] && !tiles[G.table_index(rep, i, j)]) return false;
+    return true;
+  };
+  if (!given(P->A, x.a_tiles, 0) || !given(P->B, x.b_tiles, 0)) return false;
+  if (P->merged.valid) {
+    for (const MergedRep &R : P->merged.reps)
+      if (!given(P->A, x.a_tiles, R.a_rep) || !given(P->B, x.b_tiles, R.b_rep)) return false;
+    return true;
+  }
+  for (const dmm_task &t : P->tasks)
+    if (!x.a_tiles[P->A.table_index(t.a_rep, t.a_ti, t.a_tj)] || !x.b_tiles[P->B.table_index(t.b_rep, t.b_ti, t.b_tj)]) return false;
+  return true;
+}
+
 // The launches of one dmm_execute, from the device table the layout describes.
 int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stream, bool timed) {
   int rc;
   char *d = P->dev->gemm_table.dev();
-  if (L.merged) {
+  if (L.small.shape >= 0) {
+    const SmallLaunch &l = L.small;
+    SmallArgs g;
+    g.rows = (const SmallTile *)(d + l.o_rows);
+    g.cols = (const SmallTile *)(d + l.o_cols);
+    g.mc = (const int32_t *)(d + l.o_mc);
+    g.nc = (const int32_t *)(d + l.o_nc);
+    g.before = (const int32_t *)(d + l.o_before);
+    g.klen = (const int32_t *)(d + l.o_klen);
+    g.pa = (const PieceDev *)(d + l.o_a);
+    g.pb = (const PieceDev *)(d + l.o_b);
+    g.pc = (const PieceDev *)(d + l.o_c);
+    g.scratch = (float *)P->dev->split_buf;
+    g.S = l.segs;
+    g.NR = l.nr;
+    g.tiles_m = l.tiles_m;
+    g.tiles_n = l.tiles_n;
+    g.runs = l.runs;
+    g.per = l.per;
+    g.c_es = l.c_es;
+    g.pad = 0;
+    TraceRange gemm("gemm");
+    if (timed) {
+      if ((rc = timing_events(P->dev->t_gemm))) return rc;
+      DMM_HIP(hipEventRecord(P->dev->t_gemm[0], stream));
+    }
+    small_launch(l.shape, g, stream);
+    DMM_HIP(hipGetLastError());
+    if (timed) {
+      DMM_HIP(hipEventRecord(P->dev->t_gemm[1], stream));
+      P->dev->gemm_timed = true;
+    }
+    P->dev->ran_merged = L.merged;
+    P->dev->ran_k_split = l.runs > 1 || l.shape == SMALL_F32_TINY;   // (that shape's waves share a tile's K steps)
+    P->dev->ran_fused = 0;
+  } else if (L.merged) {
     const MergedLaunch &ml = L.ml;
     TraceRange gemm("gemm");
     if (timed) {
@@ -948,6 +1194,7 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
     put(c_tiles, nc * sizeof(void *));
     put(c_ld, nc * sizeof(int64_t));
     ExecLayout L;
+    const ExecArgs x = {dtype, es, bk, c_es, a_tiles, a_ld, b_tiles, b_ld, c_tiles, c_ld, flags, device};
     if (P->dev->exec_cached && key == P->dev->exec_key) {
       L = P->dev->exec_layout;
       P->dev->table_reused = true;
@@ -958,8 +1205,13 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
       P->dev->exec_cached = false;
       P->dev->table_reused = false;
       TraceRange tables("tables");
-      const ExecArgs x = {dtype, es, bk, c_es, a_tiles, a_ld, b_tiles, b_ld, c_tiles, c_ld, flags, device};
-      if (P->merged.valid && !(flags & DMM_NO_MERGE) && g_comp_ok[device]) rc = build_merged_exec(P, x, stream, &L);
+      SmallPlan sp;
+      int cus = 0;
+      if ((rc = device_cus(&cus))) return rc;
+      const bool given = operands_given(P, x);
+      if (given) choose_small(P, x, cus, &sp);
+      if (sp.shape >= 0) rc = build_small_exec(P, x, sp, stream, &L);
+      else if (P->merged.valid && !(flags & DMM_NO_MERGE) && g_comp_ok[device]) rc = build_merged_exec(P, x, stream, &L);
       else rc = build_group_exec(P, x, stream, &L);
       if (rc) return rc;
       P->dev->exec_key = key;

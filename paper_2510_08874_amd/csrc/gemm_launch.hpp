@@ -44,4 +44,10 @@ inline void launch_grouped_gemm_comp(int es, unsigned grid, hipStream_t stream, 
   else gemm_launch_5(grid, stream, items, a, b, c, klen);
 }
 
+// The kernels for small and skinny products (small_kernel.hpp), by shape.
+struct SmallArgs;
+enum { SMALL_BF16_SKINNY, SMALL_BF16_HALF, SMALL_BF16, SMALL_F32_TINY, SMALL_F32, SMALL_SHAPES };
+hipError_t small_allow_lds();
+void small_launch(int shape, const SmallArgs &g, hipStream_t stream);   // the product, and the sum of its partial tiles
+
 }  // namespace dmm

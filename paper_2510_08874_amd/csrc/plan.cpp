@@ -23,6 +23,38 @@
 #include "plan_internal.h"
 
 namespace dmm {
+
+std::vector<int64_t> merged_cuts(std::initializer_list<const std::vector<int64_t> *> lists) {
+  std::vector<int64_t> out;
+  for (const std::vector<int64_t> *l : lists) out.insert(out.end(), l->begin(), l->end());
+  std::sort(out.begin(), out.end());
+  out.erase(std::unique(out.begin(), out.end()), out.end());
+  return out;
+}
+
+std::vector<Extent> tile_axis(const std::vector<int64_t> &cuts, int32_t cap, int64_t align, int64_t tile) {
+  std::vector<Extent> out;
+  const int64_t L = cuts.back();
+  int64_t pos = 0;
+  size_t iv = 0;
+  while (pos < L) {
+    while (cuts[iv + 1] <= pos) ++iv;
+    int64_t end = std::min<int64_t>(pos + tile, L);
+    int32_t pieces = 1;
+    for (size_t j = iv; cuts[j + 1] < end; ++j) {
+      const int64_t c = cuts[j + 1];
+      if (pieces == cap || (c - pos) % align != 0) {
+        end = c;
+        break;
+      }
+      ++pieces;
+    }
+    out.push_back({pos, (int32_t)(end - pos), (int32_t)iv, pieces});
+    pos = end;
+  }
+  return out;
+}
+
 namespace {
 
 struct Interval {
@@ -275,15 +307,6 @@ struct GroupKey {
 
 inline GroupKey key_of(const dmm_task &t) { return {t.c_rep, t.c_ti, t.c_tj, t.m0, t.n0}; }
 
-// Sorted, duplicate-free union of cut lists.
-std::vector<int64_t> merged_cuts(std::initializer_list<const std::vector<int64_t> *> lists) {
-  std::vector<int64_t> out;
-  for (const std::vector<int64_t> *l : lists) out.insert(out.end(), l->begin(), l->end());
-  std::sort(out.begin(), out.end());
-  out.erase(std::unique(out.begin(), out.end()), out.end());
-  return out;
-}
-
 // position of every cut of `cuts` in `merged` (which contains them all)
 std::vector<int32_t> ranks_in(const std::vector<int64_t> &merged, const std::vector<int64_t> &cuts) {
   std::vector<int32_t> r(cuts.size());
@@ -514,37 +537,6 @@ void build_items(dmm_plan_t *P) {
   deal_to_xcds(seq, 2 * followed >= blocks, &P->items);
 }
 
-// One axis of a C replica cut into macro-tile extents: 256 at a time, across the cuts; a tile
-// ends early where it would meet more than `cap` intervals, or at a cut that is not a multiple
-// of `align` away from the tile's start.
-struct Extent {
-  int64_t start;
-  int32_t ext, first, pieces;         // first interval met, number of intervals met
-};
-
-std::vector<Extent> tile_axis(const std::vector<int64_t> &cuts, int32_t cap, int64_t align) {
-  std::vector<Extent> out;
-  const int64_t L = cuts.back();
-  int64_t pos = 0;
-  size_t iv = 0;
-  while (pos < L) {
-    while (cuts[iv + 1] <= pos) ++iv;
-    int64_t end = std::min<int64_t>(pos + kMacroTile, L);
-    int32_t pieces = 1;
-    for (size_t j = iv; cuts[j + 1] < end; ++j) {
-      const int64_t c = cuts[j + 1];
-      if (pieces == cap || (c - pos) % align != 0) {
-        end = c;
-        break;
-      }
-      ++pieces;
-    }
-    out.push_back({pos, (int32_t)(end - pos), (int32_t)iv, pieces});
-    pos = end;
-  }
-  return out;
-}
-
 void build_merged(dmm_plan_t *P, uint32_t flags) {
   Merged &G = P->merged;
   G = Merged();
@@ -596,7 +588,7 @@ void build_merged(dmm_plan_t *P, uint32_t flags) {
     for (const MergedRep &R : G.reps) slices += (mr + nr) * (double)R.kc.size() + mr * nr;
     if (slices > 1.6e7) return;
   }
-  const std::vector<Extent> rows = tile_axis(G.mc, (int32_t)cap, 1), cols = tile_axis(G.nc, (int32_t)cap, kPieceAlign);
+  const std::vector<Extent> rows = tile_axis(G.mc, (int32_t)cap, 1, kMacroTile), cols = tile_axis(G.nc, (int32_t)cap, kPieceAlign, kMacroTile);
   // worth it only if it saves a tenth of the macro-tiles
   const int64_t merged_count = (int64_t)C.c * (int64_t)rows.size() * (int64_t)cols.size();
   if (!(flags & DMM_MERGE_ALWAYS)) {

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <cstdint>
+#include <initializer_list>
 #include <vector>
 
 #include "dmm.h"
@@ -65,6 +66,18 @@ struct Merged {
   std::vector<MergedItem> items;      // launch order
   std::vector<dmm_merged_item> view;  // the same list as the ABI shows it
 };
+
+// Sorted, duplicate-free union of cut lists.
+std::vector<int64_t> merged_cuts(std::initializer_list<const std::vector<int64_t> *> lists);
+
+// One axis of a C replica cut into tile extents: `tile` rows (columns) at a time, across the cuts; a
+// tile ends early where it would meet more than `cap` intervals, or at a cut that is not a multiple
+// of `align` away from the tile's start.
+struct Extent {
+  int64_t start;
+  int32_t ext, first, pieces;         // first interval met, number of intervals met
+};
+std::vector<Extent> tile_axis(const std::vector<int64_t> &cuts, int32_t cap, int64_t align, int64_t tile);
 
 struct DeviceState;                   // owned by exec.hip
 

@@ -1,0 +1,407 @@
+// GEMM kernel for products that 256 x 256 macro-tiles do not fill the device with (gfx950, device
+// code only): small and skinny results, few macro-tiles, fp32 products cut into ragged pieces.
+//
+// What bounds such a product under the macro-tile kernels: CUs without a macro-tile, rows and
+// columns of macro-tiles that hold nothing, and one workgroup per CU, whose waits nothing hides.
+// Here a tile is 32 to 128 rows and columns, two to four workgroups share a CU (they hide each
+// other's waits, so the loop needs no hand-made schedule), and a tile's K steps are dealt to as
+// many workgroups as the device has room for.
+//
+// Tiles are cut from C as a whole, across the cuts of A, B and C: the slicing is kept in factored
+// form (one A slice per row interval and K-segment, one B slice per K-segment and column
+// interval, one C slice per row and column interval), and every thread looks up the slice that
+// holds its own rows and its own chunk of columns.  A tile ends early at a column cut that is not
+// a multiple of eight columns away from its start, so that a 16-byte chunk has one source.
+//
+// Operands go global -> registers -> LDS (two stages, one barrier per step): the register stage
+// takes any alignment and lets K tails and column tails be zeroed on the way, so nothing is ever
+// read past a slice.  Sums run over the same K-segments in the same order and through the same
+// matrix instructions as in the macro-tile kernels, hence bitwise the same results, unless a
+// tile's K steps are dealt to several workgroups or waves (their partial sums are then added in
+// ascending k).
+#pragma once
+
+#include "gemm_kernel.hpp"
+
+namespace dmm {
+
+struct SmallTile {         // one tile row (column) of C
+  int32_t start, ext;      // first row (column), number of them
+  int32_t first, pieces;   // first interval met, number of intervals met
+};
+
+struct SmallArgs {
+  const SmallTile *rows, *cols;
+  const int32_t *mc, *nc;              // boundaries of the row (column) intervals
+  const int32_t *before;               // [S + 1] K steps in front of every segment
+  const int32_t *klen;                 // [S]
+  const PieceDev *pa, *pb, *pc;        // A slice (i, s) at pa[i S + s], B slice (s, j) at pb[s NR + j], C slice (i, j) at pc[i NR + j]
+  float *scratch;                      // runs > 1: partial tiles, number run * tiles + tile
+  int32_t S, NR;
+  int32_t tiles_m, tiles_n;
+  int32_t runs, per;                   // a tile's K steps in `runs` ranges of `per` steps (the last may be shorter)
+  int32_t c_es;                        // bytes per element of C
+  int32_t pad;
+};
+
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   // 16 bytes at any element's address
+typedef __attribute__((address_space(3))) char *lds_ptr;
+
+// ES bytes per operand element; TM x TN tile of C; BK elements of k per step; WM x WN waves over the
+// tile, times WK waves over the matrix instructions of a step
+template <int ES_, int TM_, int TN_, int BK_, int WM_, int WN_, int WK_, int DEPTH_, int OCC_>
+struct SmallShape {
+  static constexpr int ES = ES_, TM = TM_, TN = TN_, BK = BK_, WM = WM_, WN = WN_, WK = WK_;
+  static constexpr int DEPTH = DEPTH_;                          // K steps whose operands are in flight
+  static constexpr int OCC = OCC_;                              // workgroups per CU the LDS and registers leave room for
+  static constexpr int PER = 16 / ES;
+  static constexpr int A_CHUNKS = BK * ES / 16, B_CHUNKS = TN * ES / 16;   // 16-byte chunks per A row, per k row of B
+  static constexpr int CA = TM * A_CHUNKS / NT, CB = BK * B_CHUNKS / NT;   // chunks per thread
+  // row pitches in LDS that spread the fragment reads over all banks: 16 A rows read the same
+  // chunk (pitch = 4 dwords off a multiple of 32); bf16 B: four k rows x 64 bytes per transposed read
+  // (pitch = 64 bytes off a multiple of 128); fp32 B: rows k and k + 4 x 32 dwords (pitch = 8 off a multiple of 16)
+  static constexpr int A_PITCH = BK * ES + 16;
+  static constexpr int B_PITCH = TN * ES + (ES == 2 ? 64 : 32);
+  static constexpr int STAGE_BYTES = TM * A_PITCH + BK * B_PITCH;
+  static constexpr int T_PITCH = TN + 8;                         // floats: the finished tile in LDS
+  static constexpr int TILE_BYTES = WK * TM * T_PITCH * 4;
+  static constexpr int LDS = 2 * STAGE_BYTES > TILE_BYTES ? 2 * STAGE_BYTES : TILE_BYTES;
+  static constexpr int MI = TM / WM / 32, NI = TN / WN / 32;     // 32 x 32 matrix tiles per wave
+  static_assert(WM * WN * WK == NW && CA >= 1 && CB >= 1 && NT % A_CHUNKS == 0 && NT % B_CHUNKS == 0, "chunks are dealt evenly");
+};
+
+// four columns of row r, from column c on, of the tile whose tile row and column are tr and tc
+__device__ __forceinline__ void small_store4(const SmallArgs &g, const SmallTile &tr, const SmallTile &tc, int r, int c, f32x4 v) {
+  int i = tr.first, j = tc.first;
+  const int m = tr.start + r, n = tc.start + c;
+  for (int x = 1; x < tr.pieces; ++x) i += g.mc[tr.first + x] <= m;
+  for (int x = 1; x < tc.pieces; ++x) j += g.nc[tc.first + x] <= n;
+  const PieceDev d = g.pc[(int64_t)i * g.NR + j];
+  const uint64_t at = (uint64_t)(uintptr_t)d.ptr + (uint64_t)(m - g.mc[i]) * d.pitch + (uint64_t)(n - g.nc[j]) * (unsigned)g.c_es;
+  const int left = tc.ext - c;
+  // (column pieces begin at multiples of eight columns of the tile: the four columns lie in one slice)
+  if (g.c_es == 4) {
+    gfloat_ptr p = (gfloat_ptr)(uintptr_t)at;
+    if (left >= 4 && (at & 15) == 0) {
+      *(__attribute__((address_space(1))) f32x4 *)p = v;
+    } else {
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        if (x < left) p[x] = v[x];
+    }
+  } else {
+    gushort_ptr p = (gushort_ptr)(uintptr_t)at;
+    unsigned short e[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) e[x] = __builtin_bit_cast(unsigned short, (__bf16)v[x]);
+    if (left >= 4 && (at & 7) == 0) {
+      typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+      *(__attribute__((address_space(1))) u32x2 *)p = u32x2{e[0] | (unsigned)e[1] << 16, e[2] | (unsigned)e[3] << 16};
+    } else {
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        if (x < left) p[x] = e[x];
+    }
+  }
+}
+
+template <class SH>
+__global__ __launch_bounds__(NT, SH::OCC) void small_gemm_kernel(const SmallArgs g) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  constexpr int ES = SH::ES, BK = SH::BK, PER = SH::PER, CA = SH::CA, CB = SH::CB, DEPTH = SH::DEPTH, MI = SH::MI, NI = SH::NI;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave % SH::WK, wn = wave / SH::WK % SH::WN, wm = wave / SH::WK / SH::WN;
+  // Workgroup id mod 8 is the XCD: each XCD takes a contiguous eighth of the (run, tile row, tile
+  // column) sequence, so that the workgroups that share an L2 share A rows, B columns and k ranges.
+  const int total = (int)gridDim.x, q8 = total >> 3, r8 = total & 7;
+  const int xcd = blockIdx.x & 7, pos = blockIdx.x >> 3;
+  const int id = xcd * q8 + (xcd < r8 ? xcd : r8) + pos;
+  const int tiles = g.tiles_m * g.tiles_n;
+  const int run = id / tiles, tile = id - run * tiles;
+  const SmallTile tr = g.rows[tile / g.tiles_n], tc = g.cols[tile % g.tiles_n];
+  const int S = g.S, NR = g.NR;
+  const int t0 = run * g.per, t_end = g.before[S];
+  const int t1 = t0 + g.per < t_end ? t0 + g.per : t_end;
+  const int n = t1 - t0;                                  // at least 1: the host sees to it
+
+  // ---- this thread's chunks ------------------------------------------------------------
+  const int ak = tid % SH::A_CHUNKS * PER;                // first k of its A chunks inside a step
+  const int bn = tid % SH::B_CHUNKS * PER;                // first column of its B chunks inside the tile
+  const int bk = tid / SH::B_CHUNKS;                      // k row of its first B chunk
+  constexpr int A_ROWS = NT / SH::A_CHUNKS, B_ROWS = NT / SH::B_CHUNKS;   // rows from one chunk to the next
+  const PieceDev *ap[CA];                                 // the A slices of its rows, at segment 0
+  int64_t arow[CA];                                       // row inside the slice's tile part
+#pragma unroll
+  for (int x = 0; x < CA; ++x) {
+    int row = tid / SH::A_CHUNKS + x * A_ROWS;
+    row = tr.start + (row < tr.ext ? row : tr.ext - 1);   // (rows past the tile's end read its last row; never stored)
+    int i = tr.first;
+    for (int y = 1; y < tr.pieces; ++y) i += g.mc[tr.first + y] <= row;
+    ap[x] = g.pa + (int64_t)i * S;
+    arow[x] = row - g.mc[i];
+  }
+  int bvalid = tc.ext - bn;                               // columns of its chunk that exist
+  bvalid = bvalid < 0 ? 0 : bvalid < PER ? bvalid : PER;
+  const bool edge = tc.ext < SH::TN;
+  const PieceDev *bp;
+  int64_t bcol;                                           // byte column inside the slice
+  {
+    const int col = tc.start + (bvalid > 0 ? bn : 0);
+    int j = tc.first;
+    for (int y = 1; y < tc.pieces; ++y) j += g.nc[tc.first + y] <= col;
+    bp = g.pb + j;
+    bcol = (int64_t)(col - g.nc[j]) * ES;
+  }
+
+  // ---- cursor over the K steps whose loads are issued ------------------------------------
+  // The descriptors of the segment after the cursor's are fetched a segment ahead: loads return in
+  // order, so waiting for a descriptor asked for just now would wait for all operands in flight.
+  int seg = 0, krem = 0;                                  // segment; elements of it left
+  gptr pa[CA], pb;
+  int64_t bpitch = 0;
+  PieceDev na[CA], nb;                                    // descriptors of the coming segment
+  int nlen = 0;
+  // Which of its chunks a thread may read in full where only the first elements count (a K tail, the
+  // last columns): all but those that would cross the end of a tile buffer.
+  unsigned asafe = 0;                                     // bit x: A chunk x of the segment's last step
+  bool bsafe = false;                                     // the B chunk of the segment's last k row
+  bool quick = true;                                      // the chunks of all its other rows, in every lane
+  auto fetch = [&](int s) {
+#pragma unroll
+    for (int x = 0; x < CA; ++x) na[x] = ap[x][s];
+    nb = bp[(int64_t)s * NR];
+    nlen = g.klen[s];
+  };
+  auto open = [&](int kpos) __attribute__((always_inline)) {                             // the cursor enters the segment fetched last
+    krem = nlen - kpos;
+    const int64_t last = (int64_t)((nlen - 1) / BK) * (BK * ES) + ak * ES;
+    asafe = 0;
+#pragma unroll
+    for (int x = 0; x < CA; ++x) {
+      const int64_t off = arow[x] * na[x].pitch;
+      pa[x] = (gptr)na[x].ptr + (off + (int64_t)(kpos + ak) * ES);
+      asafe |= (na[x].room - off - last >= 16 ? 1u : 0u) << x;
+    }
+    bpitch = nb.pitch;
+    pb = (gptr)nb.ptr + ((int64_t)(kpos + bk) * bpitch + bcol);
+    bsafe = nb.room - (nlen - 1) * bpitch - bcol >= 16;
+    quick = !edge || __builtin_amdgcn_ballot_w64(bpitch < 16) == 0;
+    if (seg + 1 < S) fetch(seg + 1);
+  };
+  {
+    int lo = 0, hi = S - 1;                               // the last segment that starts at or before step t0
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (g.before[mid] <= t0) lo = mid;
+      else hi = mid - 1;
+    }
+    seg = lo;
+    fetch(lo);
+    open((t0 - g.before[lo]) * BK);
+  }
+  u32x4 ra[DEPTH][CA], rb[DEPTH][CB];                     // operands of DEPTH steps in flight
+  int rk[DEPTH];                                          // elements of the segment left at those steps
+  auto load16 = [](gptr p) -> u32x4 { return *(const __attribute__((address_space(1))) u32x4_any *)p; };
+  auto load_step = [&](u32x4 (&va)[CA], u32x4 (&vb)[CB], int &left_k, bool more) __attribute__((always_inline)) {
+    left_k = krem;
+    if (__builtin_expect(krem > BK ? quick : krem == BK && !edge, 1)) {
+#pragma unroll
+      for (int x = 0; x < CA; ++x) va[x] = load16(pa[x]);
+      gptr p = pb;
+#pragma unroll
+      for (int x = 0; x < CB; ++x) {
+        vb[x] = load16(p);
+        p += (int64_t)B_ROWS * bpitch;
+      }
+    } else {
+      // the segment's last step: what is read past the segment in k is zeroed on the way to LDS, so
+      // that no load is waited for here (columns past the tile's end stay as they are: never stored)
+      const int an = krem - ak;
+#pragma unroll
+      for (int x = 0; x < CA; ++x) {
+        va[x] = u32x4{0u, 0u, 0u, 0u};
+        if (an >= PER || (an > 0 && (asafe >> x & 1))) va[x] = load16(pa[x]);
+        else if (an > 0) va[x] = load_partial<ES>(pa[x], an);
+      }
+      gptr p = pb;
+#pragma unroll
+      for (int x = 0; x < CB; ++x) {
+        const int left = krem - (bk + x * B_ROWS);        // k rows of the segment from this one on
+        vb[x] = u32x4{0u, 0u, 0u, 0u};
+        if (left > 0 && bvalid > 0) {
+          if (bvalid == PER || bsafe || (left > 1 && bpitch >= 16)) vb[x] = load16(p);
+          else vb[x] = load_partial<ES>(p, bvalid);
+        }
+        p += (int64_t)B_ROWS * bpitch;
+      }
+    }
+    if (!more) return;
+    krem -= BK;
+    if (krem <= 0) {
+      ++seg;
+      open(0);
+    } else {
+#pragma unroll
+      for (int x = 0; x < CA; ++x) pa[x] += BK * ES;
+      pb += (int64_t)BK * bpitch;
+    }
+  };
+  const lds_ptr lds3 = (lds_ptr)(lds_void_ptr)lds;
+  auto write_step = [&](int stage, u32x4 (&va)[CA], u32x4 (&vb)[CB], int left_k) __attribute__((always_inline)) {
+    if (__builtin_expect(left_k < BK, 0)) {
+#pragma unroll
+      for (int x = 0; x < CA; ++x) va[x] = keep_first<ES>(va[x], left_k - ak);
+    }
+    const lds_ptr sa = lds3 + stage * SH::STAGE_BYTES, sb = sa + SH::TM * SH::A_PITCH;
+#pragma unroll
+    for (int x = 0; x < CA; ++x)
+      *(__attribute__((address_space(3))) u32x4 *)(sa + (tid / SH::A_CHUNKS + x * A_ROWS) * SH::A_PITCH + ak * ES) = va[x];
+#pragma unroll
+    for (int x = 0; x < CB; ++x)
+      *(__attribute__((address_space(3))) u32x4 *)(sb + (bk + x * B_ROWS) * SH::B_PITCH + bn * ES) = vb[x];
+  };
+
+  // ---- the K loop: step t is multiplied while the loads of the DEPTH steps after it travel -----------------
+  floatx16 acc[MI][NI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  const int a_row = wm * (MI * 32) + (lane & 31), half = lane >> 5;
+  auto multiply = [&](int stage) __attribute__((always_inline)) {
+    const lds_ptr sa = lds3 + stage * SH::STAGE_BYTES, sb = sa + SH::TM * SH::A_PITCH;
+    if constexpr (ES == 2) {
+      const int gr = lane >> 4, li = lane & 15;
+#pragma unroll
+      for (int q = 0; q < BK / 16 / SH::WK; ++q) {
+        const int qq = q * SH::WK + wk;
+        bf16x8 fa[MI], fb[NI];
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+          fa[i] = *(const __attribute__((address_space(3))) bf16x8 *)(sa + (a_row + i * 32) * SH::A_PITCH + qq * 32 + half * 16);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+          union { short4_t h[2]; bf16x8 v; } u;
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            u.h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (lds_short4_ptr)(sb + (qq * 16 + (gr >> 1) * 8 + (li >> 2) + 4 * h) * SH::B_PITCH +
+                                 (wn * (NI * 32) + j * 32 + (gr & 1) * 16 + (li & 3) * 4) * 2));
+          fb[j] = u.v;
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < BK / 8 / SH::WK; ++q) {
+        const int qq = q * SH::WK + wk;
+        f32x4 fa[MI];
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+          fa[i] = *(const __attribute__((address_space(3))) f32x4 *)(sa + (a_row + i * 32) * SH::A_PITCH + qq * 32 + half * 16);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int j = 0; j < NI; ++j) {
+            const float fb = *(const __attribute__((address_space(3))) float *)(sb + (qq * 8 + half * 4 + e) * SH::B_PITCH +
+                                                                               (wn * (NI * 32) + j * 32 + (lane & 31)) * 4);
+#pragma unroll
+            for (int i = 0; i < MI; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][e], fb, acc[i][j], 0, 0, 0);
+          }
+      }
+    }
+  };
+  static_for<DEPTH>([&](auto dc) {
+    constexpr int d = decltype(dc)::value;
+    if (d < n) load_step(ra[d], rb[d], rk[d], d + 1 < n);
+  });
+  for (int t = 0; t < n; t += DEPTH) {
+    static_for<DEPTH>([&](auto dc) {
+      constexpr int d = decltype(dc)::value;
+      if (t + d < n) {
+        // (the stage's last readers multiplied step t + d - 2 and have passed the barrier of the step between)
+        write_step((t + d) & 1, ra[d], rb[d], rk[d]);
+        if (t + d + DEPTH < n) load_step(ra[d], rb[d], rk[d], t + d + DEPTH + 1 < n);
+        __syncthreads();
+        multiply((t + d) & 1);
+      }
+    });
+  }
+
+  // ---- epilogue: through LDS, four consecutive columns per thread ----------------------------
+  __syncthreads();
+  typedef __attribute__((address_space(3))) float *lds_float;
+  const lds_float out = (lds_float)lds3 + wk * (SH::TM * SH::T_PITCH);
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        out[(wm * (MI * 32) + i * 32 + 8 * (e >> 2) + 4 * half + (e & 3)) * SH::T_PITCH + wn * (NI * 32) + j * 32 + (lane & 31)] = acc[i][j][e];
+  __syncthreads();
+  float *part = g.scratch + (int64_t)(run * tiles + tile) * (SH::TM * SH::TN);
+#pragma unroll 2
+  for (int x = tid; x < SH::TM * SH::TN / 4; x += NT) {
+    const int r = x / (SH::TN / 4), c = x % (SH::TN / 4) * 4;
+    if (r >= tr.ext || c >= tc.ext) continue;
+    f32x4 v = *(const __attribute__((address_space(3))) f32x4 *)((lds_float)lds3 + r * SH::T_PITCH + c);
+#pragma unroll
+    for (int w = 1; w < SH::WK; ++w)
+      v = v + *(const __attribute__((address_space(3))) f32x4 *)((lds_float)lds3 + (w * SH::TM + r) * SH::T_PITCH + c);
+    if (g.runs > 1) *(__attribute__((address_space(1))) f32x4 *)(part + r * SH::TN + c) = v;
+    else small_store4(g, tr, tc, r, c, v);
+  }
+}
+
+// The partial tiles of every tile, added up in ascending k.  A workgroup takes 1024 elements.
+template <class SH>
+__global__ __launch_bounds__(NT) void small_sum_kernel(const SmallArgs g) {
+  constexpr int BLOCKS = SH::TM * SH::TN / 1024;
+  const int tile = blockIdx.x / BLOCKS, x = (blockIdx.x % BLOCKS) * NT + threadIdx.x;
+  const int tiles = g.tiles_m * g.tiles_n;
+  const SmallTile tr = g.rows[tile / g.tiles_n], tc = g.cols[tile % g.tiles_n];
+  const int r = x / (SH::TN / 4), c = x % (SH::TN / 4) * 4;
+  if (r >= tr.ext || c >= tc.ext) return;
+  typedef const __attribute__((address_space(1))) f32x4 *gvec;
+  const int64_t step = (int64_t)tiles * (SH::TM * SH::TN);
+  const float *p = g.scratch + (int64_t)tile * (SH::TM * SH::TN) + r * SH::TN + c;
+  f32x4 s = *(gvec)p;
+  constexpr int QB = 8;                                   // runs whose loads are in flight at a time
+  for (int q0 = 1; q0 < g.runs; q0 += QB) {
+    f32x4 v[QB];
+#pragma unroll
+    for (int q = 0; q < QB; ++q)
+      if (q0 + q < g.runs) v[q] = *(gvec)(p + (q0 + q) * step);
+#pragma unroll
+    for (int q = 0; q < QB; ++q)
+      if (q0 + q < g.runs) s = s + v[q];
+  }
+  small_store4(g, tr, tc, r, c, s);
+}
+
+//                ES   TM   TN  BK WM WN WK DEPTH OCC
+typedef SmallShape<2, 32, 128, 64, 1, 4, 1, 1, 3> SmallBf16Skinny;
+typedef SmallShape<2, 64, 128, 64, 2, 2, 1, 2, 2> SmallBf16Half;
+typedef SmallShape<2, 128, 128, 64, 2, 2, 1, 2, 2> SmallBf16;
+typedef SmallShape<4, 32, 32, 64, 1, 1, 4, 1, 4> SmallF32Tiny;
+typedef SmallShape<4, 64, 64, 32, 2, 2, 1, 2, 4> SmallF32;
+
+// What the host's choice between them knows of a shape: microseconds per K step and tile, measured.
+struct SmallKind {
+  int es, tm, tn, bk, occ;
+  double step;        // per workgroup where `occ` of them share every CU
+  double alone;       // from a step to the next where a workgroup has a CU to itself
+};
+template <class SH>
+constexpr SmallKind small_kind(double step, double alone) {
+  return {SH::ES, SH::TM, SH::TN, SH::BK, SH::OCC, step, alone};
+}
+
+}  // namespace dmm
