@@ -275,13 +275,93 @@ struct ExecLayout {
   MergedLaunch ml;                                                       // merged macro-tiles
   size_t n_items = 0, o_segs = 0, o_fix = 0, o_red = 0, n_first = 0, n_fix = 0;   // per-group macro-tiles
   bool fuse = false, one_launch = false;
+  bool dense = false;           // the operands are copied first and DeviceState::dense runs the product
   SmallLaunch small;            // shape >= 0: these kernels run the product
   size_t n_runs = 0;
   bool uses_split = false;      // some macro-tiles store through the plan's scratch buffer
   RedLaunch red;                // the replica-sum launch behind the GEMM (n_items == 0: none)
 };
 
+// Buffers for dense copies of operands (pack_kernel.hpp), up to a few hundred MB each: of those not
+// in use the pool keeps 2 GiB in all, and none is handed out for less than half its size.
+class PackPool {
+ public:
+  // DMM_ENOMEM (nothing recorded): there is no room, the caller does without
+  int acquire(size_t bytes, char **out, size_t *cap) {
+    int device = 0;
+    DMM_HIP(hipGetDevice(&device));
+    std::lock_guard<std::mutex> g(mu_);
+    for (size_t i = 0; i < free_.size(); ++i)
+      if (free_[i].device == device && free_[i].cap >= bytes && free_[i].cap / 2 <= bytes) {
+        *out = free_[i].p;
+        *cap = free_[i].cap;
+        held_ -= free_[i].cap;
+        free_.erase(free_.begin() + (long)i);
+        return DMM_OK;
+      }
+    const size_t want = (bytes + ((size_t)32 << 20) - 1) >> 25 << 25;
+    char *p = nullptr;
+    if (hipMalloc((void **)&p, want) != hipSuccess) {
+      (void)hipGetLastError();
+      return DMM_ENOMEM;
+    }
+    *out = p;
+    *cap = want;
+    return DMM_OK;
+  }
+  // The caller guarantees that no stream work still uses the buffer.
+  void release(char **p, size_t *cap, int device) {
+    if (!*p) return;
+    std::lock_guard<std::mutex> g(mu_);
+    // the oldest go first
+    while (!free_.empty() && held_ + *cap > kMost) {
+      (void)hipFree(free_[0].p);
+      held_ -= free_[0].cap;
+      free_.erase(free_.begin());
+    }
+    if (*cap <= kMost) {
+      free_.push_back({*p, *cap, device});
+      held_ += *cap;
+    } else {
+      (void)hipFree(*p);
+    }
+    *p = nullptr;
+    *cap = 0;
+  }
+
+ private:
+  static constexpr size_t kMost = (size_t)2 << 30;
+  struct Entry {
+    char *p;
+    size_t cap;
+    int device;
+  };
+  std::mutex mu_;
+  std::vector<Entry> free_;
+  size_t held_ = 0;
+};
+
+PackPool &pack_pool() {
+  static PackPool *p = new PackPool;   // never destroyed, like the slab pool
+  return *p;
+}
+
 struct DeviceState {
+  // A product that runs on dense copies of its operands: the plan it runs as, the copies, and the
+  // tables of the kernel that makes them.
+  dmm_plan_t *dense = nullptr;
+  char *pack_buf = nullptr;
+  size_t pack_cap = 0;
+  int pack_device = 0;
+  Uploader pack_table;
+  int pack_jobs = 0, pack_blocks = 0;
+  size_t pack_o_tiles = 0, pack_o_cuts = 0;
+  char *pack_b = nullptr;              // the copy of B
+  std::vector<const void *> pack_a;    // the copy of A, one tile per replica of C
+  std::vector<int64_t> pack_lda;
+  int64_t pack_ldb = 0;
+  bool ran_dense = false;              // the last dmm_execute did so
+  hipEvent_t t_pack[2] = {nullptr, nullptr};
   char *split_buf = nullptr;   // partial sums of K-split items
   size_t split_cap = 0;
   Uploader gemm_table;   // [ItemDev x items][SegDev x segments]
@@ -309,6 +389,11 @@ void destroy_device_state(DeviceState *d) {
   if (!d) return;
   // wait for this plan's own work only, then hand the buffers back to the pool
   if (d->last_use_recorded) (void)hipEventSynchronize(d->last_use);
+  if (d->dense) dmm_plan_destroy(d->dense);
+  d->pack_table.release();
+  pack_pool().release(&d->pack_buf, &d->pack_cap, d->pack_device);
+  for (int i = 0; i < 2; ++i)
+    if (d->t_pack[i]) (void)hipEventDestroy(d->t_pack[i]);
   d->gemm_table.release();
   d->red_table.release();
   scratch_pool().release(&d->split_buf, &d->split_cap);

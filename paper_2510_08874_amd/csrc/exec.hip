@@ -17,6 +17,7 @@
 #include "device_state.hpp"
 #include "gemm_kernel.hpp"
 #include "gemm_launch.hpp"
+#include "pack_kernel.hpp"
 #include "plan_internal.h"
 #include "small_kernel.hpp"
 
@@ -1006,8 +1007,191 @@ int build_small_exec(dmm_plan_t *P, const ExecArgs &x, const SmallPlan &sp, hipS
   return DMM_OK;
 }
 
+// ---- products on dense copies of their operands (pack_kernel.hpp) -----------------------------------
+
+// Whether the rows of an operand's tiles, from some K-segment or column on, start at addresses that
+// are not multiples of 16 bytes.
+bool misaligned(const Grid &G, const void *const *tiles, const int64_t *ld, const std::vector<int64_t> &cuts) {
+  for (int32_t i = 0; i < G.gr; ++i)
+    for (int32_t j = 0; j < G.gc; ++j)
+      if (G.rc[i + 1] > G.rc[i] && G.cc[j + 1] > G.cc[j]) {
+        const int64_t x = G.table_index(0, i, j);
+        if (((uintptr_t)tiles[x] & 15) || (ld[x] & 7)) return true;
+      }
+  for (int64_t c : cuts) {              // where segments (column intervals) begin inside their tiles
+    const int64_t in = c - *(std::upper_bound(G.cc.begin(), G.cc.end(), c) - 1);
+    if (in & 7) return true;
+  }
+  return false;
+}
+
+// Whether a large bf16 product pays for dense copies of A and B: the estimated time of the copy plus
+// the macro-tiles on it against that of the macro-tiles on the operands as they are.  A K step of
+// rows that are not 16-byte aligned costs 1.27 of an aligned one (8192^3 against 8190^3 packed: 1127
+// and 1428 cycles), a segment one and a half more steps, a macro-tile that spans tiles 1.13; the copy
+// runs at 4.5 TB/s and more (0.93 GB in 190 us).  Measured, us per call on the operands -> on copies:
+// 12289 x 9973 x 11003 in uneven packed tiles 3075 -> 2320, the same with rows padded to 16 bytes 2766 ->
+// 2294; 8192^3 in 128 x 128 block-cyclic tiles 1074 -> 984; 4096 x 4032 x 8152 in 100 x 100 ones, packed,
+// 454 -> 299; 11168 x 7584 x 2304 (two rounds either way, the copy as long as what it saves) 518 against
+// 545: stays.
+bool choose_dense(const dmm_plan_t *P, const ExecArgs &x, int cus) {
+  const Grid &A = P->A, &B = P->B, &C = P->C;
+  const int64_t M = C.rows, K = A.cols, N = C.cols, lim = (int64_t)1 << 30;
+  if (x.es != 2 || P->dense_copy || (P->flags & DMM_MERGE_ALWAYS) || (x.flags & DMM_NO_MERGE)) return false;
+  if ((P->flags & (DMM_STATIONARY_B | DMM_STATIONARY_A)) && (A.c != 1 || B.c != 1 || C.c != 1)) return false;   // (their replicas do not split K)
+  if (M < 1024 || N < 1024 || K < 1024 * (int64_t)C.c || M >= lim || K >= lim || N >= lim) return false;
+  if (A.tiles_per_rep() + B.tiles_per_rep() > 65536) return false;
+  const double bytes = 2.0 * ((double)M * K + (double)K * N);
+  if (bytes > 2.0e9) return false;
+  size_t items = 0;
+  if (P->merged.valid) items = P->merged.items.size();
+  else
+    for (const dmm_work_item &w : P->items) items += w.group >= 0;
+  if (items < (size_t)cus) return false;
+  int64_t dense_items = 0, merged_items = 0;
+  for (int32_t i = 0; i < C.gr; ++i)
+    for (int32_t j = 0; j < C.gc; ++j)
+      dense_items += ((C.rc[i + 1] - C.rc[i] + kMacroTile - 1) / kMacroTile) * ((C.cc[j + 1] - C.cc[j] + kMacroTile - 1) / kMacroTile);
+  merged_items = ((M + kMacroTile - 1) / kMacroTile) * ((N + kMacroTile - 1) / kMacroTile);
+  const bool merge = merged_items * 10 <= dense_items * 9;            // (what dmm_plan will choose)
+  const std::vector<int64_t> kc = merged_cuts({&A.cc, &B.rc}), nc = merged_cuts({&B.cc, &C.cc});
+  const double steps = (double)K / C.c / (double)x.bk, segs = (double)(kc.size() - 1) / C.c, us = 0.72;
+  const bool odd = misaligned(A, x.a_tiles, x.a_ld, kc) || misaligned(B, x.b_tiles, x.b_ld, nc);
+  // rounds of macro-tiles; the last one is cut along K where it is at most half full
+  auto rounds = [&](int64_t n) {
+    const int64_t tail = n % cus, runs = tail > 0 && tail <= cus / 2 ? std::min<int64_t>(cus / tail, (int64_t)steps / MIN_RUN) : 1;
+    return (double)(n / cus) + (tail > 0 ? 1.0 / (double)std::max<int64_t>(1, runs) : 0.0);
+  };
+  const double now = rounds((int64_t)items) * (steps + 1.5 * segs) * us * (odd ? 1.27 : 1.0) * (P->merged.valid ? 1.13 : 1.0);
+  const double then = rounds((merge ? merged_items : dense_items) * C.c) * (steps + 1.5) * us * (merge ? 1.08 : 1.0) + 2.0 * bytes / 4.5e6 + 5;
+  return then < 0.93 * now;
+}
+
+// The plan on the copies, the copies' buffer and the tables of the copy.  DMM_ENOMEM: no room.
+int build_dense_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecLayout *L) {
+  int rc;
+  DeviceState &D = *P->dev;
+  const Grid &A = P->A, &B = P->B, &C = P->C;
+  const int64_t M = C.rows, K = A.cols, N = C.cols;
+  // K split as the replicas of C share it, every share a tile of A with rows of its own
+  std::vector<int64_t> shares;
+  for (int32_t r = 0; r <= C.c; ++r) shares.push_back((int64_t)r * K / C.c);
+  if (!D.dense) {
+    const int64_t all_m[2] = {0, M}, all_k[2] = {0, K}, all_n[2] = {0, N};
+    const dmm_matrix_desc a = {M, K, 1, C.c, all_m, shares.data(), 1, 1, 1}, b = {K, N, 1, 1, all_k, all_n, 1, 1, 1},
+                          c = {M, N, C.gr, C.gc, C.rc.data(), C.cc.data(), C.pr, C.pc, C.c};
+    if ((rc = dmm_plan(&a, &b, &c, P->nranks, 0, &D.dense))) return rc;
+    D.dense->dense_copy = true;
+  }
+  auto padded = [](int64_t cols) { return (cols + 63) & ~(int64_t)63; };
+  size_t need = 0;
+  std::vector<size_t> at;
+  D.pack_lda.clear();
+  for (int32_t r = 0; r < C.c; ++r) {
+    D.pack_lda.push_back(padded(shares[(size_t)r + 1] - shares[(size_t)r]));
+    at.push_back(need);
+    need += (size_t)(M * D.pack_lda.back()) * 2;
+  }
+  D.pack_ldb = padded(N);
+  const size_t at_b = need;
+  need += (size_t)(K * D.pack_ldb) * 2;
+  // the copies are shared by all calls on this plan: order this call behind the last one
+  if (D.last_use_recorded) DMM_HIP(hipStreamWaitEvent(stream, D.last_use, 0));
+  if (need > D.pack_cap) {
+    if (D.pack_buf) {
+      DMM_HIP(hipStreamSynchronize(stream));
+      pack_pool().release(&D.pack_buf, &D.pack_cap, D.pack_device);
+    }
+    if ((rc = pack_pool().acquire(need, &D.pack_buf, &D.pack_cap))) return rc;
+    D.pack_device = x.device;
+  }
+  std::vector<int32_t> cuts;
+  std::vector<PackTile> tiles;
+  std::vector<PackJob> jobs;
+  int32_t blocks = 0;
+  // columns [col0, col0 + cols) of an operand to dense rows at `where`: a job per tile row
+  auto copy = [&](const Grid &G, size_t first_tile, size_t first_cut, size_t where, int64_t ld, int64_t col0, int64_t cols) {
+    for (int32_t i = 0; i < G.gr; ++i) {
+      PackJob j;
+      std::memset(&j, 0, sizeof(j));
+      j.rows = (int32_t)(G.rc[i + 1] - G.rc[i]);
+      if (j.rows <= 0) continue;
+      j.dst = D.pack_buf + where + (size_t)(G.rc[i] * ld) * 2;
+      j.pitch = ld * 2;
+      j.col0 = (int32_t)col0;
+      j.cols = (int32_t)cols;
+      j.gc = G.gc;
+      j.cc = (int32_t)first_cut;
+      j.tiles = (int32_t)(first_tile + (size_t)i * G.gc);
+      j.first_block = blocks;
+      j.blocks_c = (int32_t)((cols + PACK_COLS - 1) / PACK_COLS);
+      blocks += j.blocks_c * ((j.rows + PACK_ROWS - 1) / PACK_ROWS);
+      jobs.push_back(j);
+    }
+  };
+  auto operand = [&](const Grid &G, const void *const *ptr, const int64_t *ld) {
+    for (int64_t c : G.cc) cuts.push_back((int32_t)c);
+    for (int32_t i = 0; i < G.gr; ++i)
+      for (int32_t k = 0; k < G.gc; ++k) {
+        const int64_t idx = G.table_index(0, i, k);
+        tiles.push_back({(const char *)ptr[idx], ld[idx] * 2});
+      }
+  };
+  operand(A, x.a_tiles, x.a_ld);
+  const size_t b_tile = tiles.size(), b_cut = cuts.size();
+  operand(B, x.b_tiles, x.b_ld);
+  D.pack_a.clear();
+  for (int32_t r = 0; r < C.c; ++r) {
+    copy(A, 0, 0, at[(size_t)r], D.pack_lda[(size_t)r], shares[(size_t)r], shares[(size_t)r + 1] - shares[(size_t)r]);
+    D.pack_a.push_back(D.pack_buf + at[(size_t)r]);
+  }
+  copy(B, b_tile, b_cut, at_b, D.pack_ldb, 0, N);
+  D.pack_b = D.pack_buf + at_b;
+  D.pack_jobs = (int)jobs.size();
+  D.pack_blocks = blocks;
+  D.pack_o_tiles = jobs.size() * sizeof(PackJob);
+  D.pack_o_cuts = D.pack_o_tiles + tiles.size() * sizeof(PackTile);
+  std::vector<char> &h = D.host;
+  h.assign(D.pack_o_cuts + cuts.size() * 4, 0);
+  std::memcpy(h.data(), jobs.data(), jobs.size() * sizeof(PackJob));
+  std::memcpy(h.data() + D.pack_o_tiles, tiles.data(), tiles.size() * sizeof(PackTile));
+  std::memcpy(h.data() + D.pack_o_cuts, cuts.data(), cuts.size() * 4);
+  if ((rc = D.pack_table.upload(h.data(), h.size(), stream, busy_event(P)))) return rc;
+  L->dense = true;
+  L->uses_split = true;
+  return DMM_OK;
+}
+
+int launch_dense(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, bool timed) {
+  int rc;
+  DeviceState &D = *P->dev;
+  if (timed) {
+    if ((rc = timing_events(D.t_pack))) return rc;
+    DMM_HIP(hipEventRecord(D.t_pack[0], stream));
+  }
+  {
+    TraceRange tr("copy_operands");
+    const char *d = D.pack_table.dev();
+    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)D.pack_blocks), dim3(256), 0, stream, (const PackJob *)d, D.pack_jobs,
+                       (const int32_t *)(d + D.pack_o_cuts), (const PackTile *)(d + D.pack_o_tiles));
+    DMM_HIP(hipGetLastError());
+  }
+  if (timed) DMM_HIP(hipEventRecord(D.t_pack[1], stream));
+  const void *b = D.pack_b;
+  rc = dmm_execute(D.dense, x.dtype, D.pack_a.data(), D.pack_lda.data(), &b, &D.pack_ldb, x.c_tiles, x.c_ld, x.flags, stream);
+  const int rc2 = mark_use(P, stream);      // (also behind a copy whose product failed)
+  if (rc || rc2) return rc ? rc : rc2;
+  dmm_execute_report r;
+  if ((rc = dmm_plan_last_execute(D.dense, &r))) return rc;
+  D.ran_merged = r.ran_merged != 0;
+  D.ran_k_split = r.ran_k_split != 0;
+  D.ran_fused = r.ran_fused;
+  D.ran_dense = true;
+  return DMM_OK;
+}
+
 // Whether every tile that the call's own work list would read has a pointer, and every tile of the
-// first replicas of A and B: the kernels for small products read only these
+// first replicas of A and B: the kernels for small products and the copies read only these
 // (replicas are copies of each other, Section 3); what the other work lists refuse is refused all
 // the same, and what they accept they get.
 bool operands_given(const dmm_plan_t *P, const ExecArgs &x) {
@@ -1198,7 +1382,7 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
     if (P->dev->exec_cached && key == P->dev->exec_key) {
       L = P->dev->exec_layout;
       P->dev->table_reused = true;
-      if ((rc = P->dev->gemm_table.order_behind_copy(stream))) return rc;
+      if ((rc = (L.dense ? P->dev->pack_table : P->dev->gemm_table).order_behind_copy(stream))) return rc;
       // (the scratch buffer of macro-tiles cut along K is shared by all calls on this plan)
       if (L.uses_split && P->dev->last_use_recorded) DMM_HIP(hipStreamWaitEvent(stream, P->dev->last_use, 0));
     } else {
@@ -1210,7 +1394,10 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
       if ((rc = device_cus(&cus))) return rc;
       const bool given = operands_given(P, x);
       if (given) choose_small(P, x, cus, &sp);
-      if (sp.shape >= 0) rc = build_small_exec(P, x, sp, stream, &L);
+      rc = DMM_ENOMEM;
+      if (given && sp.shape < 0 && choose_dense(P, x, cus)) rc = build_dense_exec(P, x, stream, &L);   // (no room for copies: without)
+      if (L.dense || rc != DMM_ENOMEM) {
+      } else if (sp.shape >= 0) rc = build_small_exec(P, x, sp, stream, &L);
       else if (P->merged.valid && !(flags & DMM_NO_MERGE) && g_comp_ok[device]) rc = build_merged_exec(P, x, stream, &L);
       else rc = build_group_exec(P, x, stream, &L);
       if (rc) return rc;
@@ -1218,6 +1405,8 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
       P->dev->exec_layout = L;
       P->dev->exec_cached = true;
     }
+    P->dev->ran_dense = false;
+    if (L.dense) return launch_dense(P, x, stream, timed);
     return launch_exec(P, L, es, stream, timed);
   } catch (const std::bad_alloc &) {
     return DMM_ENOMEM;
@@ -1229,6 +1418,7 @@ int dmm_plan_gemm_launch_ms(dmm_plan_t *P, float ms[2], double flops[2]) {
   if (!P || !ms || !flops) return DMM_EINVAL;
   ms[0] = ms[1] = -1.f;
   flops[0] = flops[1] = 0.0;
+  if (P->dev && P->dev->ran_dense) return dmm_plan_gemm_launch_ms(P->dev->dense, ms, flops);
   if (!P->dev || !P->dev->gemm_timed || !P->dev->mid_timed) return DMM_OK;
   DMM_HIP(hipEventSynchronize(P->dev->t_gemm[1]));
   DMM_HIP(hipEventElapsedTime(&ms[0], P->dev->t_gemm[0], P->dev->t_mid));
@@ -1253,6 +1443,16 @@ int dmm_plan_elapsed_ms(dmm_plan_t *P, float *gemm_ms, float *reduce_ms) {
   using namespace dmm;
   if (!P) return DMM_EINVAL;
   float g = -1.f, r = -1.f;
+  if (P->dev && P->dev->ran_dense) {
+    // (the copy of the operands counts as part of the product)
+    float ms = 0.f;
+    int rc = dmm_plan_elapsed_ms(P->dev->dense, &g, &r);
+    if (rc) return rc;
+    if (g >= 0.f) {
+      DMM_HIP(hipEventElapsedTime(&ms, P->dev->t_pack[0], P->dev->t_pack[1]));
+      g += ms;
+    }
+  }
   if (P->dev && P->dev->gemm_timed) {
     DMM_HIP(hipEventSynchronize(P->dev->t_gemm[1]));
     DMM_HIP(hipEventElapsedTime(&g, P->dev->t_gemm[0], P->dev->t_gemm[1]));

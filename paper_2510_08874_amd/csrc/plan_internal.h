@@ -94,6 +94,7 @@ struct dmm_plan_s {
   std::vector<dmm::Group> groups;
   std::vector<dmm_work_item> items;   // launch order
   dmm::Merged merged;                 // the alternative to `items` where it pays
+  bool dense_copy = false;            // of another plan's product on dense copies of its operands
   dmm::DeviceState *dev = nullptr;
 };
 
