@@ -253,7 +253,8 @@ int dmm_reduce_replicas_static(dmm_plan_t *p, void *const *c_tiles, const int64_
  *   ran_merged    1: it ran tiles that span several tiles of A, B and C: the merged macro-tiles (the
  *                 plan has such a list, DMM_NO_MERGE was not given and the device grants a workgroup
  *                 the 160 KB of LDS their kernel asks for) or, in their place, the tiles of the
- *                 kernels for small products
+ *                 kernels for small products.  (A product that ran on dense copies of its operands
+ *                 reports what ran there: only C's tiles are left to span.)
  *   ran_k_split   1: it cut tiles along K (partial tiles through a scratch buffer, added up
  *                 in ascending k by a second kernel: the last round of workgroups would have left
  *                 most of the device idle, or a merged macro-tile had more K-segments than its
@@ -277,7 +278,8 @@ int dmm_plan_last_execute(const dmm_plan_t *p, dmm_execute_report *out);
 /* Device time of the kernels of the last dmm_execute(..., DMM_TIMING, ...) on this plan, in
  * milliseconds, excluding the work-table upload: gemm_ms from in front of the first GEMM launch
  * to behind the last (one launch, two with a fused replica sum that needs two, plus the pass
- * that adds up macro-tiles cut along K), reduce_ms the replica-sum kernel.  Blocks until those
+ * that adds up macro-tiles cut along K; the copy of the operands where there is one counts
+ * too), reduce_ms the replica-sum kernel.  Blocks until those
  * kernels have finished.  A kernel that was not timed (or did not run) reports -1.  Either
  * output pointer may be null.  (Measurement aid for the roofline figures: Section 5.2
  * reports the best of repeated runs.) */

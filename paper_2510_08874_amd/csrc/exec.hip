@@ -1394,12 +1394,21 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
       if ((rc = device_cus(&cus))) return rc;
       const bool given = operands_given(P, x);
       if (given) choose_small(P, x, cus, &sp);
-      rc = DMM_ENOMEM;
-      if (given && sp.shape < 0 && choose_dense(P, x, cus)) rc = build_dense_exec(P, x, stream, &L);   // (no room for copies: without)
-      if (L.dense || rc != DMM_ENOMEM) {
-      } else if (sp.shape >= 0) rc = build_small_exec(P, x, sp, stream, &L);
-      else if (P->merged.valid && !(flags & DMM_NO_MERGE) && g_comp_ok[device]) rc = build_merged_exec(P, x, stream, &L);
-      else rc = build_group_exec(P, x, stream, &L);
+      bool built = false;
+      if (given && (sp.shape >= 0 || choose_dense(P, x, cus))) {
+        rc = sp.shape >= 0 ? build_small_exec(P, x, sp, stream, &L) : build_dense_exec(P, x, stream, &L);
+        if (rc == DMM_ENOMEM) {
+          // no room for partial tiles or copies: the call's own work list, which may do with less
+          (void)hipGetLastError();
+          L = ExecLayout();
+        } else {
+          built = true;
+        }
+      }
+      if (!built) {
+        if (P->merged.valid && !(flags & DMM_NO_MERGE) && g_comp_ok[device]) rc = build_merged_exec(P, x, stream, &L);
+        else rc = build_group_exec(P, x, stream, &L);
+      }
       if (rc) return rc;
       P->dev->exec_key = key;
       P->dev->exec_layout = L;

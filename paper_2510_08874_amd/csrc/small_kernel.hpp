@@ -19,6 +19,13 @@
 // matrix instructions as in the macro-tile kernels, hence bitwise the same results, unless a
 // tile's K steps are dealt to several workgroups or waves (their partial sums are then added in
 // ascending k).
+//
+// Measured (kernel alone, us; macro-tile kernels -> these): fp32 256^3 50 -> 5; bf16 2048^3 41 -> 36,
+// where a step of 64 k takes 0.9 us, of which 0.25 are matrix instructions (one workgroup per CU:
+// LDS writes, barrier, LDS reads and multiplication follow each other); 32 x 12288 x 49152 275 -> 221
+// (5.5 TB/s).  Operands of one, two or three steps in flight made no difference.  Reading all
+// fragments of a step ahead of its first matrix instruction gained 5 to 11 % with two workgroups on
+// every CU, lost 5 % with one and 10 to 18 % for fp32 (registers).
 #pragma once
 
 #include "gemm_kernel.hpp"
