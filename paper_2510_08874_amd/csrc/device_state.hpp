@@ -26,6 +26,56 @@ thread_local int g_last_hip_error = 0;
     }                                            \
   } while (0)
 
+// The calls of a plan whose kernels may still be running: an event behind the last call on each of
+// the streams it was used on.  Whoever writes a buffer that those kernels use waits for all of them
+// (one event for the plan would forget a stream as soon as the next call came on another).
+class Uses {
+ public:
+  // behind everything the call enqueued on `stream`
+  int mark(hipStream_t stream) {
+    Entry *e = nullptr;
+    for (int i = 0; i < n_ && !e; ++i)
+      if (uses_[i].stream == stream) e = &uses_[i];
+    if (!e && n_ < kMost) {
+      e = &uses_[n_];
+      DMM_HIP(hipEventCreateWithFlags(&e->ev, hipEventDisableTiming));
+      ++n_;
+    } else if (!e) {
+      // more streams than entries: the new event takes over from the one of another stream by
+      // being recorded behind it too
+      e = &uses_[next_];
+      next_ = (next_ + 1) % kMost;
+      DMM_HIP(hipStreamWaitEvent(stream, e->ev, 0));
+    }
+    e->stream = stream;
+    DMM_HIP(hipEventRecord(e->ev, stream));
+    return DMM_OK;
+  }
+  // orders what follows on `stream` behind all of them
+  int order(hipStream_t stream) const {
+    for (int i = 0; i < n_; ++i) DMM_HIP(hipStreamWaitEvent(stream, uses_[i].ev, 0));
+    return DMM_OK;
+  }
+  // blocks until they have finished
+  int wait() const {
+    for (int i = 0; i < n_; ++i) DMM_HIP(hipEventSynchronize(uses_[i].ev));
+    return DMM_OK;
+  }
+  void destroy() {
+    for (int i = 0; i < n_; ++i) (void)hipEventDestroy(uses_[i].ev);
+    n_ = 0;
+  }
+
+ private:
+  static constexpr int kMost = 8;
+  struct Entry {
+    hipStream_t stream;
+    hipEvent_t ev;
+  };
+  Entry uses_[kMost] = {};
+  int n_ = 0, next_ = 0;
+};
+
 // One device buffer plus two pinned staging slots and their events.  Slabs are
 // recycled through a process-wide pool (in the spirit of the memory pool of
 // Section 4.2: allocate once, sub-allocate from the CPU side), so creating and
@@ -128,26 +178,24 @@ int copy_stream(hipStream_t *out) {
 
 // upload() copies host bytes to the slab's device buffer on the copy stream and makes the
 // caller's stream wait for that copy; it skips the copy when those bytes are already resident.
-// `busy_until`, if given, is an event after which earlier readers of the device buffer (kernels
-// of a previous call on this plan) are done: the copy waits for it.
+// `readers` are the calls whose kernels may still read the device buffer: the copy waits for them.
 struct Uploader {
   Slab slab;
   bool ev_used[2] = {false, false};
   int cur = 0;
 
   char *dev() const { return slab.dev; }
-  int upload(const void *src, size_t bytes, hipStream_t stream, hipEvent_t busy_until = nullptr) {
+  int upload(const void *src, size_t bytes, hipStream_t stream, const Uses &readers) {
     if (bytes == 0) return DMM_OK;
     if (bytes > slab.cap) {
-      // growing: the old slab may still be read by enqueued work of this plan, on this stream or,
-      // from an earlier call, on another one (busy_until is behind all of it)
+      // growing: the old slab may still be read by enqueued work of this plan
+      int rc;
       if (slab.dev) {
-        if (busy_until) DMM_HIP(hipEventSynchronize(busy_until));
+        if ((rc = readers.wait())) return rc;
         DMM_HIP(hipStreamSynchronize(stream));
         pool().release(&slab);
       }
-      int rc = pool().acquire(bytes, &slab);
-      if (rc) return rc;
+      if ((rc = pool().acquire(bytes, &slab))) return rc;
       ev_used[0] = ev_used[1] = false;
     }
     std::vector<char> &resident = *slab.mirror;
@@ -165,7 +213,7 @@ struct Uploader {
     hipStream_t cs = nullptr;
     int rc = copy_stream(&cs);
     if (rc) return rc;
-    if (busy_until) DMM_HIP(hipStreamWaitEvent(cs, busy_until, 0));
+    if ((rc = readers.order(cs))) return rc;
     DMM_HIP(hipMemcpyAsync(slab.dev, slab.pinned[cur], bytes, hipMemcpyHostToDevice, cs));
     DMM_HIP(hipEventRecord(slab.ev[cur], cs));
     DMM_HIP(hipStreamWaitEvent(stream, slab.ev[cur], 0));
@@ -367,8 +415,7 @@ struct DeviceState {
   Uploader gemm_table;   // [ItemDev x items][SegDev x segments]
   Uploader red_table;    // [RedItem][RedTile][part pointers][part lds]
   std::vector<char> host;  // scratch for table assembly
-  hipEvent_t last_use = nullptr;      // recorded after the last launch of every call
-  bool last_use_recorded = false;
+  Uses uses;                          // marked after the last launch of every call
   hipEvent_t t_gemm[2] = {nullptr, nullptr}, t_red[2] = {nullptr, nullptr};  // DMM_TIMING
   hipEvent_t t_mid = nullptr;         // ... between the two GEMM launches of a fused replica sum
   bool gemm_timed = false, red_timed = false, mid_timed = false;
@@ -388,7 +435,7 @@ struct DeviceState {
 void destroy_device_state(DeviceState *d) {
   if (!d) return;
   // wait for this plan's own work only, then hand the buffers back to the pool
-  if (d->last_use_recorded) (void)hipEventSynchronize(d->last_use);
+  (void)d->uses.wait();
   if (d->dense) dmm_plan_destroy(d->dense);
   d->pack_table.release();
   pack_pool().release(&d->pack_buf, &d->pack_cap, d->pack_device);
@@ -397,7 +444,7 @@ void destroy_device_state(DeviceState *d) {
   d->gemm_table.release();
   d->red_table.release();
   scratch_pool().release(&d->split_buf, &d->split_cap);
-  if (d->last_use) (void)hipEventDestroy(d->last_use);
+  d->uses.destroy();
   for (int i = 0; i < 2; ++i) {
     if (d->t_gemm[i]) (void)hipEventDestroy(d->t_gemm[i]);
     if (d->t_red[i]) (void)hipEventDestroy(d->t_red[i]);

@@ -74,7 +74,6 @@ int ensure_state(dmm_plan_t *P) {
   if (!P->dev) {
     P->dev = new (std::nothrow) DeviceState;
     if (!P->dev) return DMM_ENOMEM;
-    DMM_HIP(hipEventCreateWithFlags(&P->dev->last_use, hipEventDisableTiming));
   }
   return DMM_OK;
 }
@@ -93,15 +92,6 @@ int device_cus(int *out) {
     cus[dev] = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1;
   }
   *out = cus[dev];
-  return DMM_OK;
-}
-
-// Event after which the kernels of this plan's earlier calls have finished (null: none yet).
-hipEvent_t busy_event(dmm_plan_t *P) { return P->dev->last_use_recorded ? P->dev->last_use : nullptr; }
-
-int mark_use(dmm_plan_t *P, hipStream_t stream) {
-  DMM_HIP(hipEventRecord(P->dev->last_use, stream));
-  P->dev->last_use_recorded = true;
   return DMM_OK;
 }
 
@@ -200,7 +190,7 @@ int stage_reduce(dmm_plan_t *P, void *const *c_tiles, const int64_t *c_ld, int32
   h.clear();
   int rc = build_reduce(P, c_tiles, c_ld, origin, &h, 0, L);
   if (rc || L->n_items == 0) return rc;
-  if ((rc = P->dev->red_table.upload(h.data(), h.size(), stream, busy_event(P)))) return rc;
+  if ((rc = P->dev->red_table.upload(h.data(), h.size(), stream, P->dev->uses))) return rc;
   L->dev_base = P->dev->red_table.dev();
   return DMM_OK;
 }
@@ -237,11 +227,12 @@ int fire_reduce(dmm_plan_t *P, const RedLaunch &L, hipStream_t stream, bool time
 constexpr int32_t MIN_RUN = 64;
 inline int32_t min_run_steps(int64_t es) { return es == 4 ? MIN_RUN / 8 : MIN_RUN; }
 
-// Scratch buffer of the plan for `need` bytes of partial tiles; orders this call behind the plan's last one.
+// Scratch buffer of the plan for `need` bytes of partial tiles; orders this call behind the plan's earlier ones.
 int acquire_split_buffer(dmm_plan_t *P, size_t need, hipStream_t stream) {
-  // the scratch buffer is shared by all calls on this plan: order this call behind the last one
-  // (a no-op when both are on the same stream)
-  if (P->dev->last_use_recorded) DMM_HIP(hipStreamWaitEvent(stream, P->dev->last_use, 0));
+  // the scratch buffer is shared by all calls on this plan: order this call behind the others
+  // (a no-op when all are on the same stream)
+  int rc = P->dev->uses.order(stream);
+  if (rc) return rc;
   if (need > P->dev->split_cap) {
     // growing: earlier calls on this plan may still use the old buffer
     if (P->dev->split_buf) {
@@ -562,7 +553,7 @@ int build_merged_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, Exec
   if ((rc = build_merged_tables(P, x.es, x.bk, x.c_es, x.a_tiles, x.a_ld, x.b_tiles, x.b_ld, x.c_tiles, x.c_ld, cus, stream, &h, &ml)))
     return rc;
   if (!(x.flags & DMM_NO_REDUCE) && (rc = build_reduce(P, x.c_tiles, x.c_ld, 0, &h, ml.total, &red))) return rc;
-  if ((rc = P->dev->gemm_table.upload(h.data(), h.size(), stream, busy_event(P)))) return rc;
+  if ((rc = P->dev->gemm_table.upload(h.data(), h.size(), stream, P->dev->uses))) return rc;
   red.dev_base = P->dev->gemm_table.dev();
   L->merged = true;
   L->ml = ml;
@@ -801,7 +792,7 @@ int build_group_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
   }
   if (!(flags & DMM_NO_REDUCE) && !fuse && (rc = build_reduce(P, c_tiles, c_ld, 0, &h, total, &red))) return rc;
   if (!h.empty()) {
-    if ((rc = P->dev->gemm_table.upload(h.data(), h.size(), stream, busy_event(P)))) return rc;
+    if ((rc = P->dev->gemm_table.upload(h.data(), h.size(), stream, P->dev->uses))) return rc;
     red.dev_base = P->dev->gemm_table.dev();
   }
   L->merged = false;
@@ -1001,7 +992,7 @@ int build_small_exec(dmm_plan_t *P, const ExecArgs &x, const SmallPlan &sp, hipS
   if (sp.runs > 1 &&
       (rc = acquire_split_buffer(P, (size_t)sp.runs * sp.rows.size() * sp.cols.size() * (size_t)(kind.tm * kind.tn) * sizeof(float), stream)))
     return rc;
-  if ((rc = P->dev->gemm_table.upload(h.data(), h.size(), stream, busy_event(P)))) return rc;
+  if ((rc = P->dev->gemm_table.upload(h.data(), h.size(), stream, P->dev->uses))) return rc;
   L->merged = P->merged.valid;
   L->uses_split = sp.runs > 1;
   return DMM_OK;
@@ -1095,8 +1086,8 @@ int build_dense_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
   D.pack_ldb = padded(N);
   const size_t at_b = need;
   need += (size_t)(K * D.pack_ldb) * 2;
-  // the copies are shared by all calls on this plan: order this call behind the last one
-  if (D.last_use_recorded) DMM_HIP(hipStreamWaitEvent(stream, D.last_use, 0));
+  // the copies are shared by all calls on this plan: order this call behind the others
+  if ((rc = D.uses.order(stream))) return rc;
   if (need > D.pack_cap) {
     if (D.pack_buf) {
       DMM_HIP(hipStreamSynchronize(stream));
@@ -1156,7 +1147,7 @@ int build_dense_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
   std::memcpy(h.data(), jobs.data(), jobs.size() * sizeof(PackJob));
   std::memcpy(h.data() + D.pack_o_tiles, tiles.data(), tiles.size() * sizeof(PackTile));
   std::memcpy(h.data() + D.pack_o_cuts, cuts.data(), cuts.size() * 4);
-  if ((rc = D.pack_table.upload(h.data(), h.size(), stream, busy_event(P)))) return rc;
+  if ((rc = D.pack_table.upload(h.data(), h.size(), stream, P->dev->uses))) return rc;
   L->dense = true;
   L->uses_split = true;
   return DMM_OK;
@@ -1179,7 +1170,7 @@ int launch_dense(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, bool time
   if (timed) DMM_HIP(hipEventRecord(D.t_pack[1], stream));
   const void *b = D.pack_b;
   rc = dmm_execute(D.dense, x.dtype, D.pack_a.data(), D.pack_lda.data(), &b, &D.pack_ldb, x.c_tiles, x.c_ld, x.flags, stream);
-  const int rc2 = mark_use(P, stream);      // (also behind a copy whose product failed)
+  const int rc2 = P->dev->uses.mark(stream);      // (also behind a copy whose product failed)
   if (rc || rc2) return rc ? rc : rc2;
   dmm_execute_report r;
   if ((rc = dmm_plan_last_execute(D.dense, &r))) return rc;
@@ -1324,7 +1315,7 @@ int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stre
     TraceRange tr("replica_sum");
     if ((rc = fire_reduce(P, L.red, stream, timed))) return rc;
   }
-  return mark_use(P, stream);
+  return P->dev->uses.mark(stream);
 }
 
 }  // namespace
@@ -1384,7 +1375,7 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
       P->dev->table_reused = true;
       if ((rc = (L.dense ? P->dev->pack_table : P->dev->gemm_table).order_behind_copy(stream))) return rc;
       // (the scratch buffer of macro-tiles cut along K is shared by all calls on this plan)
-      if (L.uses_split && P->dev->last_use_recorded) DMM_HIP(hipStreamWaitEvent(stream, P->dev->last_use, 0));
+      if (L.uses_split && (rc = P->dev->uses.order(stream))) return rc;
     } else {
       P->dev->exec_cached = false;
       P->dev->table_reused = false;
@@ -1488,7 +1479,7 @@ int dmm_reduce_replicas(dmm_plan_t *P, void *const *c_tiles, const int64_t *c_ld
     RedLaunch red;
     if ((rc = stage_reduce(P, c_tiles, c_ld, origin_replica, (hipStream_t)hip_stream, &red))) return rc;
     if ((rc = fire_reduce(P, red, (hipStream_t)hip_stream, false))) return rc;
-    return P->C.c > 1 ? mark_use(P, (hipStream_t)hip_stream) : DMM_OK;
+    return P->C.c > 1 ? P->dev->uses.mark((hipStream_t)hip_stream) : DMM_OK;
   } catch (const std::bad_alloc &) {
     return DMM_ENOMEM;
   }
@@ -1513,7 +1504,7 @@ int dmm_broadcast_replica(dmm_plan_t *P, void *const *c_tiles, const int64_t *c_
                        (const RedItem *)(d + L.o_items), (const RedTile *)(d + L.o_tiles),
                        (float *const *)(d + L.o_parts), (const int64_t *)(d + L.o_lds), L.nparts, L.vec_ok ? 1 : 0);
     DMM_HIP(hipGetLastError());
-    return mark_use(P, stream);
+    return P->dev->uses.mark(stream);
   } catch (const std::bad_alloc &) {
     return DMM_ENOMEM;
   }

@@ -1,0 +1,210 @@
+// A stand-in for the HIP runtime that runs no kernel: loaded in front of the library under test it
+// keeps a record of what the library enqueues where, and answers which of two operations is ordered
+// behind the other (stream order, events, host synchronisation).  Device memory is host memory
+// that is never read by anything but copies; its amount can be limited.  Test infrastructure: no GPU.
+#include <hip/hip_runtime_api.h>
+
+#include <cxxabi.h>
+#include <sys/mman.h>
+
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+namespace {
+
+struct Op {
+  std::string name;             // kernel, "copy", "event"
+  void *stream;
+  uint64_t arg, bytes;          // kernel: first eight bytes of its first argument; copy: destination and size
+  std::vector<int> behind;
+  int done_at = -1;             // known on the host to have finished before operation number done_at was enqueued
+};
+struct Stream {
+  int last = -1;
+  std::vector<int> waits;
+  bool capturing = false;
+};
+
+std::vector<Op> ops;
+std::map<void *, Stream> streams;
+std::map<void *, int> events;                       // the record it stands for, -1: none yet
+std::map<const void *, std::string> kernels;
+std::map<const void *, void *> symbols;
+std::map<void *, size_t> memory;
+size_t live = 0, limit = ~(size_t)0;
+hipError_t last_error = hipSuccess;
+dim3 cfg_grid, cfg_block;
+size_t cfg_lds;
+hipStream_t cfg_stream;
+
+hipError_t fail(hipError_t e) { return last_error = e; }
+
+int enqueue(const std::string &name, void *stream, uint64_t arg, uint64_t bytes) {
+  Stream &s = streams[stream];
+  Op o;
+  o.name = name;
+  o.stream = stream;
+  o.arg = arg;
+  o.bytes = bytes;
+  if (s.last >= 0) o.behind.push_back(s.last);
+  o.behind.insert(o.behind.end(), s.waits.begin(), s.waits.end());
+  s.waits.clear();
+  ops.push_back(o);
+  return s.last = (int)ops.size() - 1;
+}
+
+void finish(int i) {                                // the host has waited for operation i
+  if (i < 0 || ops[(size_t)i].done_at >= 0) return;
+  ops[(size_t)i].done_at = (int)ops.size();
+  for (int b : ops[(size_t)i].behind) finish(b);
+}
+
+void finish_all() {
+  for (size_t i = 0; i < ops.size(); ++i) finish((int)i);
+}
+
+bool before(int a, int b) {                         // a has finished when b starts, whatever the device does
+  if (a == b) return true;
+  if (ops[(size_t)a].done_at >= 0 && ops[(size_t)a].done_at <= b) return true;
+  for (int x : ops[(size_t)b].behind)
+    if (before(a, x)) return true;
+  return false;
+}
+
+void *fresh() {
+  static char *next = (char *)0x1000;
+  return next += 16;
+}
+
+}  // namespace
+
+extern "C" {
+
+// ---- for the test -----------------------------------------------------------------------------------
+int rec_count() { return (int)ops.size(); }
+const char *rec_name(int i) { return ops[(size_t)i].name.c_str(); }
+uint64_t rec_stream(int i) { return (uint64_t)ops[(size_t)i].stream; }
+uint64_t rec_arg(int i) { return ops[(size_t)i].arg; }
+uint64_t rec_bytes(int i) { return ops[(size_t)i].bytes; }
+int rec_before(int a, int b) { return before(a, b); }
+uint64_t rec_new_stream() { return (uint64_t)fresh(); }
+void rec_finish_stream(uint64_t s) { finish(streams[(void *)s].last); }
+void rec_set_capturing(uint64_t s, int on) { streams[(void *)s].capturing = on != 0; }
+void rec_set_limit(uint64_t bytes) { limit = bytes; }
+uint64_t rec_live() { return live; }
+
+// ---- the runtime ------------------------------------------------------------------------------------
+void **__hipRegisterFatBinary(const void *) { static void *h; return &h; }
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterFunction(void **, const void *host, char *, const char *device, unsigned, void *, void *, dim3 *, dim3 *, int *) {
+  int status = 0;
+  char *s = abi::__cxa_demangle(device, nullptr, nullptr, &status);
+  std::string n = status == 0 ? s : device;
+  free(s);
+  n = n.substr(0, n.find('('));
+  n = n.substr(0, n.find('<'));
+  const size_t at = n.rfind("dmm::");
+  kernels[host] = at == std::string::npos ? n : n.substr(at + 5);
+}
+void __hipRegisterVar(void **, void *var, char *, char *, int, size_t size, int, int) { symbols[var] = calloc(1, size); }
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
+  cfg_grid = grid;
+  cfg_block = block;
+  cfg_lds = lds;
+  cfg_stream = stream;
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *stream) {
+  *grid = cfg_grid;
+  *block = cfg_block;
+  *lds = cfg_lds;
+  *stream = cfg_stream;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipStream_t stream) {
+  uint64_t first;
+  memcpy(&first, args[0], sizeof first);
+  enqueue(kernels[f], stream, first, 0);
+  return hipSuccess;
+}
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) {
+  memset(p, 0, sizeof *p);
+  p->multiProcessorCount = 256;
+  return hipSuccess;
+}
+hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipGetLastError() {
+  hipError_t e = last_error;
+  last_error = hipSuccess;
+  return e;
+}
+hipError_t hipPeekAtLastError() { return last_error; }
+hipError_t hipGetSymbolAddress(void **p, const void *s) { *p = symbols[s]; return hipSuccess; }
+
+hipError_t hipMalloc(void **p, size_t n) {
+  if (live + n > limit) return fail(hipErrorOutOfMemory);
+  void *m = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+  if (m == MAP_FAILED) return fail(hipErrorOutOfMemory);
+  memory[*p = m] = n;
+  live += n;
+  return hipSuccess;
+}
+hipError_t hipFree(void *p) {
+  finish_all();                                     // (it waits for the device)
+  auto it = memory.find(p);
+  if (it == memory.end()) return fail(hipErrorInvalidValue);
+  munmap(p, it->second);
+  live -= it->second;
+  memory.erase(it);
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = malloc(n); return *p ? hipSuccess : fail(hipErrorOutOfMemory); }
+hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
+  finish_all();
+  memcpy(d, s, n);
+  return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t stream) {
+  memcpy(d, s, n);
+  enqueue("copy", stream, (uint64_t)d, n);
+  return hipSuccess;
+}
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)fresh(); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) {
+  Stream &t = streams[s];
+  finish(t.last);
+  for (int w : t.waits) finish(w);
+  return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *status) {
+  *status = streams[s].capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
+  *e = (hipEvent_t)fresh();
+  events[*e] = -1;
+  return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t *e) { return hipEventCreateWithFlags(e, 0); }
+hipError_t hipEventDestroy(hipEvent_t e) { events.erase(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+  events[e] = enqueue("event", s, (uint64_t)e, 0);
+  return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t e) { finish(events[e]); return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t e) {
+  const int i = events[e];
+  return i < 0 || ops[(size_t)i].done_at >= 0 ? hipSuccess : hipErrorNotReady;   // (not an error to be read back later)
+}
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0.125f; return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+  if (events[e] >= 0) streams[s].waits.push_back(events[e]);
+  return hipSuccess;
+}
+
+}  // extern "C"

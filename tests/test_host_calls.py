@@ -1,0 +1,199 @@
+"""What the device half of the library enqueues, without a GPU: the built library runs on top of a
+stand-in for the HIP runtime (tests/native/hip_recorder.cpp) that records launches, copies and events
+and knows which of them are ordered behind each other.  Device pointers are made-up numbers.  Every
+scenario runs in a process of its own, so that the stand-in is the only runtime the library sees."""
+import ctypes
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+if ROOT not in sys.path:
+    sys.path.insert(0, ROOT)
+
+import workloads  # noqa: E402
+
+
+# ---- inside the scenario's process --------------------------------------------------------------------
+
+class Recorder:
+    def __init__(self, path):
+        self.so = ctypes.CDLL(path, mode=ctypes.RTLD_GLOBAL)          # in front of the runtime the library names
+        for f in ("rec_stream", "rec_arg", "rec_bytes", "rec_new_stream", "rec_live"):
+            getattr(self.so, f).restype = ctypes.c_uint64
+        self.so.rec_name.restype = ctypes.c_char_p
+        for f in ("rec_finish_stream", "rec_set_limit"):
+            getattr(self.so, f).argtypes = [ctypes.c_uint64]
+        self.so.rec_set_capturing.argtypes = [ctypes.c_uint64, ctypes.c_int]
+
+    def stream(self):
+        return int(self.so.rec_new_stream())
+
+    def ops(self, start=0):
+        s = self.so
+        return [(i, s.rec_name(i).decode(), int(s.rec_stream(i)), int(s.rec_arg(i)), int(s.rec_bytes(i)))
+                for i in range(start, s.rec_count())]
+
+    def before(self, a, b):
+        return bool(self.so.rec_before(a, b))
+
+    def launches(self, start=0):
+        return [o for o in self.ops(start) if o[1] not in ("copy", "event")]
+
+    def check_tables(self):
+        """No table is overwritten under a kernel that reads it: a copy onto memory that the first
+        argument of an earlier launch lies in is ordered behind that launch, and a launch is ordered
+        behind the last copy onto the memory its first argument lies in."""
+        ops = self.ops()
+        for i, name, _, at, size in ops:
+            if name == "copy":
+                for j, other, _, arg, _ in ops[:i]:
+                    if other not in ("copy", "event") and at <= arg < at + size:
+                        assert self.before(j, i), f"copy {i} overwrites the table of {other} {j}"
+            elif name != "event":
+                copies = [j for j, other, _, to, n in ops[:i] if other == "copy" and to <= at < to + n]
+                if copies:
+                    assert self.before(copies[-1], i), f"{name} {i} does not wait for the copy of its table"
+
+
+
+
+def tables(desc, base, size, ld_multiple=8, off=0):
+    """Made-up device addresses and leading dimensions of a matrix' tiles."""
+    ptr, ld = [], []
+    for _ in range(desc["replication"]):
+        for r0, r1 in zip(desc["row_cuts"], desc["row_cuts"][1:]):
+            for c0, c1 in zip(desc["col_cuts"], desc["col_cuts"][1:]):
+                w = max(-(-(c1 - c0) // ld_multiple) * ld_multiple, 1)
+                ld.append(w)
+                ptr.append(base + off if r1 > r0 and c1 > c0 else None)
+                base += -(-(r1 - r0) * w * size // 512) * 512 + 512
+    return ptr, ld
+
+
+class Product:
+    """A plan and made-up tiles: `aligned` rows at multiples of 16 bytes, or packed 2-byte aligned ones."""
+
+    def __init__(self, descs, nranks, flags=0, dtype="bf16"):
+        from paper_2510_08874_amd import binding
+        self.b = binding
+        self.descs, self.plan = descs, binding.Plan(*descs, nranks, flags)
+        self.dtype = binding.DMM_BF16 if dtype == "bf16" else binding.DMM_F32
+        self.size = 2 if dtype == "bf16" else 4
+
+    def args(self, aligned=True, where=0):
+        a, b, c = self.descs
+        kw = dict(ld_multiple=8) if aligned else dict(ld_multiple=1, off=self.size)
+        base = (1 << 44) + (where << 40)
+        return self.plan.marshal(*tables(a, base, self.size, **kw), *tables(b, base + (1 << 38), self.size, **kw),
+                                 *tables(c, base + (2 << 38), 4, ld_multiple=4))
+
+    def run(self, args, flags=0, stream=0):
+        self.plan.execute_marshalled(self.dtype, args, flags, stream)
+
+
+def row_col(m, k, n, p=8):
+    block = workloads.block_desc
+    return block(m, k, p, 1), block(k, n, 1, p), block(m, n, 4, p // 4)
+
+
+def dense_calls_and_others_on_two_streams(rec):
+    """One plan, its calls alternating between operands that are copied first and operands that are not,
+    on two streams: a call's copies must not be made before the product that reads the copies of an
+    earlier call has finished, whatever ran in between on the other stream."""
+    p = Product(row_col(8192, 8192, 8192), 8)
+    s1, s2 = rec.stream(), rec.stream()
+    for other in ("aligned", "no merge"):
+        plain, flags = (p.args(), 0) if other == "aligned" else (p.args(False, 3), p.b.DMM_NO_MERGE)
+        seen = []
+        for args, fl, stream in ((plain, flags, s2), (p.args(False, 1), 0, s1), (plain, flags, s2), (p.args(False, 2), 0, s2)):
+            at = len(rec.ops())
+            p.run(args, fl, stream)
+            seen.append([(o[0], o[1]) for o in rec.launches(at)])
+        copied = [any(n == "pack_kernel" for _, n in call) for call in seen]
+        assert copied == [False, True, False, True], seen
+        last_reader, next_copy = seen[1][-1][0], seen[3][0][0]
+        assert rec.before(last_reader, next_copy), f"{other}: the copies of call 1 are overwritten under its product"
+        rec.check_tables()
+    p.plan.destroy()
+    rec.check_tables()
+
+
+def destroy_waits_for_every_stream(rec):
+    """A plan used on two streams gives its buffers back only when both have finished with them."""
+    p = Product(row_col(1024, 512, 1024), 8)
+    s1, s2 = rec.stream(), rec.stream()
+    args = p.args()
+    p.run(args, 0, s1)
+    p.run(args, 0, s2)                       # the same tables, not ordered behind the first call
+    readers = [o[0] for o in rec.launches()]
+    p.plan.destroy()
+    q = Product(row_col(1024, 520, 1024), 8)
+    q.run(q.args(), 0, rec.stream())         # may get the same buffer for its tables
+    rec.check_tables()
+    mark = rec.ops()[-1][0]
+    assert all(rec.before(r, mark) for r in readers)
+    q.plan.destroy()
+
+
+def scratch_is_not_shared_by_calls_that_overlap(rec):
+    """A replicated product cut along K on one stream, the replica sum alone on another, the product again
+    there: the partial tiles of the first call lie in the scratch buffer that the last one writes."""
+    block = workloads.block_desc
+    d = (block(512, 65536, 1, 1, replication=2), block(65536, 512, 1, 1, replication=2), block(512, 512, 1, 1, replication=2))
+    p = Product(d, 2)
+    s1, s2 = rec.stream(), rec.stream()
+    args = p.args()
+    c_ptr, c_ld = list(args[4]), list(args[5])
+    p.plan.reduce_replicas(c_ptr, c_ld, 0, s2)
+    p.run(args, 0, s1)
+    assert p.plan.ran_k_split()
+    first = [o[0] for o in rec.launches()][-1]
+    p.plan.reduce_replicas(c_ptr, c_ld, 0, s2)
+    at = len(rec.ops())
+    p.run(args, 0, s2)
+    again = rec.launches(at)[0][0]
+    assert rec.before(first, again), "the scratch buffer is overwritten under the first call"
+    rec.check_tables()
+    p.plan.destroy()
+
+
+def more_streams_than_the_plan_remembers(rec):
+    """Calls on many streams, then new operands: the new tables wait for every one of the calls."""
+    p = Product(row_col(1024, 512, 1024), 8)
+    args = p.args()
+    for _ in range(11):
+        p.run(args, 0, rec.stream())
+    p.run(p.args(where=1), 0, rec.stream())
+    rec.check_tables()
+    p.plan.destroy()
+
+
+SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
+             more_streams_than_the_plan_remembers]
+
+
+# ---- the tests ----------------------------------------------------------------------------------------
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("needs g++")
+    so = str(tmp_path_factory.mktemp("recorder") / "hip_recorder.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(ROOT, "tests", "native", "hip_recorder.cpp"), "-o", so], check=True, capture_output=True, text=True)
+    return so
+
+
+@pytest.mark.parametrize("scenario", [f.__name__ for f in SCENARIOS])
+def test_scenario(recorder, scenario):
+    run = subprocess.run([sys.executable, os.path.abspath(__file__), recorder, scenario], capture_output=True, text=True,
+                         cwd=ROOT, timeout=300)
+    assert run.returncode == 0, run.stdout[-2000:] + run.stderr[-4000:]
+
+
+if __name__ == "__main__":
+    {f.__name__: f for f in SCENARIOS}[sys.argv[2]](Recorder(sys.argv[1]))
