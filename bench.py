@@ -94,6 +94,19 @@ def parity_sample(prob, cfg, A, B, np, omatmul):
             "tolerance": 2e-3 if cfg["dtype"] == "bf16" else 1e-5}
 
 
+def kernels_of(plan, dtype):
+    """The kernels between the two events of the last timed execute on a plan whose replica sum, if any,
+    was not fused: gemm_ms covers all of them."""
+    small, es = plan.small_tile(), "2" if dtype == "bf16" else "4"
+    if small:
+        names = [f"small_gemm_kernel ({small[0]} x {small[1]} tiles)"] + (["small_sum_kernel"] if plan.last_kernels().small_runs > 1 else [])
+    else:
+        names = [f"grouped_gemm_comp_kernel<{es}>" if plan.ran_merged() else f"grouped_gemm_kernel<{es}, false>"]
+        if plan.ran_k_split():
+            names.append("sum_parts_kernel")
+    return " + ".join((["pack_kernel"] if plan.ran_dense() else []) + names)
+
+
 def short_run(name, ld_multiple, np, torch, workloads, binding, DeviceProblem, omatmul, steps=12, kernel_steps=12, dtype=None):
     """One of the other configurations: `steps` plan + execute steps between two synchronisations,
     then `kernel_steps` more with events around the kernels, then the parity sample."""
@@ -130,7 +143,7 @@ def short_run(name, ld_multiple, np, torch, workloads, binding, DeviceProblem, o
     for _ in range(kernel_steps):
         p = one(binding.DMM_TIMING | binding.DMM_SEPARATE_REDUCE)   # one GEMM launch, then the replica-sum kernel
         gm, rm = p.elapsed_ms()
-        ran_merged = p.ran_merged()
+        ran_merged, kernels = p.ran_merged(), kernels_of(p, cfg["dtype"])
         p.destroy()
         g.append(gm)
         r.append(rm)
@@ -139,7 +152,7 @@ def short_run(name, ld_multiple, np, torch, workloads, binding, DeviceProblem, o
            "ran_merged": ran_merged, "steps": steps,
            "ms_per_step": round(ms, 4), "value": round(fl / (ms * 1e-3) / 1e12, 2), "unit": "TFLOP/s",
            "pct_of_mfma_peak": round(100.0 * fl / (ms * 1e-3) / 1e12 / peak, 2),
-           "gemm_kernel": {"launch": "all macro-tiles in one launch", "avg_ms": round(float(np.mean(g)), 4), "median_ms": round(float(np.median(g)), 4),
+           "gemm_kernel": {"kernel": kernels, "avg_ms": round(float(np.mean(g)), 4), "median_ms": round(float(np.median(g)), 4),
                            "best_ms": round(float(np.min(g)), 4), "launches_timed": len(g),
                            "achieved": round(fl / (float(np.mean(g)) * 1e-3) / 1e12, 2), "peak": peak, "unit": "TFLOP/s",
                            "frac": round(fl / (float(np.mean(g)) * 1e-3) / 1e12 / peak, 4)},
@@ -376,7 +389,7 @@ def main() -> int:
         pl.num_tasks()
         pl.destroy()
     list_us = (time.perf_counter() - tp0) / 5 * 1e6
-    ran_merged = prob.plan.ran_merged()
+    ran_merged, plain_kernels = prob.plan.ran_merged(), kernels_of(prob.plan, cfg["dtype"])
 
     ms_per_step = (t1 - t0) * 1e3 / args.steps
     fl = workloads.flops(cfg)
@@ -415,7 +428,7 @@ def main() -> int:
                                 "epilogue adds the other replicas' partial sums (written by the same workgroup earlier "
                                 "in the launch)", partial_sum_bytes_read=sum_read, traffic=traffic.get("gemm_fused_bytes"))
     else:
-        roof = mfma_line("grouped_gemm_comp_kernel" if ran_merged else f"grouped_gemm_kernel<{es_tag}, false>", fl, gemm_ms,
+        roof = mfma_line(plain_kernels, fl, gemm_ms,
                          traffic=traffic.get("gemm_bytes"))
     achieved = roof["achieved"]
     fused_ran = fused_launches > 0

@@ -250,11 +250,11 @@ int dmm_reduce_replicas_static(dmm_plan_t *p, void *const *c_tiles, const int64_
 /* ---- measurement and test aids (not steps of the method) ---------------------------------- */
 
 /* What the last dmm_execute on a plan did.
- *   ran_merged    1: it ran tiles that span several tiles of A, B and C: the merged macro-tiles (the
- *                 plan has such a list, DMM_NO_MERGE was not given and the device grants a workgroup
- *                 the 160 KB of LDS their kernel asks for) or, in their place, the tiles of the
- *                 kernels for small products.  (A product that ran on dense copies of its operands
- *                 reports what ran there: only C's tiles are left to span.)
+ *   ran_merged    1: it ran the merged macro-tiles (the plan has such a list, DMM_NO_MERGE was not
+ *                 given, the device grants a workgroup the 160 KB of LDS their kernel asks for and
+ *                 neither the kernels for small products nor dense copies were taken instead), or
+ *                 merged macro-tiles on dense copies of the operands.  dmm_plan_last_kernels says
+ *                 which of these it was
  *   ran_k_split   1: it cut tiles along K (partial tiles through a scratch buffer, added up
  *                 in ascending k by a second kernel: the last round of workgroups would have left
  *                 most of the device idle, or a merged macro-tile had more K-segments than its
@@ -274,6 +274,19 @@ typedef struct {
   int32_t ran_merged, ran_k_split, ran_fused, table_reused;
 } dmm_execute_report;
 int dmm_plan_last_execute(const dmm_plan_t *p, dmm_execute_report *out);
+
+/* Which kernels the last dmm_execute on a plan ran in place of the macro-tile kernels on the operands
+ * as they are.
+ *   small_rows, small_cols   tile of the kernels for small products, where they ran (else 0)
+ *   small_runs               ranges of K their tiles were cut into (1: not cut; 0: they did not run)
+ *   ran_dense                1: A and B were copied to dense rows first (then dmm_execute_report tells
+ *                            which macro-tiles ran on the copies)
+ * All zero where the macro-tile kernels ran on the operands, for a plan that has not been executed,
+ * and for a null plan.  DMM_EINVAL if out is null. */
+typedef struct {
+  int32_t small_rows, small_cols, small_runs, ran_dense;
+} dmm_kernel_report;
+int dmm_plan_last_kernels(const dmm_plan_t *p, dmm_kernel_report *out);
 
 /* Device time of the kernels of the last dmm_execute(..., DMM_TIMING, ...) on this plan, in
  * milliseconds, excluding the work-table upload: gemm_ms from in front of the first GEMM launch
@@ -311,9 +324,9 @@ void dmm_plan_destroy(dmm_plan_t *p);
 
 const char *dmm_strerror(int status);
 int dmm_last_hip_error(void); /* hipError_t of the last failed HIP call on this thread, 0 if none */
-int dmm_version(void);         /* 4: the replica sum is fused into the GEMM unless DMM_SEPARATE_REDUCE asks
+int dmm_version(void);         /* 5: dmm_plan_last_kernels (4: the replica sum is fused into the GEMM unless DMM_SEPARATE_REDUCE asks
                                   for the kernel of its own; dmm_plan_last_execute replaces the
-                                  dmm_plan_ran_* accessors (3: flag values of dmm_plan and dmm_execute disjoint,
+                                  dmm_plan_ran_* accessors; 3: flag values of dmm_plan and dmm_execute disjoint,
                                   dmm_reduce_replicas_static) */
 
 #ifdef __cplusplus

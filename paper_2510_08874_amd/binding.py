@@ -67,6 +67,10 @@ class dmm_execute_report(C.Structure):
     _fields_ = [("ran_merged", C.c_int32), ("ran_k_split", C.c_int32), ("ran_fused", C.c_int32), ("table_reused", C.c_int32)]
 
 
+class dmm_kernel_report(C.Structure):
+    _fields_ = [("small_rows", C.c_int32), ("small_cols", C.c_int32), ("small_runs", C.c_int32), ("ran_dense", C.c_int32)]
+
+
 class DmmError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = status
@@ -111,6 +115,8 @@ def lib() -> C.CDLL:
         L.dmm_plan_merged_items.argtypes = [P]
         L.dmm_plan_last_execute.restype = C.c_int
         L.dmm_plan_last_execute.argtypes = [P, C.POINTER(dmm_execute_report)]
+        L.dmm_plan_last_kernels.restype = C.c_int
+        L.dmm_plan_last_kernels.argtypes = [P, C.POINTER(dmm_kernel_report)]
         L.dmm_plan_macro_tile.restype = C.c_int32
         L.dmm_plan_macro_tile.argtypes = [P]
         L.dmm_execute.restype = C.c_int
@@ -139,7 +145,7 @@ def lib() -> C.CDLL:
 
 EXPORTS = ("dmm_plan", "dmm_plan_num_tasks", "dmm_plan_tasks", "dmm_plan_order", "dmm_plan_num_groups",
            "dmm_plan_group_offsets", "dmm_plan_num_items", "dmm_plan_items", "dmm_plan_macro_tile",
-           "dmm_plan_num_merged_items", "dmm_plan_merged_items", "dmm_plan_last_execute",
+           "dmm_plan_num_merged_items", "dmm_plan_merged_items", "dmm_plan_last_execute", "dmm_plan_last_kernels",
            "dmm_reduce_replicas_static",
            "dmm_execute", "dmm_reduce_replicas", "dmm_broadcast_replica", "dmm_plan_elapsed_ms", "dmm_plan_gemm_launch_ms", "dmm_plan_destroy", "dmm_strerror",
            "dmm_last_hip_error", "dmm_version", "dmm_measure_mfma_rate")
@@ -242,6 +248,23 @@ class Plan:
 
     def ran_k_split(self) -> bool:
         return bool(self.last_execute().ran_k_split)
+
+    def last_kernels(self) -> "dmm_kernel_report":
+        """Which kernels the last execute ran in place of the macro-tiles on the operands (dmm_plan_last_kernels)."""
+        rep = dmm_kernel_report()
+        rc = lib().dmm_plan_last_kernels(self._h, C.byref(rep))
+        if rc != DMM_OK:
+            raise DmmError(rc, "dmm_plan_last_kernels")
+        return rep
+
+    def small_tile(self):
+        """(rows, columns) of the tiles of the kernels for small products, if the last execute ran them, else None."""
+        rep = self.last_kernels()
+        return (int(rep.small_rows), int(rep.small_cols)) if rep.small_rows else None
+
+    def ran_dense(self) -> bool:
+        """The last execute copied A and B to dense rows first."""
+        return bool(self.last_kernels().ran_dense)
 
     def macro_tile(self) -> int:
         return int(lib().dmm_plan_macro_tile(self._h))

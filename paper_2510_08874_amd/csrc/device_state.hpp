@@ -409,6 +409,7 @@ struct DeviceState {
   std::vector<int64_t> pack_lda;
   int64_t pack_ldb = 0;
   bool ran_dense = false;              // the last dmm_execute did so
+  int ran_small = -1, small_runs = 0;  // ... ran the kernels for small products: their shape, its tiles in so many ranges of K
   hipEvent_t t_pack[2] = {nullptr, nullptr};
   char *split_buf = nullptr;   // partial sums of K-split items
   size_t split_cap = 0;

@@ -993,7 +993,6 @@ int build_small_exec(dmm_plan_t *P, const ExecArgs &x, const SmallPlan &sp, hipS
       (rc = acquire_split_buffer(P, (size_t)sp.runs * sp.rows.size() * sp.cols.size() * (size_t)(kind.tm * kind.tn) * sizeof(float), stream)))
     return rc;
   if ((rc = P->dev->gemm_table.upload(h.data(), h.size(), stream, P->dev->uses))) return rc;
-  L->merged = P->merged.valid;
   L->uses_split = sp.runs > 1;
   return DMM_OK;
 }
@@ -1177,6 +1176,8 @@ int launch_dense(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, bool time
   D.ran_merged = r.ran_merged != 0;
   D.ran_k_split = r.ran_k_split != 0;
   D.ran_fused = r.ran_fused;
+  D.ran_small = D.dense->dev->ran_small;
+  D.small_runs = D.dense->dev->small_runs;
   D.ran_dense = true;
   return DMM_OK;
 }
@@ -1239,7 +1240,9 @@ int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stre
       DMM_HIP(hipEventRecord(P->dev->t_gemm[1], stream));
       P->dev->gemm_timed = true;
     }
-    P->dev->ran_merged = L.merged;
+    P->dev->ran_merged = false;
+    P->dev->ran_small = l.shape;
+    P->dev->small_runs = l.runs;
     P->dev->ran_k_split = l.runs > 1 || l.shape == SMALL_F32_TINY;   // (that shape's waves share a tile's K steps)
     P->dev->ran_fused = 0;
   } else if (L.merged) {
@@ -1406,6 +1409,7 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
       P->dev->exec_cached = true;
     }
     P->dev->ran_dense = false;
+    P->dev->ran_small = -1;
     if (L.dense) return launch_dense(P, x, stream, timed);
     return launch_exec(P, L, es, stream, timed);
   } catch (const std::bad_alloc &) {
@@ -1436,6 +1440,20 @@ int dmm_plan_last_execute(const dmm_plan_t *P, dmm_execute_report *out) {
   out->ran_k_split = P->dev->ran_k_split ? 1 : 0;
   out->ran_fused = P->dev->ran_fused;
   out->table_reused = P->dev->table_reused ? 1 : 0;
+  return DMM_OK;
+}
+
+int dmm_plan_last_kernels(const dmm_plan_t *P, dmm_kernel_report *out) {
+  using namespace dmm;
+  if (!out) return DMM_EINVAL;
+  *out = dmm_kernel_report{0, 0, 0, 0};
+  if (!P || !P->dev) return DMM_OK;
+  if (P->dev->ran_small >= 0) {
+    out->small_rows = kSmall[P->dev->ran_small].tm;
+    out->small_cols = kSmall[P->dev->ran_small].tn;
+    out->small_runs = P->dev->small_runs;
+  }
+  out->ran_dense = P->dev->ran_dense ? 1 : 0;
   return DMM_OK;
 }
 

@@ -740,6 +740,6 @@ const char *dmm_strerror(int status) {
   }
 }
 
-int dmm_version(void) { return 4; }
+int dmm_version(void) { return 5; }
 
 }  // extern "C"

@@ -50,8 +50,39 @@ def _run_full(cfg, ld_multiple=1):
     A64, B64 = _to_f64(A, cfg), _to_f64(B, cfg)
     C_ref = omatmul.matmul(A, B, bf16=(cfg["dtype"] == "bf16"))
     err = _check(C_gpu, C_ref, A64, B64, cfg, cfg["name"])
+    if prob.plan.small_tile() or prob.plan.ran_dense():
+        # the kernels for small products or dense copies ran: the macro-tiles on the operands as well
+        split = prob.plan.ran_k_split()
+        _macro_tiles(prob)
+        C_gpu2 = prob.c_global(0)
+        _check(C_gpu2, C_ref, A64, B64, cfg, cfg["name"] + " macro-tiles")
+        if not split and not prob.plan.ran_k_split():
+            assert np.array_equal(C_gpu, C_gpu2)
     prob.close()
     return err
+
+
+def _macro_tiles(prob):
+    """The product on the plan's own macro-tiles, into C tiles of NaN."""
+    from paper_2510_08874_amd import binding
+    for t in prob.C.tensors:
+        if t is not None:
+            t.fill_(float("nan"))
+    prob.execute(flags=binding.DMM_NO_MERGE)
+    assert prob.plan.small_tile() is None and not prob.plan.ran_dense()
+
+
+def _merged_problem(cfg, A, B, **kw):
+    """A problem whose plan has merged macro-tiles by itself, made to run these (DMM_MERGE_ALWAYS) and not
+    the kernels for small products or dense copies."""
+    plain = _device_problem(cfg, A, B, **kw)
+    assert plain.plan.num_merged_items() > 0
+    plain.close()
+    return _device_problem(dict(cfg, merge_always=True), A, B, **kw)
+
+
+def _ran_merged_itself(prob):
+    return prob.plan.ran_merged() and prob.plan.small_tile() is None and not prob.plan.ran_dense()
 
 
 # ---- element-by-element at sizes the oracle finishes in seconds ------------------
@@ -193,15 +224,17 @@ def test_k_split_of_the_last_round(dtype, dims, kcuts):
                dist=("normal", 1.0), seeds=(41, 42))
     A, B = workloads.make_operands(cfg)
     prob = _device_problem(cfg, A, B, c_fill=float("nan"))
-    prob.execute()
+    _macro_tiles(prob)
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:    # (the sizes above are cut for 256 CUs)
         assert prob.plan.ran_k_split()
     first = prob.c_global(0)
     A64, B64 = _to_f64(A, cfg), _to_f64(B, cfg)
     C_ref = omatmul.matmul(A, B, bf16=(dtype == "bf16"))
     _check(first, C_ref, A64, B64, cfg, cfg["name"])
-    prob.execute()
+    _macro_tiles(prob)
     assert np.array_equal(first, prob.c_global(0))
+    prob.execute()                                                          # whatever the library takes by itself
+    _check(prob.c_global(0), C_ref, A64, B64, cfg, cfg["name"] + " default")
     prob.close()
 
 
@@ -266,13 +299,13 @@ def test_repeated_execute_reuses_the_work_tables(name, dims, path):
     from paper_2510_08874_amd.tiles import TileSet
     cfg = workloads.scaled_config(name, *dims)
     A, B = workloads.make_operands(cfg)
-    prob = _device_problem(cfg, A, B, c_fill=float("nan"))
+    prob = (_merged_problem if path == "merged" else _device_problem)(cfg, A, B, c_fill=float("nan"))
     stream = torch.cuda.current_stream().cuda_stream
     c = cfg["C"]["replication"]
     base = 0 if path == "merged" else binding.DMM_NO_MERGE
     prob.execute(flags=base)
     assert not prob.plan.table_reused()
-    assert prob.plan.ran_merged() == (path == "merged")
+    assert prob.plan.ran_merged() == (path == "merged") and prob.plan.small_tile() is None
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
         assert prob.plan.ran_k_split() == (path == "k-split")
     first = [prob.c_global(r) for r in range(c)]
@@ -350,17 +383,24 @@ def _check_rows_streaming(prob, cfg, A, B, row_sets, what):
     return err
 
 
-@pytest.mark.parametrize("name,ldm", [("cfg2", 1), ("cfg4", 1), ("cfg5", 1), ("cfg5", 8), ("cfg3", 1), ("bc128", 1), ("bc256", 1)])
-def test_full_size_every_element(name, ldm):
+@pytest.mark.parametrize("name,ldm,path", [("cfg2", 1, ""), ("cfg4", 1, ""), ("cfg5", 1, "copies"), ("cfg5", 8, "copies"), ("cfg3", 1, ""),
+                                           ("bc128", 1, "copies"), ("bc256", 1, "copies"),
+                                           ("cfg5", 1, "direct"), ("cfg5", 8, "direct"), ("bc128", 1, "merged"), ("bc256", 1, "merged")])
+def test_full_size_every_element(name, ldm, path):
     """The configurations at full size, as the benchmark launches them (cfg5 also with leading
     dimensions padded to a multiple of 8 elements; 8192^3 in 128 x 128 and 256 x 256 tiles dealt
-    block-cyclically, which run the merged macro-tiles): every element of C against the oracle, in
+    block-cyclically), and those that run on dense copies of their operands also without (per-group
+    or merged macro-tiles on the operands as they are): every element of C against the oracle, in
     chunks of rows; and every element of every replica was written."""
+    from paper_2510_08874_amd import binding
     cfg = workloads.config(name)
     A, B = workloads.make_operands(cfg)
-    prob = _device_problem(cfg, A, B, ld_multiple=ldm, c_fill=float("nan"))
-    prob.execute()
+    prob = (_merged_problem if path == "merged" else _device_problem)(cfg, A, B, ld_multiple=ldm, c_fill=float("nan"))
+    prob.execute(flags=binding.DMM_NO_MERGE if path == "direct" else 0)
     torch.cuda.synchronize()
+    assert prob.plan.small_tile() is None
+    assert prob.plan.ran_dense() == (path == "copies")
+    assert path != "merged" or _ran_merged_itself(prob)
     step = 2048
     sets = [np.arange(r, min(r + step, cfg["M"])) for r in range(0, cfg["M"], step)]
     _check_rows_streaming(prob, cfg, A, B, sets, f"{name} ld x{ldm}")
@@ -384,6 +424,8 @@ def test_all_ones_gives_exactly_k(name, dims):
     prob.execute()
     C = prob.c_global(0)
     assert (C == np.float32(cfg["K"])).all()
+    _macro_tiles(prob)
+    assert (prob.c_global(0) == np.float32(cfg["K"])).all()
     prob.close()
 
 
@@ -399,6 +441,8 @@ def test_identity_reproduces_b_exactly(dtype):
         want = B
     prob = _device_problem(cfg, A, B)
     prob.execute()
+    assert np.array_equal(prob.c_global(0), want)
+    _macro_tiles(prob)
     assert np.array_equal(prob.c_global(0), want)
     prob.close()
 
@@ -419,11 +463,12 @@ def test_run_to_run_bitwise_identical():
 
 # ---- edges ----------------------------------------------------------------------------
 
-def test_padding_of_c_is_never_written():
+@pytest.mark.parametrize("flags", [0, 0x800], ids=["default", "no_merge"])
+def test_padding_of_c_is_never_written(flags):
     cfg = workloads.scaled_config("cfg5", 523, 300, 517)
     A, B = workloads.make_operands(cfg)
     prob = _device_problem(cfg, A, B, ld_multiple=16, c_fill=-7.0)
-    prob.execute()
+    prob.execute(flags=flags)
     torch.cuda.synchronize()
     for idx, t in enumerate(prob.C.tensors):
         ti, tj = divmod(idx % (prob.C.gr * prob.C.gc), prob.C.gc)
@@ -596,6 +641,12 @@ def test_bf16_c_tiles(name, dims, ldm):
         r0, r1, c0, c1 = prob.C.bounds(ti, tj)
         if t is not None and ld > c1 - c0:
             assert torch.isnan(t[:, c1 - c0:]).all(), "padding of a bf16 C tile was written"
+    if prob.plan.small_tile():                       # the macro-tiles' own epilogue too
+        split = prob.plan.ran_k_split()
+        _macro_tiles(prob)
+        got2 = prob.c_global(0)
+        _check_bf16_out(got2, C_ref, A64, B64, cfg["name"] + " macro-tiles")
+        assert split or prob.plan.ran_k_split() or np.array_equal(got, got2)
     prob.close()
     wide = _device_problem(cfg, A, B, ld_multiple=ldm, c_fill=float("nan"))
     wide.execute()
@@ -617,6 +668,10 @@ def test_bf16_c_tiles_k_split_and_zero_fill():
     _check_bf16_out(got, omatmul.matmul(A, B, bf16=True), _to_f64(A, cfg), _to_f64(B, cfg), cfg["name"])
     prob.execute()
     assert np.array_equal(got, prob.c_global(0))
+    _macro_tiles(prob)
+    got = prob.c_global(0)
+    assert prob.plan.ran_k_split()
+    _check_bf16_out(got, omatmul.matmul(A, B, bf16=True), _to_f64(A, cfg), _to_f64(B, cfg), cfg["name"] + " macro-tiles")
     prob.close()
     cfg = dict(name="k0-bf16out", M=40, K=0, N=30, dtype="f32", nranks=2,
                A=workloads.block_desc(40, 0, 2, 1), B=workloads.block_desc(0, 30, 1, 2),
@@ -672,10 +727,9 @@ def test_merged_macro_tiles(dims, nb, dtype, ldm, reps, p):
     from paper_2510_08874_amd import binding
     cfg = _bc(dims, nb, dtype, reps, p)
     A, B = workloads.make_operands(cfg)
-    prob = _device_problem(cfg, A, B, ld_multiple=ldm, c_fill=float("nan"))
-    assert prob.plan.num_merged_items() > 0
+    prob = _merged_problem(cfg, A, B, ld_multiple=ldm, c_fill=float("nan"))
     prob.execute()
-    assert prob.plan.ran_merged()
+    assert _ran_merged_itself(prob)
     merged_cut = prob.plan.ran_k_split()
     got = prob.c_global(0)
     A64, B64 = _to_f64(A, cfg), _to_f64(B, cfg)
@@ -732,15 +786,14 @@ def test_merged_macro_tiles_stationary_b_and_a(mode):
     on other ranks, so its merged macro-tiles are the same and so is C, bit for bit."""
     cfg = _bc((700, 333, 517), 96, "bf16")
     A, B = workloads.make_operands(cfg)
-    ref = _device_problem(cfg, A, B, c_fill=float("nan"))
+    ref = _merged_problem(cfg, A, B, c_fill=float("nan"))
     ref.execute()
     want = ref.c_global(0)
     ref.close()
-    prob = _device_problem(dict(cfg, stationary=mode), A, B, c_fill=float("nan"))
-    assert prob.plan.num_merged_items() > 0
+    prob = _merged_problem(dict(cfg, stationary=mode), A, B, c_fill=float("nan"))
     assert {t[0] for t in prob.plan.tasks()} == set(range(8))
     prob.execute()
-    assert prob.plan.ran_merged()
+    assert _ran_merged_itself(prob)
     assert np.array_equal(want, prob.c_global(0))
     _check(want, omatmul.matmul(A, B, bf16=True), _to_f64(A, cfg), _to_f64(B, cfg), cfg, cfg["name"])
     prob.close()
@@ -756,10 +809,10 @@ def test_merged_macro_tiles_k_split_of_the_last_round(dims, nb, dtype, c_dtype):
     adds the partial tiles up writes every piece to its own C tile.  Parity, rerun bitwise equal."""
     cfg = _bc(dims, nb, dtype)
     A, B = workloads.make_operands(cfg)
-    prob = _device_problem(cfg, A, B, c_fill=float("nan"), c_dtype=c_dtype)
+    prob = _merged_problem(cfg, A, B, c_fill=float("nan"), c_dtype=c_dtype)
     assert 0 < prob.plan.num_merged_items() <= 8
     prob.execute()
-    assert prob.plan.ran_merged()
+    assert _ran_merged_itself(prob) and prob.plan.ran_k_split()
     got = prob.c_global(0)
     A64, B64 = _to_f64(A, cfg), _to_f64(B, cfg)
     C_ref = omatmul.matmul(A, B, bf16=(dtype == "bf16"))
@@ -776,9 +829,9 @@ def test_merged_macro_tiles_bf16_c_and_rerun():
     from paper_2510_08874_amd import binding
     cfg = _bc((700, 333, 517), 96, "bf16")
     A, B = workloads.make_operands(cfg)
-    prob = _device_problem(cfg, A, B, c_fill=float("nan"), c_dtype="bf16")
-    assert prob.plan.num_merged_items() > 0
+    prob = _merged_problem(cfg, A, B, c_fill=float("nan"), c_dtype="bf16")
     prob.execute()
+    assert _ran_merged_itself(prob)
     got = prob.c_global(0)
     _check_bf16_out(got, omatmul.matmul(A, B, bf16=True), _to_f64(A, cfg), _to_f64(B, cfg), cfg["name"])
     prob.execute()
@@ -795,8 +848,7 @@ def test_merged_macro_tiles_across_a_4gb_line():
     from paper_2510_08874_amd import binding
     cfg = _bc((300, 520, 300), 64, "bf16")
     A, B = workloads.make_operands(cfg)
-    prob = _device_problem(cfg, A, B, c_fill=float("nan"))
-    assert prob.plan.num_merged_items() > 0
+    prob = _merged_problem(cfg, A, B, c_fill=float("nan"))
     prob.execute()
     want = prob.c_global(0)
     big = torch.empty((1 << 32) + (64 << 20), dtype=torch.uint8, device="cuda")
@@ -818,7 +870,7 @@ def test_merged_macro_tiles_across_a_4gb_line():
             if t is not None:
                 t.fill_(float("nan"))
         prob.execute()
-        assert prob.plan.ran_merged()
+        assert _ran_merged_itself(prob)
         assert np.array_equal(want, prob.c_global(0))
         ts.tensors[:] = kept
     C_ref = omatmul.matmul(A, B, bf16=True)

@@ -172,8 +172,56 @@ def more_streams_than_the_plan_remembers(rec):
     p.plan.destroy()
 
 
+def reports_say_what_ran(rec):
+    """dmm_plan_last_execute and dmm_plan_last_kernels against the launches of every kind of call."""
+    cyclic = workloads.block_cyclic_desc
+    s = rec.stream()
+
+    def check(p, args, flags, kernels, merged=False, small=None, dense=False, split=False, fused=0):
+        at = len(rec.ops())
+        p.run(args, flags, s)
+        got = [o[1] for o in rec.launches(at)]
+        assert got == kernels, got
+        rep = p.plan.last_execute()
+        assert (bool(rep.ran_merged), bool(rep.ran_k_split), rep.ran_fused) == (merged, split, fused), (merged, split, fused)
+        assert p.plan.small_tile() == small and p.plan.ran_dense() == dense, (p.plan.small_tile(), p.plan.ran_dense())
+
+    def fine(m, k, n, flags=0):              # tiles finer than the macro-tile: the plan has a merged list
+        p = Product((cyclic(m, k, 128, 128, 2, 4, 1), cyclic(k, n, 128, 128, 2, 4, 1), cyclic(m, n, 128, 128, 2, 4, 1)), 8, flags)
+        assert p.plan.num_merged_items() > 0
+        return p
+
+    p = fine(700, 333, 517)
+    check(p, p.args(), 0, ["small_gemm_kernel"], small=(32, 128))
+    check(p, p.args(), p.b.DMM_NO_MERGE, ["grouped_gemm_kernel"])
+    check(p, p.args(), 0, ["small_gemm_kernel"], small=(32, 128))
+    q = fine(700, 333, 517, p.b.DMM_MERGE_ALWAYS)
+    check(q, q.args(), 0, ["grouped_gemm_comp_kernel"], merged=True)
+    q = fine(700, 18000, 500, p.b.DMM_MERGE_ALWAYS)
+    check(q, q.args(), 0, ["grouped_gemm_comp_kernel", "sum_parts_kernel"], merged=True, split=True)
+    q = Product(row_col(8192, 8192, 8192), 8)                              # no merged list
+    assert q.plan.num_merged_items() == 0
+    check(q, q.args(), 0, ["grouped_gemm_kernel"])
+    q = Product(row_col(256, 256, 256, 4), 4, dtype="f32")                 # four waves share a tile's K
+    check(q, q.args(), 0, ["small_gemm_kernel"], small=(32, 32), split=True)
+    q = Product(row_col(2048, 2048, 2048), 8)
+    assert q.plan.num_merged_items() == 0
+    check(q, q.args(), 0, ["small_gemm_kernel"], small=(128, 128))
+    assert q.plan.last_kernels().small_runs == 1
+    q = Product(row_col(1024, 16384, 1024), 8)
+    check(q, q.args(), 0, ["small_gemm_kernel", "small_sum_kernel"], small=(128, 128), split=True)
+    assert q.plan.last_kernels().small_runs > 1
+    cfg = workloads.config("cfg4")
+    q = Product((cfg["A"], cfg["B"], cfg["C"]), cfg["nranks"])
+    check(q, q.args(), 0, ["grouped_gemm_kernel"], fused=1)
+    check(q, q.args(), q.b.DMM_SEPARATE_REDUCE, ["grouped_gemm_kernel", "reduce_replicas_kernel"])
+    q = fine(8192, 8192, 8192)
+    check(q, q.args(False), 0, ["pack_kernel", "grouped_gemm_comp_kernel"], merged=True, dense=True)
+    check(q, q.args(False), q.b.DMM_NO_MERGE, ["grouped_gemm_kernel"])
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
-             more_streams_than_the_plan_remembers]
+             more_streams_than_the_plan_remembers, reports_say_what_ran]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------

@@ -180,6 +180,10 @@ def test_null_arguments_rejected():
     rep = binding.dmm_execute_report(7, 7, 7, 7)
     assert L.dmm_plan_last_execute(None, rep) == binding.DMM_OK
     assert (rep.ran_merged, rep.ran_k_split, rep.ran_fused, rep.table_reused) == (0, 0, 0, 0)
+    assert L.dmm_plan_last_kernels(None, None) == binding.DMM_EINVAL
+    ker = binding.dmm_kernel_report(7, 7, 7, 7)
+    assert L.dmm_plan_last_kernels(None, ker) == binding.DMM_OK
+    assert (ker.small_rows, ker.small_cols, ker.small_runs, ker.ran_dense) == (0, 0, 0, 0)
     assert L.dmm_plan_gemm_launch_ms(None, None, None) == binding.DMM_EINVAL
     ok = dict(rows=8, cols=8, row_cuts=(0, 8), col_cuts=(0, 8), proc_rows=1, proc_cols=1, replication=1)
     fresh = binding.Plan(ok, ok, ok, 1)
