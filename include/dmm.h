@@ -138,7 +138,7 @@ typedef struct {
  * inside the macro-tile a column piece starts at a multiple of 8 columns.  One workgroup
  * accumulates it over the K-segments of the replica's share of k in ascending k, exactly as the
  * macro-tiles of dmm_plan_items do for their group, so both lists give bitwise the same C (except
- * where dmm_execute cuts the last round of one list along K and not of the other: see there). */
+ * where dmm_execute cuts tiles of one list along K and not of the other: see there). */
 typedef struct {
   int64_t m0, n0;
   int32_t m_ext, n_ext;
@@ -188,7 +188,8 @@ int32_t dmm_plan_macro_tile(const dmm_plan_t *p);           /* edge of the squar
  * of k, and (c) merging saves at least a tenth of the macro-tiles (tile grids much finer than the
  * macro-tile: block-cyclic layouts), or the op list is long against the work list (at least 4096
  * ops and 16 per macro-tile), so that running from the factored form saves the host the time to
- * write the list out.  dmm_execute then runs this list instead of dmm_plan_items. */
+ * write the list out.  dmm_execute then runs this list instead of dmm_plan_items (unless the kernels
+ * for small products or dense copies take its place: see there). */
 int64_t dmm_plan_num_merged_items(const dmm_plan_t *p);
 const dmm_merged_item *dmm_plan_merged_items(const dmm_plan_t *p);
 
@@ -207,10 +208,16 @@ const dmm_merged_item *dmm_plan_merged_items(const dmm_plan_t *p);
  * of macro-tiles leaves most of the device idle in the last round of workgroups,
  * those macro-tiles are cut along K into runs whose partial sums go through a
  * scratch buffer and are added in ascending k (fixed cut, fixed order: results
- * stay bitwise reproducible on a given device).  The first call on a plan takes
- * the plan's device work table (and, if needed, that scratch buffer) from a
- * process-wide pool, allocating only when the pool has none that fits; later
- * calls with the same arguments allocate nothing and do not synchronise. */
+ * stay bitwise reproducible on a given device).  Products that macro-tiles would fill
+ * badly run on kernels for small products instead, and large bf16 products whose rows are
+ * not 16-byte aligned or whose K is finely cut run on dense copies of A and B made in
+ * the call, where an estimate finds that faster (DMM_NO_MERGE keeps the macro-tiles;
+ * dmm_plan_last_kernels tells).  The shape, the element types and the device decide
+ * how the sums are cut along K: the copies, which a call takes or not by where its
+ * operands lie and by what memory is free, leave the bits of the result as they are.
+ * The first call on a plan takes the plan's device work table (and, if needed, that
+ * scratch buffer) from a process-wide pool, allocating only when the pool has none that
+ * fits; later calls with the same arguments allocate nothing and do not synchronise. */
 int dmm_execute(dmm_plan_t *p, int dtype,
                 const void *const *a_tiles, const int64_t *a_ld,
                 const void *const *b_tiles, const int64_t *b_ld,

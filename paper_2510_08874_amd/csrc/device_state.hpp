@@ -403,7 +403,7 @@ struct DeviceState {
   int pack_device = 0;
   Uploader pack_table;
   int pack_jobs = 0, pack_blocks = 0;
-  size_t pack_o_tiles = 0, pack_o_cuts = 0;
+  size_t pack_o_tiles = 0, pack_o_runs = 0;
   char *pack_b = nullptr;              // the copy of B
   std::vector<const void *> pack_a;    // the copy of A, one tile per replica of C
   std::vector<int64_t> pack_lda;

@@ -246,7 +246,7 @@ int acquire_split_buffer(dmm_plan_t *P, size_t need, hipStream_t stream) {
 
 int build_merged_tables(dmm_plan_t *P, int64_t es, int64_t bk, int64_t c_es, const void *const *a_tiles,
                         const int64_t *a_ld, const void *const *b_tiles, const int64_t *b_ld, void *const *c_tiles,
-                        const int64_t *c_ld, int cus, hipStream_t stream, std::vector<char> *hp, MergedLaunch *L) {
+                        const int64_t *c_ld, int cus, bool uncut, hipStream_t stream, std::vector<char> *hp, MergedLaunch *L) {
   const Merged &G = P->merged;
   const Grid &A = P->A, &B = P->B, &C = P->C;
   const size_t MR = G.mc.size() - 1, NR = G.nc.size() - 1;
@@ -380,7 +380,9 @@ int build_merged_tables(dmm_plan_t *P, int64_t es, int64_t bk, int64_t c_es, con
     if (G.window > 0 && items[x].S > G.window) want[x] = (items[x].S + G.window - 1) / G.window;
     total += (size_t)want[x];
   }
-  if (total <= (size_t)cus / 2) {
+  if (uncut) {
+    // (and the plan has no windows)
+  } else if (total <= (size_t)cus / 2) {
     const int32_t f = (int32_t)((size_t)cus / total);
     for (size_t x = 0; x < n_whole; ++x) want[x] *= f;
   } else if (G.window == 0) {
@@ -539,6 +541,7 @@ struct ExecArgs {
   const int64_t *c_ld;
   uint32_t flags;
   int device;
+  bool uncut;                   // no list is cut along K (see choose_dense)
 };
 
 // Work tables of the merged macro-tiles:  merged tables | replica-sum tables, one copy.
@@ -550,7 +553,7 @@ int build_merged_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, Exec
   h.clear();
   int cus = 0;
   if ((rc = device_cus(&cus))) return rc;
-  if ((rc = build_merged_tables(P, x.es, x.bk, x.c_es, x.a_tiles, x.a_ld, x.b_tiles, x.b_ld, x.c_tiles, x.c_ld, cus, stream, &h, &ml)))
+  if ((rc = build_merged_tables(P, x.es, x.bk, x.c_es, x.a_tiles, x.a_ld, x.b_tiles, x.b_ld, x.c_tiles, x.c_ld, cus, x.uncut, stream, &h, &ml)))
     return rc;
   if (!(x.flags & DMM_NO_REDUCE) && (rc = build_reduce(P, x.c_tiles, x.c_ld, 0, &h, ml.total, &red))) return rc;
   if ((rc = P->dev->gemm_table.upload(h.data(), h.size(), stream, P->dev->uses))) return rc;
@@ -638,7 +641,7 @@ int build_group_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
   if ((rc = device_cus(&cus))) return rc;
   size_t working = 0;
   for (const ItemDev &d : hi) working += d.nsteps > 0;
-  const size_t tail = working % (size_t)cus;
+  const size_t tail = x.uncut ? 0 : working % (size_t)cus;
   size_t n_runs = 0;
   if (tail > 0 && tail <= (size_t)cus / 2) {
     const int32_t max_runs = (int32_t)((size_t)cus / tail);
@@ -842,7 +845,7 @@ int64_t count_steps(const std::vector<int64_t> &kc, int64_t bk) {
 void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
   const Grid &A = P->A, &B = P->B, &C = P->C;
   const int64_t M = C.rows, K = A.cols, N = C.cols, lim = (int64_t)1 << 30;
-  if (C.c != 1 || M <= 0 || K <= 0 || N <= 0 || M >= lim || K >= lim || N >= lim) return;
+  if (P->dense_copy || C.c != 1 || M <= 0 || K <= 0 || N <= 0 || M >= lim || K >= lim || N >= lim) return;
   if ((P->flags & DMM_MERGE_ALWAYS) || (x.flags & DMM_NO_MERGE)) return;      // the caller named a work list
   SmallPlan c;
   c.mc = merged_cuts({&A.rc, &C.rc});
@@ -999,62 +1002,137 @@ int build_small_exec(dmm_plan_t *P, const ExecArgs &x, const SmallPlan &sp, hipS
 
 // ---- products on dense copies of their operands (pack_kernel.hpp) -----------------------------------
 
-// Whether the rows of an operand's tiles, from some K-segment or column on, start at addresses that
-// are not multiples of 16 bytes.
-bool misaligned(const Grid &G, const void *const *tiles, const int64_t *ld, const std::vector<int64_t> &cuts) {
+// The share of an operand's columns in K-segments (column intervals) that begin inside their tile's rows
+// at positions that are not multiples of 16 bytes,
+double cut_misaligned(const Grid &G, const std::vector<int64_t> &cuts) {
+  int64_t odd = 0;
+  for (size_t i = 0; i + 1 < cuts.size(); ++i) {
+    const int64_t in = cuts[i] - *(std::upper_bound(G.cc.begin(), G.cc.end(), cuts[i]) - 1);
+    if (in & 7) odd += cuts[i + 1] - cuts[i];
+  }
+  return (double)odd / (double)std::max<int64_t>(1, cuts.back());
+}
+
+// and whether rows of its tiles do.
+bool placed_misaligned(const Grid &G, const void *const *tiles, const int64_t *ld) {
   for (int32_t i = 0; i < G.gr; ++i)
     for (int32_t j = 0; j < G.gc; ++j)
       if (G.rc[i + 1] > G.rc[i] && G.cc[j + 1] > G.cc[j]) {
         const int64_t x = G.table_index(0, i, j);
         if (((uintptr_t)tiles[x] & 15) || (ld[x] & 7)) return true;
       }
-  for (int64_t c : cuts) {              // where segments (column intervals) begin inside their tiles
-    const int64_t in = c - *(std::upper_bound(G.cc.begin(), G.cc.end(), c) - 1);
-    if (in & 7) return true;
-  }
   return false;
 }
 
-// Whether a large bf16 product pays for dense copies of A and B: the estimated time of the copy plus
-// the macro-tiles on it against that of the macro-tiles on the operands as they are.  A K step of
-// rows that are not 16-byte aligned costs 1.27 of an aligned one (8192^3 against 8190^3 packed: 1127
-// and 1428 cycles), a segment one and a half more steps, a macro-tile that spans tiles 1.13; the copy
-// runs at 4.5 TB/s and more (0.93 GB in 190 us).  Measured, us per call on the operands -> on copies:
-// 12289 x 9973 x 11003 in uneven packed tiles 3075 -> 2320, the same with rows padded to 16 bytes 2766 ->
-// 2294; 8192^3 in 128 x 128 block-cyclic tiles 1074 -> 984; 4096 x 4032 x 8152 in 100 x 100 ones, packed,
-// 454 -> 299; 11168 x 7584 x 2304 (two rounds either way, the copy as long as what it saves) 518 against
-// 545: stays.
-bool choose_dense(const dmm_plan_t *P, const ExecArgs &x, int cus) {
+// How the copies hold K: one share per replica of C, each of `len` columns of A's copy (rows of B's).
+// The K-segments of a share start at multiples of a K step and are filled up with zeros; where the
+// shares differ in length, zeros stand in front (sums that start at zero do not change by adding zero).
+struct DenseShape {
+  std::vector<int64_t> shares;        // where the shares begin in K, and K
+  std::vector<int64_t> kc;            // the segments' cuts
+  std::vector<int32_t> share;         // of every segment
+  std::vector<int64_t> at;            // where a segment begins inside its share of the copy
+  int64_t len = 0;
+};
+
+void dense_shape(const dmm_plan_t *P, int64_t bk, DenseShape *shape) {
+  DenseShape &d = *shape;
+  const int64_t K = P->A.cols, c = P->C.c;
+  for (int64_t r = 0; r <= c; ++r) d.shares.push_back(r * K / c);
+  d.kc = merged_cuts({&P->A.cc, &P->B.rc, &d.shares});
+  std::vector<int64_t> len((size_t)c, 0);
+  for (size_t s = 0; s + 1 < d.kc.size(); ++s) {
+    const int32_t r = (int32_t)(std::upper_bound(d.shares.begin(), d.shares.end(), d.kc[s]) - d.shares.begin()) - 1;
+    d.share.push_back(r);
+    d.at.push_back(len[(size_t)r]);
+    len[(size_t)r] += (d.kc[s + 1] - d.kc[s] + bk - 1) / bk * bk;
+  }
+  for (int64_t l : len) d.len = std::max(d.len, l);
+  for (size_t s = 0; s < d.at.size(); ++s) d.at[s] += d.len - len[(size_t)d.share[s]];
+}
+
+constexpr int64_t kDenseMost = (int64_t)2 << 30;      // bytes of copies a product may ask for
+
+// leading dimension of a copy with that many columns
+int64_t dense_ld(int64_t cols) { return (cols + 63) & ~(int64_t)63; }
+
+int64_t dense_bytes(const dmm_plan_t *P, const DenseShape &d) {
+  return 2 * P->C.c * (P->C.rows * dense_ld(d.len) + d.len * dense_ld(P->C.cols));
+}
+
+// Whether macro-tiles of a list of `n` would be cut along K to fill its last round.
+bool last_round_is_cut(int64_t n, int64_t steps, int64_t es, int cus) {
+  const int64_t tail = n % cus;
+  return tail > 0 && tail <= cus / 2 && steps >= 2 * min_run_steps(es);
+}
+
+// Whether a segment list is too long for a merged macro-tile's descriptors (which is then cut along K).
+bool in_windows(const dmm_plan_t *P) {
+  if (!P->merged.valid || P->merged.window <= 0) return false;
+  for (const MergedRep &R : P->merged.reps)
+    if ((int64_t)R.kc.size() - 1 > P->merged.window) return true;
+  return false;
+}
+
+// Whether a large bf16 product runs on dense copies of A and B: the estimated time of the copy plus
+// the macro-tiles on it against that of the macro-tiles on the operands as they are.  The copies
+// must not show in the result, since a call takes them or not by where its operands lie and by what
+// memory is free: they hold the very K steps of the operands (pack_kernel.hpp) and their list is
+// never cut along K, so the bits are those of the product's own list uncut.  Where that list would be
+// cut, the shape alone decides: either such a product always runs uncut (*uncut: on the copies, or on
+// its own list where it cannot have them), or it never runs on copies.
+// A K step takes 1.27 of the time where segments (a tenth of them and more) begin at odd places, 1.12 where
+// rows do (8102 x 4002 x 8102 in 2 x 2 tiles packed against padded rows: 544 and 486 us), a segment another step and a half, a
+// macro-tile that spans tiles 1.13; the copy runs at 4.5 TB/s and more (0.93 GB in 165 us).  Measured, us per call on the operands -> on
+// copies: 12289 x 9973 x 11003 in uneven packed tiles 3040 -> 2320, the same with rows padded to 16 bytes
+// 2750 -> 2330; 8192^3 in block-cyclic tiles of 128 1035 -> 980, of 256 960 -> 940; 6784 x 3003 x 7824 in
+// 100 x 100 ones, packed, 1890 -> 985; 12223 x 8751 x 2891 uneven (three rounds either way) stays.
+bool choose_dense(const dmm_plan_t *P, const ExecArgs &x, bool given, int cus, bool *uncut) {
   const Grid &A = P->A, &B = P->B, &C = P->C;
   const int64_t M = C.rows, K = A.cols, N = C.cols, lim = (int64_t)1 << 30;
   if (x.es != 2 || P->dense_copy || (P->flags & DMM_MERGE_ALWAYS) || (x.flags & DMM_NO_MERGE)) return false;
+  if (P->merged.valid && !g_comp_ok[x.device]) return false;
   if ((P->flags & (DMM_STATIONARY_B | DMM_STATIONARY_A)) && (A.c != 1 || B.c != 1 || C.c != 1)) return false;   // (their replicas do not split K)
   if (M < 1024 || N < 1024 || K < 1024 * (int64_t)C.c || M >= lim || K >= lim || N >= lim) return false;
   if (A.tiles_per_rep() + B.tiles_per_rep() > 65536) return false;
   const double bytes = 2.0 * ((double)M * K + (double)K * N);
-  if (bytes > 2.0e9) return false;
+  if (bytes > (double)kDenseMost) return false;
   size_t items = 0;
   if (P->merged.valid) items = P->merged.items.size();
   else
     for (const dmm_work_item &w : P->items) items += w.group >= 0;
   if (items < (size_t)cus) return false;
+  DenseShape d;
+  dense_shape(P, x.bk, &d);
+  if (dense_bytes(P, d) > kDenseMost) return false;
   int64_t dense_items = 0, merged_items = 0;
   for (int32_t i = 0; i < C.gr; ++i)
     for (int32_t j = 0; j < C.gc; ++j)
       dense_items += ((C.rc[i + 1] - C.rc[i] + kMacroTile - 1) / kMacroTile) * ((C.cc[j + 1] - C.cc[j] + kMacroTile - 1) / kMacroTile);
   merged_items = ((M + kMacroTile - 1) / kMacroTile) * ((N + kMacroTile - 1) / kMacroTile);
   const bool merge = merged_items * 10 <= dense_items * 9;            // (what dmm_plan will choose)
-  const std::vector<int64_t> kc = merged_cuts({&A.cc, &B.rc}), nc = merged_cuts({&B.cc, &C.cc});
-  const double steps = (double)K / C.c / (double)x.bk, segs = (double)(kc.size() - 1) / C.c, us = 0.72;
-  const bool odd = misaligned(A, x.a_tiles, x.a_ld, kc) || misaligned(B, x.b_tiles, x.b_ld, nc);
-  // rounds of macro-tiles; the last one is cut along K where it is at most half full
-  auto rounds = [&](int64_t n) {
-    const int64_t tail = n % cus, runs = tail > 0 && tail <= cus / 2 ? std::min<int64_t>(cus / tail, (int64_t)steps / MIN_RUN) : 1;
-    return (double)(n / cus) + (tail > 0 ? 1.0 / (double)std::max<int64_t>(1, runs) : 0.0);
-  };
-  const double now = rounds((int64_t)items) * (steps + 1.5 * segs) * us * (odd ? 1.27 : 1.0) * (P->merged.valid ? 1.13 : 1.0);
-  const double then = rounds((merge ? merged_items : dense_items) * C.c) * (steps + 1.5) * us * (merge ? 1.08 : 1.0) + 2.0 * bytes / 4.5e6 + 5;
-  return then < 0.93 * now;
+  const std::vector<int64_t> nc = merged_cuts({&B.cc, &C.cc});
+  const int64_t steps = d.len / x.bk;                                 // (of the longest share)
+  const double segs = (double)(d.kc.size() - 1) / C.c, us = 0.72;
+  // rounds of macro-tiles; the own list's last one is cut along K where it is at most half full
+  const bool cut = last_round_is_cut((int64_t)items, steps, x.es, cus);
+  auto rounds = [&](int64_t n) { return (double)((n + cus - 1) / cus); };
+  double own = rounds((int64_t)items);
+  if (cut) {
+    const int64_t tail = (int64_t)items % cus;
+    own += 1.0 / (double)std::min<int64_t>(cus / tail, steps / min_run_steps(x.es)) - 1.0;
+  }
+  own *= ((double)steps + 1.5 * segs) * us * (P->merged.valid ? 1.13 : 1.0);
+  const double then = rounds((merge ? merged_items : dense_items) * C.c) * ((double)steps + 1.5) * us * (merge ? 1.08 : 1.0) +
+                      ((double)dense_bytes(P, d) + bytes) / 4.5e6 + 5;
+  if (std::max(cut_misaligned(A, d.kc), cut_misaligned(B, nc)) > 0.1) own *= 1.27;
+  const bool by_shape = then < 0.93 * own;
+  if (cut || in_windows(P)) {
+    *uncut = by_shape;
+    return by_shape && given;
+  }
+  if (!given) return false;
+  return by_shape || (then < 0.93 * 1.12 * own && (placed_misaligned(A, x.a_tiles, x.a_ld) || placed_misaligned(B, x.b_tiles, x.b_ld)));
 }
 
 // The plan on the copies, the copies' buffer and the tables of the copy.  DMM_ENOMEM: no room.
@@ -1062,91 +1140,101 @@ int build_dense_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
   int rc;
   DeviceState &D = *P->dev;
   const Grid &A = P->A, &B = P->B, &C = P->C;
-  const int64_t M = C.rows, K = A.cols, N = C.cols;
-  // K split as the replicas of C share it, every share a tile of A with rows of its own
-  std::vector<int64_t> shares;
-  for (int32_t r = 0; r <= C.c; ++r) shares.push_back((int64_t)r * K / C.c);
+  const int64_t M = C.rows, N = C.cols;
+  DenseShape d;
+  dense_shape(P, x.bk, &d);
   if (!D.dense) {
-    const int64_t all_m[2] = {0, M}, all_k[2] = {0, K}, all_n[2] = {0, N};
-    const dmm_matrix_desc a = {M, K, 1, C.c, all_m, shares.data(), 1, 1, 1}, b = {K, N, 1, 1, all_k, all_n, 1, 1, 1},
+    const int64_t len = d.len * C.c, all_m[2] = {0, M}, all_k[2] = {0, len}, all_n[2] = {0, N};
+    std::vector<int64_t> shares;        // (the planner's own split of K: the shares are of one length)
+    for (int32_t r = 0; r <= C.c; ++r) shares.push_back(r * d.len);
+    const dmm_matrix_desc a = {M, len, 1, C.c, all_m, shares.data(), 1, 1, 1}, b = {len, N, 1, 1, all_k, all_n, 1, 1, 1},
                           c = {M, N, C.gr, C.gc, C.rc.data(), C.cc.data(), C.pr, C.pc, C.c};
     if ((rc = dmm_plan(&a, &b, &c, P->nranks, 0, &D.dense))) return rc;
     D.dense->dense_copy = true;
   }
-  auto padded = [](int64_t cols) { return (cols + 63) & ~(int64_t)63; };
-  size_t need = 0;
-  std::vector<size_t> at;
-  D.pack_lda.clear();
-  for (int32_t r = 0; r < C.c; ++r) {
-    D.pack_lda.push_back(padded(shares[(size_t)r + 1] - shares[(size_t)r]));
-    at.push_back(need);
-    need += (size_t)(M * D.pack_lda.back()) * 2;
-  }
-  D.pack_ldb = padded(N);
-  const size_t at_b = need;
-  need += (size_t)(K * D.pack_ldb) * 2;
+  const int64_t lda = dense_ld(d.len), share_bytes = 2 * M * lda, need = dense_bytes(P, d);
+  D.pack_ldb = dense_ld(N);
   // the copies are shared by all calls on this plan: order this call behind the others
   if ((rc = D.uses.order(stream))) return rc;
-  if (need > D.pack_cap) {
+  if ((size_t)need > D.pack_cap) {
     if (D.pack_buf) {
       DMM_HIP(hipStreamSynchronize(stream));
       pack_pool().release(&D.pack_buf, &D.pack_cap, D.pack_device);
     }
-    if ((rc = pack_pool().acquire(need, &D.pack_buf, &D.pack_cap))) return rc;
+    if ((rc = pack_pool().acquire((size_t)need, &D.pack_buf, &D.pack_cap))) return rc;
     D.pack_device = x.device;
   }
-  std::vector<int32_t> cuts;
+  std::vector<PackRun> runs;
   std::vector<PackTile> tiles;
   std::vector<PackJob> jobs;
   int32_t blocks = 0;
-  // columns [col0, col0 + cols) of an operand to dense rows at `where`: a job per tile row
-  auto copy = [&](const Grid &G, size_t first_tile, size_t first_cut, size_t where, int64_t ld, int64_t col0, int64_t cols) {
-    for (int32_t i = 0; i < G.gr; ++i) {
-      PackJob j;
-      std::memset(&j, 0, sizeof(j));
-      j.rows = (int32_t)(G.rc[i + 1] - G.rc[i]);
-      if (j.rows <= 0) continue;
-      j.dst = D.pack_buf + where + (size_t)(G.rc[i] * ld) * 2;
-      j.pitch = ld * 2;
-      j.col0 = (int32_t)col0;
-      j.cols = (int32_t)cols;
-      j.gc = G.gc;
-      j.cc = (int32_t)first_cut;
-      j.tiles = (int32_t)(first_tile + (size_t)i * G.gc);
-      j.first_block = blocks;
-      j.blocks_c = (int32_t)((cols + PACK_COLS - 1) / PACK_COLS);
-      blocks += j.blocks_c * ((j.rows + PACK_ROWS - 1) / PACK_ROWS);
-      jobs.push_back(j);
-    }
-  };
   auto operand = [&](const Grid &G, const void *const *ptr, const int64_t *ld) {
-    for (int64_t c : G.cc) cuts.push_back((int32_t)c);
-    for (int32_t i = 0; i < G.gr; ++i)
-      for (int32_t k = 0; k < G.gc; ++k) {
-        const int64_t idx = G.table_index(0, i, k);
-        tiles.push_back({(const char *)ptr[idx], ld[idx] * 2});
-      }
+    for (int64_t i = 0; i < G.tiles_per_rep(); ++i) tiles.push_back({(const char *)ptr[i], ld[i] * 2});
   };
+  // `rows_out` rows of a copy, `rows` of them from a tile row; runs [first_run, end) say where their columns come from
+  auto job = [&](int64_t first_tile, int64_t row, int64_t rows, int64_t rows_out, size_t first_run, int64_t cols_out, char *dst, int64_t ld) {
+    PackJob j;
+    std::memset(&j, 0, sizeof(j));
+    j.dst = dst;
+    j.pitch = ld * 2;
+    j.rows = (int32_t)rows;
+    j.rows_out = (int32_t)rows_out;
+    j.row = (int32_t)row;
+    j.cols_out = (int32_t)cols_out;
+    j.runs = (int32_t)first_run;
+    j.n_runs = (int32_t)(runs.size() - first_run);
+    j.tiles = (int32_t)first_tile;
+    j.first_block = blocks;
+    j.blocks_c = (int32_t)((cols_out + PACK_COLS - 1) / PACK_COLS);
+    blocks += j.blocks_c * (int32_t)((rows_out + PACK_ROWS - 1) / PACK_ROWS);
+    jobs.push_back(j);
+  };
+  auto holder = [](const std::vector<int64_t> &cuts, int64_t pos) {
+    return (int32_t)(std::upper_bound(cuts.begin(), cuts.end() - 1, pos) - cuts.begin()) - 1;
+  };
+  const size_t S = d.kc.size() - 1;
   operand(A, x.a_tiles, x.a_ld);
-  const size_t b_tile = tiles.size(), b_cut = cuts.size();
-  operand(B, x.b_tiles, x.b_ld);
   D.pack_a.clear();
+  D.pack_lda.assign((size_t)C.c, lda);
   for (int32_t r = 0; r < C.c; ++r) {
-    copy(A, 0, 0, at[(size_t)r], D.pack_lda[(size_t)r], shares[(size_t)r], shares[(size_t)r + 1] - shares[(size_t)r]);
-    D.pack_a.push_back(D.pack_buf + at[(size_t)r]);
+    const size_t first = runs.size();
+    char *dst = D.pack_buf + r * share_bytes;
+    for (size_t s = 0; s < S; ++s)
+      if (d.share[s] == r) {
+        if (runs.size() == first && d.at[s] > 0) runs.push_back({0, 0, 0, 0});
+        const int32_t tj = holder(A.cc, d.kc[s]);
+        runs.push_back({(int32_t)d.at[s], (int32_t)(d.kc[s + 1] - d.kc[s]), tj, (int32_t)(d.kc[s] - A.cc[tj])});
+      }
+    for (int32_t i = 0; i < A.gr; ++i) {
+      const int64_t h = A.rc[i + 1] - A.rc[i];
+      if (h > 0) job((int64_t)i * A.gc, 0, h, h, first, d.len, dst + 2 * A.rc[i] * lda, lda);
+    }
+    D.pack_a.push_back(dst);
   }
-  copy(B, b_tile, b_cut, at_b, D.pack_ldb, 0, N);
-  D.pack_b = D.pack_buf + at_b;
+  const int64_t b_tile = (int64_t)tiles.size();
+  const size_t b_runs = runs.size();
+  operand(B, x.b_tiles, x.b_ld);
+  D.pack_b = D.pack_buf + C.c * share_bytes;
+  for (int32_t k = 0; k < B.gc; ++k)
+    if (B.cc[k + 1] > B.cc[k]) runs.push_back({(int32_t)B.cc[k], (int32_t)(B.cc[k + 1] - B.cc[k]), k, 0});
+  for (size_t s = 0; s < S; ++s) {
+    const int64_t base = d.share[s] * d.len, len = d.kc[s + 1] - d.kc[s];
+    const bool first = s == 0 || d.share[s - 1] != d.share[s], last = s + 1 == S || d.share[s + 1] != d.share[s];
+    const int32_t ti = holder(B.rc, d.kc[s]);
+    if (first && d.at[s] > 0) job(b_tile, 0, 0, d.at[s], b_runs, N, D.pack_b + 2 * base * D.pack_ldb, D.pack_ldb);
+    job(b_tile + (int64_t)ti * B.gc, d.kc[s] - B.rc[ti], len, (last ? d.len : d.at[s + 1]) - d.at[s], b_runs, N,
+        D.pack_b + 2 * (base + d.at[s]) * D.pack_ldb, D.pack_ldb);
+  }
   D.pack_jobs = (int)jobs.size();
   D.pack_blocks = blocks;
   D.pack_o_tiles = jobs.size() * sizeof(PackJob);
-  D.pack_o_cuts = D.pack_o_tiles + tiles.size() * sizeof(PackTile);
+  D.pack_o_runs = D.pack_o_tiles + tiles.size() * sizeof(PackTile);
   std::vector<char> &h = D.host;
-  h.assign(D.pack_o_cuts + cuts.size() * 4, 0);
+  h.assign(D.pack_o_runs + runs.size() * sizeof(PackRun), 0);
   std::memcpy(h.data(), jobs.data(), jobs.size() * sizeof(PackJob));
   std::memcpy(h.data() + D.pack_o_tiles, tiles.data(), tiles.size() * sizeof(PackTile));
-  std::memcpy(h.data() + D.pack_o_cuts, cuts.data(), cuts.size() * 4);
-  if ((rc = D.pack_table.upload(h.data(), h.size(), stream, P->dev->uses))) return rc;
+  std::memcpy(h.data() + D.pack_o_runs, runs.data(), runs.size() * sizeof(PackRun));
+  if ((rc = D.pack_table.upload(h.data(), h.size(), stream, D.uses))) return rc;
   L->dense = true;
   L->uses_split = true;
   return DMM_OK;
@@ -1163,7 +1251,7 @@ int launch_dense(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, bool time
     TraceRange tr("copy_operands");
     const char *d = D.pack_table.dev();
     hipLaunchKernelGGL(pack_kernel, dim3((unsigned)D.pack_blocks), dim3(256), 0, stream, (const PackJob *)d, D.pack_jobs,
-                       (const int32_t *)(d + D.pack_o_cuts), (const PackTile *)(d + D.pack_o_tiles));
+                       (const PackRun *)(d + D.pack_o_runs), (const PackTile *)(d + D.pack_o_tiles));
     DMM_HIP(hipGetLastError());
   }
   if (timed) DMM_HIP(hipEventRecord(D.t_pack[1], stream));
@@ -1176,8 +1264,6 @@ int launch_dense(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, bool time
   D.ran_merged = r.ran_merged != 0;
   D.ran_k_split = r.ran_k_split != 0;
   D.ran_fused = r.ran_fused;
-  D.ran_small = D.dense->dev->ran_small;
-  D.small_runs = D.dense->dev->small_runs;
   D.ran_dense = true;
   return DMM_OK;
 }
@@ -1372,7 +1458,7 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
     put(c_tiles, nc * sizeof(void *));
     put(c_ld, nc * sizeof(int64_t));
     ExecLayout L;
-    const ExecArgs x = {dtype, es, bk, c_es, a_tiles, a_ld, b_tiles, b_ld, c_tiles, c_ld, flags, device};
+    ExecArgs x = {dtype, es, bk, c_es, a_tiles, a_ld, b_tiles, b_ld, c_tiles, c_ld, flags, device, P->dense_copy};
     if (P->dev->exec_cached && key == P->dev->exec_key) {
       L = P->dev->exec_layout;
       P->dev->table_reused = true;
@@ -1389,7 +1475,7 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
       const bool given = operands_given(P, x);
       if (given) choose_small(P, x, cus, &sp);
       bool built = false;
-      if (given && (sp.shape >= 0 || choose_dense(P, x, cus))) {
+      if ((given && sp.shape >= 0) || choose_dense(P, x, given, cus, &x.uncut)) {
         rc = sp.shape >= 0 ? build_small_exec(P, x, sp, stream, &L) : build_dense_exec(P, x, stream, &L);
         if (rc == DMM_ENOMEM) {
           // no room for partial tiles or copies: the call's own work list, which may do with less
@@ -1400,7 +1486,7 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
         }
       }
       if (!built) {
-        if (P->merged.valid && !(flags & DMM_NO_MERGE) && g_comp_ok[device]) rc = build_merged_exec(P, x, stream, &L);
+        if (P->merged.valid && !(flags & DMM_NO_MERGE) && g_comp_ok[device] && !(x.uncut && in_windows(P))) rc = build_merged_exec(P, x, stream, &L);
         else rc = build_group_exec(P, x, stream, &L);
       }
       if (rc) return rc;

@@ -2,7 +2,11 @@
 // exec.hip).  Large products whose operands lie in rows that are not 16-byte aligned, or in many
 // K-segments, run the grouped GEMM on such a copy: every row of it starts at a multiple of 128
 // bytes and K is one segment per replica of C, so no 64-byte row piece of a K step straddles two
-// cache lines and no segment has a tail or a switch.
+// cache lines and no segment switch interrupts the K loop.
+// Every K-segment of the operands keeps the K steps it has there: it starts at a multiple of a
+// step and is filled up with zeros, in A's columns and in B's rows alike, as the macro-tile kernels
+// do on the way to LDS.  The products on the copies are therefore those on the operands, step by
+// step, and so are the sums, bit for bit.
 // Bound: HBM, one read and one write of the operands (12289 x 9973 and 9973 x 11003 in uneven
 // packed tiles: 0.93 GB).  A thread moves 16 bytes of each of eight rows, all eight loads issued before
 // the first store; reads are contiguous along the source's rows whatever their alignment.
@@ -21,20 +25,43 @@ struct PackTile {          // one tile of the operand
   int64_t pitch;           // bytes
 };
 
-struct PackJob {           // columns [col0, col0 + cols) of one tile row of an operand -> dense rows at dst
+struct PackRun {           // columns [start, start + len) of a copy's rows are columns [col, col + len) of a tile;
+  int32_t start, len;      // what lies between two runs, and behind the last, is zero
+  int32_t tile, col;
+};
+
+struct PackJob {           // rows of one tile row of an operand -> dense rows at dst
   char *dst;               // 16-byte aligned, like the pitch
   int64_t pitch;           // bytes
-  int32_t rows, col0, cols;
-  int32_t gc;              // tiles side by side
-  int32_t cc, tiles;       // where the column cuts (in cuts[]) and the row's tiles (in tiles[]) begin
+  int32_t rows, rows_out;  // rows copied, rows written (the others are zero)
+  int32_t row;             // first row inside the tiles
+  int32_t cols_out;        // columns written, up to the next multiple of eight
+  int32_t runs, n_runs;    // in runs[]; the first run starts at 0
+  int32_t tiles;           // where the tile row begins in tiles[]
   int32_t first_block;     // the workgroups of the job begin here
   int32_t blocks_c;        // workgroups side by side
+  int32_t pad;
 };
 
 constexpr int PACK_ROWS = 8;
 constexpr int PACK_COLS = 256 * 8;
 
-__global__ __launch_bounds__(256) void pack_kernel(const PackJob *__restrict__ jobs, int n_jobs, const int32_t *__restrict__ cuts,
+// the upper 8 - n of eight bf16 elements moved down to the front, zeros behind them (0 <= n < 8)
+__device__ __forceinline__ u32x4 drop_first(u32x4 v, int n) {
+  union { u32x4 v; uint64_t q[2]; } u;
+  u.v = v;
+  const int s = n * 16;
+  if (s >= 64) {
+    u.q[0] = u.q[1] >> (s - 64);
+    u.q[1] = 0;
+  } else if (s > 0) {
+    u.q[0] = u.q[0] >> s | u.q[1] << (64 - s);
+    u.q[1] >>= s;
+  }
+  return u.v;
+}
+
+__global__ __launch_bounds__(256) void pack_kernel(const PackJob *__restrict__ jobs, int n_jobs, const PackRun *__restrict__ all_runs,
                                                    const PackTile *__restrict__ tiles) {
   // the last of `n` that does not lie behind `at`
   auto last_not_above = [](int n, int at, auto value) {
@@ -48,45 +75,68 @@ __global__ __launch_bounds__(256) void pack_kernel(const PackJob *__restrict__ j
   };
   const PackJob j = jobs[last_not_above(n_jobs, (int)blockIdx.x, [&](int x) { return jobs[x].first_block; })];
   const int b = (int)blockIdx.x - j.first_block, row0 = b / j.blocks_c * PACK_ROWS;
-  const int at = (b % j.blocks_c * 256 + (int)threadIdx.x) * 8;          // column inside the job
-  if (at >= j.cols) return;
-  const int32_t *cc = cuts + j.cc;
+  const int at = (b % j.blocks_c * 256 + (int)threadIdx.x) * 8;          // column of the copy
+  if (at >= j.cols_out) return;
+  const PackRun *runs = all_runs + j.runs;
   const PackTile *t = tiles + j.tiles;
-  const int n = j.cols - at < 8 ? j.cols - at : 8;
-  const int c = j.col0 + at;
-  int tj = last_not_above(j.gc, c, [&](int x) { return cc[x]; });
-  const int rows = j.rows - row0 < PACK_ROWS ? j.rows - row0 : PACK_ROWS;
+  int x = last_not_above(j.n_runs, at, [&](int i) { return runs[i].start; });
+  const PackRun u = runs[x];
+  const int off = at - u.start, n = u.len - off;                         // the run has n columns from here on
+  const bool alone = x + 1 == j.n_runs || runs[x + 1].start >= at + 8;   // no other run begins in the eight columns
+  const int out = j.rows_out - row0 < PACK_ROWS ? j.rows_out - row0 : PACK_ROWS;
+  const int rows = j.rows - row0 < out ? j.rows - row0 : out;            // of these rows hold values (may be 0 or less)
   const gptr dst = (gptr)j.dst + ((int64_t)row0 * j.pitch + (int64_t)at * 2);
   typedef __attribute__((address_space(1))) u32x4 *gvec;
-  // (rows past the block's end read its last row, so that the loads are free of branches)
-  if (n == 8 && c + 8 <= cc[tj + 1]) {                                   // all eight columns in one tile
-    const PackTile s = t[tj];
-    const gptr p = (gptr)s.ptr + ((int64_t)row0 * s.pitch + (int64_t)(c - cc[tj]) * 2);
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  if (rows <= 0 || (n <= 0 && alone)) {
+    for (int r = 0; r < out; ++r) *(gvec)(dst + r * j.pitch) = zero;
+  } else if (n >= 8 || (n > 0 && u.len >= 8 && alone)) {
+    // all columns in one tile; at the end of a run the run's last eight columns are read and moved to the
+    // front.  (Rows past the last read that one again, so that the loads are free of branches.)
+    const int back = n >= 8 ? 0 : 8 - n;
+    const PackTile s = t[u.tile];
+    const gptr p = (gptr)s.ptr + ((int64_t)(j.row + row0) * s.pitch + (int64_t)(u.col + off - back) * 2);
     u32x4 v[PACK_ROWS];
 #pragma unroll
     for (int r = 0; r < PACK_ROWS; ++r) v[r] = *(const __attribute__((address_space(1))) u32x4_any *)(p + (r < rows ? r : rows - 1) * s.pitch);
 #pragma unroll
     for (int r = 0; r < PACK_ROWS; ++r)
-      if (r < rows) *(gvec)(dst + r * j.pitch) = v[r];
+      if (r < out) *(gvec)(dst + r * j.pitch) = r < rows ? drop_first(v[r], back) : zero;
   } else {
-    gptr p[8];
-    int64_t pitch[8];
+    // (columns without a value read the last one that has one)
+    gptr p[8], last = nullptr;
+    int64_t pitch[8], last_pitch = 0;
+    unsigned have = 0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int col = c + (e < n ? e : n - 1);
-      while (col >= cc[tj + 1]) ++tj;
-      const PackTile s = t[tj];
-      pitch[e] = s.pitch;
-      p[e] = (gptr)s.ptr + ((int64_t)row0 * s.pitch + (int64_t)(col - cc[tj]) * 2);
+      while (x + 1 < j.n_runs && runs[x + 1].start <= at + e) ++x;
+      const PackRun w = runs[x];
+      const int o = at + e - w.start;
+      if (o < w.len) {
+        const PackTile s = t[w.tile];
+        last_pitch = s.pitch;
+        last = (gptr)s.ptr + ((int64_t)(j.row + row0) * s.pitch + (int64_t)(w.col + o) * 2);
+        have |= 1u << e;
+      }
+      p[e] = last;
+      pitch[e] = last_pitch;
     }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (!(have & ((2u << e) - 1))) {                                   // nothing at or in front of it
+        p[e] = last;
+        pitch[e] = last_pitch;
+      }
 #pragma unroll 2
     for (int r = 0; r < rows; ++r) {
-      unsigned u[8];
+      unsigned q[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) u[e] = *(const __attribute__((address_space(1))) unsigned short *)(p[e] + r * pitch[e]);
-      // (the last chunk of a row is written whole: the dense rows are padded to a multiple of 64 columns)
-      *(gvec)(dst + r * j.pitch) = u32x4{u[0] | u[1] << 16, u[2] | u[3] << 16, u[4] | u[5] << 16, u[6] | u[7] << 16};
+      for (int e = 0; e < 8; ++e) q[e] = *(const __attribute__((address_space(1))) unsigned short *)(p[e] + r * pitch[e]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) q[e] = have >> e & 1 ? q[e] : 0u;
+      *(gvec)(dst + r * j.pitch) = u32x4{q[0] | q[1] << 16, q[2] | q[3] << 16, q[4] | q[5] << 16, q[6] | q[7] << 16};
     }
+    for (int r = rows; r < out; ++r) *(gvec)(dst + r * j.pitch) = zero;
   }
 }
 

@@ -19,6 +19,8 @@ struct Op {
   std::string name;             // kernel, "copy", "event"
   void *stream;
   uint64_t arg, bytes;          // kernel: first eight bytes of its first argument; copy: destination and size
+  uint64_t more[3] = {0, 0, 0}; // pack_kernel: its other arguments
+  unsigned blocks = 0;
   std::vector<int> behind;
   int done_at = -1;             // known on the host to have finished before operation number done_at was enqueued
 };
@@ -89,6 +91,8 @@ const char *rec_name(int i) { return ops[(size_t)i].name.c_str(); }
 uint64_t rec_stream(int i) { return (uint64_t)ops[(size_t)i].stream; }
 uint64_t rec_arg(int i) { return ops[(size_t)i].arg; }
 uint64_t rec_bytes(int i) { return ops[(size_t)i].bytes; }
+uint64_t rec_more(int i, int k) { return ops[(size_t)i].more[k]; }
+unsigned rec_blocks(int i) { return ops[(size_t)i].blocks; }
 int rec_before(int a, int b) { return before(a, b); }
 uint64_t rec_new_stream() { return (uint64_t)fresh(); }
 void rec_finish_stream(uint64_t s) { finish(streams[(void *)s].last); }
@@ -124,10 +128,16 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipSt
   *stream = cfg_stream;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipStream_t stream) {
+hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, hipStream_t stream) {
   uint64_t first;
   memcpy(&first, args[0], sizeof first);
-  enqueue(kernels[f], stream, first, 0);
+  Op &o = ops[(size_t)enqueue(kernels[f], stream, first, 0)];
+  o.blocks = grid.x;
+  if (o.name == "pack_kernel") {                    // (jobs, number of them, runs, tiles)
+    o.more[0] = *(int *)args[1];
+    memcpy(&o.more[1], args[2], 8);
+    memcpy(&o.more[2], args[3], 8);
+  }
   return hipSuccess;
 }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }

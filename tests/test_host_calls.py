@@ -5,6 +5,7 @@ scenario runs in a process of its own, so that the stand-in is the only runtime 
 import ctypes
 import os
 import shutil
+import struct
 import subprocess
 import sys
 
@@ -22,7 +23,7 @@ import workloads  # noqa: E402
 class Recorder:
     def __init__(self, path):
         self.so = ctypes.CDLL(path, mode=ctypes.RTLD_GLOBAL)          # in front of the runtime the library names
-        for f in ("rec_stream", "rec_arg", "rec_bytes", "rec_new_stream", "rec_live"):
+        for f in ("rec_stream", "rec_arg", "rec_bytes", "rec_more", "rec_new_stream", "rec_live"):
             getattr(self.so, f).restype = ctypes.c_uint64
         self.so.rec_name.restype = ctypes.c_char_p
         for f in ("rec_finish_stream", "rec_set_limit"):
@@ -104,7 +105,8 @@ def dense_calls_and_others_on_two_streams(rec):
     """One plan, its calls alternating between operands that are copied first and operands that are not,
     on two streams: a call's copies must not be made before the product that reads the copies of an
     earlier call has finished, whatever ran in between on the other stream."""
-    p = Product(row_col(8192, 8192, 8192), 8)
+    block = workloads.block_desc
+    p = Product((block(6656, 3840, 8, 8), block(3840, 5376, 8, 8), block(6656, 5376, 8, 8)), 64)
     s1, s2 = rec.stream(), rec.stream()
     for other in ("aligned", "no merge"):
         plain, flags = (p.args(), 0) if other == "aligned" else (p.args(False, 3), p.b.DMM_NO_MERGE)
@@ -220,8 +222,165 @@ def reports_say_what_ran(rec):
     check(q, q.args(False), q.b.DMM_NO_MERGE, ["grouped_gemm_kernel"])
 
 
+def _pack_tables(rec, op):
+    """The tables of a launch of pack_kernel: jobs, runs and tiles as lists of tuples."""
+    so, n = rec.so, int(rec.so.rec_more(op, 0))
+    job, run, tile = struct.Struct("<qq10i"), struct.Struct("<4i"), struct.Struct("<qq")
+    jobs = [job.unpack(ctypes.string_at(rec.so.rec_arg(op) + i * job.size, job.size)) for i in range(n)]
+    n_runs = max(j[6] + j[7] for j in jobs)
+    runs = [run.unpack(ctypes.string_at(so.rec_more(op, 1) + i * run.size, run.size)) for i in range(n_runs)]
+    return jobs, runs, lambda i: tile.unpack(ctypes.string_at(so.rec_more(op, 2) + i * tile.size, tile.size))
+
+
+def _columns_of(job, runs, at):
+    """What a thread of pack_kernel puts into eight columns of a copy from column `at` on, step by step as
+    the kernel does it: ([(tile, column inside it) or None] * 8, [(tile, first column read, last)])."""
+    rs = runs[job[6]:job[6] + job[7]]
+    x = max(i for i, r in enumerate(rs) if r[0] <= at)
+    start, length, tile, col = rs[x]
+    off = at - start
+    n, alone = length - off, x + 1 == len(rs) or rs[x + 1][0] >= at + 8
+    if n <= 0 and alone:
+        return [None] * 8, []
+    if n >= 8 or (n > 0 and length >= 8 and alone):
+        back = 0 if n >= 8 else 8 - n
+        first = col + off - back
+        return [(tile, first + back + e) if e + back < 8 else None for e in range(8)], [(tile, first, first + 7)]
+    got, reads = [], []
+    for e in range(8):
+        while x + 1 < len(rs) and rs[x + 1][0] <= at + e:
+            x += 1
+        start, length, tile, col = rs[x]
+        o = at + e - start
+        got.append((tile, col + o) if o < length else None)
+        if got[-1]:
+            reads.append((tile, col + o, col + o))
+    return got, reads
+
+
+def the_copies_hold_the_k_steps_of_the_operands(rec):
+    """The tables of pack_kernel, followed as the kernel follows them: every element of the copies is written
+    once, holds the element of A (B) that belongs there or a zero, no read leaves a tile, and the K-segments
+    begin at multiples of the macro-tile kernels' K step (32), filled up with zeros."""
+    import numpy as np
+    cyclic, cuts, desc = workloads.block_cyclic_desc, workloads.jittered_cuts, workloads.desc
+
+    def uneven(m, k, n, s):
+        return (desc(m, k, cuts(m, 3, s), cuts(k, 5, s + 1), 3, 5), desc(k, n, cuts(k, 7, s + 2), cuts(n, 2, s + 5), 7, 2),
+                desc(m, n, cuts(m, 5, s + 3), cuts(n, 3, s + 4), 5, 3)), 15
+
+    def blocks(m, k, n, nb, c):
+        return tuple(cyclic(r, q, nb, nb, 2, 4, c) for r, q in ((m, k), (k, n), (m, n))), 8 * c
+
+    with_empty = (desc(4100, 1030, (0, 0, 2050, 2050, 4100), (0, 3, 3, 500, 1030), 4, 4), desc(1030, 4101, (0, 500, 500, 1027, 1030), (0, 0, 1, 4101), 4, 3),
+                  desc(4100, 4101, tuple(min(i * 100, 4100) for i in range(42)), tuple(min(i * 100, 4101) for i in range(43)), 2, 2))
+    for (descs, p) in (uneven(8025, 2369, 4107, 77), blocks(4101, 2051, 4099, 100, 1), blocks(3001, 4099, 4102, 99, 2),
+                       blocks(4099, 3333, 4104, 100, 3), (with_empty, 16)):
+        q = Product(descs, p)
+        a, b, c = descs
+        at = len(rec.ops())
+        q.run(q.args(False), 0, rec.stream())
+        assert q.plan.ran_dense() and not q.plan.ran_k_split()
+        op = [o[0] for o in rec.launches(at) if o[1] == "pack_kernel"][0]
+        jobs, runs, tile_at = _pack_tables(rec, op)
+        M, K, N, reps = a["rows"], a["cols"], b["cols"], c["replication"]
+        shares = [r * K // reps for r in range(reps + 1)]
+        kc = sorted(set(a["col_cuts"]) | set(b["row_cuts"]) | set(shares))
+        segs = [[(k0, k1) for k0, k1 in zip(kc, kc[1:]) if shares[r] <= k0 < shares[r + 1]] for r in range(reps)]
+        length = max(sum(-(-(k1 - k0) // 32) * 32 for k0, k1 in s) for s in segs)
+        k_of = np.full((reps, length), -1)                                # which k a column of A's copy (a row of B's) holds
+        for r, s in enumerate(segs):
+            pos = length - sum(-(-(k1 - k0) // 32) * 32 for k0, k1 in s)
+            for k0, k1 in s:
+                assert pos % 32 == 0
+                k_of[r, pos:pos + k1 - k0] = np.arange(k0, k1)
+                pos += -(-(k1 - k0) // 32) * 32
+        lda, ldb = -(-length // 64) * 64, -(-N // 64) * 64
+        base = min(j[0] for j in jobs)
+        wrote_a, wrote_b = np.zeros((reps, M), int), np.zeros(reps * length, int)
+        tiles_a = (len(a["row_cuts"]) - 1) * (len(a["col_cuts"]) - 1)
+        block = 0
+        for j in jobs:
+            dst, pitch, rows, rows_out, row, cols_out, _, _, tile0, first_block, blocks_c, _ = j[:12]
+            assert dst % 16 == 0 and pitch % 16 == 0 and first_block == block and blocks_c == -(-cols_out // 2048)
+            block += blocks_c * -(-rows_out // 8)
+            off = dst - base
+            of_a = off < 2 * reps * M * lda
+            if of_a:
+                rep, first_row = divmod(off // (2 * lda), M)
+                assert off % (2 * lda) == 0 and pitch == 2 * lda and cols_out == length and rows == rows_out
+                wrote_a[rep, first_row:first_row + rows_out] += 1
+                G, where = a, tile0
+                ti, left = divmod(where, len(a["col_cuts"]) - 1)
+                assert left == 0 and a["row_cuts"][ti] + row == first_row and rows <= a["row_cuts"][ti + 1] - first_row
+            else:
+                first_row, left = divmod(off - 2 * reps * M * lda, 2 * ldb)
+                assert left == 0 and pitch == 2 * ldb and cols_out == N
+                wrote_b[first_row:first_row + rows_out] += 1
+                held = k_of.reshape(-1)[first_row:first_row + rows_out]
+                G, where = b, tile0 - tiles_a
+                ti, left = divmod(where, len(b["col_cuts"]) - 1)
+                assert left == 0 and (held[rows:] == -1).all()
+                if rows:
+                    assert (held[:rows] == b["row_cuts"][ti] + row + np.arange(rows)).all() and held[0] + rows <= b["row_cuts"][ti + 1]
+            if rows == 0:
+                continue
+            cc = G["col_cuts"]
+            for col in range(0, cols_out, 8):
+                got, reads = _columns_of(j, runs, col)
+                for tile, lo, hi in reads:
+                    assert 0 <= lo and hi < cc[tile + 1] - cc[tile], "a read leaves its tile"
+                    ptr, src_pitch = tile_at(tile0 + tile)
+                    assert ptr and src_pitch == 2 * (cc[tile + 1] - cc[tile])
+                for e, g in enumerate(got):
+                    want = k_of[rep, col + e] if of_a and col + e < length else col + e if not of_a and col + e < N else -1
+                    assert (cc[g[0]] + g[1] if g else -1) == want
+        assert block == rec.so.rec_blocks(op) and (wrote_a == 1).all() and (wrote_b == 1).all()
+        q.plan.destroy()
+
+
+def copies_do_not_show_in_the_bits(rec):
+    """Whether a call takes the copies depends on where its operands lie and on free memory; its bits must not.
+    What runs on copies is never cut along K, and then neither is what runs in their place."""
+    import random
+    rng, cyclic, cuts, desc = random.Random(11), workloads.block_cyclic_desc, workloads.jittered_cuts, workloads.desc
+    dense = was_cut = 0
+    problems = []
+    for _ in range(60):
+        m, k, n = rng.randrange(5000, 9000), rng.randrange(6500, 16000), rng.randrange(5000, 9000)    # copies of 130 MB and more
+        if rng.random() < 0.5:
+            s = rng.randrange(1000)
+            descs, p = (desc(m, k, cuts(m, 3, s), cuts(k, 5, s + 1), 3, 5), desc(k, n, cuts(k, 7, s + 2), (0, n), 7, 1),
+                        desc(m, n, cuts(m, 5, s + 3), cuts(n, 3, s + 4), 5, 3)), 15
+        else:
+            c, nb = rng.choice((1, 2)), rng.choice((100, 128, 250))
+            descs, p = tuple(cyclic(r, q, nb, nb, 2, 4, c) for r, q in ((m, k), (k, n), (m, n))), 8 * c
+        problems.append((descs, p))
+    seen = [set() for _ in problems]
+    for room in (False, True):                                          # (without room first: buffers taken once stay in a pool)
+        for i, (descs, p) in enumerate(problems):
+            for aligned in (True, False):
+                rec.so.rec_set_limit(2 ** 63 if room else rec.so.rec_live() + (120 << 20))      # tables and partial tiles, no copies
+                q = Product(descs, p)
+                q.run(q.args(aligned), 0, rec.stream())
+                seen[i].add((q.plan.small_tile(), q.plan.ran_k_split()))
+                if q.plan.ran_dense():
+                    assert room and not q.plan.ran_k_split()
+                    dense += 1
+                    # (what the plan's own list does where it is asked for by name)
+                    own = Product(descs, p, q.b.DMM_MERGE_ALWAYS) if q.plan.num_merged_items() else q
+                    own.run(own.args(aligned, 1), 0 if own is not q else q.b.DMM_NO_MERGE, rec.stream())
+                    was_cut += own.plan.ran_k_split()
+                q.plan.destroy()
+    for (descs, _), s in zip(problems, seen):
+        assert len(s) == 1, (descs, s)
+    cut = sum(split for s in seen for _, split in s)
+    assert dense >= 20 and cut >= 8 and was_cut >= 4, (dense, cut, was_cut)
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
-             more_streams_than_the_plan_remembers, reports_say_what_ran]
+             more_streams_than_the_plan_remembers, reports_say_what_ran,
+             the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
