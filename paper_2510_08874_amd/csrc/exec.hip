@@ -1135,7 +1135,36 @@ bool choose_dense(const dmm_plan_t *P, const ExecArgs &x, bool given, int cus, b
   return by_shape || (then < 0.93 * 1.12 * own && (placed_misaligned(A, x.a_tiles, x.a_ld) || placed_misaligned(B, x.b_tiles, x.b_ld)));
 }
 
-// The plan on the copies, the copies' buffer and the tables of the copy.  DMM_ENOMEM: no room.
+int stage(dmm_plan_t *P, ExecArgs &x, hipStream_t stream, ExecLayout *L);
+
+// The tables of the product on the copies.
+int stage_dense(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecLayout *L) {
+  DeviceState &D = *P->dev;
+  const void *b = D.pack_b;
+  ExecArgs in = x;
+  in.a_tiles = D.pack_a.data();
+  in.a_ld = D.pack_lda.data();
+  in.b_tiles = &b;
+  in.b_ld = &D.pack_ldb;
+  in.uncut = true;
+  const int rc = ensure_state(D.dense);
+  return rc ? rc : stage(D.dense, in, stream, L);
+}
+
+// Gives back everything that is there for products on copies.
+int drop_dense(dmm_plan_t *P) {
+  DeviceState &D = *P->dev;
+  const int rc = D.uses.wait();
+  if (D.dense) dmm_plan_destroy(D.dense);
+  D.dense = nullptr;
+  D.pack_table.release();
+  pack_pool().release(&D.pack_buf, &D.pack_cap, D.pack_device);
+  return rc;
+}
+
+// The plan on the copies, the copies' buffer, the tables of the copy and those of the product on it:
+// all that such a call needs memory for, so that a call with these tables in place cannot run out of
+// it.  DMM_ENOMEM: no room.
 int build_dense_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecLayout *L) {
   int rc;
   DeviceState &D = *P->dev;
@@ -1235,36 +1264,10 @@ int build_dense_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
   std::memcpy(h.data() + D.pack_o_tiles, tiles.data(), tiles.size() * sizeof(PackTile));
   std::memcpy(h.data() + D.pack_o_runs, runs.data(), runs.size() * sizeof(PackRun));
   if ((rc = D.pack_table.upload(h.data(), h.size(), stream, D.uses))) return rc;
+  ExecLayout product;
+  if ((rc = stage_dense(P, x, stream, &product))) return rc;
   L->dense = true;
   L->uses_split = true;
-  return DMM_OK;
-}
-
-int launch_dense(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, bool timed) {
-  int rc;
-  DeviceState &D = *P->dev;
-  if (timed) {
-    if ((rc = timing_events(D.t_pack))) return rc;
-    DMM_HIP(hipEventRecord(D.t_pack[0], stream));
-  }
-  {
-    TraceRange tr("copy_operands");
-    const char *d = D.pack_table.dev();
-    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)D.pack_blocks), dim3(256), 0, stream, (const PackJob *)d, D.pack_jobs,
-                       (const PackRun *)(d + D.pack_o_runs), (const PackTile *)(d + D.pack_o_tiles));
-    DMM_HIP(hipGetLastError());
-  }
-  if (timed) DMM_HIP(hipEventRecord(D.t_pack[1], stream));
-  const void *b = D.pack_b;
-  rc = dmm_execute(D.dense, x.dtype, D.pack_a.data(), D.pack_lda.data(), &b, &D.pack_ldb, x.c_tiles, x.c_ld, x.flags, stream);
-  const int rc2 = P->dev->uses.mark(stream);      // (also behind a copy whose product failed)
-  if (rc || rc2) return rc ? rc : rc2;
-  dmm_execute_report r;
-  if ((rc = dmm_plan_last_execute(D.dense, &r))) return rc;
-  D.ran_merged = r.ran_merged != 0;
-  D.ran_k_split = r.ran_k_split != 0;
-  D.ran_fused = r.ran_fused;
-  D.ran_dense = true;
   return DMM_OK;
 }
 
@@ -1407,6 +1410,96 @@ int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stre
   return P->dev->uses.mark(stream);
 }
 
+int launch_dense(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, bool timed) {
+  int rc;
+  DeviceState &D = *P->dev;
+  ExecLayout product;
+  if ((rc = stage_dense(P, x, stream, &product))) return rc;       // (they are in place: this orders the stream behind them)
+  if (timed) {
+    if ((rc = timing_events(D.t_pack))) return rc;
+    DMM_HIP(hipEventRecord(D.t_pack[0], stream));
+  }
+  {
+    TraceRange tr("copy_operands");
+    const char *d = D.pack_table.dev();
+    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)D.pack_blocks), dim3(256), 0, stream, (const PackJob *)d, D.pack_jobs,
+                       (const PackRun *)(d + D.pack_o_runs), (const PackTile *)(d + D.pack_o_tiles));
+    DMM_HIP(hipGetLastError());
+  }
+  if (timed) DMM_HIP(hipEventRecord(D.t_pack[1], stream));
+  rc = launch_exec(D.dense, product, x.es, stream, timed);
+  const int rc2 = P->dev->uses.mark(stream);      // (also behind a copy whose product failed)
+  if (rc || rc2) return rc ? rc : rc2;
+  dmm_execute_report r;
+  if ((rc = dmm_plan_last_execute(D.dense, &r))) return rc;
+  D.ran_merged = r.ran_merged != 0;
+  D.ran_k_split = r.ran_k_split != 0;
+  D.ran_fused = r.ran_fused;
+  D.ran_dense = true;
+  return DMM_OK;
+}
+
+// Decides what a call runs and puts its work tables in place.
+int stage(dmm_plan_t *P, ExecArgs &x, hipStream_t stream, ExecLayout *L) {
+  int rc;
+  DeviceState &D = *P->dev;
+  D.gemm_timed = D.red_timed = D.mid_timed = false;
+  D.ran_dense = false;
+  D.ran_small = -1;
+  // The call's inputs, side by side: when they are those of the plan's last dmm_execute, the
+  // device table of that call is still in place and describes this one too (DMM_TIMING changes
+  // nothing in it), so the assembly of the tables and their upload are skipped.
+  std::vector<char> &key = D.key_scratch;
+  key.clear();
+  auto put = [&key](const void *p, size_t bytes) { key.insert(key.end(), (const char *)p, (const char *)p + bytes); };
+  const int64_t head[3] = {x.dtype, (int64_t)(x.flags & ~DMM_TIMING), x.device};
+  put(head, sizeof head);
+  const size_t na = (size_t)(P->A.c * P->A.tiles_per_rep()), nb = (size_t)(P->B.c * P->B.tiles_per_rep()),
+               nc = (size_t)(P->C.c * P->C.tiles_per_rep());
+  put(x.a_tiles, na * sizeof(void *));
+  put(x.a_ld, na * sizeof(int64_t));
+  put(x.b_tiles, nb * sizeof(void *));
+  put(x.b_ld, nb * sizeof(int64_t));
+  put(x.c_tiles, nc * sizeof(void *));
+  put(x.c_ld, nc * sizeof(int64_t));
+  if (D.exec_cached && key == D.exec_key) {
+    *L = D.exec_layout;
+    D.table_reused = true;
+    if ((rc = (L->dense ? D.pack_table : D.gemm_table).order_behind_copy(stream))) return rc;
+    // (the scratch buffer of macro-tiles cut along K is shared by all calls on this plan)
+    return L->uses_split ? D.uses.order(stream) : DMM_OK;
+  }
+  D.exec_cached = false;
+  D.table_reused = false;
+  TraceRange tables("tables");
+  SmallPlan sp;
+  int cus = 0;
+  if ((rc = device_cus(&cus))) return rc;
+  const bool given = operands_given(P, x);
+  if (given) choose_small(P, x, cus, &sp);
+  bool built = false;
+  if ((given && sp.shape >= 0) || choose_dense(P, x, given, cus, &x.uncut)) {
+    rc = sp.shape >= 0 ? build_small_exec(P, x, sp, stream, L) : build_dense_exec(P, x, stream, L);
+    if (rc == DMM_ENOMEM) {
+      // no room for partial tiles or copies: the call's own work list, which may do with less
+      (void)hipGetLastError();
+      if (sp.shape < 0 && (rc = drop_dense(P))) return rc;
+      *L = ExecLayout();
+    } else {
+      built = true;
+    }
+  }
+  if (!built) {
+    if (P->merged.valid && !(x.flags & DMM_NO_MERGE) && g_comp_ok[x.device] && !(x.uncut && in_windows(P))) rc = build_merged_exec(P, x, stream, L);
+    else rc = build_group_exec(P, x, stream, L);
+  }
+  if (rc) return rc;
+  D.exec_key = key;
+  D.exec_layout = *L;
+  D.exec_cached = true;
+  return DMM_OK;
+}
+
 }  // namespace
 }  // namespace dmm
 
@@ -1438,64 +1531,11 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
   TraceRange whole("dmm_execute");
   try {
     if ((rc = ensure_state(P))) return rc;
-    P->dev->gemm_timed = P->dev->red_timed = P->dev->mid_timed = false;
     int device = 0;
     DMM_HIP(hipGetDevice(&device));
-    // The call's inputs, side by side: when they are those of the plan's last dmm_execute, the
-    // device table of that call is still in place and describes this one too (DMM_TIMING changes
-    // nothing in it), so the assembly of the tables and their upload are skipped.
-    std::vector<char> &key = P->dev->key_scratch;
-    key.clear();
-    auto put = [&key](const void *p, size_t bytes) { key.insert(key.end(), (const char *)p, (const char *)p + bytes); };
-    const int64_t head[3] = {dtype, (int64_t)(flags & ~DMM_TIMING), device};
-    put(head, sizeof head);
-    const size_t na = (size_t)(P->A.c * P->A.tiles_per_rep()), nb = (size_t)(P->B.c * P->B.tiles_per_rep()),
-                 nc = (size_t)(P->C.c * P->C.tiles_per_rep());
-    put(a_tiles, na * sizeof(void *));
-    put(a_ld, na * sizeof(int64_t));
-    put(b_tiles, nb * sizeof(void *));
-    put(b_ld, nb * sizeof(int64_t));
-    put(c_tiles, nc * sizeof(void *));
-    put(c_ld, nc * sizeof(int64_t));
+    ExecArgs x = {dtype, es, bk, c_es, a_tiles, a_ld, b_tiles, b_ld, c_tiles, c_ld, flags, device, false};
     ExecLayout L;
-    ExecArgs x = {dtype, es, bk, c_es, a_tiles, a_ld, b_tiles, b_ld, c_tiles, c_ld, flags, device, P->dense_copy};
-    if (P->dev->exec_cached && key == P->dev->exec_key) {
-      L = P->dev->exec_layout;
-      P->dev->table_reused = true;
-      if ((rc = (L.dense ? P->dev->pack_table : P->dev->gemm_table).order_behind_copy(stream))) return rc;
-      // (the scratch buffer of macro-tiles cut along K is shared by all calls on this plan)
-      if (L.uses_split && (rc = P->dev->uses.order(stream))) return rc;
-    } else {
-      P->dev->exec_cached = false;
-      P->dev->table_reused = false;
-      TraceRange tables("tables");
-      SmallPlan sp;
-      int cus = 0;
-      if ((rc = device_cus(&cus))) return rc;
-      const bool given = operands_given(P, x);
-      if (given) choose_small(P, x, cus, &sp);
-      bool built = false;
-      if ((given && sp.shape >= 0) || choose_dense(P, x, given, cus, &x.uncut)) {
-        rc = sp.shape >= 0 ? build_small_exec(P, x, sp, stream, &L) : build_dense_exec(P, x, stream, &L);
-        if (rc == DMM_ENOMEM) {
-          // no room for partial tiles or copies: the call's own work list, which may do with less
-          (void)hipGetLastError();
-          L = ExecLayout();
-        } else {
-          built = true;
-        }
-      }
-      if (!built) {
-        if (P->merged.valid && !(flags & DMM_NO_MERGE) && g_comp_ok[device] && !(x.uncut && in_windows(P))) rc = build_merged_exec(P, x, stream, &L);
-        else rc = build_group_exec(P, x, stream, &L);
-      }
-      if (rc) return rc;
-      P->dev->exec_key = key;
-      P->dev->exec_layout = L;
-      P->dev->exec_cached = true;
-    }
-    P->dev->ran_dense = false;
-    P->dev->ran_small = -1;
+    if ((rc = stage(P, x, stream, &L))) return rc;
     if (L.dense) return launch_dense(P, x, stream, timed);
     return launch_exec(P, L, es, stream, timed);
   } catch (const std::bad_alloc &) {

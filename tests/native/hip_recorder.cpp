@@ -37,6 +37,7 @@ std::map<const void *, std::string> kernels;
 std::map<const void *, void *> symbols;
 std::map<void *, size_t> memory;
 size_t live = 0, limit = ~(size_t)0;
+int fail_in = -1;                                   // allocations until one fails
 hipError_t last_error = hipSuccess;
 dim3 cfg_grid, cfg_block;
 size_t cfg_lds;
@@ -99,6 +100,8 @@ void rec_finish_stream(uint64_t s) { finish(streams[(void *)s].last); }
 void rec_set_capturing(uint64_t s, int on) { streams[(void *)s].capturing = on != 0; }
 void rec_set_limit(uint64_t bytes) { limit = bytes; }
 uint64_t rec_live() { return live; }
+void rec_fail_allocation(int n) { fail_in = n; }
+int rec_failed() { return fail_in < 0; }
 
 // ---- the runtime ------------------------------------------------------------------------------------
 void **__hipRegisterFatBinary(const void *) { static void *h; return &h; }
@@ -156,6 +159,7 @@ hipError_t hipPeekAtLastError() { return last_error; }
 hipError_t hipGetSymbolAddress(void **p, const void *s) { *p = symbols[s]; return hipSuccess; }
 
 hipError_t hipMalloc(void **p, size_t n) {
+  if (fail_in >= 0 && fail_in-- == 0) return fail(hipErrorOutOfMemory);
   if (live + n > limit) return fail(hipErrorOutOfMemory);
   void *m = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
   if (m == MAP_FAILED) return fail(hipErrorOutOfMemory);

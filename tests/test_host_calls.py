@@ -378,9 +378,40 @@ def copies_do_not_show_in_the_bits(rec):
     assert dense >= 20 and cut >= 8 and was_cut >= 4, (dense, cut, was_cut)
 
 
+def a_failed_allocation_costs_no_call(rec):
+    """Each device allocation of a call that would run on copies fails once: the call then runs its own work
+    list (whose tables there is room for), enqueues nothing of the copies, and goes on like that."""
+    block, cyclic, keep = workloads.block_desc, workloads.block_cyclic_desc, []
+    for descs, ranks in ((tuple(cyclic(r, q, 100, 100, 2, 4, 1) for r, q in ((4101, 8200), (8200, 4099), (4101, 4099))), 8),
+                         (tuple(cyclic(r, q, 100, 100, 2, 4, 2) for r, q in ((4200, 4099), (4099, 4102), (4200, 4102))), 16),
+                         ((block(6656, 3840, 8, 8), block(3840, 5376, 8, 8), block(6656, 5376, 8, 8)), 64)):
+        n, failed = 0, True
+        while failed:
+            for _ in range(3):                                           # (plans that live on keep the pools empty)
+                keep.append(Product(descs, ranks))
+                keep[-1].run(keep[-1].args(False, 99), 0, rec.stream())
+            p, s = Product(descs, ranks), rec.stream()
+            args = p.args(False, n)
+            at = len(rec.ops())
+            rec.so.rec_fail_allocation(n)
+            p.run(args, 0, s)
+            failed = bool(rec.so.rec_failed())
+            rec.so.rec_fail_allocation(-1)
+            first = [o[1] for o in rec.launches(at)]
+            at = len(rec.ops())
+            p.run(args, 0, s)
+            assert [o[1] for o in rec.launches(at)] == first and p.plan.last_execute().table_reused
+            assert ("pack_kernel" in first) == p.plan.ran_dense() == (not failed), (n, first)
+            assert len([o for o in first if "gemm" in o]) == 1, first
+            rec.check_tables()
+            keep.append(p)
+            n += 1
+        assert n >= 4                        # the copies, two sets of tables, none
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
              more_streams_than_the_plan_remembers, reports_say_what_ran,
-             the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits]
+             the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
