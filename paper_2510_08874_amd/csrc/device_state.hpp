@@ -28,7 +28,9 @@ thread_local int g_last_hip_error = 0;
 
 // The calls of a plan whose kernels may still be running: an event behind the last call on each of
 // the streams it was used on.  Whoever writes a buffer that those kernels use waits for all of them
-// (one event for the plan would forget a stream as soon as the next call came on another).
+// (one event for the plan would forget a stream as soon as the next call came on another).  A stream
+// is not made to wait for its own event: it is in order by itself, and while it is being captured the
+// runtime refuses to let it wait for what was recorded on it before.
 class Uses {
  public:
   // behind everything the call enqueued on `stream`
@@ -53,7 +55,8 @@ class Uses {
   }
   // orders what follows on `stream` behind all of them
   int order(hipStream_t stream) const {
-    for (int i = 0; i < n_; ++i) DMM_HIP(hipStreamWaitEvent(stream, uses_[i].ev, 0));
+    for (int i = 0; i < n_; ++i)
+      if (uses_[i].stream != stream) DMM_HIP(hipStreamWaitEvent(stream, uses_[i].ev, 0));
     return DMM_OK;
   }
   // blocks until they have finished

@@ -28,6 +28,7 @@ struct Stream {
   int last = -1;
   std::vector<int> waits;
   bool capturing = false;
+  int since = 0;                // operations in front of the capture
 };
 
 std::vector<Op> ops;
@@ -97,7 +98,10 @@ unsigned rec_blocks(int i) { return ops[(size_t)i].blocks; }
 int rec_before(int a, int b) { return before(a, b); }
 uint64_t rec_new_stream() { return (uint64_t)fresh(); }
 void rec_finish_stream(uint64_t s) { finish(streams[(void *)s].last); }
-void rec_set_capturing(uint64_t s, int on) { streams[(void *)s].capturing = on != 0; }
+void rec_set_capturing(uint64_t s, int on) {
+  streams[(void *)s].capturing = on != 0;
+  streams[(void *)s].since = (int)ops.size();
+}
 void rec_set_limit(uint64_t bytes) { limit = bytes; }
 uint64_t rec_live() { return live; }
 void rec_fail_allocation(int n) { fail_in = n; }
@@ -217,7 +221,9 @@ hipError_t hipEventQuery(hipEvent_t e) {
 }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0.125f; return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
-  if (events[e] >= 0) streams[s].waits.push_back(events[e]);
+  const int i = events[e];
+  if (i >= 0 && streams[s].capturing && ops[(size_t)i].stream == s && i < streams[s].since) return fail(hipErrorStreamCaptureIsolation);
+  if (i >= 0) streams[s].waits.push_back(i);
   return hipSuccess;
 }
 

@@ -409,9 +409,39 @@ def a_failed_allocation_costs_no_call(rec):
         assert n >= 4                        # the copies, two sets of tables, none
 
 
+def calls_can_be_captured(rec):
+    """A plan that has run on a stream runs again while that stream is captured (the runtime then refuses waits
+    for events that the stream recorded before): on the operands, on copies, with tiles cut along K, and by
+    every kind of kernel."""
+    block, cyclic = workloads.block_desc, workloads.block_cyclic_desc
+    fine = tuple(cyclic(8192, 8192, 128, 128, 2, 4, 1) for _ in range(3))
+    long = (block(1024, 16384, 8, 1), block(16384, 1024, 1, 8), block(1024, 1024, 4, 2))
+    column = (block(32, 12288, 1, 1, replication=8), block(12288, 49152, 1, 8), block(32, 49152, 1, 8))
+    for descs, ranks, kw, kernels in ((row_col(8192, 8192, 8192), 8, {}, ["grouped_gemm_kernel"]),
+                                      (fine, 8, {}, ["pack_kernel", "grouped_gemm_comp_kernel"]),
+                                      (long, 8, {}, ["small_gemm_kernel", "small_sum_kernel"]),
+                                      (column, 8, {}, None),
+                                      (row_col(2501, 1999, 1777), 8, dict(dtype="f32"), None)):
+        p, s, other = Product(descs, ranks, **kw), rec.stream(), rec.stream()
+        args = p.args()
+        p.run(args, 0, other)
+        p.run(args, 0, s)
+        rec.so.rec_set_capturing(s, 1)
+        for _ in range(2):
+            at = len(rec.ops())
+            p.run(args, 0, s)
+            got = [o[1] for o in rec.launches(at)]
+            assert got == kernels or kernels is None, got
+        rec.so.rec_set_capturing(s, 0)
+        p.run(args, 0, other)
+        p.run(p.args(where=1), 0, s)
+        rec.check_tables()
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
              more_streams_than_the_plan_remembers, reports_say_what_ran,
-             the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call]
+             the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call,
+             calls_can_be_captured]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
