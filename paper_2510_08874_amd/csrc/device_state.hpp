@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <cstdint>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -26,6 +28,19 @@ thread_local int g_last_hip_error = 0;
     }                                            \
   } while (0)
 
+// A stream as the calling thread means it: hipStreamPerThread names another one in every thread.
+struct StreamKey {
+  hipStream_t stream = nullptr;
+  uint64_t thread = 0;                 // (a number of our own: the system's are used again)
+
+  static StreamKey of(hipStream_t stream) {
+    static std::atomic<uint64_t> threads{0};
+    static thread_local const uint64_t mine = ++threads;
+    return {stream, stream == hipStreamPerThread ? mine : 0};
+  }
+  bool operator==(const StreamKey &o) const { return stream == o.stream && thread == o.thread; }
+};
+
 // The calls of a plan whose kernels may still be running: an event behind the last call on each of
 // the streams it was used on.  Whoever writes a buffer that those kernels use waits for all of them
 // (one event for the plan would forget a stream as soon as the next call came on another).  A stream
@@ -35,9 +50,10 @@ class Uses {
  public:
   // behind everything the call enqueued on `stream`
   int mark(hipStream_t stream) {
+    const StreamKey key = StreamKey::of(stream);
     Entry *e = nullptr;
     for (int i = 0; i < n_ && !e; ++i)
-      if (uses_[i].stream == stream) e = &uses_[i];
+      if (uses_[i].key == key) e = &uses_[i];
     if (!e && n_ < kMost) {
       e = &uses_[n_];
       DMM_HIP(hipEventCreateWithFlags(&e->ev, hipEventDisableTiming));
@@ -49,14 +65,15 @@ class Uses {
       next_ = (next_ + 1) % kMost;
       DMM_HIP(hipStreamWaitEvent(stream, e->ev, 0));
     }
-    e->stream = stream;
+    e->key = key;
     DMM_HIP(hipEventRecord(e->ev, stream));
     return DMM_OK;
   }
   // orders what follows on `stream` behind all of them
   int order(hipStream_t stream) const {
+    const StreamKey key = StreamKey::of(stream);
     for (int i = 0; i < n_; ++i)
-      if (uses_[i].stream != stream) DMM_HIP(hipStreamWaitEvent(stream, uses_[i].ev, 0));
+      if (!(uses_[i].key == key)) DMM_HIP(hipStreamWaitEvent(stream, uses_[i].ev, 0));
     return DMM_OK;
   }
   // blocks until they have finished
@@ -72,8 +89,8 @@ class Uses {
  private:
   static constexpr int kMost = 8;
   struct Entry {
-    hipStream_t stream;
-    hipEvent_t ev;
+    StreamKey key;
+    hipEvent_t ev = nullptr;
   };
   Entry uses_[kMost] = {};
   int n_ = 0, next_ = 0;

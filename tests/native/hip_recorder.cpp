@@ -46,6 +46,18 @@ hipStream_t cfg_stream;
 
 hipError_t fail(hipError_t e) { return last_error = e; }
 
+void *fresh() {
+  static char *next = (char *)0x1000;
+  return next += 16;
+}
+
+hipStream_t real(hipStream_t s) {                   // hipStreamPerThread: a stream of the calling thread's own
+  static thread_local hipStream_t mine = nullptr;
+  if (s != hipStreamPerThread) return s;
+  if (!mine) mine = (hipStream_t)fresh();
+  return mine;
+}
+
 int enqueue(const std::string &name, void *stream, uint64_t arg, uint64_t bytes) {
   Stream &s = streams[stream];
   Op o;
@@ -76,11 +88,6 @@ bool before(int a, int b) {                         // a has finished when b sta
   for (int x : ops[(size_t)b].behind)
     if (before(a, x)) return true;
   return false;
-}
-
-void *fresh() {
-  static char *next = (char *)0x1000;
-  return next += 16;
 }
 
 }  // namespace
@@ -136,6 +143,7 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipSt
   return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, hipStream_t stream) {
+  stream = real(stream);
   uint64_t first;
   memcpy(&first, args[0], sizeof first);
   Op &o = ops[(size_t)enqueue(kernels[f], stream, first, 0)];
@@ -189,18 +197,18 @@ hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
 }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t stream) {
   memcpy(d, s, n);
-  enqueue("copy", stream, (uint64_t)d, n);
+  enqueue("copy", real(stream), (uint64_t)d, n);
   return hipSuccess;
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)fresh(); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) {
-  Stream &t = streams[s];
+  Stream &t = streams[real(s)];
   finish(t.last);
   for (int w : t.waits) finish(w);
   return hipSuccess;
 }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *status) {
-  *status = streams[s].capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  *status = streams[real(s)].capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
   return hipSuccess;
 }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
@@ -211,7 +219,7 @@ hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
 hipError_t hipEventCreate(hipEvent_t *e) { return hipEventCreateWithFlags(e, 0); }
 hipError_t hipEventDestroy(hipEvent_t e) { events.erase(e); return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
-  events[e] = enqueue("event", s, (uint64_t)e, 0);
+  events[e] = enqueue("event", real(s), (uint64_t)e, 0);
   return hipSuccess;
 }
 hipError_t hipEventSynchronize(hipEvent_t e) { finish(events[e]); return hipSuccess; }
@@ -222,6 +230,7 @@ hipError_t hipEventQuery(hipEvent_t e) {
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0.125f; return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
   const int i = events[e];
+  s = real(s);
   if (i >= 0 && streams[s].capturing && ops[(size_t)i].stream == s && i < streams[s].since) return fail(hipErrorStreamCaptureIsolation);
   if (i >= 0) streams[s].waits.push_back(i);
   return hipSuccess;

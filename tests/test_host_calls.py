@@ -8,6 +8,7 @@ import shutil
 import struct
 import subprocess
 import sys
+import threading
 
 import pytest
 
@@ -438,10 +439,25 @@ def calls_can_be_captured(rec):
         rec.check_tables()
 
 
+def a_stream_for_every_thread(rec):
+    """hipStreamPerThread is another stream in every thread: new tables wait for the calls of all of them, one
+    thread's call does not take another's place."""
+    per_thread = 2
+    p = Product(row_col(1024, 512, 1024), 8)
+    args, others = p.args(), p.args(where=1)
+    for a in (args, args, args, others):
+        t = threading.Thread(target=p.run, args=(a, 0, per_thread))
+        t.start()
+        t.join()
+    assert len({o[2] for o in rec.launches()}) == 4
+    rec.check_tables()
+    p.plan.destroy()
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
              more_streams_than_the_plan_remembers, reports_say_what_ran,
              the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call,
-             calls_can_be_captured]
+             calls_can_be_captured, a_stream_for_every_thread]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
