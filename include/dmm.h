@@ -217,7 +217,14 @@ const dmm_merged_item *dmm_plan_merged_items(const dmm_plan_t *p);
  * operands lie and by what memory is free, leave the bits of the result as they are.
  * The first call on a plan takes the plan's device work table (and, if needed, that
  * scratch buffer) from a process-wide pool, allocating only when the pool has none that
- * fits; later calls with the same arguments allocate nothing and do not synchronise. */
+ * fits; later calls with the same arguments allocate nothing and do not synchronise.
+ * The copies of A and B (at most 2 GiB a call) belong to no plan: all calls on a device
+ * share buffers of 2 GiB together, one per stream as long as these suffice, so that calls
+ * on copies may wait for each other across streams; a call that is captured keeps its
+ * buffer until the plan is destroyed (launch the graph on the stream it was captured on, or behind
+ * what was enqueued before the capture).  The buffers stay allocated for later calls; the
+ * library gives them up where it finds no memory for tables or partial sums (a later call
+ * allocates them anew). */
 int dmm_execute(dmm_plan_t *p, int dtype,
                 const void *const *a_tiles, const int64_t *a_ld,
                 const void *const *b_tiles, const int64_t *b_ld,

@@ -96,6 +96,131 @@ class Uses {
   int n_ = 0, next_ = 0;
 };
 
+// Buffers for dense copies of operands (pack_kernel.hpp), up to 2 GiB each, shared by all plans.  The
+// copies live for one call: it takes a buffer, enqueues the copy and the product on it, and hands
+// the buffer back behind them.  Calls on one stream share a buffer in stream order, calls on different
+// streams have buffers of their own as long as all of a device's stay within 2 GiB, and wait for
+// each other beyond that.  (More than 2 GiB are held only where that many are taken at one time, or
+// kept for a captured graph.)
+class PackPool {
+ public:
+  struct Lease {
+    char *p = nullptr;
+    size_t cap = 0;
+    int device = 0;
+    StreamKey stream;                  // that of the last call, behind which `done` is recorded
+    hipEvent_t done = nullptr;
+  };
+  // A buffer for what is enqueued on `stream` from now on; the one at `last` if that is there, since
+  // the caller has tables for it.  DMM_ENOMEM (nothing recorded): there is no room, the caller does without.
+  int acquire(size_t bytes, hipStream_t stream, const char *last, Lease *out) {
+    int device = 0;
+    DMM_HIP(hipGetDevice(&device));
+    if (device < 0 || device >= 64) return DMM_EINVAL;
+    const StreamKey key = StreamKey::of(stream);
+    std::lock_guard<std::mutex> g(mu_);
+    int own = -1, any = -1;
+    for (int i = 0; i < (int)free_.size(); ++i) {
+      const Lease &e = free_[(size_t)i];
+      if (e.device != device || e.cap < bytes) continue;
+      if (e.p == last) return take(i, stream, out);
+      if (e.stream == key && (own < 0 || e.cap < free_[(size_t)own].cap)) own = i;
+      if (any < 0) any = i;                                  // (the one that has been free for longest)
+    }
+    if (own >= 0) return take(own, stream, out);
+    const size_t want = (bytes + ((size_t)32 << 20) - 1) >> 25 << 25;
+    if (held(device) + want <= kMost && allocate(want, device, out)) return DMM_OK;
+    if (any >= 0) return take(any, stream, out);
+    while (held(device) + want > kMost && drop_oldest(device)) {}
+    if (allocate(want, device, out)) return DMM_OK;
+    while (drop_oldest(device)) {}
+    return allocate(want, device, out) ? DMM_OK : DMM_ENOMEM;
+  }
+  // behind everything on `stream` that uses it
+  void give_back(Lease *l, hipStream_t stream) {
+    if (!l->p) return;
+    l->stream = StreamKey::of(stream);
+    if (hipEventRecord(l->done, stream) != hipSuccess) (void)hipStreamSynchronize(stream);
+    put(l);
+  }
+  // of a buffer that no call uses any more
+  void put(Lease *l) {
+    if (!l->p) return;
+    std::lock_guard<std::mutex> g(mu_);
+    free_.push_back(*l);
+    out_[l->device] -= l->cap;
+    *l = Lease();
+  }
+  // Gives up the buffers of a device that no call has at this moment; false: there are none.
+  bool trim(int device) {
+    std::lock_guard<std::mutex> g(mu_);
+    bool any = false;
+    while (drop_oldest(device)) any = true;
+    return any;
+  }
+
+ private:
+  static constexpr size_t kMost = (size_t)2 << 30;
+  int take(int i, hipStream_t stream, Lease *out) {
+    if (!(free_[(size_t)i].stream == StreamKey::of(stream))) DMM_HIP(hipStreamWaitEvent(stream, free_[(size_t)i].done, 0));
+    *out = free_[(size_t)i];
+    out_[out->device] += out->cap;
+    free_.erase(free_.begin() + i);
+    return DMM_OK;
+  }
+  bool allocate(size_t bytes, int device, Lease *out) {
+    Lease l;
+    l.cap = bytes;
+    l.device = device;
+    if (hipEventCreateWithFlags(&l.done, hipEventDisableTiming) != hipSuccess || hipMalloc((void **)&l.p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      if (l.done) (void)hipEventDestroy(l.done);
+      return false;
+    }
+    *out = l;
+    out_[device] += bytes;
+    return true;
+  }
+  bool drop_oldest(int device) {
+    for (size_t i = 0; i < free_.size(); ++i)
+      if (free_[i].device == device) {
+        const Lease l = free_[i];
+        (void)hipEventSynchronize(l.done);
+        (void)hipFree(l.p);
+        (void)hipEventDestroy(l.done);
+        free_.erase(free_.begin() + (long)i);
+        return true;
+      }
+    return false;
+  }
+  size_t held(int device) const {
+    size_t n = out_[device];
+    for (const Lease &e : free_)
+      if (e.device == device) n += e.cap;
+    return n;
+  }
+  std::mutex mu_;
+  std::vector<Lease> free_;            // in the order in which they came back
+  size_t out_[64] = {};                // bytes that calls have
+};
+
+PackPool &pack_pool() {
+  static PackPool *p = new PackPool;   // never destroyed, like the slab pool
+  return *p;
+}
+
+// hipMalloc on the current device; where there is no room, buffers that only wait for another product on
+// copies are given up for it.
+hipError_t device_malloc(char **p, size_t bytes) {
+  hipError_t e = hipMalloc((void **)p, bytes);
+  int device = 0;
+  if (e == hipErrorOutOfMemory && hipGetDevice(&device) == hipSuccess && pack_pool().trim(device)) {
+    (void)hipGetLastError();
+    e = hipMalloc((void **)p, bytes);
+  }
+  return e;
+}
+
 // One device buffer plus two pinned staging slots and their events.  Slabs are
 // recycled through a process-wide pool (in the spirit of the memory pool of
 // Section 4.2: allocate once, sub-allocate from the CPU side), so creating and
@@ -133,7 +258,7 @@ class SlabPool {
     size_t want = 64 * 1024;
     while (want < bytes) want *= 2;
     Slab s;
-    hipError_t e = hipMalloc((void **)&s.dev, want);
+    hipError_t e = device_malloc(&s.dev, want);
     for (int i = 0; i < 2 && e == hipSuccess; ++i) {
       e = hipHostMalloc((void **)&s.pinned[i], want, hipHostMallocDefault);
       if (e == hipSuccess) e = hipEventCreateWithFlags(&s.ev[i], hipEventDisableTiming);
@@ -279,7 +404,7 @@ class ScratchPool {
     size_t want = (size_t)4 << 20;
     while (want < bytes) want *= 2;
     char *p = nullptr;
-    hipError_t e = hipMalloc((void **)&p, want);
+    hipError_t e = device_malloc(&p, want);
     if (e != hipSuccess) {
       g_last_hip_error = (int)e;
       return e == hipErrorOutOfMemory ? DMM_ENOMEM : DMM_EHIP;
@@ -350,77 +475,14 @@ struct ExecLayout {
   RedLaunch red;                // the replica-sum launch behind the GEMM (n_items == 0: none)
 };
 
-// Buffers for dense copies of operands (pack_kernel.hpp), up to a few hundred MB each: of those not
-// in use the pool keeps 2 GiB in all, and none is handed out for less than half its size.
-class PackPool {
- public:
-  // DMM_ENOMEM (nothing recorded): there is no room, the caller does without
-  int acquire(size_t bytes, char **out, size_t *cap) {
-    int device = 0;
-    DMM_HIP(hipGetDevice(&device));
-    std::lock_guard<std::mutex> g(mu_);
-    for (size_t i = 0; i < free_.size(); ++i)
-      if (free_[i].device == device && free_[i].cap >= bytes && free_[i].cap / 2 <= bytes) {
-        *out = free_[i].p;
-        *cap = free_[i].cap;
-        held_ -= free_[i].cap;
-        free_.erase(free_.begin() + (long)i);
-        return DMM_OK;
-      }
-    const size_t want = (bytes + ((size_t)32 << 20) - 1) >> 25 << 25;
-    char *p = nullptr;
-    if (hipMalloc((void **)&p, want) != hipSuccess) {
-      (void)hipGetLastError();
-      return DMM_ENOMEM;
-    }
-    *out = p;
-    *cap = want;
-    return DMM_OK;
-  }
-  // The caller guarantees that no stream work still uses the buffer.
-  void release(char **p, size_t *cap, int device) {
-    if (!*p) return;
-    std::lock_guard<std::mutex> g(mu_);
-    // the oldest go first
-    while (!free_.empty() && held_ + *cap > kMost) {
-      (void)hipFree(free_[0].p);
-      held_ -= free_[0].cap;
-      free_.erase(free_.begin());
-    }
-    if (*cap <= kMost) {
-      free_.push_back({*p, *cap, device});
-      held_ += *cap;
-    } else {
-      (void)hipFree(*p);
-    }
-    *p = nullptr;
-    *cap = 0;
-  }
-
- private:
-  static constexpr size_t kMost = (size_t)2 << 30;
-  struct Entry {
-    char *p;
-    size_t cap;
-    int device;
-  };
-  std::mutex mu_;
-  std::vector<Entry> free_;
-  size_t held_ = 0;
-};
-
-PackPool &pack_pool() {
-  static PackPool *p = new PackPool;   // never destroyed, like the slab pool
-  return *p;
-}
-
 struct DeviceState {
-  // A product that runs on dense copies of its operands: the plan it runs as, the copies, and the
-  // tables of the kernel that makes them.
+  // A product that runs on dense copies of its operands: the plan it runs as, where the copies are, and
+  // the tables of the kernel that makes them.
   dmm_plan_t *dense = nullptr;
-  char *pack_buf = nullptr;
-  size_t pack_cap = 0;
-  int pack_device = 0;
+  PackPool::Lease pack;                // the copies' buffer, during a call
+  bool pack_kept = false;              // ... for as long as the plan lives: a captured graph refers to it
+  const char *pack_at = nullptr;       // where the tables say that the copies are
+  size_t pack_need = 0;
   Uploader pack_table;
   int pack_jobs = 0, pack_blocks = 0;
   size_t pack_o_tiles = 0, pack_o_runs = 0;
@@ -459,7 +521,7 @@ void destroy_device_state(DeviceState *d) {
   (void)d->uses.wait();
   if (d->dense) dmm_plan_destroy(d->dense);
   d->pack_table.release();
-  pack_pool().release(&d->pack_buf, &d->pack_cap, d->pack_device);
+  pack_pool().put(&d->pack);
   for (int i = 0; i < 2; ++i)
     if (d->t_pack[i]) (void)hipEventDestroy(d->t_pack[i]);
   d->gemm_table.release();

@@ -1152,14 +1152,26 @@ int stage_dense(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecLayout
 }
 
 // Gives back everything that is there for products on copies.
-int drop_dense(dmm_plan_t *P) {
+int drop_dense(dmm_plan_t *P, hipStream_t stream) {
   DeviceState &D = *P->dev;
+  if (D.pack_kept) return DMM_OK;
   const int rc = D.uses.wait();
   if (D.dense) dmm_plan_destroy(D.dense);
   D.dense = nullptr;
   D.pack_table.release();
-  pack_pool().release(&D.pack_buf, &D.pack_cap, D.pack_device);
+  pack_pool().give_back(&D.pack, stream);
   return rc;
+}
+
+// A buffer of D.pack_need bytes for the copies of this call.
+int take_copies(DeviceState &D, hipStream_t stream) {
+  if (D.pack_kept) return D.uses.order(stream);
+  int rc;
+  if (!D.pack.p && (rc = pack_pool().acquire(D.pack_need, stream, D.pack_at, &D.pack))) return rc;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();
+  D.pack_kept = status == hipStreamCaptureStatusActive;     // (the graph may run any time from now on)
+  return DMM_OK;
 }
 
 // The plan on the copies, the copies' buffer, the tables of the copy and those of the product on it:
@@ -1183,16 +1195,9 @@ int build_dense_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
   }
   const int64_t lda = dense_ld(d.len), share_bytes = 2 * M * lda, need = dense_bytes(P, d);
   D.pack_ldb = dense_ld(N);
-  // the copies are shared by all calls on this plan: order this call behind the others
-  if ((rc = D.uses.order(stream))) return rc;
-  if ((size_t)need > D.pack_cap) {
-    if (D.pack_buf) {
-      DMM_HIP(hipStreamSynchronize(stream));
-      pack_pool().release(&D.pack_buf, &D.pack_cap, D.pack_device);
-    }
-    if ((rc = pack_pool().acquire((size_t)need, &D.pack_buf, &D.pack_cap))) return rc;
-    D.pack_device = x.device;
-  }
+  D.pack_need = (size_t)need;
+  if ((rc = take_copies(D, stream))) return rc;
+  D.pack_at = D.pack.p;
   std::vector<PackRun> runs;
   std::vector<PackTile> tiles;
   std::vector<PackJob> jobs;
@@ -1227,7 +1232,7 @@ int build_dense_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
   D.pack_lda.assign((size_t)C.c, lda);
   for (int32_t r = 0; r < C.c; ++r) {
     const size_t first = runs.size();
-    char *dst = D.pack_buf + r * share_bytes;
+    char *dst = D.pack.p + r * share_bytes;
     for (size_t s = 0; s < S; ++s)
       if (d.share[s] == r) {
         if (runs.size() == first && d.at[s] > 0) runs.push_back({0, 0, 0, 0});
@@ -1243,7 +1248,7 @@ int build_dense_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
   const int64_t b_tile = (int64_t)tiles.size();
   const size_t b_runs = runs.size();
   operand(B, x.b_tiles, x.b_ld);
-  D.pack_b = D.pack_buf + C.c * share_bytes;
+  D.pack_b = D.pack.p + C.c * share_bytes;
   for (int32_t k = 0; k < B.gc; ++k)
     if (B.cc[k + 1] > B.cc[k]) runs.push_back({(int32_t)B.cc[k], (int32_t)(B.cc[k + 1] - B.cc[k]), k, 0});
   for (size_t s = 0; s < S; ++s) {
@@ -1267,7 +1272,6 @@ int build_dense_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
   ExecLayout product;
   if ((rc = stage_dense(P, x, stream, &product))) return rc;
   L->dense = true;
-  L->uses_split = true;
   return DMM_OK;
 }
 
@@ -1465,9 +1469,11 @@ int stage(dmm_plan_t *P, ExecArgs &x, hipStream_t stream, ExecLayout *L) {
   if (D.exec_cached && key == D.exec_key) {
     *L = D.exec_layout;
     D.table_reused = true;
-    if ((rc = (L->dense ? D.pack_table : D.gemm_table).order_behind_copy(stream))) return rc;
     // (the scratch buffer of macro-tiles cut along K is shared by all calls on this plan)
-    return L->uses_split ? D.uses.order(stream) : DMM_OK;
+    if (!L->dense) return (rc = D.gemm_table.order_behind_copy(stream)) || !L->uses_split ? rc : D.uses.order(stream);
+    if (!(rc = take_copies(D, stream)) && D.pack.p == D.pack_at) return D.pack_table.order_behind_copy(stream);
+    if (rc && rc != DMM_ENOMEM) return rc;
+    *L = ExecLayout();             // the copies get another place, or none
   }
   D.exec_cached = false;
   D.table_reused = false;
@@ -1483,7 +1489,7 @@ int stage(dmm_plan_t *P, ExecArgs &x, hipStream_t stream, ExecLayout *L) {
     if (rc == DMM_ENOMEM) {
       // no room for partial tiles or copies: the call's own work list, which may do with less
       (void)hipGetLastError();
-      if (sp.shape < 0 && (rc = drop_dense(P))) return rc;
+      if (sp.shape < 0 && (rc = drop_dense(P, stream))) return rc;
       *L = ExecLayout();
     } else {
       built = true;
@@ -1535,6 +1541,13 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
     DMM_HIP(hipGetDevice(&device));
     ExecArgs x = {dtype, es, bk, c_es, a_tiles, a_ld, b_tiles, b_ld, c_tiles, c_ld, flags, device, false};
     ExecLayout L;
+    struct HandBack {                  // the copies' buffer, behind all that was enqueued
+      DeviceState &D;
+      hipStream_t stream;
+      ~HandBack() {
+        if (!D.pack_kept) pack_pool().give_back(&D.pack, stream);
+      }
+    } hand_back = {*P->dev, stream};
     if ((rc = stage(P, x, stream, &L))) return rc;
     if (L.dense) return launch_dense(P, x, stream, timed);
     return launch_exec(P, L, es, stream, timed);

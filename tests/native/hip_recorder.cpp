@@ -7,6 +7,7 @@
 #include <cxxabi.h>
 #include <sys/mman.h>
 
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <map>
@@ -38,7 +39,7 @@ std::map<const void *, std::string> kernels;
 std::map<const void *, void *> symbols;
 std::map<void *, size_t> memory;
 size_t live = 0, limit = ~(size_t)0;
-int fail_in = -1;                                   // allocations until one fails
+int fail_in = -1, fail_n = 0;                       // allocations until some fail, and how many do
 hipError_t last_error = hipSuccess;
 dim3 cfg_grid, cfg_block;
 size_t cfg_lds;
@@ -83,10 +84,18 @@ void finish_all() {
 }
 
 bool before(int a, int b) {                         // a has finished when b starts, whatever the device does
-  if (a == b) return true;
-  if (ops[(size_t)a].done_at >= 0 && ops[(size_t)a].done_at <= b) return true;
-  for (int x : ops[(size_t)b].behind)
-    if (before(a, x)) return true;
+  std::vector<int> todo = {b};
+  std::vector<char> seen((size_t)std::max(a, b) + 1, 0);
+  while (!todo.empty()) {
+    const int x = todo.back();
+    todo.pop_back();
+    if (x == a || (ops[(size_t)a].done_at >= 0 && ops[(size_t)a].done_at <= x)) return true;
+    for (int y : ops[(size_t)x].behind)             // (what an operation is behind has been enqueued earlier)
+      if (!seen[(size_t)y] && y >= a) {
+        seen[(size_t)y] = 1;
+        todo.push_back(y);
+      }
+  }
   return false;
 }
 
@@ -111,7 +120,10 @@ void rec_set_capturing(uint64_t s, int on) {
 }
 void rec_set_limit(uint64_t bytes) { limit = bytes; }
 uint64_t rec_live() { return live; }
-void rec_fail_allocation(int n) { fail_in = n; }
+void rec_fail_allocations(int in, int n) {
+  fail_in = in;
+  fail_n = n;
+}
 int rec_failed() { return fail_in < 0; }
 
 // ---- the runtime ------------------------------------------------------------------------------------
@@ -171,7 +183,12 @@ hipError_t hipPeekAtLastError() { return last_error; }
 hipError_t hipGetSymbolAddress(void **p, const void *s) { *p = symbols[s]; return hipSuccess; }
 
 hipError_t hipMalloc(void **p, size_t n) {
-  if (fail_in >= 0 && fail_in-- == 0) return fail(hipErrorOutOfMemory);
+  if (fail_in <= 0 && fail_n > 0) {
+    fail_in = -1;
+    --fail_n;
+    return fail(hipErrorOutOfMemory);
+  }
+  if (fail_in > 0) --fail_in;
   if (live + n > limit) return fail(hipErrorOutOfMemory);
   void *m = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
   if (m == MAP_FAILED) return fail(hipErrorOutOfMemory);

@@ -380,34 +380,40 @@ def copies_do_not_show_in_the_bits(rec):
 
 
 def a_failed_allocation_costs_no_call(rec):
-    """Each device allocation of a call that would run on copies fails once: the call then runs its own work
-    list (whose tables there is room for), enqueues nothing of the copies, and goes on like that."""
-    block, cyclic, keep = workloads.block_desc, workloads.block_cyclic_desc, []
+    """One device allocation after another of a call that would run on copies fails, alone or with the one behind
+    it: the call then runs its own work list (whose tables there is room for), enqueues nothing of the
+    copies, and goes on like that."""
+    block, cyclic, keep, s = workloads.block_desc, workloads.block_cyclic_desc, [], rec.stream()
+    p = Product(tuple(cyclic(8192, 8192, 128, 128, 2, 4, 1) for _ in range(3)), 8)
+    rec.so.rec_fail_allocations(0, 3)
+    p.run(p.args(False), 0, s)               # no room for copies
+    assert rec.so.rec_failed() and [o[1] for o in rec.launches()] == ["grouped_gemm_comp_kernel"]
     for descs, ranks in ((tuple(cyclic(r, q, 100, 100, 2, 4, 1) for r, q in ((4101, 8200), (8200, 4099), (4101, 4099))), 8),
                          (tuple(cyclic(r, q, 100, 100, 2, 4, 2) for r, q in ((4200, 4099), (4099, 4102), (4200, 4102))), 16),
                          ((block(6656, 3840, 8, 8), block(3840, 5376, 8, 8), block(6656, 5376, 8, 8)), 64)):
-        n, failed = 0, True
-        while failed:
-            for _ in range(3):                                           # (plans that live on keep the pools empty)
-                keep.append(Product(descs, ranks))
-                keep[-1].run(keep[-1].args(False, 99), 0, rec.stream())
-            p, s = Product(descs, ranks), rec.stream()
-            args = p.args(False, n)
-            at = len(rec.ops())
-            rec.so.rec_fail_allocation(n)
-            p.run(args, 0, s)
-            failed = bool(rec.so.rec_failed())
-            rec.so.rec_fail_allocation(-1)
-            first = [o[1] for o in rec.launches(at)]
-            at = len(rec.ops())
-            p.run(args, 0, s)
-            assert [o[1] for o in rec.launches(at)] == first and p.plan.last_execute().table_reused
-            assert ("pack_kernel" in first) == p.plan.ran_dense() == (not failed), (n, first)
-            assert len([o for o in first if "gemm" in o]) == 1, first
-            rec.check_tables()
-            keep.append(p)
-            n += 1
-        assert n >= 4                        # the copies, two sets of tables, none
+        for times in (1, 2):
+            n, failed = 0, True
+            while failed:
+                for _ in range(3):                                       # (plans that live on keep the pools of tables empty)
+                    keep.append(Product(descs, ranks))
+                    keep[-1].run(keep[-1].args(False, 99), 0, s)
+                p = Product(descs, ranks)
+                args = p.args(False, n)
+                at = len(rec.ops())
+                rec.so.rec_fail_allocations(n, times)
+                p.run(args, 0, s)
+                failed = bool(rec.so.rec_failed())
+                rec.so.rec_fail_allocations(-1, 0)
+                first = [o[1] for o in rec.launches(at)]
+                at = len(rec.ops())
+                p.run(args, 0, s)
+                assert [o[1] for o in rec.launches(at)] == first and p.plan.last_execute().table_reused
+                assert ("pack_kernel" in first) == p.plan.ran_dense() == (not failed), (n, first)
+                assert len([o for o in first if "gemm" in o]) == 1, first
+                rec.check_tables()
+                keep.append(p)
+                n += 1
+            assert n >= 3                    # two sets of tables, none
 
 
 def calls_can_be_captured(rec):
@@ -454,10 +460,90 @@ def a_stream_for_every_thread(rec):
     p.plan.destroy()
 
 
+class Copies:
+    """Where the copies of the calls of a scenario lay, and which launches read and wrote them."""
+
+    def __init__(self, rec):
+        self.rec, self.calls = rec, []
+
+    def run(self, p, args, stream):
+        """A call on copies; the address range of the copies."""
+        at = len(self.rec.ops())
+        p.run(args, 0, stream)
+        launches = self.rec.launches(at)
+        assert p.plan.ran_dense() and launches[0][1] == "pack_kernel", launches
+        jobs, _, _ = _pack_tables(self.rec, launches[0][0])
+        lo = min(j[0] for j in jobs)
+        hi = max(j[0] + j[3] * j[1] for j in jobs)
+        for first, last, lo2, hi2 in self.calls:
+            if lo < hi2 and lo2 < hi:
+                assert self.rec.before(last, launches[0][0]), "copies are made over those that an earlier product reads"
+        self.calls.append((launches[0][0], launches[-1][0], lo, hi))
+        self.rec.check_tables()
+        return lo, hi
+
+
+def copies_share_their_memory(rec):
+    """Many plans that are kept, all on copies: on one stream they take one buffer, whose place stays good for
+    their tables; on several streams they overlap only in order; all copies together stay within 2 GiB."""
+    cyclic = workloads.block_cyclic_desc
+    sizes = [(8192, 8192, 8192, 128), (4101, 2051, 4099, 100), (8192, 4096, 8192, 128), (8192, 8192, 8192, 128), (12288, 12288, 8192, 128)]
+    plans = []
+    for m, k, n, nb in sizes:
+        p = Product(tuple(cyclic(r, q, nb, nb, 2, 4, 1) for r, q in ((m, k), (k, n), (m, n))), 8)
+        plans.append((p, p.args(False, len(plans))))
+    copies, s = Copies(rec), rec.stream()
+    start = rec.so.rec_live()
+    for times in range(3):
+        for p, args in plans[::-1]:
+            copies.run(p, args, s)
+            assert times < 1 or p.plan.last_execute().table_reused
+    assert len({lo for _, _, lo, _ in copies.calls}) == 1
+    assert rec.so.rec_live() - start < (520 << 20)
+    import random
+    rng, streams = random.Random(5), [rec.stream() for _ in range(6)] + [s]
+    for _ in range(60):
+        p, args = rng.choice(plans)
+        copies.run(p, args, rng.choice(streams))
+        assert rec.so.rec_live() - start <= (2 << 30) + (64 << 20)
+    for p, _ in plans:
+        p.plan.destroy()
+    big = Product(tuple(cyclic(r, q, 128, 128, 2, 4, 1) for r, q in ((16384, 24576), (24576, 16384), (16384, 16384))), 8)   # 1.6 GB: the others make room
+    big.run(big.args(False, 9), 0, s)
+    assert big.plan.ran_dense() and rec.so.rec_live() - start <= (2 << 30) + (64 << 20)
+    # tables that need more than there is left take it from the copies
+    rec.so.rec_set_limit(rec.so.rec_live() + (1 << 16))
+    p = Product(tuple(cyclic(4096, 4096, 16, 16, 2, 4, 1) for _ in range(3)), 8)
+    p.run(p.args(), 0, s)
+
+
+def a_captured_call_keeps_its_copies(rec):
+    """The buffer of a call that is captured goes to no other plan until its own is destroyed."""
+    cyclic = workloads.block_cyclic_desc
+    d = tuple(cyclic(8192, 8192, 128, 128, 2, 4, 1) for _ in range(3))
+    p, q, r = (Product(d, 8) for _ in range(3))
+    copies, s, other = Copies(rec), rec.stream(), rec.stream()
+    pa, qa, ra = p.args(False), q.args(False, 1), r.args(False, 2)
+    copies.run(p, pa, s)
+    where = copies.run(q, qa, s)
+    rec.so.rec_set_capturing(s, 1)
+    assert copies.run(p, pa, s) == where
+    rec.so.rec_set_capturing(s, 0)
+    for x, args in ((q, qa), (r, ra), (q, qa)):
+        for stream in (s, other):
+            lo, hi = copies.run(x, args, stream)
+            assert hi <= where[0] or where[1] <= lo
+    assert copies.run(p, pa, other) == where
+    p.plan.destroy()
+    rec.so.rec_set_limit(rec.so.rec_live())
+    assert copies.run(Product(d, 8), p.args(False, 3), rec.stream())
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
              more_streams_than_the_plan_remembers, reports_say_what_ran,
              the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call,
-             calls_can_be_captured, a_stream_for_every_thread]
+             calls_can_be_captured, a_stream_for_every_thread,
+             copies_share_their_memory, a_captured_call_keeps_its_copies]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
