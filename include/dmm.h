@@ -214,7 +214,11 @@ const dmm_merged_item *dmm_plan_merged_items(const dmm_plan_t *p);
  * the call, where an estimate finds that faster (DMM_NO_MERGE keeps the macro-tiles;
  * dmm_plan_last_kernels tells).  The shape, the element types and the device decide
  * how the sums are cut along K: the copies, which a call takes or not by where its
- * operands lie and by what memory is free, leave the bits of the result as they are.
+ * operands lie and by what memory is free, leave the bits of the result as they are,
+ * and a small product without room for all of its partial sums takes its tiles in several
+ * launches.  (Only where the device has no memory left at all, not for a small product's
+ * work table or the partial sums of one tile, does a call try the macro-tiles in its place,
+ * which may cut K otherwise.)
  * The first call on a plan takes the plan's device work table (and, if needed, that
  * scratch buffer) from a process-wide pool, allocating only when the pool has none that
  * fits; later calls with the same arguments allocate nothing and do not synchronise.

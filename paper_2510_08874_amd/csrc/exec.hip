@@ -914,7 +914,7 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
 //   SmallTile rows[] | cols[] | PieceDev a[] | b[] | c[] | int32 mc[] | nc[] | before[] | klen[]
 // DMM_EINVAL where a tile that the op list names has no pointer.
 int build_small_exec(dmm_plan_t *P, const ExecArgs &x, const SmallPlan &sp, hipStream_t stream, ExecLayout *L) {
-  int rc;
+  int rc = DMM_OK;
   const Grid &A = P->A, &B = P->B, &C = P->C;
   const SmallKind &kind = kSmall[sp.shape];
   const size_t MR = sp.mc.size() - 1, NR = sp.nc.size() - 1, S = sp.kc.size() - 1;
@@ -992,9 +992,17 @@ int build_small_exec(dmm_plan_t *P, const ExecArgs &x, const SmallPlan &sp, hipS
   l.runs = sp.runs;
   l.per = sp.per;
   l.c_es = (int32_t)x.c_es;
-  if (sp.runs > 1 &&
-      (rc = acquire_split_buffer(P, (size_t)sp.runs * sp.rows.size() * sp.cols.size() * (size_t)(kind.tm * kind.tn) * sizeof(float), stream)))
-    return rc;
+  // Partial tiles: how K is cut does not depend on free memory, so where there is no room for those of all
+  // tiles at once, the tiles are taken in several launches.
+  l.batch = l.tiles_m * l.tiles_n;
+  if (sp.runs > 1)
+    for (;;) {
+      rc = acquire_split_buffer(P, (size_t)sp.runs * (size_t)l.batch * (size_t)(kind.tm * kind.tn) * sizeof(float), stream);
+      if (rc != DMM_ENOMEM || l.batch == 1) break;
+      (void)hipGetLastError();
+      l.batch = (l.batch + 1) / 2;
+    }
+  if (rc) return rc;
   if ((rc = P->dev->gemm_table.upload(h.data(), h.size(), stream, P->dev->uses))) return rc;
   L->uses_split = sp.runs > 1;
   return DMM_OK;
@@ -1327,8 +1335,11 @@ int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stre
       if ((rc = timing_events(P->dev->t_gemm))) return rc;
       DMM_HIP(hipEventRecord(P->dev->t_gemm[0], stream));
     }
-    small_launch(l.shape, g, stream);
-    DMM_HIP(hipGetLastError());
+    for (g.first = 0; g.first < l.tiles_m * l.tiles_n; g.first += l.batch) {
+      g.tiles = std::min(l.batch, l.tiles_m * l.tiles_n - g.first);
+      small_launch(l.shape, g, stream);
+      DMM_HIP(hipGetLastError());
+    }
     if (timed) {
       DMM_HIP(hipEventRecord(P->dev->t_gemm[1], stream));
       P->dev->gemm_timed = true;
@@ -1487,7 +1498,7 @@ int stage(dmm_plan_t *P, ExecArgs &x, hipStream_t stream, ExecLayout *L) {
   if ((given && sp.shape >= 0) || choose_dense(P, x, given, cus, &x.uncut)) {
     rc = sp.shape >= 0 ? build_small_exec(P, x, sp, stream, L) : build_dense_exec(P, x, stream, L);
     if (rc == DMM_ENOMEM) {
-      // no room for partial tiles or copies: the call's own work list, which may do with less
+      // no room for copies (or for anything): the call's own work list, which may do with less
       (void)hipGetLastError();
       if (sp.shape < 0 && (rc = drop_dense(P, stream))) return rc;
       *L = ExecLayout();

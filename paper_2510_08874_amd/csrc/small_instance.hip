@@ -14,7 +14,7 @@ hipError_t allow() {
 
 template <class SH>
 void launch(const SmallArgs &g, hipStream_t stream) {
-  const unsigned tiles = (unsigned)(g.tiles_m * g.tiles_n);
+  const unsigned tiles = (unsigned)g.tiles;
   hipLaunchKernelGGL(small_gemm_kernel<SH>, dim3(tiles * (unsigned)g.runs), dim3(NT), SH::LDS, stream, g);
   if (g.runs > 1 && hipPeekAtLastError() == hipSuccess)
     hipLaunchKernelGGL(small_sum_kernel<SH>, dim3(tiles * (unsigned)(SH::TM * SH::TN / 1024)), dim3(NT), 0, stream, g);

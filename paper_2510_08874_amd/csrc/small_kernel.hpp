@@ -43,10 +43,11 @@ struct SmallArgs {
   const int32_t *before;               // [S + 1] K steps in front of every segment
   const int32_t *klen;                 // [S]
   const PieceDev *pa, *pb, *pc;        // A slice (i, s) at pa[i S + s], B slice (s, j) at pb[s NR + j], C slice (i, j) at pc[i NR + j]
-  float *scratch;                      // runs > 1: partial tiles, number run * tiles + tile
+  float *scratch;                      // runs > 1: partial tiles of the launch, number run * tiles + tile
   int32_t S, NR;
   int32_t tiles_m, tiles_n;
   int32_t runs, per;                   // a tile's K steps in `runs` ranges of `per` steps (the last may be shorter)
+  int32_t first, tiles;                // tiles [first, first + tiles) are this launch's
   int32_t c_es;                        // bytes per element of C
   int32_t pad;
 };
@@ -124,8 +125,8 @@ __global__ __launch_bounds__(NT, SH::OCC) void small_gemm_kernel(const SmallArgs
   const int total = (int)gridDim.x, q8 = total >> 3, r8 = total & 7;
   const int xcd = blockIdx.x & 7, pos = blockIdx.x >> 3;
   const int id = xcd * q8 + (xcd < r8 ? xcd : r8) + pos;
-  const int tiles = g.tiles_m * g.tiles_n;
-  const int run = id / tiles, tile = id - run * tiles;
+  const int tiles = g.tiles;
+  const int run = id / tiles, local = id - run * tiles, tile = g.first + local;
   const SmallTile tr = g.rows[tile / g.tiles_n], tc = g.cols[tile % g.tiles_n];
   const int S = g.S, NR = g.NR;
   const int t0 = run * g.per, t_end = g.before[S];
@@ -353,7 +354,7 @@ __global__ __launch_bounds__(NT, SH::OCC) void small_gemm_kernel(const SmallArgs
       for (int e = 0; e < 16; ++e)
         out[(wm * (MI * 32) + i * 32 + 8 * (e >> 2) + 4 * half + (e & 3)) * SH::T_PITCH + wn * (NI * 32) + j * 32 + (lane & 31)] = acc[i][j][e];
   __syncthreads();
-  float *part = g.scratch + (int64_t)(run * tiles + tile) * (SH::TM * SH::TN);
+  float *part = g.scratch + (int64_t)(run * tiles + local) * (SH::TM * SH::TN);
 #pragma unroll 2
   for (int x = tid; x < SH::TM * SH::TN / 4; x += NT) {
     const int r = x / (SH::TN / 4), c = x % (SH::TN / 4) * 4;
@@ -371,14 +372,13 @@ __global__ __launch_bounds__(NT, SH::OCC) void small_gemm_kernel(const SmallArgs
 template <class SH>
 __global__ __launch_bounds__(NT) void small_sum_kernel(const SmallArgs g) {
   constexpr int BLOCKS = SH::TM * SH::TN / 1024;
-  const int tile = blockIdx.x / BLOCKS, x = (blockIdx.x % BLOCKS) * NT + threadIdx.x;
-  const int tiles = g.tiles_m * g.tiles_n;
+  const int local = blockIdx.x / BLOCKS, tile = g.first + local, x = (blockIdx.x % BLOCKS) * NT + threadIdx.x;
   const SmallTile tr = g.rows[tile / g.tiles_n], tc = g.cols[tile % g.tiles_n];
   const int r = x / (SH::TN / 4), c = x % (SH::TN / 4) * 4;
   if (r >= tr.ext || c >= tc.ext) return;
   typedef const __attribute__((address_space(1))) f32x4 *gvec;
-  const int64_t step = (int64_t)tiles * (SH::TM * SH::TN);
-  const float *p = g.scratch + (int64_t)tile * (SH::TM * SH::TN) + r * SH::TN + c;
+  const int64_t step = (int64_t)g.tiles * (SH::TM * SH::TN);
+  const float *p = g.scratch + (int64_t)local * (SH::TM * SH::TN) + r * SH::TN + c;
   f32x4 s = *(gvec)p;
   constexpr int QB = 8;                                   // runs whose loads are in flight at a time
   for (int q0 = 1; q0 < g.runs; q0 += QB) {

@@ -539,11 +539,33 @@ def a_captured_call_keeps_its_copies(rec):
     assert copies.run(Product(d, 8), p.args(False, 3), rec.stream())
 
 
+def free_memory_does_not_show_in_the_cut(rec):
+    """A small product that is cut along K, with less and less room for its partial tiles: the same tiles, cut
+    into the same ranges, in more launches; every workgroup runs once."""
+    for descs, ranks, dtype in ((row_col(1024, 16384, 1024), 8, "bf16"), (row_col(2501, 1999, 1777), 8, "f32")):
+        seen, launches, keep = set(), [], []
+        for room in (1 << 40, 40 << 20, 20 << 20, 6 << 20):
+            p = Product(descs, ranks, dtype=dtype)
+            rec.so.rec_set_limit(rec.so.rec_live() + room)
+            at = len(rec.ops())
+            p.run(p.args(), 0, rec.stream())
+            got = rec.launches(at)
+            assert [o[1] for o in got] == ["small_gemm_kernel", "small_sum_kernel"] * (len(got) // 2)
+            k = p.plan.last_kernels()
+            blocks = [sum(rec.so.rec_blocks(o[0]) for o in got if o[1] == name) for name in ("small_gemm_kernel", "small_sum_kernel")]
+            seen.add((k.small_rows, k.small_cols, k.small_runs, *blocks))
+            launches.append(len(got))
+            rec.check_tables()
+            keep.append(p)                           # (nothing goes back to the pools)
+        assert len(seen) == 1 and k.small_runs > 1 and launches[0] == 2 < launches[-1] and launches == sorted(launches), (seen, launches)
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
              more_streams_than_the_plan_remembers, reports_say_what_ran,
              the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call,
              calls_can_be_captured, a_stream_for_every_thread,
-             copies_share_their_memory, a_captured_call_keeps_its_copies]
+             copies_share_their_memory, a_captured_call_keeps_its_copies,
+             free_memory_does_not_show_in_the_cut]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
