@@ -76,10 +76,16 @@ class Uses {
       if (!(uses_[i].key == key)) DMM_HIP(hipStreamWaitEvent(stream, uses_[i].ev, 0));
     return DMM_OK;
   }
-  // blocks until they have finished
+  // blocks until they have finished (all of them, also where one reports an error)
   int wait() const {
-    for (int i = 0; i < n_; ++i) DMM_HIP(hipEventSynchronize(uses_[i].ev));
-    return DMM_OK;
+    int rc = DMM_OK;
+    for (int i = 0; i < n_; ++i) {
+      const hipError_t e = hipEventSynchronize(uses_[i].ev);
+      if (e == hipSuccess) continue;
+      g_last_hip_error = (int)e;
+      rc = DMM_EHIP;
+    }
+    return rc;
   }
   void destroy() {
     for (int i = 0; i < n_; ++i) (void)hipEventDestroy(uses_[i].ev);

@@ -39,6 +39,7 @@ std::map<const void *, std::string> kernels;
 std::map<const void *, void *> symbols;
 std::map<void *, size_t> memory;
 size_t live = 0, limit = ~(size_t)0;
+int fail_waits = 0;                                 // waits for an event that report an error and do not wait
 int fail_in = -1, fail_n = 0;                       // allocations until some fail, and how many do
 hipError_t last_error = hipSuccess;
 dim3 cfg_grid, cfg_block;
@@ -124,6 +125,7 @@ void rec_fail_allocations(int in, int n) {
   fail_in = in;
   fail_n = n;
 }
+void rec_fail_waits(int n) { fail_waits = n; }
 int rec_failed() { return fail_in < 0; }
 
 // ---- the runtime ------------------------------------------------------------------------------------
@@ -239,7 +241,14 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
   events[e] = enqueue("event", real(s), (uint64_t)e, 0);
   return hipSuccess;
 }
-hipError_t hipEventSynchronize(hipEvent_t e) { finish(events[e]); return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t e) {
+  if (fail_waits > 0) {
+    --fail_waits;
+    return fail(hipErrorUnknown);
+  }
+  finish(events[e]);
+  return hipSuccess;
+}
 hipError_t hipEventQuery(hipEvent_t e) {
   const int i = events[e];
   return i < 0 || ops[(size_t)i].done_at >= 0 ? hipSuccess : hipErrorNotReady;   // (not an error to be read back later)

@@ -560,12 +560,27 @@ def free_memory_does_not_show_in_the_cut(rec):
         assert len(seen) == 1 and k.small_runs > 1 and launches[0] == 2 < launches[-1] and launches == sorted(launches), (seen, launches)
 
 
+def an_error_on_one_stream_leaves_the_others_waited_for(rec):
+    p = Product(row_col(1024, 512, 1024), 8)
+    args, streams = p.args(), [rec.stream() for _ in range(3)]
+    for s in streams:
+        p.run(args, 0, s)
+    readers = [o[0] for o in rec.launches()]
+    rec.so.rec_fail_waits(1)
+    p.plan.destroy()
+    q = Product(row_col(1024, 520, 1024), 8)
+    q.run(q.args(), 0, rec.stream())
+    mark = rec.ops()[-1][0]
+    assert [rec.before(r, mark) for r in readers] == [False, True, True]
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
              more_streams_than_the_plan_remembers, reports_say_what_ran,
              the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call,
              calls_can_be_captured, a_stream_for_every_thread,
              copies_share_their_memory, a_captured_call_keeps_its_copies,
-             free_memory_does_not_show_in_the_cut]
+             free_memory_does_not_show_in_the_cut,
+             an_error_on_one_stream_leaves_the_others_waited_for]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
