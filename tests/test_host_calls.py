@@ -568,6 +568,7 @@ def an_error_on_one_stream_leaves_the_others_waited_for(rec):
     readers = [o[0] for o in rec.launches()]
     rec.so.rec_fail_waits(1)
     p.plan.destroy()
+    rec.so.hipGetLastError()
     q = Product(row_col(1024, 520, 1024), 8)
     q.run(q.args(), 0, rec.stream())
     mark = rec.ops()[-1][0]
