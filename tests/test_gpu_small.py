@@ -1,7 +1,7 @@
 """GPU parity of the kernels for small and skinny products (tiles of 32 to 128 rows and columns
 cut across the cuts of A, B and C): against the fp64 oracle with the element bound of
-test_gpu_parity, and bitwise against the macro-tile kernels (DMM_NO_MERGE) where neither run cut its
-tiles along K.  The padding of every operand row holds infinities: a read past a segment that
+test_gpu_parity, and bitwise against the macro-tile kernels (DMM_NO_MERGE) where the tiles are not
+cut along K (every shape but 32 x 32, whose waves share K).  Every case names the shape that has to run.  The padding of every operand row holds infinities: a read past a segment that
 reached a sum would show as NaN."""
 import numpy as np
 import pytest
@@ -43,30 +43,43 @@ def _pad_with_inf(prob):
                 t[:, c1 - c0:] = float("inf")
 
 
-@pytest.mark.parametrize("dims,dtype,kind,ldm", [
-    ((1, 1, 1), "bf16", "whole", 1),              # pitches of one element
-    ((1, 1, 1), "f32", "whole", 1),
-    ((5, 70, 3), "bf16", "whole", 1),             # B rows of 6 bytes: a chunk spans rows
-    ((32, 64, 128), "bf16", "whole", 8),          # one tile and one step exactly
-    ((33, 65, 129), "bf16", "whole", 1),          # one more of everything
-    ((31, 63, 127), "bf16", "blocks", 8),
-    ((32, 32, 32), "f32", "whole", 1),
-    ((33, 129, 31), "f32", "blocks", 4),
-    ((65, 33, 65), "f32", "uneven", 1),
-    ((300, 143, 384), "f32", "blocks", 1),
-    ((555, 717, 359), "bf16", "uneven", 1),       # K tails in eleven segments, column cuts at odd places
-    ((555, 717, 359), "bf16", "uneven", 8),
-    ((900, 333, 1100), "bf16", "blocks", 8),
-    ((1290, 260, 1030), "bf16", "blocks", 1),     # 128 x 128 tiles, ragged
-    ((128, 2285, 4192), "bf16", "column", 8),     # runs of K steps, added up by a second launch
-    ((13, 3121, 4999), "bf16", "column", 1),
-    ((64, 5760, 1240), "bf16", "column", 8),
-    ((577, 9001, 130), "bf16", "uneven", 1),      # runs that start inside segments
-    ((640, 2048, 640), "f32", "blocks", 4),
-    ((201, 3001, 203), "f32", "uneven", 1),
+S, H, B, T, F = (32, 128), (64, 128), (128, 128), (32, 32), (64, 64)      # the tiles: three for bf16, two for fp32
+
+
+# (tile: that of the shape that has to run; runs: K is cut into several ranges)
+@pytest.mark.parametrize("dims,dtype,kind,ldm,tile,runs", [
+    ((1, 1, 1), "bf16", "whole", 1, S, False),    # pitches of one element
+    ((1, 1, 1), "f32", "whole", 1, T, False),
+    ((5, 70, 3), "bf16", "whole", 1, S, False),   # B rows of 6 bytes: a chunk spans rows
+    ((32, 64, 128), "bf16", "whole", 8, S, False),   # one tile and one step exactly
+    ((33, 65, 129), "bf16", "whole", 1, S, False),   # one more of everything
+    ((31, 63, 127), "bf16", "blocks", 8, S, False),
+    ((32, 32, 32), "f32", "whole", 1, T, False),
+    ((33, 129, 31), "f32", "blocks", 4, T, False),
+    ((65, 33, 65), "f32", "uneven", 1, T, True),
+    ((300, 143, 384), "f32", "blocks", 1, T, False),
+    ((555, 717, 359), "bf16", "uneven", 1, S, True),   # K tails in eleven segments, column cuts at odd places
+    ((555, 717, 359), "bf16", "uneven", 8, S, True),
+    ((900, 333, 1100), "bf16", "blocks", 8, S, False),
+    ((1290, 260, 1030), "bf16", "blocks", 1, S, False),
+    ((128, 2285, 4192), "bf16", "column", 8, B, True),   # runs of K steps, added up by a second launch
+    ((13, 3121, 4999), "bf16", "column", 1, S, True),
+    ((64, 5760, 1240), "bf16", "column", 8, S, True),
+    ((577, 9001, 130), "bf16", "uneven", 1, B, True),    # runs that start inside segments
+    ((640, 2048, 640), "f32", "blocks", 4, F, True),
+    ((201, 3001, 203), "f32", "uneven", 1, F, True),
+    # every shape whose sums may run uncut, ragged at all edges and with K tails
+    ((401, 325, 8753), "bf16", "whole", 1, H, False),
+    ((425, 347, 8583), "bf16", "uneven", 1, H, False),
+    ((1317, 2034, 120), "bf16", "blocks", 8, H, True),
+    ((1553, 203, 2003), "bf16", "whole", 1, B, False),
+    ((1909, 343, 1495), "bf16", "uneven", 1, B, False),
+    ((1909, 343, 1495), "bf16", "uneven", 8, B, False),
+    ((1669, 221, 279), "f32", "blocks", 1, F, False),
+    ((217, 129, 6538), "f32", "uneven", 1, F, False),
 ])
 @pytest.mark.parametrize("c_dtype", ["f32", "bf16"])
-def test_small_products(dims, dtype, kind, ldm, c_dtype):
+def test_small_products(dims, dtype, kind, ldm, tile, runs, c_dtype):
     from paper_2510_08874_amd import binding
     cfg = _cfg(dims, dtype, kind)
     A, B = workloads.make_operands(cfg)
@@ -74,6 +87,8 @@ def test_small_products(dims, dtype, kind, ldm, c_dtype):
     _pad_with_inf(prob)
     prob.execute()
     split = prob.plan.ran_k_split()
+    assert prob.plan.small_tile() == tile and (prob.plan.last_kernels().small_runs > 1) == runs
+    assert split == (runs or tile == T)                  # (the four waves of a 32 x 32 tile share its K steps)
     got = prob.c_global(0)
     for t, ld, (ti, tj) in zip(prob.C.tensors, prob.C.ld, [(i, j) for i in range(prob.C.gr) for j in range(prob.C.gc)]):
         r0, r1, c0, c1 = prob.C.bounds(ti, tj)
@@ -90,6 +105,8 @@ def test_small_products(dims, dtype, kind, ldm, c_dtype):
     prob.execute()
     assert np.array_equal(got, prob.c_global(0))
     prob.execute(flags=binding.DMM_NO_MERGE | (binding.DMM_C_BF16 if c_dtype == "bf16" else 0))
-    if not split and not prob.plan.ran_k_split():
+    assert prob.plan.small_tile() is None
+    if not split:
+        assert not prob.plan.ran_k_split()
         assert np.array_equal(got, prob.c_global(0))
     prob.close()
