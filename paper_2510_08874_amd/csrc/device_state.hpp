@@ -483,8 +483,8 @@ struct ExecLayout {
 };
 
 struct DeviceState {
-  // A product that runs on dense copies of its operands: the plan it runs as, where the copies are, and
-  // the tables of the kernel that makes them.
+  // A product that runs on dense copies of its operands: the plan it runs as, whose `uses` stand for these
+  // calls, where the copies are, and the tables of the kernel that makes them.
   dmm_plan_t *dense = nullptr;
   PackPool::Lease pack;                // the copies' buffer, during a call
   bool pack_kept = false;              // ... for as long as the plan lives: a captured graph refers to it
@@ -497,6 +497,7 @@ struct DeviceState {
   std::vector<const void *> pack_a;    // the copy of A, one tile per replica of C
   std::vector<int64_t> pack_lda;
   int64_t pack_ldb = 0;
+  bool pack_launched = false;          // the copy of this call is under way
   bool ran_dense = false;              // the last dmm_execute did so
   int ran_small = -1, small_runs = 0;  // ... ran the kernels for small products: their shape, its tiles in so many ranges of K
   hipEvent_t t_pack[2] = {nullptr, nullptr};

@@ -1155,25 +1155,41 @@ int stage_dense(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecLayout
   in.b_tiles = &b;
   in.b_ld = &D.pack_ldb;
   in.uncut = true;
-  const int rc = ensure_state(D.dense);
-  return rc ? rc : stage(D.dense, in, stream, L);
+  return stage(D.dense, in, stream, L);
+}
+
+// Launches the copy, whose tables are in place.
+int launch_copy(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream) {
+  int rc;
+  DeviceState &D = *P->dev;
+  const bool timed = (x.flags & DMM_TIMING) != 0;
+  if (timed) {
+    if ((rc = timing_events(D.t_pack))) return rc;
+    DMM_HIP(hipEventRecord(D.t_pack[0], stream));
+  }
+  TraceRange tr("copy_operands");
+  const char *d = D.pack_table.dev();
+  hipLaunchKernelGGL(pack_kernel, dim3((unsigned)D.pack_blocks), dim3(256), 0, stream, (const PackJob *)d, D.pack_jobs,
+                     (const PackRun *)(d + D.pack_o_runs), (const PackTile *)(d + D.pack_o_tiles));
+  DMM_HIP(hipGetLastError());
+  D.pack_launched = true;
+  if (timed) DMM_HIP(hipEventRecord(D.t_pack[1], stream));
+  return DMM_OK;
 }
 
 // Gives back everything that is there for products on copies.
-int drop_dense(dmm_plan_t *P, hipStream_t stream) {
+void drop_dense(dmm_plan_t *P, hipStream_t stream) {
   DeviceState &D = *P->dev;
-  if (D.pack_kept) return DMM_OK;
-  const int rc = D.uses.wait();
-  if (D.dense) dmm_plan_destroy(D.dense);
+  if (D.pack_kept) return;
+  if (D.dense) dmm_plan_destroy(D.dense);       // (waits for the calls on copies)
   D.dense = nullptr;
   D.pack_table.release();
   pack_pool().give_back(&D.pack, stream);
-  return rc;
 }
 
 // A buffer of D.pack_need bytes for the copies of this call.
 int take_copies(DeviceState &D, hipStream_t stream) {
-  if (D.pack_kept) return D.uses.order(stream);
+  if (D.pack_kept) return D.dense->dev->uses.order(stream);
   int rc;
   if (!D.pack.p && (rc = pack_pool().acquire(D.pack_need, stream, D.pack_at, &D.pack))) return rc;
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -1182,9 +1198,10 @@ int take_copies(DeviceState &D, hipStream_t stream) {
   return DMM_OK;
 }
 
-// The plan on the copies, the copies' buffer, the tables of the copy and those of the product on it:
-// all that such a call needs memory for, so that a call with these tables in place cannot run out of
-// it.  DMM_ENOMEM: no room.
+// The plan on the copies, the copies' buffer, the tables of the copy and, while the copy runs already,
+// those of the product on it (70 us of host work for 8192^3 in 128 x 128 tiles).  With them in
+// place a call cannot run out of memory any more.  DMM_ENOMEM: no room (if it was the last tables that
+// had none, the copy was for nothing).
 int build_dense_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecLayout *L) {
   int rc;
   DeviceState &D = *P->dev;
@@ -1201,6 +1218,7 @@ int build_dense_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
     if ((rc = dmm_plan(&a, &b, &c, P->nranks, 0, &D.dense))) return rc;
     D.dense->dense_copy = true;
   }
+  if ((rc = ensure_state(D.dense))) return rc;
   const int64_t lda = dense_ld(d.len), share_bytes = 2 * M * lda, need = dense_bytes(P, d);
   D.pack_ldb = dense_ld(N);
   D.pack_need = (size_t)need;
@@ -1276,9 +1294,13 @@ int build_dense_exec(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, ExecL
   std::memcpy(h.data(), jobs.data(), jobs.size() * sizeof(PackJob));
   std::memcpy(h.data() + D.pack_o_tiles, tiles.data(), tiles.size() * sizeof(PackTile));
   std::memcpy(h.data() + D.pack_o_runs, runs.data(), runs.size() * sizeof(PackRun));
-  if ((rc = D.pack_table.upload(h.data(), h.size(), stream, D.uses))) return rc;
+  if ((rc = D.pack_table.upload(h.data(), h.size(), stream, D.dense->dev->uses))) return rc;
+  if ((rc = launch_copy(P, x, stream))) return rc;
   ExecLayout product;
-  if ((rc = stage_dense(P, x, stream, &product))) return rc;
+  if ((rc = stage_dense(P, x, stream, &product))) {
+    const int rc2 = D.dense->dev->uses.mark(stream);      // (of the copy)
+    return rc2 ? rc2 : rc;
+  }
   L->dense = true;
   return DMM_OK;
 }
@@ -1429,22 +1451,13 @@ int launch_dense(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, bool time
   int rc;
   DeviceState &D = *P->dev;
   ExecLayout product;
-  if ((rc = stage_dense(P, x, stream, &product))) return rc;       // (they are in place: this orders the stream behind them)
-  if (timed) {
-    if ((rc = timing_events(D.t_pack))) return rc;
-    DMM_HIP(hipEventRecord(D.t_pack[0], stream));
+  if (!D.pack_launched && (rc = launch_copy(P, x, stream))) return rc;
+  // (the tables are in place: this orders the stream behind them)
+  if (!(rc = stage_dense(P, x, stream, &product))) rc = launch_exec(D.dense, product, x.es, stream, timed);
+  if (rc) {
+    const int rc2 = D.dense->dev->uses.mark(stream);      // (of a copy whose product failed)
+    return rc2 ? rc2 : rc;
   }
-  {
-    TraceRange tr("copy_operands");
-    const char *d = D.pack_table.dev();
-    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)D.pack_blocks), dim3(256), 0, stream, (const PackJob *)d, D.pack_jobs,
-                       (const PackRun *)(d + D.pack_o_runs), (const PackTile *)(d + D.pack_o_tiles));
-    DMM_HIP(hipGetLastError());
-  }
-  if (timed) DMM_HIP(hipEventRecord(D.t_pack[1], stream));
-  rc = launch_exec(D.dense, product, x.es, stream, timed);
-  const int rc2 = P->dev->uses.mark(stream);      // (also behind a copy whose product failed)
-  if (rc || rc2) return rc ? rc : rc2;
   dmm_execute_report r;
   if ((rc = dmm_plan_last_execute(D.dense, &r))) return rc;
   D.ran_merged = r.ran_merged != 0;
@@ -1459,7 +1472,7 @@ int stage(dmm_plan_t *P, ExecArgs &x, hipStream_t stream, ExecLayout *L) {
   int rc;
   DeviceState &D = *P->dev;
   D.gemm_timed = D.red_timed = D.mid_timed = false;
-  D.ran_dense = false;
+  D.ran_dense = D.pack_launched = false;
   D.ran_small = -1;
   // The call's inputs, side by side: when they are those of the plan's last dmm_execute, the
   // device table of that call is still in place and describes this one too (DMM_TIMING changes
@@ -1500,7 +1513,7 @@ int stage(dmm_plan_t *P, ExecArgs &x, hipStream_t stream, ExecLayout *L) {
     if (rc == DMM_ENOMEM) {
       // no room for copies (or for anything): the call's own work list, which may do with less
       (void)hipGetLastError();
-      if (sp.shape < 0 && (rc = drop_dense(P, stream))) return rc;
+      if (sp.shape < 0) drop_dense(P, stream);
       *L = ExecLayout();
     } else {
       built = true;

@@ -381,8 +381,8 @@ def copies_do_not_show_in_the_bits(rec):
 
 def a_failed_allocation_costs_no_call(rec):
     """One device allocation after another of a call that would run on copies fails, alone or with the one behind
-    it: the call then runs its own work list (whose tables there is room for), enqueues nothing of the
-    copies, and goes on like that."""
+    it: the call then runs its own work list (whose tables there is room for; a copy that was under way by
+    then is for nothing), and goes on like that."""
     block, cyclic, keep, s = workloads.block_desc, workloads.block_cyclic_desc, [], rec.stream()
     p = Product(tuple(cyclic(8192, 8192, 128, 128, 2, 4, 1) for _ in range(3)), 8)
     rec.so.rec_fail_allocations(0, 3)
@@ -407,8 +407,9 @@ def a_failed_allocation_costs_no_call(rec):
                 first = [o[1] for o in rec.launches(at)]
                 at = len(rec.ops())
                 p.run(args, 0, s)
-                assert [o[1] for o in rec.launches(at)] == first and p.plan.last_execute().table_reused
-                assert ("pack_kernel" in first) == p.plan.ran_dense() == (not failed), (n, first)
+                again = [o[1] for o in rec.launches(at)]
+                assert again == [o for o in first if o != "pack_kernel" or not failed] and p.plan.last_execute().table_reused
+                assert ("pack_kernel" in again) == p.plan.ran_dense() == (not failed), (n, again)
                 assert len([o for o in first if "gemm" in o]) == 1, first
                 rec.check_tables()
                 keep.append(p)
