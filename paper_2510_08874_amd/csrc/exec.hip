@@ -1453,11 +1453,7 @@ int launch_dense(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, bool time
   ExecLayout product;
   if (!D.pack_launched && (rc = launch_copy(P, x, stream))) return rc;
   // (the tables are in place: this orders the stream behind them)
-  if (!(rc = stage_dense(P, x, stream, &product))) rc = launch_exec(D.dense, product, x.es, stream, timed);
-  if (rc) {
-    const int rc2 = D.dense->dev->uses.mark(stream);      // (of a copy whose product failed)
-    return rc2 ? rc2 : rc;
-  }
+  if ((rc = stage_dense(P, x, stream, &product)) || (rc = launch_exec(D.dense, product, x.es, stream, timed))) return rc;
   dmm_execute_report r;
   if ((rc = dmm_plan_last_execute(D.dense, &r))) return rc;
   D.ran_merged = r.ran_merged != 0;
@@ -1569,6 +1565,7 @@ int dmm_execute(dmm_plan_t *P, int dtype, const void *const *a_tiles, const int6
       DeviceState &D;
       hipStream_t stream;
       ~HandBack() {
+        if (D.pack_launched && !D.ran_dense && D.dense) (void)D.dense->dev->uses.mark(stream);   // (a copy whose product failed)
         if (!D.pack_kept) pack_pool().give_back(&D.pack, stream);
       }
     } hand_back = {*P->dev, stream};

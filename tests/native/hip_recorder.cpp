@@ -39,7 +39,7 @@ std::map<const void *, std::string> kernels;
 std::map<const void *, void *> symbols;
 std::map<void *, size_t> memory;
 size_t live = 0, limit = ~(size_t)0;
-int fail_waits = 0;                                 // waits for an event that report an error and do not wait
+int wait_in = -1;                                   // waits for an event until one reports an error and does not wait
 int fail_in = -1, fail_n = 0;                       // allocations until some fail, and how many do
 hipError_t last_error = hipSuccess;
 dim3 cfg_grid, cfg_block;
@@ -125,7 +125,7 @@ void rec_fail_allocations(int in, int n) {
   fail_in = in;
   fail_n = n;
 }
-void rec_fail_waits(int n) { fail_waits = n; }
+void rec_fail_wait(int in) { wait_in = in; }
 int rec_failed() { return fail_in < 0; }
 
 // ---- the runtime ------------------------------------------------------------------------------------
@@ -242,10 +242,7 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
   return hipSuccess;
 }
 hipError_t hipEventSynchronize(hipEvent_t e) {
-  if (fail_waits > 0) {
-    --fail_waits;
-    return fail(hipErrorUnknown);
-  }
+  if (wait_in >= 0 && wait_in-- == 0) return fail(hipErrorUnknown);
   finish(events[e]);
   return hipSuccess;
 }

@@ -567,7 +567,7 @@ def an_error_on_one_stream_leaves_the_others_waited_for(rec):
     for s in streams:
         p.run(args, 0, s)
     readers = [o[0] for o in rec.launches()]
-    rec.so.rec_fail_waits(1)
+    rec.so.rec_fail_wait(0)
     p.plan.destroy()
     rec.so.hipGetLastError()
     q = Product(row_col(1024, 520, 1024), 8)
@@ -576,13 +576,36 @@ def an_error_on_one_stream_leaves_the_others_waited_for(rec):
     assert [rec.before(r, mark) for r in readers] == [False, True, True]
 
 
+def a_copy_whose_product_failed_is_waited_for(rec):
+    """The copy is launched before the product's tables are in place; if these fail, the next call's tables
+    wait for the copy all the same."""
+    cyclic = workloads.block_cyclic_desc
+    p = Product(tuple(cyclic(8192, 8192, 128, 128, 2, 4, 1) for _ in range(3)), 8)
+    s, other = rec.stream(), rec.stream()
+    for i in range(2):
+        p.run(p.args(False, i), 0, s)
+    at = len(rec.ops())
+    rec.so.rec_fail_wait(1)                      # (the third tables reuse the first staging slot: of the copy, of the product)
+    try:
+        p.run(p.args(False, 2), 0, s)
+        raise AssertionError("the wait did not fail")
+    except p.b.DmmError:
+        rec.so.hipGetLastError()
+    assert [o[1] for o in rec.launches(at)] == ["pack_kernel"]
+    p.run(p.args(False, 3), 0, other)
+    assert p.plan.ran_dense()
+    rec.check_tables()
+    p.plan.destroy()
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
              more_streams_than_the_plan_remembers, reports_say_what_ran,
              the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call,
              calls_can_be_captured, a_stream_for_every_thread,
              copies_share_their_memory, a_captured_call_keeps_its_copies,
              free_memory_does_not_show_in_the_cut,
-             an_error_on_one_stream_leaves_the_others_waited_for]
+             an_error_on_one_stream_leaves_the_others_waited_for,
+             a_copy_whose_product_failed_is_waited_for]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
