@@ -139,3 +139,37 @@ def test_dense_copies_of_infinities_and_nan():
     assert np.array_equal(got, own, equal_nan=True)
     assert 0 < np.count_nonzero(~np.isfinite(got)) <= 3 * 4102
     prob.close()
+
+
+def test_plans_share_the_copies_buffers():
+    """Kept plans of different sizes on copies, first on one stream, then each round on another of three: the
+    buffers of the copies are shared, no call may see another's."""
+    probs, wants = [], []
+    for cfg in (CASES[0], CASES[1], CASES[2]):
+        prob = _device_problem(cfg, *workloads.make_operands(cfg), c_fill=float("nan"))
+        prob.execute()
+        assert prob.plan.ran_dense()
+        torch.cuda.synchronize()
+        wants.append([None if t is None else t.clone() for t in prob.C.tensors])
+        for t in prob.C.tensors:
+            if t is not None:
+                t.fill_(float("nan"))
+        probs.append(prob)
+    main, streams = torch.cuda.current_stream(), [torch.cuda.Stream() for _ in probs]
+    for used in ([streams[0]] * 3, streams):
+        for s in streams:
+            s.wait_stream(main)
+        for turn in range(6):
+            for i, prob in enumerate(probs):
+                s = used[(i + turn) % 3]
+                s.wait_stream(used[(i + turn - 1) % 3])  # (of this problem's own last call: it wrote the same tiles of C)
+                prob.execute(stream=s.cuda_stream)
+                assert prob.plan.ran_dense()
+        for s in streams:
+            main.wait_stream(s)
+        torch.cuda.synchronize()
+        for prob, want in zip(probs, wants):
+            for t, w in zip(prob.C.tensors, want):
+                assert t is None or torch.equal(t, w)
+    for prob in probs:
+        prob.close()
