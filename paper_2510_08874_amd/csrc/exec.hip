@@ -841,7 +841,7 @@ int64_t count_steps(const std::vector<int64_t> &kc, int64_t bk) {
 // of 128 x 128) 45 -> 38, 3072^3 (144 macro-tiles) 69 against 105: stays; 32 x 12288 x 49152 280 -> 228
 // (5.3 TB/s), 128 x 12288 x 49152 300 against 299, 200 rows 331 against 456: stays; 1024 x 16384 x 1024
 // 67 -> 56; 64 x 5760 x 4960 61 -> 24; fp32 577 x 28352 x 512 216 -> 176; bf16 4838 x 2368 x 1437 in
-// uneven block-cyclic tiles 389 -> 184.  Over 70 drawn products none got more than 4 % slower.
+// uneven block-cyclic tiles 389 -> 184.
 void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
   const Grid &A = P->A, &B = P->B, &C = P->C;
   const int64_t M = C.rows, K = A.cols, N = C.cols, lim = (int64_t)1 << 30;
@@ -1091,10 +1091,11 @@ bool in_windows(const dmm_plan_t *P) {
 // its own list where it cannot have them), or it never runs on copies.
 // A K step takes 1.27 of the time where segments (a tenth of them and more) begin at odd places, 1.12 where
 // rows do (8102 x 4002 x 8102 in 2 x 2 tiles packed against padded rows: 544 and 486 us), a segment another step and a half, a
-// macro-tile that spans tiles 1.13; the copy runs at 4.5 TB/s and more (0.93 GB in 165 us).  Measured, us per call on the operands -> on
+// macro-tile that spans tiles 1.13; the copy runs at 4.5 TB/s and more (0.93 GB in 171 us).  Measured, us per call on the operands -> on
 // copies: 12289 x 9973 x 11003 in uneven packed tiles 3040 -> 2320, the same with rows padded to 16 bytes
 // 2750 -> 2330; 8192^3 in block-cyclic tiles of 128 1035 -> 980, of 256 960 -> 940; 6784 x 3003 x 7824 in
-// 100 x 100 ones, packed, 1890 -> 985; 12223 x 8751 x 2891 uneven (three rounds either way) stays.
+// 100 x 100 ones, packed, 1890 -> 985; 12223 x 8751 x 2891 uneven (three rounds either way) and 11441 x 9344 x 4245
+// in column blocks of 530 and 531 (four rounds and a cut one, 1173; five on copies, 1570) stay.
 bool choose_dense(const dmm_plan_t *P, const ExecArgs &x, bool given, int cus, bool *uncut) {
   const Grid &A = P->A, &B = P->B, &C = P->C;
   const int64_t M = C.rows, K = A.cols, N = C.cols, lim = (int64_t)1 << 30;
@@ -1117,8 +1118,10 @@ bool choose_dense(const dmm_plan_t *P, const ExecArgs &x, bool given, int cus, b
   for (int32_t i = 0; i < C.gr; ++i)
     for (int32_t j = 0; j < C.gc; ++j)
       dense_items += ((C.rc[i + 1] - C.rc[i] + kMacroTile - 1) / kMacroTile) * ((C.cc[j + 1] - C.cc[j] + kMacroTile - 1) / kMacroTile);
-  merged_items = ((M + kMacroTile - 1) / kMacroTile) * ((N + kMacroTile - 1) / kMacroTile);
-  const bool merge = merged_items * 10 <= dense_items * 9;            // (what dmm_plan will choose)
+  // (what dmm_plan will choose: merged macro-tiles end at column cuts that are not aligned)
+  merged_items = (int64_t)(tile_axis(merged_cuts({&C.rc}), kMaxPieces, 1, kMacroTile).size() *
+                           tile_axis(merged_cuts({&C.cc}), kMaxPieces, kPieceAlign, kMacroTile).size());
+  const bool merge = g_comp_ok[x.device] && merged_items * 10 <= dense_items * 9;
   const std::vector<int64_t> nc = merged_cuts({&B.cc, &C.cc});
   const int64_t steps = d.len / x.bk;                                 // (of the longest share)
   const double segs = (double)(d.kc.size() - 1) / C.c, us = 0.72;

@@ -598,6 +598,15 @@ def a_copy_whose_product_failed_is_waited_for(rec):
     p.plan.destroy()
 
 
+def what_was_slower_stays_as_it_is(rec):
+    """Products that were timed and found slower on copies run on their operands."""
+    block = workloads.block_desc
+    for descs, ranks, aligned in (((block(11441, 9344, 1, 1, replication=8), block(9344, 4245, 1, 8), block(11441, 4245, 1, 8)), 8, True),):
+        p = Product(descs, ranks)
+        p.run(p.args(aligned), 0, rec.stream())
+        assert not p.plan.ran_dense() and p.plan.small_tile() is None
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
              more_streams_than_the_plan_remembers, reports_say_what_ran,
              the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call,
@@ -605,7 +614,7 @@ SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stre
              copies_share_their_memory, a_captured_call_keeps_its_copies,
              free_memory_does_not_show_in_the_cut,
              an_error_on_one_stream_leaves_the_others_waited_for,
-             a_copy_whose_product_failed_is_waited_for]
+             a_copy_whose_product_failed_is_waited_for, what_was_slower_stays_as_it_is]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
