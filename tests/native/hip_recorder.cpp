@@ -41,6 +41,7 @@ std::map<void *, size_t> memory;
 size_t live = 0, limit = ~(size_t)0;
 int wait_in = -1;                                   // waits for an event until one reports an error and does not wait
 int fail_in = -1, fail_n = 0;                       // allocations until some fail, and how many do
+uint64_t next_at = 0;                               // where the next large allocation goes
 hipError_t last_error = hipSuccess;
 dim3 cfg_grid, cfg_block;
 size_t cfg_lds;
@@ -120,6 +121,7 @@ void rec_set_capturing(uint64_t s, int on) {
   streams[(void *)s].since = (int)ops.size();
 }
 void rec_set_limit(uint64_t bytes) { limit = bytes; }
+void rec_next_at(uint64_t p) { next_at = p; }
 uint64_t rec_live() { return live; }
 void rec_fail_allocations(int in, int n) {
   fail_in = in;
@@ -192,7 +194,9 @@ hipError_t hipMalloc(void **p, size_t n) {
   }
   if (fail_in > 0) --fail_in;
   if (live + n > limit) return fail(hipErrorOutOfMemory);
-  void *m = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+  void *at = n >= (size_t)32 << 20 ? (void *)next_at : nullptr;
+  if (at) next_at = 0;
+  void *m = mmap(at, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE | (at ? MAP_FIXED_NOREPLACE : 0), -1, 0);
   if (m == MAP_FAILED) return fail(hipErrorOutOfMemory);
   memory[*p = m] = n;
   live += n;

@@ -27,7 +27,7 @@ class Recorder:
         for f in ("rec_stream", "rec_arg", "rec_bytes", "rec_more", "rec_new_stream", "rec_live"):
             getattr(self.so, f).restype = ctypes.c_uint64
         self.so.rec_name.restype = ctypes.c_char_p
-        for f in ("rec_finish_stream", "rec_set_limit"):
+        for f in ("rec_finish_stream", "rec_set_limit", "rec_next_at"):
             getattr(self.so, f).argtypes = [ctypes.c_uint64]
         self.so.rec_set_capturing.argtypes = [ctypes.c_uint64, ctypes.c_int]
 
@@ -607,6 +607,21 @@ def what_was_slower_stays_as_it_is(rec):
         assert not p.plan.ran_dense() and p.plan.small_tile() is None
 
 
+def copies_do_not_lie_across_a_4gb_line(rec):
+    """The merged macro-tile kernel loads a K-segment step by step that a multiple of 2^32 runs through."""
+    cyclic = workloads.block_cyclic_desc
+    d = tuple(cyclic(8192, 8192, 128, 128, 2, 4, 1) for _ in range(3))
+    for limit in (None, 300 << 20):                              # with and without room for two buffers at a time
+        line = (0x7100 if limit else 0x7000) << 32
+        rec.so.rec_next_at(line - (48 << 20))
+        if limit:
+            rec.so.rec_set_limit(rec.so.rec_live() + limit)
+        p, copies = Product(d, 8), Copies(rec)
+        lo, hi = copies.run(p, p.args(False), rec.stream())
+        assert (lo >> 32 == (hi - 1) >> 32) == (limit is None)
+        rec.so.rec_set_limit(2 ** 63)
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
              more_streams_than_the_plan_remembers, reports_say_what_ran,
              the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call,
@@ -614,7 +629,8 @@ SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stre
              copies_share_their_memory, a_captured_call_keeps_its_copies,
              free_memory_does_not_show_in_the_cut,
              an_error_on_one_stream_leaves_the_others_waited_for,
-             a_copy_whose_product_failed_is_waited_for, what_was_slower_stays_as_it_is]
+             a_copy_whose_product_failed_is_waited_for, what_was_slower_stays_as_it_is,
+             copies_do_not_lie_across_a_4gb_line]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
