@@ -839,7 +839,7 @@ int64_t count_steps(const std::vector<int64_t> &kc, int64_t bk) {
 // how many segments it has, so it is drawn by an estimate and not by a size.  Measured, us per call
 // with macro-tiles -> with these kernels: fp32 256^3 54 -> 8.6; bf16 2048^3 (64 macro-tiles, 256 tiles
 // of 128 x 128) 45 -> 38, 3072^3 (144 macro-tiles) 69 against 105: stays; 32 x 12288 x 49152 280 -> 228
-// (5.3 TB/s), 128 x 12288 x 49152 300 against 299, 200 rows 331 against 456: stays; 1024 x 16384 x 1024
+// (5.3 TB/s), 200 rows 331 against 456: stays; 1024 x 16384 x 1024
 // 67 -> 56; 64 x 5760 x 4960 61 -> 24; fp32 577 x 28352 x 512 216 -> 176; bf16 4838 x 2368 x 1437 in
 // uneven block-cyclic tiles 389 -> 184.
 void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
@@ -870,7 +870,7 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
     const int64_t runs = tail <= cus / 2 ? std::max<int64_t>(1, std::min<int64_t>(cus / tail, big_steps / min_run_steps(x.es))) : 1;
     least += (double)((big_steps + runs - 1) / runs) * big_step + item + (runs > 1 ? 6 : 0);
   }
-  least *= 0.97;                                                               // (not for a tie)
+  least *= x.es == 2 ? 0.95 : 0.97;                                            // (not for a tie)
   // These kernels: rounds of `occ` workgroups per CU, operands at no more than 5.3 TB/s, and a second
   // launch that adds the partial tiles up.
   const double bytes = (double)x.es * ((double)M * K + (double)K * N) + (double)x.c_es * (double)M * N;
@@ -881,6 +881,12 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
     c.cols = tile_axis(c.nc, 1 << 30, kPieceAlign, s.tn);
     const int64_t tiles = (int64_t)(c.rows.size() * c.cols.size()), steps = count_steps(c.kc, s.bk);
     if (tiles > (1 << 20)) continue;
+    // B comes from memory again for every tile row that is not in flight together with the one before (an
+    // XCD holds so many workgroups at a time): 64 x 10392 x 38990 in 32 x 128 tiles 280 us, macro-tiles
+    // 228.  What the workgroups of the 32-row shape load in all, from whatever cache, comes at 7.4 TB/s.
+    const double in_flight = std::max(1.0, cus / 8.0 * s.occ / (double)c.cols.size());
+    const double mem = (bytes + std::max(0.0, (double)c.rows.size() / in_flight - 1.0) * (double)x.es * (double)K * N) / 5.3e6;
+    const double load = s.es == 2 && s.tm == 32 ? (double)(tiles * steps * s.bk) * (s.tm + s.tn) * s.es / 7.4e6 : 0.0;
     // a run has at least 256 (fp32: 128) elements of k, and the partial tiles fit 64 MB, which is
     // what the macro-tile kernels use at most
     const int64_t least_per = (s.es == 2 ? 256 : 128) / s.bk;
@@ -893,7 +899,7 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
       double t = (double)whole * ((double)per * std::max(s.step * s.occ, s.alone) + 2);
       if (rest > 0) t += (double)per * std::max(s.step * (double)rest, s.alone) + 2;
       t += segs / (double)runs;
-      t = 4 + std::max(t, bytes / 5.3e6);
+      t = 4 + std::max({t, mem, load});
       if (runs > 1) t += 4 + 2.0 * (double)part_bytes / 12e6;
       if (t < least) {
         least = t;
@@ -1089,7 +1095,7 @@ bool in_windows(const dmm_plan_t *P) {
 // never cut along K, so the bits are those of the product's own list uncut.  Where that list would be
 // cut, the shape alone decides: either such a product always runs uncut (*uncut: on the copies, or on
 // its own list where it cannot have them), or it never runs on copies.
-// A K step takes 1.27 of the time where segments (a tenth of them and more) begin at odd places, 1.12 where
+// A K step takes 1.27 of the time where segments (a tenth of them and more) begin at odd places, else 1.12 where
 // rows do (8102 x 4002 x 8102 in 2 x 2 tiles packed against padded rows: 544 and 486 us), a segment another step and a half, a
 // macro-tile that spans tiles 1.13; the copy runs at 4.5 TB/s and more (0.93 GB in 171 us).  Measured, us per call on the operands -> on
 // copies: 12289 x 9973 x 11003 in uneven packed tiles 3040 -> 2320, the same with rows padded to 16 bytes
@@ -1136,14 +1142,18 @@ bool choose_dense(const dmm_plan_t *P, const ExecArgs &x, bool given, int cus, b
   own *= ((double)steps + 1.5 * segs) * us * (P->merged.valid ? 1.13 : 1.0);
   const double then = rounds((merge ? merged_items : dense_items) * C.c) * ((double)steps + 1.5) * us * (merge ? 1.08 : 1.0) +
                       ((double)dense_bytes(P, d) + bytes) / 4.5e6 + 5;
-  if (std::max(cut_misaligned(A, d.kc), cut_misaligned(B, nc)) > 0.1) own *= 1.27;
-  const bool by_shape = then < 0.93 * own;
+  const bool odd = std::max(cut_misaligned(A, d.kc), cut_misaligned(B, nc)) > 0.1;
+  if (odd) own *= 1.27;
+  // (not for a tie: of per-group lists the estimate is good to a tenth; 8832 x 10112 x 2847 uneven, 0.93 by the
+  // estimate, took 655 us on copies and 567 on its operands)
+  const double much = P->merged.valid ? 0.93 : 0.88;
+  const bool by_shape = then < much * own;
   if (cut || in_windows(P)) {
     *uncut = by_shape;
     return by_shape && given;
   }
   if (!given) return false;
-  return by_shape || (then < 0.93 * 1.12 * own && (placed_misaligned(A, x.a_tiles, x.a_ld) || placed_misaligned(B, x.b_tiles, x.b_ld)));
+  return by_shape || (!odd && then < much * 1.12 * own && (placed_misaligned(A, x.a_tiles, x.a_ld) || placed_misaligned(B, x.b_tiles, x.b_ld)));
 }
 
 int stage(dmm_plan_t *P, ExecArgs &x, hipStream_t stream, ExecLayout *L);

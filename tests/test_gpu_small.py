@@ -60,11 +60,11 @@ S, H, B, T, F = (32, 128), (64, 128), (128, 128), (32, 32), (64, 64)      # the 
     ((300, 143, 384), "f32", "blocks", 1, T, False),
     ((555, 717, 359), "bf16", "uneven", 1, S, True),   # K tails in eleven segments, column cuts at odd places
     ((555, 717, 359), "bf16", "uneven", 8, S, True),
-    ((900, 333, 1100), "bf16", "blocks", 8, S, False),
-    ((1290, 260, 1030), "bf16", "blocks", 1, S, False),
+    ((900, 333, 1100), "bf16", "blocks", 8, H, False),
+    ((1290, 260, 1030), "bf16", "blocks", 1, B, False),
     ((128, 2285, 4192), "bf16", "column", 8, B, True),   # runs of K steps, added up by a second launch
     ((13, 3121, 4999), "bf16", "column", 1, S, True),
-    ((64, 5760, 1240), "bf16", "column", 8, S, True),
+    ((64, 5760, 1240), "bf16", "column", 8, H, True),
     ((577, 9001, 130), "bf16", "uneven", 1, B, True),    # runs that start inside segments
     ((640, 2048, 640), "f32", "blocks", 4, F, True),
     ((201, 3001, 203), "f32", "uneven", 1, F, True),
