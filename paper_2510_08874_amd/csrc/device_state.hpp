@@ -478,8 +478,8 @@ struct MergedLaunch {
 // their arguments.
 struct SmallLaunch {
   int shape = -1;               // SMALL_* (gemm_launch.hpp)
-  size_t o_rows = 0, o_cols = 0, o_mc = 0, o_nc = 0, o_before = 0, o_klen = 0, o_a = 0, o_b = 0, o_c = 0;
-  int32_t segs = 0, nr = 0, tiles_m = 0, tiles_n = 0, runs = 1, per = 0, c_es = 4;
+  size_t o_rows = 0, o_cols = 0, o_mc = 0, o_nc = 0, o_starts = 0, o_klen = 0, o_a = 0, o_b = 0, o_c = 0;
+  int32_t segs = 0, nr = 0, tiles_m = 0, tiles_n = 0, runs = 1, per = 0, steps = 0, c_es = 4;
   int32_t batch = 0;            // tiles per launch: all of them where there is room for their partial sums
 };
 

@@ -19,6 +19,7 @@
 #include "gemm_launch.hpp"
 #include "pack_kernel.hpp"
 #include "plan_internal.h"
+#include "ring_kernel.hpp"
 #include "small_kernel.hpp"
 
 namespace dmm {
@@ -822,8 +823,10 @@ struct SmallPlan {
   std::vector<Extent> rows, cols;
 };
 
+constexpr int64_t kSmallMost = 1 << 20;    // workgroups of a launch (small_div)
+
 constexpr SmallKind kSmall[SMALL_SHAPES] = {
-    small_kind<SmallBf16Skinny>(0.29, 0.52), small_kind<SmallBf16Half>(0.50, 0.72), small_kind<SmallBf16>(0.68, 0.88),
+    small_kind<RingSkinny>(0.25, 0.46), small_kind<RingHalf>(0.31, 0.46), small_kind<RingPair>(0.44, 0.62),
     small_kind<SmallF32Tiny>(0.39, 0.72), small_kind<SmallF32>(0.52, 0.78),
 };
 
@@ -833,15 +836,33 @@ int64_t count_steps(const std::vector<int64_t> &kc, int64_t bk) {
   return n;
 }
 
+// The share of an operand's columns in K-segments (column intervals) that begin inside their tile's rows
+// at positions that are not multiples of 16 bytes.
+double cut_misaligned(const Grid &G, const std::vector<int64_t> &cuts) {
+  int64_t odd = 0;
+  for (size_t i = 0; i + 1 < cuts.size(); ++i) {
+    const int64_t in = cuts[i] - *(std::upper_bound(G.cc.begin(), G.cc.end(), cuts[i]) - 1);
+    if (in & 7) odd += cuts[i + 1] - cuts[i];
+  }
+  return (double)odd / (double)std::max<int64_t>(1, cuts.back());
+}
+
+// segments whose last step is a K tail
+int64_t count_tails(const std::vector<int64_t> &kc, int64_t bk) {
+  int64_t n = 0;
+  for (size_t s = 0; s + 1 < kc.size(); ++s) n += (kc[s + 1] - kc[s]) % bk != 0;
+  return n;
+}
+
 // Whether (and how) the kernels for small products run this call: the estimated time of the best of
 // their shapes and numbers of runs against that of the macro-tile kernels.  The line between the two
 // depends on how many macro-tiles there are for the CUs, how much of them is product, how long K is and
 // how many segments it has, so it is drawn by an estimate and not by a size.  Measured, us per call
-// with macro-tiles -> with these kernels: fp32 256^3 54 -> 8.6; bf16 2048^3 (64 macro-tiles, 256 tiles
-// of 128 x 128) 45 -> 38, 3072^3 (144 macro-tiles) 69 against 105: stays; 32 x 12288 x 49152 280 -> 228
-// (5.3 TB/s), 200 rows 331 against 456: stays; 1024 x 16384 x 1024
-// 67 -> 56; 64 x 5760 x 4960 61 -> 24; fp32 577 x 28352 x 512 216 -> 176; bf16 4838 x 2368 x 1437 in
-// uneven block-cyclic tiles 389 -> 184.
+// with macro-tiles -> with these kernels: fp32 256^3 54 -> 8.6; bf16 3072^3 (144 macro-tiles) 69 against 80: stays;
+// 868 x 6784 x 8448 160 -> 117; 2700 x 1630 x 2180 uneven 101 -> 57; 425 x 2623 x 41280 137 against 152: stays;
+// 64 x 5760 x 4960 61 -> 19; fp32 577 x 28352 x 512 216 -> 176.  Between these shapes, us in tiles of 32, 64 and 128
+// rows: 128 x 8960 x 8576 60, 49, 40; 64 x 6615 x 45440 177, 146, 156; 640 x 247 x 384 11, 12, 16 (a 128-row tile's prologue
+// and epilogue take 5 us longer, which shows where they do not fill the CUs); 900 x 333 x 1100 14, 16, 19.
 void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
   const Grid &A = P->A, &B = P->B, &C = P->C;
   const int64_t M = C.rows, K = A.cols, N = C.cols, lim = (int64_t)1 << 30;
@@ -863,44 +884,53 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
   // prologue and an epilogue, every segment a switch.
   const double segs = (double)(c.kc.size() - 1);
   const int64_t big_steps = count_steps(c.kc, x.bk), tail = (int64_t)(items % (size_t)cus), full = (int64_t)items / cus;
-  const double fill = full > 0 ? 1.0 : (double)tail / cus;
-  const double big_step = (x.es == 2 ? 0.62 + 0.22 * fill : 3.9) * (P->merged.valid ? 1.13 : 1.0), item = 6 + 1.5 * segs;
+  const int64_t big_runs = tail > 0 && tail <= cus / 2 ? std::max<int64_t>(1, std::min<int64_t>(cus / tail, big_steps / min_run_steps(x.es))) : 1;
+  const double fill = full > 0 ? 1.0 : (double)(tail * big_runs) / cus;
+  const double big_step = (x.es == 2 ? 0.46 + 0.31 * fill : 3.9) * (P->merged.valid ? 1.06 : 1.0);
+  const double item = 6 + (x.es == 2 ? 1.5 * segs + 2.5 * (double)count_tails(c.kc, x.bk) : 1.5 * segs);
   double least = 4 + (double)full * ((double)big_steps * big_step + item);
   if (tail > 0) {
-    const int64_t runs = tail <= cus / 2 ? std::max<int64_t>(1, std::min<int64_t>(cus / tail, big_steps / min_run_steps(x.es))) : 1;
-    least += (double)((big_steps + runs - 1) / runs) * big_step + item + (runs > 1 ? 6 : 0);
+    least += (double)((big_steps + big_runs - 1) / big_runs) * big_step + item;
+    if (big_runs > 1) least += 4 + 2.0 * (double)(tail * big_runs) * sizeof(float) * BM * BN / 12e6;
   }
-  least *= x.es == 2 ? 0.95 : 0.97;                                            // (not for a tie)
-  // These kernels: rounds of `occ` workgroups per CU, operands at no more than 5.3 TB/s, and a second
+  least *= x.es == 2 ? 0.93 : 0.97;                                            // (not for a tie)
+  // These kernels: rounds of `occ` workgroups per CU, operands at no more than 5.6 TB/s, and a second
   // launch that adds the partial tiles up.
   const double bytes = (double)x.es * ((double)M * K + (double)K * N) + (double)x.c_es * (double)M * N;
+  const double odd = std::max(cut_misaligned(A, c.kc), cut_misaligned(B, c.nc)) > 0.1 ? 1.25 : 1.0;
   for (int k = 0; k < SMALL_SHAPES; ++k) {
     const SmallKind &s = kSmall[k];
     if (s.es != (int)x.es) continue;
     c.rows = tile_axis(c.mc, 1 << 30, 1, s.tm);
     c.cols = tile_axis(c.nc, 1 << 30, kPieceAlign, s.tn);
     const int64_t tiles = (int64_t)(c.rows.size() * c.cols.size()), steps = count_steps(c.kc, s.bk);
-    if (tiles > (1 << 20)) continue;
-    // B comes from memory again for every tile row that is not in flight together with the one before (an
-    // XCD holds so many workgroups at a time): 64 x 10392 x 38990 in 32 x 128 tiles 280 us, macro-tiles
-    // 228.  What the workgroups of the 32-row shape load in all, from whatever cache, comes at 7.4 TB/s.
-    const double in_flight = std::max(1.0, cus / 8.0 * s.occ / (double)c.cols.size());
-    const double mem = (bytes + std::max(0.0, (double)c.rows.size() / in_flight - 1.0) * (double)x.es * (double)K * N) / 5.3e6;
-    const double load = s.es == 2 && s.tm == 32 ? (double)(tiles * steps * s.bk) * (s.tm + s.tn) * s.es / 7.4e6 : 0.0;
+    const int64_t tails = count_tails(c.kc, s.bk);
+    if (tiles >= kSmallMost) continue;
+    // B comes again for every tile row but the first: from memory (64 x 6615 x 45440 in 32 x 128 tiles 187 us, in
+    // 64 x 128 tiles 161), or, where the last-level cache holds it, from there.
+    const double b_bytes = (double)x.es * (double)K * N;
+    const double mem = bytes / 5.6e6 + (double)(c.rows.size() - 1) * b_bytes / (b_bytes > 128e6 ? 6.5e6 : 14e6);
     // a run has at least 256 (fp32: 128) elements of k, and the partial tiles fit 64 MB, which is
     // what the macro-tile kernels use at most
     const int64_t least_per = (s.es == 2 ? 256 : 128) / s.bk;
     for (int64_t r = 1; r <= std::max<int64_t>(1, std::min<int64_t>(64, steps / least_per)); ++r) {
       const int64_t per = (steps + r - 1) / r, runs = (steps + per - 1) / per;
-      if (runs != r) continue;
+      if (runs != r || runs * tiles >= kSmallMost) continue;
       const int64_t part_bytes = runs * tiles * s.tm * s.tn * 4;
       if (runs > 1 && part_bytes > (int64_t)64 << 20) break;
       const int64_t per_cu = (tiles * runs + cus - 1) / cus, whole = per_cu / s.occ, rest = per_cu % s.occ;
       double t = (double)whole * ((double)per * std::max(s.step * s.occ, s.alone) + 2);
       if (rest > 0) t += (double)per * std::max(s.step * (double)rest, s.alone) + 2;
-      t += segs / (double)runs;
-      t = 4 + std::max({t, mem, load});
-      if (runs > 1) t += 4 + 2.0 * (double)part_bytes / 12e6;
+      if (s.es == 2) {
+        if (k == SMALL_BF16 && per_cu == 1) t = (double)per * (0.36 + 0.12 * (double)(tiles * runs) / cus) + 2;   // (the ring of four stages)
+        // K-segments that begin at odd places; a switch, and what a K tail costs
+        t = t * odd + (double)(whole + (rest > 0)) * (0.4 * segs + (s.tm == 32 ? 0.75 : 0.9) * (double)tails) / (double)runs;
+        t += k == SMALL_BF16 ? (tiles * runs < 140 ? 6 : 1.5) : 1;
+      } else {
+        t += segs / (double)runs;
+      }
+      t = 4 + std::max(t, s.es == 2 ? mem * std::max(1.0, 187.0 / (double)std::min<int64_t>(cus, tiles * runs)) : mem);
+      if (runs > 1) t += (x.es == 2 ? 3 : 4) + 2.0 * (double)part_bytes / 12e6;
       if (t < least) {
         least = t;
         best->shape = k;
@@ -917,7 +947,7 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
 }
 
 // Work tables of the kernels for small products:
-//   SmallTile rows[] | cols[] | PieceDev a[] | b[] | c[] | int32 mc[] | nc[] | before[] | klen[]
+//   SmallTile rows[] | cols[] | PieceDev a[] | b[] | c[] | SmallStart starts[] | int32 mc[] | nc[] | klen[]
 // DMM_EINVAL where a tile that the op list names has no pointer.
 int build_small_exec(dmm_plan_t *P, const ExecArgs &x, const SmallPlan &sp, hipStream_t stream, ExecLayout *L) {
   int rc = DMM_OK;
@@ -933,19 +963,19 @@ int build_small_exec(dmm_plan_t *P, const ExecArgs &x, const SmallPlan &sp, hipS
   l.o_a = l.o_cols + sp.cols.size() * sizeof(SmallTile);
   l.o_b = l.o_a + MR * S * sizeof(PieceDev);
   l.o_c = l.o_b + S * NR * sizeof(PieceDev);
-  l.o_mc = l.o_c + MR * NR * sizeof(PieceDev);
+  l.o_starts = l.o_c + MR * NR * sizeof(PieceDev);
+  l.o_mc = l.o_starts + (size_t)sp.runs * sizeof(SmallStart);
   l.o_nc = l.o_mc + (MR + 1) * 4;
-  l.o_before = l.o_nc + (NR + 1) * 4;
-  l.o_klen = l.o_before + (S + 1) * 4;
+  l.o_klen = l.o_nc + (NR + 1) * 4;
   const size_t total = l.o_klen + S * 4;
   std::vector<char> &h = P->dev->host;
   h.assign(total, 0);
-  auto tiles = [&](size_t at, const std::vector<Extent> &v) {
+  auto tiles = [&](size_t at, const std::vector<Extent> &v, const std::vector<int64_t> &cuts) {
     SmallTile *t = (SmallTile *)(h.data() + at);
-    for (size_t i = 0; i < v.size(); ++i) t[i] = {(int32_t)v[i].start, v[i].ext, v[i].first, v[i].pieces};
+    for (size_t i = 0; i < v.size(); ++i) t[i] = {(int32_t)v[i].start, v[i].ext, v[i].first, v[i].pieces, (int32_t)cuts[(size_t)v[i].first], 0};
   };
-  tiles(l.o_rows, sp.rows);
-  tiles(l.o_cols, sp.cols);
+  tiles(l.o_rows, sp.rows, sp.mc);
+  tiles(l.o_cols, sp.cols, sp.nc);
   auto piece = [](const void *base, int64_t ld, int64_t r, int64_t c, int64_t hh, int64_t w, int64_t esz) {
     PieceDev d;
     const int64_t off = r * ld + c;
@@ -981,15 +1011,18 @@ int build_small_exec(dmm_plan_t *P, const ExecArgs &x, const SmallPlan &sp, hipS
       pc[i * NR + j] = piece(x.c_tiles[idx], x.c_ld[idx], sp.mc[i] - C.rc[c_ti[i]], sp.nc[j] - C.cc[c_tj[j]],
                              C.rc[c_ti[i] + 1] - C.rc[c_ti[i]], C.cc[c_tj[j] + 1] - C.cc[c_tj[j]], x.c_es);
     }
-  int32_t *mc = (int32_t *)(h.data() + l.o_mc), *nc = (int32_t *)(h.data() + l.o_nc), *before = (int32_t *)(h.data() + l.o_before),
-          *klen = (int32_t *)(h.data() + l.o_klen);
+  int32_t *mc = (int32_t *)(h.data() + l.o_mc), *nc = (int32_t *)(h.data() + l.o_nc), *klen = (int32_t *)(h.data() + l.o_klen);
   for (size_t i = 0; i <= MR; ++i) mc[i] = (int32_t)sp.mc[i];
   for (size_t j = 0; j <= NR; ++j) nc[j] = (int32_t)sp.nc[j];
-  before[0] = 0;
+  SmallStart *starts = (SmallStart *)(h.data() + l.o_starts);
+  int32_t before = 0, run = 0;                            // K steps in front of the segment
   for (size_t s = 0; s < S; ++s) {
     klen[s] = (int32_t)(sp.kc[s + 1] - sp.kc[s]);
-    before[s + 1] = before[s] + (klen[s] + kind.bk - 1) / kind.bk;
+    const int32_t steps = (klen[s] + kind.bk - 1) / kind.bk;
+    for (; run < sp.runs && run * sp.per < before + steps; ++run) starts[run] = {(int32_t)s, (run * sp.per - before) * kind.bk};
+    before += steps;
   }
+  l.steps = before;
   l.shape = sp.shape;
   l.segs = (int32_t)S;
   l.nr = (int32_t)NR;
@@ -1016,18 +1049,7 @@ int build_small_exec(dmm_plan_t *P, const ExecArgs &x, const SmallPlan &sp, hipS
 
 // ---- products on dense copies of their operands (pack_kernel.hpp) -----------------------------------
 
-// The share of an operand's columns in K-segments (column intervals) that begin inside their tile's rows
-// at positions that are not multiples of 16 bytes,
-double cut_misaligned(const Grid &G, const std::vector<int64_t> &cuts) {
-  int64_t odd = 0;
-  for (size_t i = 0; i + 1 < cuts.size(); ++i) {
-    const int64_t in = cuts[i] - *(std::upper_bound(G.cc.begin(), G.cc.end(), cuts[i]) - 1);
-    if (in & 7) odd += cuts[i + 1] - cuts[i];
-  }
-  return (double)odd / (double)std::max<int64_t>(1, cuts.back());
-}
-
-// and whether rows of its tiles do.
+// Whether rows of its tiles begin at positions that are not multiples of 16 bytes.
 bool placed_misaligned(const Grid &G, const void *const *tiles, const int64_t *ld) {
   for (int32_t i = 0; i < G.gr; ++i)
     for (int32_t j = 0; j < G.gc; ++j)
@@ -1351,7 +1373,7 @@ int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stre
     g.cols = (const SmallTile *)(d + l.o_cols);
     g.mc = (const int32_t *)(d + l.o_mc);
     g.nc = (const int32_t *)(d + l.o_nc);
-    g.before = (const int32_t *)(d + l.o_before);
+    g.starts = (const SmallStart *)(d + l.o_starts);
     g.klen = (const int32_t *)(d + l.o_klen);
     g.pa = (const PieceDev *)(d + l.o_a);
     g.pb = (const PieceDev *)(d + l.o_b);
@@ -1364,7 +1386,11 @@ int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stre
     g.runs = l.runs;
     g.per = l.per;
     g.c_es = l.c_es;
+    g.band = es == 2 ? SMALL_BAND : 1;
+    g.steps = l.steps;
     g.pad = 0;
+    int cus = 0;
+    if ((rc = device_cus(&cus))) return rc;
     TraceRange gemm("gemm");
     if (timed) {
       if ((rc = timing_events(P->dev->t_gemm))) return rc;
@@ -1372,7 +1398,7 @@ int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stre
     }
     for (g.first = 0; g.first < l.tiles_m * l.tiles_n; g.first += l.batch) {
       g.tiles = std::min(l.batch, l.tiles_m * l.tiles_n - g.first);
-      small_launch(l.shape, g, stream);
+      small_launch(l.shape, g, cus, stream);
       DMM_HIP(hipGetLastError());
     }
     if (timed) {

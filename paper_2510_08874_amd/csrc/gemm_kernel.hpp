@@ -321,6 +321,21 @@ __device__ __forceinline__ u32x4 keep_first(u32x4 v, int n) {
   return v;
 }
 
+// the upper 8 - n of eight bf16 elements moved down to the front, zeros behind them (0 <= n < 8)
+__device__ __forceinline__ u32x4 drop_first(u32x4 v, int n) {
+  union { u32x4 v; uint64_t q[2]; } u;
+  u.v = v;
+  const int s = n * 16;
+  if (s >= 64) {
+    u.q[0] = u.q[1] >> (s - 64);
+    u.q[1] = 0;
+  } else if (s > 0) {
+    u.q[0] = u.q[0] >> s | u.q[1] << (64 - s);
+    u.q[1] >>= s;
+  }
+  return u.v;
+}
+
 // ---- the accumulators ----------------------------------------------------------------------
 // The 256 partial sums of a lane live in the accumulator registers a0 .. a255 by name: tile (i, j)
 // of the wave's 4 x 4 tiles of 32 x 32 owns a[16 t .. 16 t + 15], t = 4 i + j.  Every instruction

@@ -48,6 +48,6 @@ inline void launch_grouped_gemm_comp(int es, unsigned grid, hipStream_t stream, 
 struct SmallArgs;
 enum { SMALL_BF16_SKINNY, SMALL_BF16_HALF, SMALL_BF16, SMALL_F32_TINY, SMALL_F32, SMALL_SHAPES };
 hipError_t small_allow_lds();
-void small_launch(int shape, const SmallArgs &g, hipStream_t stream);   // the product, and the sum of its partial tiles
+void small_launch(int shape, const SmallArgs &g, int cus, hipStream_t stream);   // the product, and the sum of its partial tiles
 
 }  // namespace dmm

@@ -46,21 +46,6 @@ struct PackJob {           // rows of one tile row of an operand -> dense rows a
 constexpr int PACK_ROWS = 8;
 constexpr int PACK_COLS = 256 * 8;
 
-// the upper 8 - n of eight bf16 elements moved down to the front, zeros behind them (0 <= n < 8)
-__device__ __forceinline__ u32x4 drop_first(u32x4 v, int n) {
-  union { u32x4 v; uint64_t q[2]; } u;
-  u.v = v;
-  const int s = n * 16;
-  if (s >= 64) {
-    u.q[0] = u.q[1] >> (s - 64);
-    u.q[1] = 0;
-  } else if (s > 0) {
-    u.q[0] = u.q[0] >> s | u.q[1] << (64 - s);
-    u.q[1] >>= s;
-  }
-  return u.v;
-}
-
 __global__ __launch_bounds__(256) void pack_kernel(const PackJob *__restrict__ jobs, int n_jobs, const PackRun *__restrict__ all_runs,
                                                    const PackTile *__restrict__ tiles) {
   // the last of `n` that does not lie behind `at`

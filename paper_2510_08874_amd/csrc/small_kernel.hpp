@@ -1,11 +1,10 @@
-// GEMM kernel for products that 256 x 256 macro-tiles do not fill the device with (gfx950, device
+// GEMM kernels for products that 256 x 256 macro-tiles do not fill the device with (gfx950, device
 // code only): small and skinny results, few macro-tiles, fp32 products cut into ragged pieces.
 //
 // What bounds such a product under the macro-tile kernels: CUs without a macro-tile, rows and
 // columns of macro-tiles that hold nothing, and one workgroup per CU, whose waits nothing hides.
-// Here a tile is 32 to 128 rows and columns, two to four workgroups share a CU (they hide each
-// other's waits, so the loop needs no hand-made schedule), and a tile's K steps are dealt to as
-// many workgroups as the device has room for.
+// Here a tile is 32 to 128 rows and columns, up to four workgroups share a CU, and a tile's K steps
+// are dealt to as many workgroups as the device has room for.
 //
 // Tiles are cut from C as a whole, across the cuts of A, B and C: the slicing is kept in factored
 // form (one A slice per row interval and K-segment, one B slice per K-segment and column
@@ -13,19 +12,16 @@
 // holds its own rows and its own chunk of columns.  A tile ends early at a column cut that is not
 // a multiple of eight columns away from its start, so that a 16-byte chunk has one source.
 //
-// Operands go global -> registers -> LDS (two stages, one barrier per step): the register stage
-// takes any alignment and lets K tails and column tails be zeroed on the way, so nothing is ever
-// read past a slice.  Sums run over the same K-segments in the same order and through the same
-// matrix instructions as in the macro-tile kernels, hence bitwise the same results, unless a
+// Here are the tables, the epilogue, the sum of partial tiles and the loop for fp32; the loop for bf16 is in
+// ring_kernel.hpp.  The fp32 loop takes operands global -> registers -> LDS (two stages, one barrier per
+// step): the register stage takes any alignment and lets K tails and column tails be zeroed on the way, so
+// nothing is ever read past a slice.  Sums run over the same K-segments in the same order and through the
+// same matrix instructions as in the macro-tile kernels, hence bitwise the same results, unless a
 // tile's K steps are dealt to several workgroups or waves (their partial sums are then added in
 // ascending k).
 //
-// Measured (kernel alone, us; macro-tile kernels -> these): fp32 256^3 50 -> 5; bf16 2048^3 41 -> 36,
-// where a step of 64 k takes 0.9 us, of which 0.25 are matrix instructions (one workgroup per CU:
-// LDS writes, barrier, LDS reads and multiplication follow each other); 32 x 12288 x 49152 275 -> 221
-// (5.5 TB/s).  Operands of one, two or three steps in flight made no difference.  Reading all
-// fragments of a step ahead of its first matrix instruction gained 5 to 11 % with two workgroups on
-// every CU, lost 5 % with one and 10 to 18 % for fp32 (registers).
+// Measured (kernel alone, us; macro-tile kernels -> these): fp32 256^3 50 -> 5.  Operands of one, two or three
+// steps in flight made no difference.
 #pragma once
 
 #include "gemm_kernel.hpp"
@@ -35,12 +31,18 @@ namespace dmm {
 struct SmallTile {         // one tile row (column) of C
   int32_t start, ext;      // first row (column), number of them
   int32_t first, pieces;   // first interval met, number of intervals met
+  int32_t base;            // where that interval begins
+  int32_t pad;
+};
+
+struct SmallStart {        // where a run of K steps begins
+  int32_t seg, kpos;
 };
 
 struct SmallArgs {
   const SmallTile *rows, *cols;
   const int32_t *mc, *nc;              // boundaries of the row (column) intervals
-  const int32_t *before;               // [S + 1] K steps in front of every segment
+  const SmallStart *starts;            // [runs]
   const int32_t *klen;                 // [S]
   const PieceDev *pa, *pb, *pc;        // A slice (i, s) at pa[i S + s], B slice (s, j) at pb[s NR + j], C slice (i, j) at pc[i NR + j]
   float *scratch;                      // runs > 1: partial tiles of the launch, number run * tiles + tile
@@ -49,6 +51,8 @@ struct SmallArgs {
   int32_t runs, per;                   // a tile's K steps in `runs` ranges of `per` steps (the last may be shorter)
   int32_t first, tiles;                // tiles [first, first + tiles) are this launch's
   int32_t c_es;                        // bytes per element of C
+  int32_t band;                        // tile rows of a band of the launch order (see small_tile_of)
+  int32_t steps;                       // K steps of a tile
   int32_t pad;
 };
 
@@ -59,6 +63,7 @@ typedef __attribute__((address_space(3))) char *lds_ptr;
 // tile, times WK waves over the matrix instructions of a step
 template <int ES_, int TM_, int TN_, int BK_, int WM_, int WN_, int WK_, int DEPTH_, int OCC_>
 struct SmallShape {
+  static constexpr bool RING = false;
   static constexpr int ES = ES_, TM = TM_, TN = TN_, BK = BK_, WM = WM_, WN = WN_, WK = WK_;
   static constexpr int DEPTH = DEPTH_;                          // K steps whose operands are in flight
   static constexpr int OCC = OCC_;                              // workgroups per CU the LDS and registers leave room for
@@ -78,14 +83,48 @@ struct SmallShape {
   static_assert(WM * WN * WK == NW && CA >= 1 && CB >= 1 && NT % A_CHUNKS == 0 && NT % B_CHUNKS == 0, "chunks are dealt evenly");
 };
 
-// four columns of row r, from column c on, of the tile whose tile row and column are tr and tc
-__device__ __forceinline__ void small_store4(const SmallArgs &g, const SmallTile &tr, const SmallTile &tc, int r, int c, f32x4 v) {
-  int i = tr.first, j = tc.first;
-  const int m = tr.start + r, n = tc.start + c;
-  for (int x = 1; x < tr.pieces; ++x) i += g.mc[tr.first + x] <= m;
-  for (int x = 1; x < tc.pieces; ++x) j += g.nc[tc.first + x] <= n;
-  const PieceDev d = g.pc[(int64_t)i * g.NR + j];
-  const uint64_t at = (uint64_t)(uintptr_t)d.ptr + (uint64_t)(m - g.mc[i]) * d.pitch + (uint64_t)(n - g.nc[j]) * (unsigned)g.c_es;
+// the interval of a tile row (column) that holds `pos`, and where it begins
+__device__ __forceinline__ int small_piece(const int32_t *bounds, const SmallTile &t, int pos, int *begin) {
+  int i = t.first;
+  *begin = t.base;
+  for (int y = 1; y < t.pieces; ++y) {
+    const int b = bounds[t.first + y];
+    if (b <= pos) {
+      i = t.first + y;
+      *begin = b;
+    }
+  }
+  return i;
+}
+
+// Where four columns of the tile, from column c on, go: the C slice that holds row r.  Looked up ahead of the
+// K loop where registers allow: looked up row by row the stores of a 128 x 128 tile took 4 us instead of 1.8.
+struct SmallOut {
+  uint64_t at;             // address of the columns in the slice's first row
+  unsigned pitch;
+  int begin, end;          // the slice's rows
+};
+struct SmallOutLoad {      // the look-up under way: small_out_of is not called before the data are wanted
+  PieceDev slice;
+  int begin, end, n;       // the slice's rows; the column inside it
+};
+__device__ __forceinline__ SmallOutLoad small_out_load(const SmallArgs &g, const SmallTile &tr, const SmallTile &tc, int r, int c) {
+  SmallOutLoad o;
+  int n0;
+  const int n = tc.start + c, i = small_piece(g.mc, tr, tr.start + r, &o.begin), j = small_piece(g.nc, tc, n, &n0);
+  o.slice = g.pc[(int64_t)i * g.NR + j];
+  o.end = i + 1 < tr.first + tr.pieces ? g.mc[i + 1] : tr.start + tr.ext;
+  o.n = n - n0;
+  return o;
+}
+__device__ __forceinline__ SmallOut small_out_of(const SmallArgs &g, const SmallOutLoad &o) {
+  return SmallOut{(uint64_t)(uintptr_t)o.slice.ptr + (uint64_t)o.n * (unsigned)g.c_es, o.slice.pitch, o.begin, o.end};
+}
+
+// four columns of row r, from column c on
+__device__ __forceinline__ void small_store4(const SmallArgs &g, const SmallTile &tr, const SmallTile &tc, SmallOut &o, int r, int c, f32x4 v) {
+  if (tr.start + r >= o.end) o = small_out_of(g, small_out_load(g, tr, tc, r, c));
+  const uint64_t at = o.at + (uint64_t)(tr.start + r - o.begin) * o.pitch;
   const int left = tc.ext - c;
   // (column pieces begin at multiples of eight columns of the tile: the four columns lie in one slice)
   if (g.c_es == 4) {
@@ -113,25 +152,105 @@ __device__ __forceinline__ void small_store4(const SmallArgs &g, const SmallTile
   }
 }
 
+constexpr int SMALL_BAND = 4;            // so that B columns that a few tile rows share are read by workgroups close to each other
+
+// a / d for 0 <= a < 2^20, 0 < d (the compiler's division takes ten times as long, and a small product waits for it)
+__device__ __forceinline__ int small_div(int a, int d) {
+  return __builtin_amdgcn_readfirstlane((int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)d)));
+}
+
+// The tile row and tile column of a tile: bands of `band` tile rows, column by column inside a band.
+__device__ __forceinline__ void small_tile_of(const SmallArgs &g, int tile, int *row, int *col) {
+  const int whole = g.band * g.tiles_n, b = small_div(tile, whole), in = tile - b * whole, r0 = b * g.band;
+  const int h = g.tiles_m - r0 < g.band ? g.tiles_m - r0 : g.band;
+  *col = small_div(in, h);
+  *row = r0 + (in - *col * h);
+}
+
+// The run and the tile of a workgroup.  Workgroup id mod 8 is the XCD: each XCD takes a contiguous eighth of
+// the (run, tile) sequence, so that the workgroups that share an L2 share A rows, B columns and k ranges.
+struct SmallPlace {
+  int run, local, row, col;
+};
+__device__ __forceinline__ SmallPlace small_place(const SmallArgs &g) {
+  const int total = (int)gridDim.x, q8 = total >> 3, r8 = total & 7;
+  const int xcd = blockIdx.x & 7, pos = blockIdx.x >> 3;
+  const int id = xcd * q8 + (xcd < r8 ? xcd : r8) + pos;
+  SmallPlace p;
+  p.run = small_div(id, g.tiles);
+  p.local = id - p.run * g.tiles;
+  small_tile_of(g, g.first + p.local, &p.row, &p.col);
+  return p;
+}
+
+// The finished tile through LDS, four consecutive columns per thread.  value(i, j, e): element e of the lane's
+// part of 32 x 32 tile (i, j), as the matrix instructions leave it.  Waves wk > 0 hold partial sums of the same elements.
+template <class SH, class F>
+__device__ __forceinline__ void small_epilogue(const SmallArgs &g, const SmallPlace &at, const SmallTile &tr, const SmallTile &tc, SmallOut &to,
+                                               lds_ptr lds3, F &&value, int wm, int wn, int wk) {
+  constexpr int MI = SH::MI, NI = SH::NI;
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+  __syncthreads();
+  typedef __attribute__((address_space(3))) float *lds_float;
+  const lds_float out = (lds_float)lds3 + wk * (SH::TM * SH::T_PITCH);
+  static_for<MI>([&](auto ic) {
+    static_for<NI>([&](auto jc) {
+      static_for<16>([&](auto ec) {
+        constexpr int i = decltype(ic)::value, j = decltype(jc)::value, e = decltype(ec)::value;
+        out[(wm * (MI * 32) + i * 32 + 8 * (e >> 2) + 4 * half + (e & 3)) * SH::T_PITCH + wn * (NI * 32) + j * 32 + (lane & 31)] = value(ic, jc, ec);
+      });
+    });
+  });
+  __syncthreads();
+  float *part = g.scratch + (int64_t)(at.run * g.tiles + at.local) * (SH::TM * SH::TN);
+  const int c = tid % (SH::TN / 4) * 4, r0 = tid / (SH::TN / 4);
+  constexpr int STEP = NT / (SH::TN / 4);                 // rows from one of a thread's to the next
+  if (c >= tc.ext || r0 >= tr.ext) return;
+  auto value4 = [&](int r) __attribute__((always_inline)) {
+    f32x4 v = *(const __attribute__((address_space(3))) f32x4 *)((lds_float)lds3 + r * SH::T_PITCH + c);
+#pragma unroll
+    for (int w = 1; w < SH::WK; ++w)
+      v = v + *(const __attribute__((address_space(3))) f32x4 *)((lds_float)lds3 + (w * SH::TM + r) * SH::T_PITCH + c);
+    return v;
+  };
+  // All of a thread's columns in one slice, at multiples of 16 bytes: an address and an increment.
+  uint64_t p = to.at + (uint64_t)(tr.start + r0 - to.begin) * to.pitch, inc = (uint64_t)to.pitch * STEP;
+  bool plain = g.c_es == 4 && tr.start + tr.ext <= to.end && tc.ext - c >= 4 && ((p | inc) & 15) == 0;
+  if (g.runs > 1) {
+    p = (uint64_t)(uintptr_t)(part + r0 * SH::TN + c);
+    inc = (uint64_t)STEP * SH::TN * 4;
+    plain = true;
+  }
+  if (plain) {
+#pragma unroll
+    for (int x = 0; x < SH::TM / STEP; ++x) {
+      if (r0 + x * STEP < tr.ext) *(__attribute__((address_space(1))) f32x4 *)p = value4(r0 + x * STEP);
+      p += inc;
+    }
+    return;
+  }
+  for (int r = r0; r < tr.ext; r += STEP) small_store4(g, tr, tc, to, r, c, value4(r));
+}
+
+// what a thread stores first, looked up ahead (nothing where partial tiles are stored)
 template <class SH>
-__global__ __launch_bounds__(NT, SH::OCC) void small_gemm_kernel(const SmallArgs g) {
-  extern __shared__ __attribute__((aligned(1024))) char lds[];
+__device__ __forceinline__ SmallOutLoad small_first_out(const SmallArgs &g, const SmallTile &tr, const SmallTile &tc) {
+  const int r = threadIdx.x / (SH::TN / 4), c = threadIdx.x % (SH::TN / 4) * 4;
+  if (g.runs == 1 && r < tr.ext && c < tc.ext) return small_out_load(g, tr, tc, r, c);
+  return SmallOutLoad{{nullptr, 0, 0u, 0u}, 0, 0, 0};
+}
+
+template <class SH>
+__device__ __forceinline__ void staged_gemm(const SmallArgs &g, char *lds) {
   constexpr int ES = SH::ES, BK = SH::BK, PER = SH::PER, CA = SH::CA, CB = SH::CB, DEPTH = SH::DEPTH, MI = SH::MI, NI = SH::NI;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wk = wave % SH::WK, wn = wave / SH::WK % SH::WN, wm = wave / SH::WK / SH::WN;
-  // Workgroup id mod 8 is the XCD: each XCD takes a contiguous eighth of the (run, tile row, tile
-  // column) sequence, so that the workgroups that share an L2 share A rows, B columns and k ranges.
-  const int total = (int)gridDim.x, q8 = total >> 3, r8 = total & 7;
-  const int xcd = blockIdx.x & 7, pos = blockIdx.x >> 3;
-  const int id = xcd * q8 + (xcd < r8 ? xcd : r8) + pos;
-  const int tiles = g.tiles;
-  const int run = id / tiles, local = id - run * tiles, tile = g.first + local;
-  const SmallTile tr = g.rows[tile / g.tiles_n], tc = g.cols[tile % g.tiles_n];
+  const SmallPlace at = small_place(g);
+  const SmallTile tr = g.rows[at.row], tc = g.cols[at.col];
   const int S = g.S, NR = g.NR;
-  const int t0 = run * g.per, t_end = g.before[S];
-  const int t1 = t0 + g.per < t_end ? t0 + g.per : t_end;
-  const int n = t1 - t0;                                  // at least 1: the host sees to it
+  const SmallStart start = g.starts[at.run];
+  const int t0 = at.run * g.per, n = g.steps - t0 < g.per ? g.steps - t0 : g.per;   // at least 1: the host sees to it
 
   // ---- this thread's chunks ------------------------------------------------------------
   const int ak = tid % SH::A_CHUNKS * PER;                // first k of its A chunks inside a step
@@ -144,10 +263,9 @@ __global__ __launch_bounds__(NT, SH::OCC) void small_gemm_kernel(const SmallArgs
   for (int x = 0; x < CA; ++x) {
     int row = tid / SH::A_CHUNKS + x * A_ROWS;
     row = tr.start + (row < tr.ext ? row : tr.ext - 1);   // (rows past the tile's end read its last row; never stored)
-    int i = tr.first;
-    for (int y = 1; y < tr.pieces; ++y) i += g.mc[tr.first + y] <= row;
-    ap[x] = g.pa + (int64_t)i * S;
-    arow[x] = row - g.mc[i];
+    int m0;
+    ap[x] = g.pa + (int64_t)small_piece(g.mc, tr, row, &m0) * S;
+    arow[x] = row - m0;
   }
   int bvalid = tc.ext - bn;                               // columns of its chunk that exist
   bvalid = bvalid < 0 ? 0 : bvalid < PER ? bvalid : PER;
@@ -156,10 +274,9 @@ __global__ __launch_bounds__(NT, SH::OCC) void small_gemm_kernel(const SmallArgs
   int64_t bcol;                                           // byte column inside the slice
   {
     const int col = tc.start + (bvalid > 0 ? bn : 0);
-    int j = tc.first;
-    for (int y = 1; y < tc.pieces; ++y) j += g.nc[tc.first + y] <= col;
-    bp = g.pb + j;
-    bcol = (int64_t)(col - g.nc[j]) * ES;
+    int n0;
+    bp = g.pb + small_piece(g.nc, tc, col, &n0);
+    bcol = (int64_t)(col - n0) * ES;
   }
 
   // ---- cursor over the K steps whose loads are issued ------------------------------------
@@ -197,17 +314,9 @@ __global__ __launch_bounds__(NT, SH::OCC) void small_gemm_kernel(const SmallArgs
     quick = !edge || __builtin_amdgcn_ballot_w64(bpitch < 16) == 0;
     if (seg + 1 < S) fetch(seg + 1);
   };
-  {
-    int lo = 0, hi = S - 1;                               // the last segment that starts at or before step t0
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (g.before[mid] <= t0) lo = mid;
-      else hi = mid - 1;
-    }
-    seg = lo;
-    fetch(lo);
-    open((t0 - g.before[lo]) * BK);
-  }
+  seg = start.seg;
+  fetch(seg);
+  open(start.kpos);
   u32x4 ra[DEPTH][CA], rb[DEPTH][CB];                     // operands of DEPTH steps in flight
   int rk[DEPTH];                                          // elements of the segment left at those steps
   auto load16 = [](gptr p) -> u32x4 { return *(const __attribute__((address_space(1))) u32x4_any *)p; };
@@ -342,42 +451,26 @@ __global__ __launch_bounds__(NT, SH::OCC) void small_gemm_kernel(const SmallArgs
     });
   }
 
-  // ---- epilogue: through LDS, four consecutive columns per thread ----------------------------
-  __syncthreads();
-  typedef __attribute__((address_space(3))) float *lds_float;
-  const lds_float out = (lds_float)lds3 + wk * (SH::TM * SH::T_PITCH);
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e)
-        out[(wm * (MI * 32) + i * 32 + 8 * (e >> 2) + 4 * half + (e & 3)) * SH::T_PITCH + wn * (NI * 32) + j * 32 + (lane & 31)] = acc[i][j][e];
-  __syncthreads();
-  float *part = g.scratch + (int64_t)(run * tiles + local) * (SH::TM * SH::TN);
-#pragma unroll 2
-  for (int x = tid; x < SH::TM * SH::TN / 4; x += NT) {
-    const int r = x / (SH::TN / 4), c = x % (SH::TN / 4) * 4;
-    if (r >= tr.ext || c >= tc.ext) continue;
-    f32x4 v = *(const __attribute__((address_space(3))) f32x4 *)((lds_float)lds3 + r * SH::T_PITCH + c);
-#pragma unroll
-    for (int w = 1; w < SH::WK; ++w)
-      v = v + *(const __attribute__((address_space(3))) f32x4 *)((lds_float)lds3 + (w * SH::TM + r) * SH::T_PITCH + c);
-    if (g.runs > 1) *(__attribute__((address_space(1))) f32x4 *)(part + r * SH::TN + c) = v;
-    else small_store4(g, tr, tc, r, c, v);
-  }
+  // (not ahead of the loop here: its registers would be in the loop's way)
+  const SmallOutLoad to_load = small_first_out<SH>(g, tr, tc);
+  SmallOut to = small_out_of(g, to_load);
+  small_epilogue<SH>(g, at, tr, tc, to, lds3, [&](auto ic, auto jc, auto ec) { return acc[decltype(ic)::value][decltype(jc)::value][decltype(ec)::value]; },
+                     wm, wn, wk);
 }
 
 // The partial tiles of every tile, added up in ascending k.  A workgroup takes 1024 elements.
 template <class SH>
 __global__ __launch_bounds__(NT) void small_sum_kernel(const SmallArgs g) {
   constexpr int BLOCKS = SH::TM * SH::TN / 1024;
-  const int local = blockIdx.x / BLOCKS, tile = g.first + local, x = (blockIdx.x % BLOCKS) * NT + threadIdx.x;
-  const SmallTile tr = g.rows[tile / g.tiles_n], tc = g.cols[tile % g.tiles_n];
+  const int local = blockIdx.x / BLOCKS, x = (blockIdx.x % BLOCKS) * NT + threadIdx.x;
+  int row, col;
+  small_tile_of(g, g.first + local, &row, &col);
+  const SmallTile tr = g.rows[row], tc = g.cols[col];
   const int r = x / (SH::TN / 4), c = x % (SH::TN / 4) * 4;
   if (r >= tr.ext || c >= tc.ext) return;
   typedef const __attribute__((address_space(1))) f32x4 *gvec;
   const int64_t step = (int64_t)g.tiles * (SH::TM * SH::TN);
+  const SmallOutLoad to_load = small_out_load(g, tr, tc, r, c);
   const float *p = g.scratch + (int64_t)local * (SH::TM * SH::TN) + r * SH::TN + c;
   f32x4 s = *(gvec)p;
   constexpr int QB = 8;                                   // runs whose loads are in flight at a time
@@ -390,13 +483,13 @@ __global__ __launch_bounds__(NT) void small_sum_kernel(const SmallArgs g) {
     for (int q = 0; q < QB; ++q)
       if (q0 + q < g.runs) s = s + v[q];
   }
-  small_store4(g, tr, tc, r, c, s);
+  SmallOut to = small_out_of(g, to_load);
+  small_store4(g, tr, tc, to, r, c, s);
 }
 
 //                ES   TM   TN  BK WM WN WK DEPTH OCC
 typedef SmallShape<2, 32, 128, 64, 1, 4, 1, 1, 3> SmallBf16Skinny;
 typedef SmallShape<2, 64, 128, 64, 2, 2, 1, 2, 2> SmallBf16Half;
-typedef SmallShape<2, 128, 128, 64, 2, 2, 1, 2, 2> SmallBf16;
 typedef SmallShape<4, 32, 32, 64, 1, 1, 4, 1, 4> SmallF32Tiny;
 typedef SmallShape<4, 64, 64, 32, 2, 2, 1, 2, 4> SmallF32;
 
