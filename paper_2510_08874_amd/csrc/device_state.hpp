@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "dmm.h"
+#include "gemm_launch.hpp"
 
 namespace dmm {
 
@@ -41,6 +42,12 @@ struct StreamKey {
   bool operator==(const StreamKey &o) const { return stream == o.stream && thread == o.thread; }
 };
 
+bool is_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();
+  return status == hipStreamCaptureStatusActive;
+}
+
 // The calls of a plan whose kernels may still be running: an event behind the last call on each of
 // the streams it was used on.  Whoever writes a buffer that those kernels use waits for all of them
 // (one event for the plan would forget a stream as soon as the next call came on another).  A stream
@@ -50,24 +57,20 @@ class Uses {
  public:
   // behind everything the call enqueued on `stream`
   int mark(hipStream_t stream) {
-    const StreamKey key = StreamKey::of(stream);
     Entry *e = nullptr;
-    for (int i = 0; i < n_ && !e; ++i)
-      if (uses_[i].key == key) e = &uses_[i];
-    if (!e && n_ < kMost) {
-      e = &uses_[n_];
-      DMM_HIP(hipEventCreateWithFlags(&e->ev, hipEventDisableTiming));
-      ++n_;
-    } else if (!e) {
-      // more streams than entries: the new event takes over from the one of another stream by
-      // being recorded behind it too
-      e = &uses_[next_];
-      next_ = (next_ + 1) % kMost;
-      DMM_HIP(hipStreamWaitEvent(stream, e->ev, 0));
-    }
-    e->key = key;
+    const int rc = entry(stream, &e);
+    if (rc) return rc;
     DMM_HIP(hipEventRecord(e->ev, stream));
     return DMM_OK;
+  }
+  // The event that the call's last launch on `stream` is to record; none while the stream is being captured: mark() then.
+  int claim(hipStream_t stream, hipEvent_t *ev) {
+    *ev = nullptr;
+    if (is_capturing(stream)) return DMM_OK;
+    Entry *e = nullptr;
+    const int rc = entry(stream, &e);
+    if (!rc) *ev = e->ev;
+    return rc;
   }
   // orders what follows on `stream` behind all of them
   int order(hipStream_t stream) const {
@@ -98,6 +101,27 @@ class Uses {
     StreamKey key;
     hipEvent_t ev = nullptr;
   };
+  // that of `stream`
+  int entry(hipStream_t stream, Entry **out) {
+    const StreamKey key = StreamKey::of(stream);
+    Entry *e = nullptr;
+    for (int i = 0; i < n_ && !e; ++i)
+      if (uses_[i].key == key) e = &uses_[i];
+    if (!e && n_ < kMost) {
+      e = &uses_[n_];
+      DMM_HIP(hipEventCreateWithFlags(&e->ev, hipEventDisableTiming));
+      ++n_;
+    } else if (!e) {
+      // more streams than entries: the new event takes over from the one of another stream by
+      // being recorded behind it too
+      e = &uses_[next_];
+      next_ = (next_ + 1) % kMost;
+      DMM_HIP(hipStreamWaitEvent(stream, e->ev, 0));
+    }
+    e->key = key;
+    *out = e;
+    return DMM_OK;
+  }
   Entry uses_[kMost] = {};
   int n_ = 0, next_ = 0;
 };
@@ -341,13 +365,27 @@ int copy_stream(hipStream_t *out) {
   return DMM_OK;
 }
 
-// upload() copies host bytes to the slab's device buffer on the copy stream and makes the
+// A small table travels as the argument of a kernel that writes it: on the caller's own stream, one launch, where the
+// copy takes the host a copy, two events and two waits (2048^3 in 2 x 2 tiles, a new plan and other buffers
+// every time: 42 -> 34 us a call, 27 of host work -> 12).
+constexpr size_t kTableWords = 448;
+struct TableArg {
+  uint64_t word[kTableWords];
+};
+__global__ __launch_bounds__(256) void table_kernel(TableArg, uint64_t *dst, int words) {
+  // (read where the launch has put the argument; taken by its name it would go through private memory)
+  const auto *src = (const __attribute__((address_space(4))) uint64_t *)__builtin_amdgcn_kernarg_segment_ptr();
+  for (int i = threadIdx.x; i < words; i += 256) dst[i] = src[i];
+}
+
+// upload() copies host bytes to the slab's device buffer (on the copy stream, or with table_kernel) and makes the
 // caller's stream wait for that copy; it skips the copy when those bytes are already resident.
 // `readers` are the calls whose kernels may still read the device buffer: the copy waits for them.
 struct Uploader {
   Slab slab;
   bool ev_used[2] = {false, false};
   int cur = 0;
+  StreamKey copied_on;                   // where the copy behind ev[cur] was made
 
   char *dev() const { return slab.dev; }
   int upload(const void *src, size_t bytes, hipStream_t stream, const Uses &readers) {
@@ -368,10 +406,23 @@ struct Uploader {
       // already resident; the caller's stream (possibly another one than last time) still has to
       // be ordered behind the copy that put it there, if this uploader made that copy (a copy made
       // for an earlier owner of the slab finished before the slab went back to the pool)
-      if (ev_used[cur]) DMM_HIP(hipStreamWaitEvent(stream, slab.ev[cur], 0));
-      return DMM_OK;
+      return order_behind_copy(stream);
     }
     resident.clear();                      // unknown contents until the copy below has been enqueued
+    if (bytes <= sizeof(TableArg) && bytes % 8 == 0 && !is_capturing(stream)) {
+      // (behind the readers on other streams, and behind a copy that a call made and failed to use)
+      int rc = readers.order(stream);
+      if (rc || (rc = order_behind_copy(stream))) return rc;
+      TableArg table;
+      std::memcpy(table.word, src, bytes);
+      if (launch_behind_only(slab.ev[cur ^ 1], table_kernel, 1, 256, 0, stream, table, (uint64_t *)slab.dev, (int)(bytes / 8))) {
+        cur ^= 1;
+        ev_used[cur] = true;
+        copied_on = StreamKey::of(stream);
+        resident.assign((const char *)src, (const char *)src + bytes);
+        return DMM_OK;
+      }
+    }
     cur ^= 1;
     if (ev_used[cur]) DMM_HIP(hipEventSynchronize(slab.ev[cur]));  // slot last used two uploads ago
     std::memcpy(slab.pinned[cur], src, bytes);
@@ -383,13 +434,14 @@ struct Uploader {
     DMM_HIP(hipEventRecord(slab.ev[cur], cs));
     DMM_HIP(hipStreamWaitEvent(stream, slab.ev[cur], 0));
     ev_used[cur] = true;
+    copied_on = StreamKey::of(cs);
     resident.assign((const char *)src, (const char *)src + bytes);
     return DMM_OK;
   }
   // Orders `stream` behind the copy that put the resident bytes in place (for a caller that knows
   // by other means that they are the bytes it wants).
   int order_behind_copy(hipStream_t stream) {
-    if (slab.dev && ev_used[cur]) DMM_HIP(hipStreamWaitEvent(stream, slab.ev[cur], 0));
+    if (slab.dev && ev_used[cur] && !(copied_on == StreamKey::of(stream))) DMM_HIP(hipStreamWaitEvent(stream, slab.ev[cur], 0));
     return DMM_OK;
   }
   // The caller guarantees that no stream work still uses the slab: in particular its last copy has

@@ -196,7 +196,8 @@ int stage_reduce(dmm_plan_t *P, void *const *c_tiles, const int64_t *c_ld, int32
   return DMM_OK;
 }
 
-int fire_reduce(dmm_plan_t *P, const RedLaunch &L, hipStream_t stream, bool timed) {
+// *marked: `behind` (if any) has been recorded by the launch.
+int fire_reduce(dmm_plan_t *P, const RedLaunch &L, hipStream_t stream, bool timed, hipEvent_t behind, bool *marked) {
   if (L.n_items == 0) return DMM_OK;
   int rc;
   char *d = L.dev_base;
@@ -207,9 +208,9 @@ int fire_reduce(dmm_plan_t *P, const RedLaunch &L, hipStream_t stream, bool time
     if ((rc = timing_events(P->dev->t_red))) return rc;
     DMM_HIP(hipEventRecord(P->dev->t_red[0], stream));
   }
-  hipLaunchKernelGGL(reduce_replicas_kernel, dim3((unsigned)L.n_items), dim3(RED_NT), 0, stream,
-                     (const RedItem *)(d + o_items), (const RedTile *)(d + o_tiles),
-                     (const float *const *)(d + o_parts), (const int64_t *)(d + o_lds), nparts, vec_ok ? 1 : 0);
+  *marked = launch_behind(behind, reduce_replicas_kernel, (unsigned)L.n_items, RED_NT, 0, stream, (const RedItem *)(d + o_items),
+                          (const RedTile *)(d + o_tiles), (const float *const *)(d + o_parts), (const int64_t *)(d + o_lds), nparts,
+                          vec_ok ? 1 : 0);
   DMM_HIP(hipGetLastError());
   if (timed) {
     DMM_HIP(hipEventRecord(P->dev->t_red[1], stream));
@@ -1227,9 +1228,7 @@ int take_copies(DeviceState &D, hipStream_t stream) {
   if (D.pack_kept) return D.dense->dev->uses.order(stream);
   int rc;
   if (!D.pack.p && (rc = pack_pool().acquire(D.pack_need, stream, D.pack_at, &D.pack))) return rc;
-  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();
-  D.pack_kept = status == hipStreamCaptureStatusActive;     // (the graph may run any time from now on)
+  D.pack_kept = is_capturing(stream);                       // (the graph may run any time from now on)
   return DMM_OK;
 }
 
@@ -1365,6 +1364,11 @@ bool operands_given(const dmm_plan_t *P, const ExecArgs &x) {
 // The launches of one dmm_execute, from the device table the layout describes.
 int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stream, bool timed) {
   int rc;
+  // the event that stands for the call goes with its last launch
+  hipEvent_t behind = nullptr;
+  bool marked = false;
+  if ((rc = P->dev->uses.claim(stream, &behind))) return rc;
+  const hipEvent_t behind_gemm = L.red.n_items > 0 ? nullptr : behind;
   char *d = P->dev->gemm_table.dev();
   if (L.small.shape >= 0) {
     const SmallLaunch &l = L.small;
@@ -1398,7 +1402,7 @@ int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stre
     }
     for (g.first = 0; g.first < l.tiles_m * l.tiles_n; g.first += l.batch) {
       g.tiles = std::min(l.batch, l.tiles_m * l.tiles_n - g.first);
-      small_launch(l.shape, g, cus, stream);
+      marked = small_launch(g.first + g.tiles < l.tiles_m * l.tiles_n ? nullptr : behind_gemm, l.shape, g, cus, stream);
       DMM_HIP(hipGetLastError());
     }
     if (timed) {
@@ -1417,12 +1421,11 @@ int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stre
       if ((rc = timing_events(P->dev->t_gemm))) return rc;
       DMM_HIP(hipEventRecord(P->dev->t_gemm[0], stream));
     }
-    launch_grouped_gemm_comp((int)es, (unsigned)ml.n_items, stream, (const CompItemDev *)d, (const PieceDev *)(d + ml.o_a),
+    marked = launch_grouped_gemm_comp(ml.n_fix > 0 ? nullptr : behind_gemm, (int)es, (unsigned)ml.n_items, stream, (const CompItemDev *)d, (const PieceDev *)(d + ml.o_a),
                              (const PieceDev *)(d + ml.o_b), (const PieceDev *)(d + ml.o_c), (const int32_t *)(d + ml.o_k));
     DMM_HIP(hipGetLastError());
     if (ml.n_fix > 0) {
-      hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)(ml.n_fix * (BM / FIX_ROWS))), dim3(256), 0, stream,
-                         (const FixItem *)(d + ml.o_fix));
+      marked = launch_behind(behind_gemm, sum_parts_kernel, (unsigned)(ml.n_fix * (BM / FIX_ROWS)), 256, 0, stream, (const FixItem *)(d + ml.o_fix));
       DMM_HIP(hipGetLastError());
     }
     if (timed) {
@@ -1455,7 +1458,8 @@ int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stre
         const bool sums = fuse && (l == 1 || one_launch);   // the launch whose macro-tiles add the other replicas' partial sums
         // one workgroup per CU at most: workgroup w walks items w, w + grid, w + 2 grid, ... of its launch
         const int count = (int)part[l][1];
-        launch_grouped_gemm((int)es, sums, (unsigned)std::min(count, cus), stream, di + part[l][0], ds, dr, count);
+        const bool ends = L.n_fix == 0 && (l == 1 || part[1][1] == 0);
+        marked = launch_grouped_gemm(ends ? behind_gemm : nullptr, (int)es, sums, (unsigned)std::min(count, cus), stream, di + part[l][0], ds, dr, count);
         DMM_HIP(hipGetLastError());
         if (timed && fuse && !one_launch && l == 0 && part[1][1] > 0) {
           if (!P->dev->t_mid) DMM_HIP(hipEventCreate(&P->dev->t_mid));
@@ -1467,8 +1471,7 @@ int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stre
         }
       }
       if (L.n_fix > 0) {
-        hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)(L.n_fix * (BM / FIX_ROWS))), dim3(256), 0, stream,
-                           (const FixItem *)(d + L.o_fix));
+        marked = launch_behind(behind_gemm, sum_parts_kernel, (unsigned)(L.n_fix * (BM / FIX_ROWS)), 256, 0, stream, (const FixItem *)(d + L.o_fix));
         DMM_HIP(hipGetLastError());
       }
       if (timed) {
@@ -1481,9 +1484,9 @@ int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stre
   }
   {
     TraceRange tr("replica_sum");
-    if ((rc = fire_reduce(P, L.red, stream, timed))) return rc;
+    if ((rc = fire_reduce(P, L.red, stream, timed, behind, &marked))) return rc;
   }
-  return P->dev->uses.mark(stream);
+  return marked ? DMM_OK : P->dev->uses.mark(stream);
 }
 
 int launch_dense(dmm_plan_t *P, const ExecArgs &x, hipStream_t stream, bool timed) {
@@ -1695,8 +1698,11 @@ int dmm_reduce_replicas(dmm_plan_t *P, void *const *c_tiles, const int64_t *c_ld
     if ((rc = ensure_state(P))) return rc;
     RedLaunch red;
     if ((rc = stage_reduce(P, c_tiles, c_ld, origin_replica, (hipStream_t)hip_stream, &red))) return rc;
-    if ((rc = fire_reduce(P, red, (hipStream_t)hip_stream, false))) return rc;
-    return P->C.c > 1 ? P->dev->uses.mark((hipStream_t)hip_stream) : DMM_OK;
+    hipEvent_t behind = nullptr;
+    bool marked = false;
+    if (P->C.c > 1 && (rc = P->dev->uses.claim((hipStream_t)hip_stream, &behind))) return rc;
+    if ((rc = fire_reduce(P, red, (hipStream_t)hip_stream, false, behind, &marked))) return rc;
+    return P->C.c > 1 && !marked ? P->dev->uses.mark((hipStream_t)hip_stream) : DMM_OK;
   } catch (const std::bad_alloc &) {
     return DMM_ENOMEM;
   }
@@ -1717,11 +1723,13 @@ int dmm_broadcast_replica(dmm_plan_t *P, void *const *c_tiles, const int64_t *c_
     if ((rc = stage_reduce(P, c_tiles, c_ld, origin_replica, stream, &L))) return rc;
     if (L.n_items == 0) return DMM_OK;
     char *d = L.dev_base;
-    hipLaunchKernelGGL(broadcast_replica_kernel, dim3((unsigned)L.n_items), dim3(RED_NT), 0, stream,
-                       (const RedItem *)(d + L.o_items), (const RedTile *)(d + L.o_tiles),
-                       (float *const *)(d + L.o_parts), (const int64_t *)(d + L.o_lds), L.nparts, L.vec_ok ? 1 : 0);
+    hipEvent_t behind = nullptr;
+    if ((rc = P->dev->uses.claim(stream, &behind))) return rc;
+    const bool marked = launch_behind(behind, broadcast_replica_kernel, (unsigned)L.n_items, RED_NT, 0, stream, (const RedItem *)(d + L.o_items),
+                                      (const RedTile *)(d + L.o_tiles), (float *const *)(d + L.o_parts), (const int64_t *)(d + L.o_lds),
+                                      L.nparts, L.vec_ok ? 1 : 0);
     DMM_HIP(hipGetLastError());
-    return P->dev->uses.mark(stream);
+    return marked ? DMM_OK : P->dev->uses.mark(stream);
   } catch (const std::bad_alloc &) {
     return DMM_ENOMEM;
   }

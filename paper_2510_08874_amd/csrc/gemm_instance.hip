@@ -24,9 +24,9 @@ hipError_t DMM_CAT(gemm_allow_lds_, DMM_INSTANCE)() {
                              LDS_BYTES);
 }
 
-void DMM_CAT(gemm_launch_, DMM_INSTANCE)(unsigned grid, hipStream_t stream, const ItemDev *items, const SegDev *segs,
+bool DMM_CAT(gemm_launch_, DMM_INSTANCE)(hipEvent_t behind, unsigned grid, hipStream_t stream, const ItemDev *items, const SegDev *segs,
                                          const RedSrc *red, int n_items) {
-  hipLaunchKernelGGL((grouped_gemm_kernel<kES, kFuse>), dim3(grid), dim3(NT), LDS_BYTES, stream, items, segs, red, n_items);
+  return launch_behind(behind, grouped_gemm_kernel<kES, kFuse>, grid, NT, LDS_BYTES, stream, items, segs, red, n_items);
 }
 
 #else
@@ -38,9 +38,9 @@ hipError_t DMM_CAT(gemm_allow_lds_, DMM_INSTANCE)() {
                              LDS_BYTES + DESC_LDS);
 }
 
-void DMM_CAT(gemm_launch_, DMM_INSTANCE)(unsigned grid, hipStream_t stream, const CompItemDev *items, const PieceDev *a,
+bool DMM_CAT(gemm_launch_, DMM_INSTANCE)(hipEvent_t behind, unsigned grid, hipStream_t stream, const CompItemDev *items, const PieceDev *a,
                                          const PieceDev *b, const PieceDev *c, const int32_t *klen) {
-  hipLaunchKernelGGL(grouped_gemm_comp_kernel<kES>, dim3(grid), dim3(NT), LDS_BYTES + DESC_LDS, stream, items, a, b, c, klen);
+  return launch_behind(behind, grouped_gemm_comp_kernel<kES>, grid, NT, LDS_BYTES + DESC_LDS, stream, items, a, b, c, klen);
 }
 
 #endif

@@ -13,11 +13,12 @@ hipError_t allow() {
 }
 
 template <class SH>
-void launch(const SmallArgs &g, hipStream_t stream) {
+bool launch(hipEvent_t behind, const SmallArgs &g, hipStream_t stream) {
   const unsigned tiles = (unsigned)g.tiles;
-  hipLaunchKernelGGL(small_gemm_kernel<SH>, dim3(tiles * (unsigned)g.runs), dim3(NT), SH::LDS, stream, g);
-  if (g.runs > 1 && hipPeekAtLastError() == hipSuccess)
-    hipLaunchKernelGGL(small_sum_kernel<SH>, dim3(tiles * (unsigned)(SH::TM * SH::TN / 1024)), dim3(NT), 0, stream, g);
+  const bool sum = g.runs > 1;
+  const bool marked = launch_behind(sum ? nullptr : behind, small_gemm_kernel<SH>, tiles * (unsigned)g.runs, NT, SH::LDS, stream, g);
+  if (!sum || hipPeekAtLastError() != hipSuccess) return marked;
+  return launch_behind(behind, small_sum_kernel<SH>, tiles * (unsigned)(SH::TM * SH::TN / 1024), NT, 0, stream, g);
 }
 
 }  // namespace
@@ -33,14 +34,14 @@ hipError_t small_allow_lds() {
   return e;
 }
 
-void small_launch(int shape, const SmallArgs &g, int cus, hipStream_t stream) {
+bool small_launch(hipEvent_t behind, int shape, const SmallArgs &g, int cus, hipStream_t stream) {
   const bool alone = g.tiles * g.runs <= cus;          // a CU for every workgroup
   switch (shape) {
-    case SMALL_BF16_SKINNY: return alone ? launch<RingSkinnyDeep>(g, stream) : launch<RingSkinny>(g, stream);
-    case SMALL_BF16_HALF: return launch<RingHalf>(g, stream);
-    case SMALL_BF16: return alone ? launch<RingDeep>(g, stream) : launch<RingPair>(g, stream);
-    case SMALL_F32_TINY: return launch<SmallF32Tiny>(g, stream);
-    default: return launch<SmallF32>(g, stream);
+    case SMALL_BF16_SKINNY: return alone ? launch<RingSkinnyDeep>(behind, g, stream) : launch<RingSkinny>(behind, g, stream);
+    case SMALL_BF16_HALF: return launch<RingHalf>(behind, g, stream);
+    case SMALL_BF16: return alone ? launch<RingDeep>(behind, g, stream) : launch<RingPair>(behind, g, stream);
+    case SMALL_F32_TINY: return launch<SmallF32Tiny>(behind, g, stream);
+    default: return launch<SmallF32>(behind, g, stream);
   }
 }
 
