@@ -276,8 +276,8 @@ int dmm_reduce_replicas_static(dmm_plan_t *p, void *const *c_tiles, const int64_
  *   ran_k_split   1: it cut tiles along K (partial tiles through a scratch buffer, added up
  *                 in ascending k by a second kernel: the last round of workgroups would have left
  *                 most of the device idle, or a merged macro-tile had more K-segments than its
- *                 workgroup can hold descriptors for).  Such a run sums in another order than an
- *                 uncut one
+ *                 workgroup can hold descriptors for), or within a workgroup, or multiplied fp32
+ *                 operands as three bf16 parts each.  Such a run rounds differently from an uncut one
  *   ran_fused     how it summed the replicas of C: 0 = not in the GEMM (one replica,
  *                 DMM_NO_REDUCE, DMM_SEPARATE_REDUCE, or the fused form did not apply), 1 = in the
  *                 GEMM, one launch, 2 = in the GEMM, replica 0's macro-tiles in a second launch

@@ -828,7 +828,7 @@ constexpr int64_t kSmallMost = 1 << 20;    // workgroups of a launch (small_div)
 
 constexpr SmallKind kSmall[SMALL_SHAPES] = {
     small_kind<RingSkinny>(0.25, 0.46), small_kind<RingHalf>(0.31, 0.46), small_kind<RingPair>(0.44, 0.62),
-    small_kind<SmallF32Tiny>(0.39, 0.72), small_kind<SmallF32>(0.52, 0.78),
+    small_kind<SmallF32Tiny>(0.39, 0.72), small_kind<SmallF32>(0.52, 0.78), small_kind<SmallF32Split>(1.38, 1.5),
 };
 
 int64_t count_steps(const std::vector<int64_t> &kc, int64_t bk) {
@@ -864,6 +864,8 @@ int64_t count_tails(const std::vector<int64_t> &kc, int64_t bk) {
 // 64 x 5760 x 4960 61 -> 19; fp32 577 x 28352 x 512 216 -> 176.  Between these shapes, us in tiles of 32, 64 and 128
 // rows: 128 x 8960 x 8576 60, 49, 40; 64 x 6615 x 45440 177, 146, 156; 640 x 247 x 384 11, 12, 16 (a 128-row tile's prologue
 // and epilogue take 5 us longer, which shows where they do not fill the CUs); 900 x 333 x 1100 14, 16, 19.
+// fp32 in tiles of 64 rows and of 128, taken apart: 1024^3 35, 37; 3840 x 1006 x 594 in 16 column strips (tiles 37 wide)
+// 99, 147; 512 x 8416 x 848 85, 77; 2432 x 4256 x 600 uneven 160, 120.  Below K = 512 or 16 tiles there is no time to win: a call is its launches.
 void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
   const Grid &A = P->A, &B = P->B, &C = P->C;
   const int64_t M = C.rows, K = A.cols, N = C.cols, lim = (int64_t)1 << 30;
@@ -879,7 +881,7 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
   if (P->merged.valid) items = P->merged.items.size();
   else
     for (const dmm_work_item &w : P->items) items += w.group >= 0;
-  if (M >= 2048 && N >= 2048 && items >= 2 * (size_t)cus) return;             // two full rounds of macro-tiles: theirs
+  if (x.es == 2 && M >= 2048 && N >= 2048 && items >= 2 * (size_t)cus) return;   // two full rounds of macro-tiles: theirs
   // Microseconds.  The macro-tile kernels: rounds of macro-tiles, the last one cut along K where it is
   // at most half full; a K step costs more the fuller the device (its clock falls), every item a
   // prologue and an epilogue, every segment a switch.
@@ -906,17 +908,22 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
     c.cols = tile_axis(c.nc, 1 << 30, kPieceAlign, s.tn);
     const int64_t tiles = (int64_t)(c.rows.size() * c.cols.size()), steps = count_steps(c.kc, s.bk);
     const int64_t tails = count_tails(c.kc, s.bk);
-    if (tiles >= kSmallMost) continue;
+    if (tiles >= kSmallMost || (k == SMALL_F32_SPLIT && (K < 512 || tiles < 16))) continue;
     // B comes again for every tile row but the first: from memory (64 x 6615 x 45440 in 32 x 128 tiles 187 us, in
     // 64 x 128 tiles 161), or, where the last-level cache holds it, from there.
     const double b_bytes = (double)x.es * (double)K * N;
     const double mem = bytes / 5.6e6 + (double)(c.rows.size() - 1) * b_bytes / (b_bytes > 128e6 ? 6.5e6 : 14e6);
+    // Rounding grows with the root of the number of terms in a chain of sums.  The split kernel's chains round 0.88 times
+    // as much as fp32 chains of the same length, so there are at least 0.8 times as many of them as there would be otherwise.
+    const int64_t least_runs = k != SMALL_F32_SPLIT ? 1 : (int64_t)std::ceil(0.8 * std::max(
+        (double)items / ((double)full * cus + (double)tail / (double)big_runs),
+        best->shape < 0 ? 1.0 : (double)best->runs * (best->shape == SMALL_F32_TINY ? SmallF32Tiny::WK : 1)));
     // a run has at least 256 (fp32: 128) elements of k, and the partial tiles fit 64 MB, which is
     // what the macro-tile kernels use at most
     const int64_t least_per = (s.es == 2 ? 256 : 128) / s.bk;
     for (int64_t r = 1; r <= std::max<int64_t>(1, std::min<int64_t>(64, steps / least_per)); ++r) {
       const int64_t per = (steps + r - 1) / r, runs = (steps + per - 1) / per;
-      if (runs != r || runs * tiles >= kSmallMost) continue;
+      if (runs != r || r < least_runs || runs * tiles >= kSmallMost) continue;
       const int64_t part_bytes = runs * tiles * s.tm * s.tn * 4;
       if (runs > 1 && part_bytes > (int64_t)64 << 20) break;
       const int64_t per_cu = (tiles * runs + cus - 1) / cus, whole = per_cu / s.occ, rest = per_cu % s.occ;
@@ -928,7 +935,7 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
         t = t * odd + (double)(whole + (rest > 0)) * (0.4 * segs + (s.tm == 32 ? 0.75 : 0.9) * (double)tails) / (double)runs;
         t += k == SMALL_BF16 ? (tiles * runs < 140 ? 6 : 1.5) : 1;
       } else {
-        t += segs / (double)runs;
+        t += segs / (double)runs + (k == SMALL_F32_SPLIT ? 5 : 0);
       }
       t = 4 + std::max(t, s.es == 2 ? mem * std::max(1.0, 187.0 / (double)std::min<int64_t>(cus, tiles * runs)) : mem);
       if (runs > 1) t += (x.es == 2 ? 3 : 4) + 2.0 * (double)part_bytes / 12e6;
@@ -1412,7 +1419,8 @@ int launch_exec(dmm_plan_t *P, const ExecLayout &L, int64_t es, hipStream_t stre
     P->dev->ran_merged = false;
     P->dev->ran_small = l.shape;
     P->dev->small_runs = l.runs;
-    P->dev->ran_k_split = l.runs > 1 || l.shape == SMALL_F32_TINY;   // (that shape's waves share a tile's K steps)
+    // (the waves of the one shape share a tile's K steps, those of the other add up 16 k at a time)
+    P->dev->ran_k_split = l.runs > 1 || l.shape == SMALL_F32_TINY || l.shape == SMALL_F32_SPLIT;
     P->dev->ran_fused = 0;
   } else if (L.merged) {
     const MergedLaunch &ml = L.ml;

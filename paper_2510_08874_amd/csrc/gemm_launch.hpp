@@ -69,7 +69,7 @@ inline bool launch_grouped_gemm_comp(hipEvent_t behind, int es, unsigned grid, h
 
 // The kernels for small and skinny products (small_kernel.hpp), by shape.
 struct SmallArgs;
-enum { SMALL_BF16_SKINNY, SMALL_BF16_HALF, SMALL_BF16, SMALL_F32_TINY, SMALL_F32, SMALL_SHAPES };
+enum { SMALL_BF16_SKINNY, SMALL_BF16_HALF, SMALL_BF16, SMALL_F32_TINY, SMALL_F32, SMALL_F32_SPLIT, SMALL_SHAPES };
 hipError_t small_allow_lds();
 bool small_launch(hipEvent_t behind, int shape, const SmallArgs &g, int cus, hipStream_t stream);   // the product, and the sum of its partial tiles
 

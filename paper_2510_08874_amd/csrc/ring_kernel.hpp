@@ -450,7 +450,19 @@ template <class SH>
 __global__ __launch_bounds__(NT, SH::OCC) void small_gemm_kernel(const SmallArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   if constexpr (SH::RING) ring_gemm<SH>(g, lds);
-  else staged_gemm<SH>(g, lds);
+  else if constexpr (!SH::SPLIT) staged_gemm<SH>(g, lds, threadIdx.x);
+  else if (staged_gemm<SH>(g, lds, threadIdx.x)) {
+    typedef SmallF32Whole Part;
+    static_assert(SH::LDS >= Part::LDS && SH::TM == Part::TM * Part::PARTS && SH::TN == Part::TN && SH::BK == Part::BK, "the same launch");
+    const int ext = g.rows[small_place(g).row].ext;
+#pragma clang loop unroll(disable)
+    for (int part = 0; part * Part::TM < ext; ++part) {
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));      // (nothing worked out for this loop is kept in registers through the other one)
+      if (part > 0) __syncthreads();     // (the part before has left the LDS)
+      staged_gemm<Part>(g, lds, tid, part);
+    }
+  }
 }
 
 // The "deep" ones run where every workgroup has a CU to itself (us per call, two stages -> deep: 2048^3 33 -> 28, 21 x 10368

@@ -31,6 +31,7 @@ hipError_t small_allow_lds() {
   if (e == hipSuccess) e = allow<RingPair>();
   if (e == hipSuccess) e = allow<SmallF32Tiny>();
   if (e == hipSuccess) e = allow<SmallF32>();
+  if (e == hipSuccess) e = allow<SmallF32Split>();
   return e;
 }
 
@@ -40,6 +41,7 @@ bool small_launch(hipEvent_t behind, int shape, const SmallArgs &g, int cus, hip
     case SMALL_BF16_SKINNY: return alone ? launch<RingSkinnyDeep>(behind, g, stream) : launch<RingSkinny>(behind, g, stream);
     case SMALL_BF16_HALF: return launch<RingHalf>(behind, g, stream);
     case SMALL_BF16: return alone ? launch<RingDeep>(behind, g, stream) : launch<RingPair>(behind, g, stream);
+    case SMALL_F32_SPLIT: return launch<SmallF32Split>(behind, g, stream);
     case SMALL_F32_TINY: return launch<SmallF32Tiny>(behind, g, stream);
     default: return launch<SmallF32>(behind, g, stream);
   }

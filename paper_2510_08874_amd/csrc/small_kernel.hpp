@@ -18,7 +18,7 @@
 // nothing is ever read past a slice.  Sums run over the same K-segments in the same order and through the
 // same matrix instructions as in the macro-tile kernels, hence bitwise the same results, unless a
 // tile's K steps are dealt to several workgroups or waves (their partial sums are then added in
-// ascending k).
+// ascending k) or fp32 operands are taken apart into three bf16 (SmallF32Split: other roundings, no larger ones).
 //
 // Measured (kernel alone, us; macro-tile kernels -> these): fp32 256^3 50 -> 5.  Operands of one, two or three
 // steps in flight made no difference.
@@ -61,10 +61,13 @@ typedef __attribute__((address_space(3))) char *lds_ptr;
 
 // ES bytes per operand element; TM x TN tile of C; BK elements of k per step; WM x WN waves over the
 // tile, times WK waves over the matrix instructions of a step
-template <int ES_, int TM_, int TN_, int BK_, int WM_, int WN_, int WK_, int DEPTH_, int OCC_>
+// SPLIT: fp32 operands as three bf16 each (see split_planes)
+// PARTS: the launch's tiles have PARTS times TM rows, and this is the loop over one of these parts
+template <int ES_, int TM_, int TN_, int BK_, int WM_, int WN_, int WK_, int DEPTH_, int OCC_, bool SPLIT_ = false, int PARTS_ = 1>
 struct SmallShape {
-  static constexpr bool RING = false;
+  static constexpr bool RING = false, SPLIT = SPLIT_;
   static constexpr int ES = ES_, TM = TM_, TN = TN_, BK = BK_, WM = WM_, WN = WN_, WK = WK_;
+  static constexpr int PARTS = PARTS_;
   static constexpr int DEPTH = DEPTH_;                          // K steps whose operands are in flight
   static constexpr int OCC = OCC_;                              // workgroups per CU the LDS and registers leave room for
   static constexpr int PER = 16 / ES;
@@ -73,12 +76,15 @@ struct SmallShape {
   // row pitches in LDS that spread the fragment reads over all banks: 16 A rows read the same
   // chunk (pitch = 4 dwords off a multiple of 32); bf16 B: four k rows x 64 bytes per transposed read
   // (pitch = 64 bytes off a multiple of 128); fp32 B: rows k and k + 4 x 32 dwords (pitch = 8 off a multiple of 16)
-  static constexpr int A_PITCH = BK * ES + 16;
-  static constexpr int B_PITCH = TN * ES + (ES == 2 ? 64 : 32);
-  static constexpr int STAGE_BYTES = TM * A_PITCH + BK * B_PITCH;
+  static constexpr int PLANES = SPLIT ? 3 : 1, LES = SPLIT ? 2 : ES;   // in LDS: so many copies, bytes per element
+  static constexpr int A_PITCH = BK * LES + 16;
+  static constexpr int B_PITCH = TN * LES + (LES == 2 ? 64 : 32);
+  static constexpr int A_PLANE = TM * A_PITCH, B_PLANE = BK * B_PITCH;
+  static constexpr int STAGE_BYTES = PLANES * (A_PLANE + B_PLANE);
+  static constexpr int STAGES = SPLIT ? 1 : 2;
   static constexpr int T_PITCH = TN + 8;                         // floats: the finished tile in LDS
   static constexpr int TILE_BYTES = WK * TM * T_PITCH * 4;
-  static constexpr int LDS = 2 * STAGE_BYTES > TILE_BYTES ? 2 * STAGE_BYTES : TILE_BYTES;
+  static constexpr int LDS = STAGES * STAGE_BYTES > TILE_BYTES ? STAGES * STAGE_BYTES : TILE_BYTES;
   static constexpr int MI = TM / WM / 32, NI = TN / WN / 32;     // 32 x 32 matrix tiles per wave
   static_assert(WM * WN * WK == NW && CA >= 1 && CB >= 1 && NT % A_CHUNKS == 0 && NT % B_CHUNKS == 0, "chunks are dealt evenly");
 };
@@ -171,6 +177,7 @@ __device__ __forceinline__ void small_tile_of(const SmallArgs &g, int tile, int 
 // the (run, tile) sequence, so that the workgroups that share an L2 share A rows, B columns and k ranges.
 struct SmallPlace {
   int run, local, row, col;
+  int slot;                // its partial tile's number
 };
 __device__ __forceinline__ SmallPlace small_place(const SmallArgs &g) {
   const int total = (int)gridDim.x, q8 = total >> 3, r8 = total & 7;
@@ -179,6 +186,7 @@ __device__ __forceinline__ SmallPlace small_place(const SmallArgs &g) {
   SmallPlace p;
   p.run = small_div(id, g.tiles);
   p.local = id - p.run * g.tiles;
+  p.slot = id;
   small_tile_of(g, g.first + p.local, &p.row, &p.col);
   return p;
 }
@@ -202,7 +210,7 @@ __device__ __forceinline__ void small_epilogue(const SmallArgs &g, const SmallPl
     });
   });
   __syncthreads();
-  float *part = g.scratch + (int64_t)(at.run * g.tiles + at.local) * (SH::TM * SH::TN);
+  float *part = g.scratch + (int64_t)at.slot * (SH::TM * SH::TN);
   const int c = tid % (SH::TN / 4) * 4, r0 = tid / (SH::TN / 4);
   constexpr int STEP = NT / (SH::TN / 4);                 // rows from one of a thread's to the next
   if (c >= tc.ext || r0 >= tr.ext) return;
@@ -240,14 +248,62 @@ __device__ __forceinline__ SmallOutLoad small_first_out(const SmallArgs &g, cons
   return SmallOutLoad{{nullptr, 0, 0u, 0u}, 0, 0, 0};
 }
 
+//                ES   TM   TN  BK WM WN WK DEPTH OCC
+typedef SmallShape<4, 32, 32, 64, 1, 1, 4, 1, 4> SmallF32Tiny;
+typedef SmallShape<4, 64, 64, 32, 2, 2, 1, 2, 4> SmallF32;
+// What bounds the fp32 shapes is the fp32 matrix instruction, 64 cycles for 2 k of 32 x 32.  Taken as three bf16 each
+// (exactly), six bf16 products of 32 cycles do 16 k: 192 cycles instead of 512.  A 128 x 128 x 32 step is 1536 cycles
+// of the matrix pipes and some 1200 of taking apart and LDS writes, which the CU's other workgroup fills with its
+// matrix instructions: hence one LDS stage of 49 KB, twice per CU.  Measured at 4096^3: matrix pipes busy 60 % of the
+// time, clock 1.77 GHz; 952 us (macro-tiles, 144 TFLOP/s) -> 745 (184); 1838 x 2746 x 5742 in uneven tiles 589 -> 440
+// (64 x 64 tiles); 5120 x 4416 x 5468 with odd pitches 3090 -> 1570.  Error against 64 bits, uncut as both: 0.84 to
+// 0.90 of the fp32 kernels' (6 roundings per 16 k instead of 8).
+typedef SmallShape<4, 128, 128, 32, 2, 2, 1, 1, 2, true> SmallF32Split;
+typedef SmallShape<4, 64, 128, 32, 2, 2, 1, 1, 2, false, 2> SmallF32Whole;   // for its tiles that cannot be split (all of them,
+                                        // 2048 x 4096 x 2048: 505 us instead of 243; in 128 rows at once registers spill)
+
+// An fp32 value as the sum of three bf16: its upper 16 bits, those of what is left, and the rest, which has 8
+// significant bits.  Nothing is lost, and no part overflows; only bits below 2^-133, the smallest bf16, have no
+// place, and they stand in the lower half of the rest: `lost` collects it.  (The matrix pipe does not flush denormals.)
+struct SplitPlanes {
+  unsigned p[3][2];                 // four values: plane, pairs of bf16
+};
+__device__ __forceinline__ SplitPlanes split_planes(u32x4 v, unsigned &lost) {
+  SplitPlanes s;
+  unsigned r1[4], r2[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const unsigned u = v[e], upper = u & 0xFFFF0000u;
+    const float r = __builtin_bit_cast(float, u) - __builtin_bit_cast(float, upper);
+    r1[e] = __builtin_bit_cast(unsigned, r);
+    r2[e] = __builtin_bit_cast(unsigned, r - __builtin_bit_cast(float, r1[e] & 0xFFFF0000u));
+    lost |= r2[e];
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    s.p[0][h] = __builtin_amdgcn_perm(v[2 * h + 1], v[2 * h], 0x07060302u);   // the upper halves of two words
+    s.p[1][h] = __builtin_amdgcn_perm(r1[2 * h + 1], r1[2 * h], 0x07060302u);
+    s.p[2][h] = __builtin_amdgcn_perm(r2[2 * h + 1], r2[2 * h], 0x07060302u);
+  }
+  return s;
+}
+
+// (SPLIT: true if the tile is not to be had this way: an operand or a sum is infinite or not a number, or bits were lost.
+// Nothing has been stored then.)
 template <class SH>
-__device__ __forceinline__ void staged_gemm(const SmallArgs &g, char *lds) {
+__device__ __forceinline__ bool staged_gemm(const SmallArgs &g, char *lds, const int tid, const int part = 0) {
   constexpr int ES = SH::ES, BK = SH::BK, PER = SH::PER, CA = SH::CA, CB = SH::CB, DEPTH = SH::DEPTH, MI = SH::MI, NI = SH::NI;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wk = wave % SH::WK, wn = wave / SH::WK % SH::WN, wm = wave / SH::WK / SH::WN;
-  const SmallPlace at = small_place(g);
-  const SmallTile tr = g.rows[at.row], tc = g.cols[at.col];
+  SmallPlace at = small_place(g);
+  SmallTile tr = g.rows[at.row];
+  const SmallTile tc = g.cols[at.col];
+  if constexpr (SH::PARTS > 1) {
+    at.slot = at.slot * SH::PARTS + part;
+    tr.start += part * SH::TM;
+    tr.ext = tr.ext - part * SH::TM < SH::TM ? tr.ext - part * SH::TM : SH::TM;
+  }
   const int S = g.S, NR = g.NR;
   const SmallStart start = g.starts[at.run];
   const int t0 = at.run * g.per, n = g.steps - t0 < g.per ? g.steps - t0 : g.per;   // at least 1: the host sees to it
@@ -365,18 +421,37 @@ __device__ __forceinline__ void staged_gemm(const SmallArgs &g, char *lds) {
     }
   };
   const lds_ptr lds3 = (lds_ptr)(lds_void_ptr)lds;
+  unsigned lost = 0;
   auto write_step = [&](int stage, u32x4 (&va)[CA], u32x4 (&vb)[CB], int left_k) __attribute__((always_inline)) {
     if (__builtin_expect(left_k < BK, 0)) {
 #pragma unroll
       for (int x = 0; x < CA; ++x) va[x] = keep_first<ES>(va[x], left_k - ak);
     }
-    const lds_ptr sa = lds3 + stage * SH::STAGE_BYTES, sb = sa + SH::TM * SH::A_PITCH;
+    const lds_ptr sa = lds3 + stage * SH::STAGE_BYTES, sb = sa + SH::PLANES * SH::A_PLANE;
+    if constexpr (SH::SPLIT) {
+      typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-    for (int x = 0; x < CA; ++x)
-      *(__attribute__((address_space(3))) u32x4 *)(sa + (tid / SH::A_CHUNKS + x * A_ROWS) * SH::A_PITCH + ak * ES) = va[x];
+      for (int x = 0; x < CA; ++x) {
+        const SplitPlanes s = split_planes(va[x], lost);
 #pragma unroll
-    for (int x = 0; x < CB; ++x)
-      *(__attribute__((address_space(3))) u32x4 *)(sb + (bk + x * B_ROWS) * SH::B_PITCH + bn * ES) = vb[x];
+        for (int p = 0; p < 3; ++p)
+          *(__attribute__((address_space(3))) u32x2 *)(sa + p * SH::A_PLANE + (tid / SH::A_CHUNKS + x * A_ROWS) * SH::A_PITCH + ak * 2) = u32x2{s.p[p][0], s.p[p][1]};
+      }
+#pragma unroll
+      for (int x = 0; x < CB; ++x) {
+        const SplitPlanes s = split_planes(vb[x], lost);
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          *(__attribute__((address_space(3))) u32x2 *)(sb + p * SH::B_PLANE + (bk + x * B_ROWS) * SH::B_PITCH + bn * 2) = u32x2{s.p[p][0], s.p[p][1]};
+      }
+    } else {
+#pragma unroll
+      for (int x = 0; x < CA; ++x)
+        *(__attribute__((address_space(3))) u32x4 *)(sa + (tid / SH::A_CHUNKS + x * A_ROWS) * SH::A_PITCH + ak * ES) = va[x];
+#pragma unroll
+      for (int x = 0; x < CB; ++x)
+        *(__attribute__((address_space(3))) u32x4 *)(sb + (bk + x * B_ROWS) * SH::B_PITCH + bn * ES) = vb[x];
+    }
   };
 
   // ---- the K loop: step t is multiplied while the loads of the DEPTH steps after it travel -----------------
@@ -389,30 +464,37 @@ __device__ __forceinline__ void staged_gemm(const SmallArgs &g, char *lds) {
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
   const int a_row = wm * (MI * 32) + (lane & 31), half = lane >> 5;
   auto multiply = [&](int stage) __attribute__((always_inline)) {
-    const lds_ptr sa = lds3 + stage * SH::STAGE_BYTES, sb = sa + SH::TM * SH::A_PITCH;
-    if constexpr (ES == 2) {
+    const lds_ptr sa = lds3 + stage * SH::STAGE_BYTES, sb = sa + SH::PLANES * SH::A_PLANE;
+    if constexpr (SH::SPLIT) {
+      // a b = a1 b1 + (a1 b2 + a2 b1) + (a2 b2 + a1 b3 + a3 b1), the small ones first; what is left out, a2 b3 and below,
+      // is 2^-23 of a product and less
       const int gr = lane >> 4, li = lane & 15;
 #pragma unroll
-      for (int q = 0; q < BK / 16 / SH::WK; ++q) {
-        const int qq = q * SH::WK + wk;
-        bf16x8 fa[MI], fb[NI];
+      for (int q = 0; q < BK / 16; ++q) {
+        bf16x8 fa[3][MI], fb[3][NI];
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
-          fa[i] = *(const __attribute__((address_space(3))) bf16x8 *)(sa + (a_row + i * 32) * SH::A_PITCH + qq * 32 + half * 16);
+        for (int p = 0; p < 3; ++p) {
 #pragma unroll
-        for (int j = 0; j < NI; ++j) {
-          union { short4_t h[2]; bf16x8 v; } u;
+          for (int i = 0; i < MI; ++i)
+            fa[p][i] = *(const __attribute__((address_space(3))) bf16x8 *)(sa + p * SH::A_PLANE + (a_row + i * 32) * SH::A_PITCH + q * 32 + half * 16);
 #pragma unroll
-          for (int h = 0; h < 2; ++h)
-            u.h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (lds_short4_ptr)(sb + (qq * 16 + (gr >> 1) * 8 + (li >> 2) + 4 * h) * SH::B_PITCH +
-                                 (wn * (NI * 32) + j * 32 + (gr & 1) * 16 + (li & 3) * 4) * 2));
-          fb[j] = u.v;
+          for (int j = 0; j < NI; ++j) {
+            union { short4_t h[2]; bf16x8 v; } u;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+              u.h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                  (lds_short4_ptr)(sb + p * SH::B_PLANE + (q * 16 + (gr >> 1) * 8 + (li >> 2) + 4 * h) * SH::B_PITCH +
+                                   (wn * (NI * 32) + j * 32 + (gr & 1) * 16 + (li & 3) * 4) * 2));
+            fb[p][j] = u.v;
+          }
         }
+        constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+        for (int x = 0; x < 6; ++x)
 #pragma unroll
-          for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+          for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[pa[x]][i], fb[pb[x]][j], acc[i][j], 0, 0, 0);
       }
     } else {
 #pragma unroll
@@ -438,17 +520,42 @@ __device__ __forceinline__ void staged_gemm(const SmallArgs &g, char *lds) {
     constexpr int d = decltype(dc)::value;
     if (d < n) load_step(ra[d], rb[d], rk[d], d + 1 < n);
   });
-  for (int t = 0; t < n; t += DEPTH) {
-    static_for<DEPTH>([&](auto dc) {
-      constexpr int d = decltype(dc)::value;
-      if (t + d < n) {
-        // (the stage's last readers multiplied step t + d - 2 and have passed the barrier of the step between)
-        write_step((t + d) & 1, ra[d], rb[d], rk[d]);
-        if (t + d + DEPTH < n) load_step(ra[d], rb[d], rk[d], t + d + DEPTH + 1 < n);
-        __syncthreads();
-        multiply((t + d) & 1);
-      }
-    });
+  if constexpr (SH::SPLIT) {
+    static_assert(!SH::SPLIT || DEPTH == 1, "one stage, one step in flight: the CU's other workgroup multiplies meanwhile");
+    for (int t = 0; t < n; ++t) {
+      if (t > 0) __syncthreads();                         // (every wave has read the stage)
+      write_step(0, ra[0], rb[0], rk[0]);
+      if (t + 1 < n) load_step(ra[0], rb[0], rk[0], t + 2 < n);
+      __syncthreads();
+      multiply(0);
+    }
+    // infinities and NaN of the operands have made NaN of the sums
+    unsigned bad = lost & 0xFFFFu;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int r = wm * (MI * 32) + i * 32 + 8 * (e >> 2) + 4 * half + (e & 3), c = wn * (NI * 32) + j * 32 + (lane & 31);
+          const float sum = acc[i][j][e];
+          const bool finite = (__builtin_bit_cast(unsigned, sum) & 0x7F800000u) != 0x7F800000u;
+          bad |= r < tr.ext && c < tc.ext && !finite;
+        }
+    if (__syncthreads_or(bad != 0)) return true;
+  } else {
+    for (int t = 0; t < n; t += DEPTH) {
+      static_for<DEPTH>([&](auto dc) {
+        constexpr int d = decltype(dc)::value;
+        if (t + d < n) {
+          // (the stage's last readers multiplied step t + d - 2 and have passed the barrier of the step between)
+          write_step((t + d) & 1, ra[d], rb[d], rk[d]);
+          if (t + d + DEPTH < n) load_step(ra[d], rb[d], rk[d], t + d + DEPTH + 1 < n);
+          __syncthreads();
+          multiply((t + d) & 1);
+        }
+      });
+    }
   }
 
   // (not ahead of the loop here: its registers would be in the loop's way)
@@ -456,6 +563,7 @@ __device__ __forceinline__ void staged_gemm(const SmallArgs &g, char *lds) {
   SmallOut to = small_out_of(g, to_load);
   small_epilogue<SH>(g, at, tr, tc, to, lds3, [&](auto ic, auto jc, auto ec) { return acc[decltype(ic)::value][decltype(jc)::value][decltype(ec)::value]; },
                      wm, wn, wk);
+  return false;
 }
 
 // The partial tiles of every tile, added up in ascending k.  A workgroup takes 1024 elements.
@@ -486,12 +594,6 @@ __global__ __launch_bounds__(NT) void small_sum_kernel(const SmallArgs g) {
   SmallOut to = small_out_of(g, to_load);
   small_store4(g, tr, tc, to, r, c, s);
 }
-
-//                ES   TM   TN  BK WM WN WK DEPTH OCC
-typedef SmallShape<2, 32, 128, 64, 1, 4, 1, 1, 3> SmallBf16Skinny;
-typedef SmallShape<2, 64, 128, 64, 2, 2, 1, 2, 2> SmallBf16Half;
-typedef SmallShape<4, 32, 32, 64, 1, 1, 4, 1, 4> SmallF32Tiny;
-typedef SmallShape<4, 64, 64, 32, 2, 2, 1, 2, 4> SmallF32;
 
 // What the host's choice between them knows of a shape: microseconds per K step and tile, measured.
 struct SmallKind {
