@@ -389,7 +389,7 @@ __device__ __forceinline__ bool staged_gemm(const SmallArgs &g, char *lds, const
       }
     } else {
       // the segment's last step: what is read past the segment in k is zeroed on the way to LDS, so
-      // that no load is waited for here (columns past the tile's end stay as they are: never stored)
+      // that no load is waited for here (columns past the tile's end stay as they are, or are zeroed there)
       const int an = krem - ak;
 #pragma unroll
       for (int x = 0; x < CA; ++x) {
@@ -436,6 +436,11 @@ __device__ __forceinline__ bool staged_gemm(const SmallArgs &g, char *lds, const
 #pragma unroll
         for (int p = 0; p < 3; ++p)
           *(__attribute__((address_space(3))) u32x2 *)(sa + p * SH::A_PLANE + (tid / SH::A_CHUNKS + x * A_ROWS) * SH::A_PITCH + ak * 2) = u32x2{s.p[p][0], s.p[p][1]};
+      }
+      // (columns past the tile's end, the padding of a row among them, have no say in how the tile is multiplied)
+      if (edge) {
+#pragma unroll
+        for (int x = 0; x < CB; ++x) vb[x] = keep_first<ES>(vb[x], bvalid);
       }
 #pragma unroll
       for (int x = 0; x < CB; ++x) {

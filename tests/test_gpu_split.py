@@ -83,6 +83,28 @@ def test_values_that_cannot_be_split(dims, value):
     _check(got[ok_row][:, ok_col], A64[ok_row] @ B64[:, ok_col], A64[ok_row], B64[:, ok_col], cfg, cfg["name"])
 
 
+@pytest.mark.parametrize("dims", [(1030, 2003, 2046, 668, 501, 515, 511), (1665, 1290, 1667, 129, 1290, 1665, 1667)])
+def test_padding_does_not_show_in_the_bits(dims):
+    """Rows whose last chunk reaches into their padding: whatever lies there (zeros, bits below the smallest bf16,
+    NaN with every bit set, infinities), C has the same bits."""
+    cfg = dict(_problem(*dims), dtype="f32")
+    A, B = workloads.make_operands(cfg)
+    prob = _device_problem(cfg, A, B, ld_multiple=8, c_fill=float("nan"))
+    seen = []
+    for bits in (0, 1, -1, 0x7F800000):
+        for ts in (prob.A, prob.B):
+            for i, t in enumerate(ts.tensors):
+                _, _, c0, c1 = ts.bounds(*divmod(i, ts.gc))
+                t.view(torch.int32)[:, c1 - c0:] = bits
+        assert all(t.shape[1] > dims[2] for t in prob.B.tensors) and dims[2] % 4
+        prob.execute()
+        assert prob.plan.small_tile() == (128, 128)
+        seen.append(prob.c_global(0))
+    prob.close()
+    for other in seen[1:]:
+        assert np.array_equal(seen[0].view(np.int32), other.view(np.int32))
+
+
 def test_tiny_operands():
     """Operands all below 2^-110, the other side large: as accurate as elsewhere."""
     cfg = dict(_problem(*SHAPES[2]), dtype="f32")
