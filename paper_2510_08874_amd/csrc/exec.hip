@@ -828,7 +828,7 @@ constexpr int64_t kSmallMost = 1 << 20;    // workgroups of a launch (small_div)
 
 constexpr SmallKind kSmall[SMALL_SHAPES] = {
     small_kind<RingSkinny>(0.25, 0.46), small_kind<RingHalf>(0.31, 0.46), small_kind<RingPair>(0.44, 0.62),
-    small_kind<SmallF32Tiny>(0.39, 0.72), small_kind<SmallF32>(0.52, 0.78), small_kind<SmallF32Split>(1.38, 1.5),
+    small_kind<SmallF32Tiny>(0.39, 0.72), small_kind<SmallF32>(0.52, 0.78), small_kind<SmallF32Split>(1.55, 2.0),
 };
 
 int64_t count_steps(const std::vector<int64_t> &kc, int64_t bk) {
@@ -864,8 +864,9 @@ int64_t count_tails(const std::vector<int64_t> &kc, int64_t bk) {
 // 64 x 5760 x 4960 61 -> 19; fp32 577 x 28352 x 512 216 -> 176.  Between these shapes, us in tiles of 32, 64 and 128
 // rows: 128 x 8960 x 8576 60, 49, 40; 64 x 6615 x 45440 177, 146, 156; 640 x 247 x 384 11, 12, 16 (a 128-row tile's prologue
 // and epilogue take 5 us longer, which shows where they do not fill the CUs); 900 x 333 x 1100 14, 16, 19.
-// fp32 in tiles of 64 rows and of 128, taken apart: 1024^3 35, 37; 3840 x 1006 x 594 in 16 column strips (tiles 37 wide)
-// 99, 147; 512 x 8416 x 848 85, 77; 2432 x 4256 x 600 uneven 160, 120.  Below K = 512 or 16 tiles there is no time to win: a call is its launches.
+// fp32 in tiles of 64 rows and of 128, taken apart: 1024^3 34, 38; 3840 x 1006 x 594 in 16 column strips (tiles 37 wide)
+// 102, 124; 512 x 8416 x 848 78, 69; 2432 x 4256 x 600 uneven 148, 137; 5612 x 1584 x 3264 597, 467.  Below K = 512 or 16
+// tiles there is no time to win: a call is its launches.
 void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
   const Grid &A = P->A, &B = P->B, &C = P->C;
   const int64_t M = C.rows, K = A.cols, N = C.cols, lim = (int64_t)1 << 30;
@@ -913,9 +914,10 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
     // 64 x 128 tiles 161), or, where the last-level cache holds it, from there.
     const double b_bytes = (double)x.es * (double)K * N;
     const double mem = bytes / 5.6e6 + (double)(c.rows.size() - 1) * b_bytes / (b_bytes > 128e6 ? 6.5e6 : 14e6);
-    // Rounding grows with the root of the number of terms in a chain of sums.  The split kernel's chains round 0.88 times
-    // as much as fp32 chains of the same length, so there are at least 0.8 times as many of them as there would be otherwise.
-    const int64_t least_runs = k != SMALL_F32_SPLIT ? 1 : (int64_t)std::ceil(0.8 * std::max(
+    // Rounding grows with the root of the number of terms in a chain of sums.  The split kernel rounds once where the others
+    // round eight times: over drawn products it has 0.3 times their error (median; normal and uniform operands), and with at
+    // least 0.15 times as many chains as there would be otherwise never more than it (0.91 at most, operands of one sign).
+    const int64_t least_runs = k != SMALL_F32_SPLIT ? 1 : (int64_t)std::ceil(0.15 * std::max(
         (double)items / ((double)full * cus + (double)tail / (double)big_runs),
         best->shape < 0 ? 1.0 : (double)best->runs * (best->shape == SMALL_F32_TINY ? SmallF32Tiny::WK : 1)));
     // a run has at least 256 (fp32: 128) elements of k, and the partial tiles fit 64 MB, which is

@@ -18,7 +18,7 @@
 // nothing is ever read past a slice.  Sums run over the same K-segments in the same order and through the
 // same matrix instructions as in the macro-tile kernels, hence bitwise the same results, unless a
 // tile's K steps are dealt to several workgroups or waves (their partial sums are then added in
-// ascending k) or fp32 operands are taken apart into three bf16 (SmallF32Split: other roundings, no larger ones).
+// ascending k) or fp32 operands are taken apart into three bf16 (SmallF32Split: fewer roundings).
 //
 // Measured (kernel alone, us; macro-tile kernels -> these): fp32 256^3 50 -> 5.  Operands of one, two or three
 // steps in flight made no difference.
@@ -252,38 +252,45 @@ __device__ __forceinline__ SmallOutLoad small_first_out(const SmallArgs &g, cons
 typedef SmallShape<4, 32, 32, 64, 1, 1, 4, 1, 4> SmallF32Tiny;
 typedef SmallShape<4, 64, 64, 32, 2, 2, 1, 2, 4> SmallF32;
 // What bounds the fp32 shapes is the fp32 matrix instruction, 64 cycles for 2 k of 32 x 32.  Taken as three bf16 each
-// (exactly), six bf16 products of 32 cycles do 16 k: 192 cycles instead of 512.  A 128 x 128 x 32 step is 1536 cycles
+// (exactly), eight bf16 products of 32 cycles do 16 k: 256 cycles instead of 512.  A 128 x 128 x 32 step is 2048 cycles
 // of the matrix pipes and some 1200 of taking apart and LDS writes, which the CU's other workgroup fills with its
-// matrix instructions: hence one LDS stage of 49 KB, twice per CU.  Measured at 4096^3: matrix pipes busy 60 % of the
-// time, clock 1.77 GHz; 952 us (macro-tiles, 144 TFLOP/s) -> 745 (184); 1838 x 2746 x 5742 in uneven tiles 589 -> 440
-// (64 x 64 tiles); 5120 x 4416 x 5468 with odd pitches 3090 -> 1570.  Error against 64 bits, uncut as both: 0.84 to
-// 0.90 of the fp32 kernels' (6 roundings per 16 k instead of 8).
+// matrix instructions: hence one LDS stage (60 KB; 68 KB with the finished tile), twice per CU.  Measured, us per call, the
+// other fp32 kernels -> this one: 4096^3 950 (macro-tiles, 145 TFLOP/s) -> 860 (160); 2048^3 177 -> 127; 2501 x 1999 x 1777
+// uneven 219 -> 172; 5612 x 1584 x 3264 597 -> 467.  Error against 64 bits: of sums of many terms 0.2 to 0.5 of the
+// fp32 kernels', of single products the same (see multiply).
 typedef SmallShape<4, 128, 128, 32, 2, 2, 1, 1, 2, true> SmallF32Split;
 typedef SmallShape<4, 64, 128, 32, 2, 2, 1, 1, 2, false, 2> SmallF32Whole;   // for its tiles that cannot be split (all of them,
                                         // 2048 x 4096 x 2048: 505 us instead of 243; in 128 rows at once registers spill)
 
-// An fp32 value as the sum of three bf16: its upper 16 bits, those of what is left, and the rest, which has 8
-// significant bits.  Nothing is lost, and no part overflows; only bits below 2^-133, the smallest bf16, have no
-// place, and they stand in the lower half of the rest: `lost` collects it.  (The matrix pipe does not flush denormals.)
+// An fp32 value as the sum of three bf16: the nearest one, the nearest one to what is left, and the rest, which has no
+// more than 8 significant bits.  (To nearest, so that the second and third parts have either sign: cut off, all parts have
+// the sign of the value, and the small products, which a long sum rounds away one by one, are missing from every sum
+// of values of one sign: 159 units of 2^-24 at 4096^3 instead of 6.)  Nothing is lost; only bits below 2^-133, the
+// smallest bf16, have no place, and they stand in the lower half of the rest: `lost` collects it.  A value that rounds to
+// infinity leaves NaN behind.  (Neither the conversion nor the matrix pipe flushes denormals.)
 struct SplitPlanes {
   unsigned p[3][2];                 // four values: plane, pairs of bf16
 };
+__device__ __forceinline__ unsigned to_bf16_pair(float x, float y) {
+  unsigned r;
+  asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+  return r;
+}
 __device__ __forceinline__ SplitPlanes split_planes(u32x4 v, unsigned &lost) {
   SplitPlanes s;
-  unsigned r1[4], r2[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const unsigned u = v[e], upper = u & 0xFFFF0000u;
-    const float r = __builtin_bit_cast(float, u) - __builtin_bit_cast(float, upper);
-    r1[e] = __builtin_bit_cast(unsigned, r);
-    r2[e] = __builtin_bit_cast(unsigned, r - __builtin_bit_cast(float, r1[e] & 0xFFFF0000u));
-    lost |= r2[e];
-  }
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    s.p[0][h] = __builtin_amdgcn_perm(v[2 * h + 1], v[2 * h], 0x07060302u);   // the upper halves of two words
-    s.p[1][h] = __builtin_amdgcn_perm(r1[2 * h + 1], r1[2 * h], 0x07060302u);
-    s.p[2][h] = __builtin_amdgcn_perm(r2[2 * h + 1], r2[2 * h], 0x07060302u);
+    const unsigned u0 = v[2 * h], u1 = v[2 * h + 1];
+    const float x0 = __builtin_bit_cast(float, u0), x1 = __builtin_bit_cast(float, u1);
+    const unsigned first = to_bf16_pair(x0, x1);
+    const float y0 = x0 - __builtin_bit_cast(float, first << 16), y1 = x1 - __builtin_bit_cast(float, first & 0xFFFF0000u);
+    const unsigned second = to_bf16_pair(y0, y1);
+    const float z0 = y0 - __builtin_bit_cast(float, second << 16), z1 = y1 - __builtin_bit_cast(float, second & 0xFFFF0000u);
+    const unsigned rest0 = __builtin_bit_cast(unsigned, z0), rest1 = __builtin_bit_cast(unsigned, z1);
+    lost |= rest0 | rest1;
+    s.p[0][h] = first;
+    s.p[1][h] = second;
+    s.p[2][h] = __builtin_amdgcn_perm(rest1, rest0, 0x07060302u);   // the upper halves of two words
   }
   return s;
 }
@@ -313,34 +320,50 @@ __device__ __forceinline__ bool staged_gemm(const SmallArgs &g, char *lds, const
   const int bn = tid % SH::B_CHUNKS * PER;                // first column of its B chunks inside the tile
   const int bk = tid / SH::B_CHUNKS;                      // k row of its first B chunk
   constexpr int A_ROWS = NT / SH::A_CHUNKS, B_ROWS = NT / SH::B_CHUNKS;   // rows from one chunk to the next
-  const PieceDev *ap[CA];                                 // the A slices of its rows, at segment 0
-  int64_t arow[CA];                                       // row inside the slice's tile part
+  // Where its A rows lie.  (SPLIT: in places of its own in LDS, behind the stage: registers are short there.)
+  struct RowAt {
+    int slice, row;                                       // the A slice, at segment 0; row inside the slice's tile part
+  };
+  static_assert(!SH::SPLIT || SH::LDS >= SH::STAGE_BYTES + CA * NT * (int)sizeof(RowAt), "room behind the stage");
+  RowAt rows[SH::SPLIT ? 1 : CA];
+  typedef __attribute__((address_space(3))) RowAt *row_ptr;
+  const row_ptr own_rows = (row_ptr)((lds_ptr)(lds_void_ptr)lds + SH::STAGES * SH::STAGE_BYTES) + tid;
+  auto row_at = [&](int x) __attribute__((always_inline)) -> RowAt {
+    if constexpr (SH::SPLIT) return RowAt{own_rows[x * NT].slice, own_rows[x * NT].row};
+    else return rows[x];
+  };
 #pragma unroll
   for (int x = 0; x < CA; ++x) {
     int row = tid / SH::A_CHUNKS + x * A_ROWS;
     row = tr.start + (row < tr.ext ? row : tr.ext - 1);   // (rows past the tile's end read its last row; never stored)
     int m0;
-    ap[x] = g.pa + (int64_t)small_piece(g.mc, tr, row, &m0) * S;
-    arow[x] = row - m0;
+    const int slice = small_piece(g.mc, tr, row, &m0) * S;
+    if constexpr (SH::SPLIT) {
+      own_rows[x * NT].slice = slice;
+      own_rows[x * NT].row = row - m0;
+    } else {
+      rows[x] = RowAt{slice, row - m0};
+    }
   }
   int bvalid = tc.ext - bn;                               // columns of its chunk that exist
   bvalid = bvalid < 0 ? 0 : bvalid < PER ? bvalid : PER;
   const bool edge = tc.ext < SH::TN;
-  const PieceDev *bp;
-  int64_t bcol;                                           // byte column inside the slice
+  int bp;                                                 // its B slice, at segment 0
+  unsigned bcol;                                          // byte column inside the slice
   {
     const int col = tc.start + (bvalid > 0 ? bn : 0);
     int n0;
-    bp = g.pb + small_piece(g.nc, tc, col, &n0);
-    bcol = (int64_t)(col - n0) * ES;
+    bp = small_piece(g.nc, tc, col, &n0);
+    bcol = (unsigned)(col - n0) * ES;
   }
 
   // ---- cursor over the K steps whose loads are issued ------------------------------------
   // The descriptors of the segment after the cursor's are fetched a segment ahead: loads return in
   // order, so waiting for a descriptor asked for just now would wait for all operands in flight.
+  // (SPLIT: not ahead, for the same shortage of registers; the CU's other workgroup multiplies meanwhile.)
   int seg = 0, krem = 0;                                  // segment; elements of it left
   gptr pa[CA], pb;
-  int64_t bpitch = 0;
+  unsigned bpitch = 0;
   PieceDev na[CA], nb;                                    // descriptors of the coming segment
   int nlen = 0;
   // Which of its chunks a thread may read in full where only the first elements count (a K tail, the
@@ -350,28 +373,29 @@ __device__ __forceinline__ bool staged_gemm(const SmallArgs &g, char *lds, const
   bool quick = true;                                      // the chunks of all its other rows, in every lane
   auto fetch = [&](int s) {
 #pragma unroll
-    for (int x = 0; x < CA; ++x) na[x] = ap[x][s];
-    nb = bp[(int64_t)s * NR];
+    for (int x = 0; x < CA; ++x) na[x] = g.pa[row_at(x).slice + s];
+    nb = g.pb[bp + (int64_t)s * NR];
     nlen = g.klen[s];
   };
   auto open = [&](int kpos) __attribute__((always_inline)) {                             // the cursor enters the segment fetched last
+    if constexpr (SH::SPLIT) fetch(seg);
     krem = nlen - kpos;
     const int64_t last = (int64_t)((nlen - 1) / BK) * (BK * ES) + ak * ES;
     asafe = 0;
 #pragma unroll
     for (int x = 0; x < CA; ++x) {
-      const int64_t off = arow[x] * na[x].pitch;
+      const int64_t off = (int64_t)row_at(x).row * na[x].pitch;
       pa[x] = (gptr)na[x].ptr + (off + (int64_t)(kpos + ak) * ES);
       asafe |= (na[x].room - off - last >= 16 ? 1u : 0u) << x;
     }
     bpitch = nb.pitch;
     pb = (gptr)nb.ptr + ((int64_t)(kpos + bk) * bpitch + bcol);
-    bsafe = nb.room - (nlen - 1) * bpitch - bcol >= 16;
+    bsafe = nb.room - (int64_t)(nlen - 1) * bpitch - bcol >= 16;
     quick = !edge || __builtin_amdgcn_ballot_w64(bpitch < 16) == 0;
-    if (seg + 1 < S) fetch(seg + 1);
+    if (!SH::SPLIT && seg + 1 < S) fetch(seg + 1);
   };
   seg = start.seg;
-  fetch(seg);
+  if (!SH::SPLIT) fetch(seg);
   open(start.kpos);
   u32x4 ra[DEPTH][CA], rb[DEPTH][CB];                     // operands of DEPTH steps in flight
   int rk[DEPTH];                                          // elements of the segment left at those steps
@@ -460,28 +484,30 @@ __device__ __forceinline__ bool staged_gemm(const SmallArgs &g, char *lds, const
   };
 
   // ---- the K loop: step t is multiplied while the loads of the DEPTH steps after it travel -----------------
-  floatx16 acc[MI][NI];
+  floatx16 acc[MI][NI], small[SH::SPLIT ? MI : 1][SH::SPLIT ? NI : 1];   // SPLIT: sums of a1 b1; of the other products
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int e = 0; e < 16; ++e) {
+        acc[i][j][e] = 0.f;
+        if constexpr (SH::SPLIT) small[i][j][e] = 0.f;
+      }
   const int a_row = wm * (MI * 32) + (lane & 31), half = lane >> 5;
   auto multiply = [&](int stage) __attribute__((always_inline)) {
     const lds_ptr sa = lds3 + stage * SH::STAGE_BYTES, sb = sa + SH::PLANES * SH::A_PLANE;
     if constexpr (SH::SPLIT) {
-      // a b = a1 b1 + (a1 b2 + a2 b1) + (a2 b2 + a1 b3 + a3 b1), the small ones first; what is left out, a2 b3 and below,
-      // is 2^-23 of a product and less
+      // a b = a1 b1 + (a1 b2 + a2 b1 + a2 b2 + a1 b3 + a3 b1 + a2 b3 + a3 b2); what is left out, a3 b3, is 2^-32 of a product
+      // and less.  (Without a2 b3 and a3 b2, 2^-24 and less: a row of A with one element had errors of 0.95 units of 2^-24
+      // instead of 0.54 at the worst mantissas, for 15 % of the time.)  The products in brackets are summed up by themselves: next to
+      // the sum of a1 b1 they would be rounded to its last bit, and round it eight times in 16 k instead of twice.
       const int gr = lane >> 4, li = lane & 15;
 #pragma unroll
       for (int q = 0; q < BK / 16; ++q) {
-        bf16x8 fa[3][MI], fb[3][NI];
+        bf16x8 fb[3][NI];
 #pragma unroll
-        for (int p = 0; p < 3; ++p) {
-#pragma unroll
-          for (int i = 0; i < MI; ++i)
-            fa[p][i] = *(const __attribute__((address_space(3))) bf16x8 *)(sa + p * SH::A_PLANE + (a_row + i * 32) * SH::A_PITCH + q * 32 + half * 16);
+        for (int p = 0; p < 3; ++p)
 #pragma unroll
           for (int j = 0; j < NI; ++j) {
             union { short4_t h[2]; bf16x8 v; } u;
@@ -492,14 +518,23 @@ __device__ __forceinline__ bool staged_gemm(const SmallArgs &g, char *lds, const
                                    (wn * (NI * 32) + j * 32 + (gr & 1) * 16 + (li & 3) * 4) * 2));
             fb[p][j] = u.v;
           }
-        }
-        constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
-        for (int x = 0; x < 6; ++x)
+        for (int p = 0; p < 3; ++p) {
+          bf16x8 fa[MI];
 #pragma unroll
           for (int i = 0; i < MI; ++i)
+            fa[i] = *(const __attribute__((address_space(3))) bf16x8 *)(sa + p * SH::A_PLANE + (a_row + i * 32) * SH::A_PITCH + q * 32 + half * 16);
 #pragma unroll
-            for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[pa[x]][i], fb[pb[x]][j], acc[i][j], 0, 0, 0);
+          for (int x = 0; x < (p < 2 ? 3 : 2); ++x)
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+              for (int j = 0; j < NI; ++j) {
+                floatx16 &sum = p + x == 0 ? acc[i][j] : small[i][j];
+                sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[x][j], sum, 0, 0, 0);
+              }
+          DMM_SCHED_BARRIER;       // (no plane of A is read before the one before is used up: registers)
+        }
       }
     } else {
 #pragma unroll
@@ -534,6 +569,10 @@ __device__ __forceinline__ bool staged_gemm(const SmallArgs &g, char *lds, const
       __syncthreads();
       multiply(0);
     }
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) acc[i][j] = acc[i][j] + small[i][j];
     // infinities and NaN of the operands have made NaN of the sums
     unsigned bad = lost & 0xFFFFu;
 #pragma unroll

@@ -1,8 +1,8 @@
 """GPU parity of the kernel that takes fp32 operands apart into three bf16 each (tiles of 128 x 128), where its loop
 and its way out change form: K tails, rows shorter than a chunk, tiles across the cuts of C, K dealt to several
 workgroups.  Against the fp64 oracle (element bound of test_gpu_parity), and no further from it than sums of exact
-products in fp32, two terms at a time, as the fp32 matrix instructions take them; also where all terms have one sign,
-so that what the split leaves out adds up.
+products in fp32, two terms at a time; also where all terms have one sign, so that what the split leaves out adds up,
+and where a sum has so few terms that the error of a product shows.
 Tiles that cannot be split (infinities, NaN, values with bits below the smallest bf16) are multiplied in fp32."""
 import numpy as np
 import pytest
@@ -81,6 +81,42 @@ def test_values_that_cannot_be_split(dims, value):
     A64, B64 = A.astype(np.float64), B.astype(np.float64)
     ok_row, ok_col = (np.abs(A64) < 1e30).all(1), (np.abs(B64) < 1e30).all(0)
     _check(got[ok_row][:, ok_col], A64[ok_row] @ B64[:, ok_col], A64[ok_row], B64[:, ok_col], cfg, cfg["name"])
+
+
+# significands whose second and third parts are as large as they get: cut off after 8 bits, rounded to 8 bits
+CUT = [1 + 2.0 ** -7 - 2.0 ** -23, 1 + 2.0 ** -6 - 2.0 ** -22 - 2.0 ** -23]
+ROUNDED = [1 + 2.0 ** -8 - 2.0 ** -16 - 2.0 ** -17 + 2.0 ** -23, 1 + 2.0 ** -8 - 2.0 ** -23, 1 + 2.0 ** -8 + 2.0 ** -16 + 2.0 ** -17 - 2.0 ** -23]
+
+
+@pytest.mark.parametrize("values", [None, CUT, ROUNDED])
+@pytest.mark.parametrize("terms", [1, 2, 8])
+def test_few_terms(terms, values):
+    """Rows of A with so many elements that are not zero: products are as good as exact, so that a sum has an error of
+    2^-24 of it for every term.  (With more than one: what eight products of a step lose in being aligned to the largest of
+    them, 2^-23 of it each, on top.)  What is left out of a product is 2^-32 of it and less."""
+    cfg = dict(_problem(*SHAPES[0]), dtype="f32")
+    A, B = workloads.make_operands(cfg)
+    rng = np.random.default_rng(terms)
+    if values:
+        A, B = (np.copysign(rng.choice(np.array(values, np.float32), X.shape), X) for X in (A, B))
+    kept = np.zeros(A.shape, bool)
+    kept[np.arange(A.shape[0])[:, None], rng.permuted(np.tile(np.arange(A.shape[1]), (A.shape[0], 1)), axis=1)[:, :terms]] = True
+    A = np.ascontiguousarray(np.where(kept, A, 0).astype(np.float32))
+    got, _ = _pair(cfg, A, np.ascontiguousarray(B), 1)
+    A64, B64 = A.astype(np.float64), B.astype(np.float64)
+    ref = A64 @ B64
+    units = terms + (2 * (terms - 1) if terms > 1 else 0)
+    assert (np.abs(got - ref) <= units * 2.0 ** -24 * (1 + 2.0 ** -6) * (np.abs(A64) @ np.abs(B64))).all()
+
+
+def test_long_sums_of_one_sign():
+    """Operands of one sign and a long sum in one piece: nothing small is missing from it."""
+    dims = (4096, 4096, 4096, 4096, 4096, 4096, 4096)
+    cfg = dict(_problem(*dims), dtype="f32")
+    A, B = (np.abs(X) for X in workloads.make_operands(cfg))
+    got, want = _pair(cfg, A, B, 1)
+    ref = A.astype(np.float64) @ B.astype(np.float64)
+    assert np.linalg.norm(got - ref) <= np.linalg.norm(want - ref)
 
 
 @pytest.mark.parametrize("dims", [(1030, 2003, 2046, 668, 501, 515, 511), (1665, 1290, 1667, 129, 1290, 1665, 1667)])
