@@ -423,18 +423,21 @@ struct Uploader {
         return DMM_OK;
       }
     }
-    cur ^= 1;
-    if (ev_used[cur]) DMM_HIP(hipEventSynchronize(slab.ev[cur]));  // slot last used two uploads ago
-    std::memcpy(slab.pinned[cur], src, bytes);
+    const int next = cur ^ 1;
+    if (ev_used[next]) DMM_HIP(hipEventSynchronize(slab.ev[next]));  // slot last used two uploads ago
+    std::memcpy(slab.pinned[next], src, bytes);
     hipStream_t cs = nullptr;
     int rc = copy_stream(&cs);
     if (rc) return rc;
-    if ((rc = readers.order(cs))) return rc;
-    DMM_HIP(hipMemcpyAsync(slab.dev, slab.pinned[cur], bytes, hipMemcpyHostToDevice, cs));
-    DMM_HIP(hipEventRecord(slab.ev[cur], cs));
-    DMM_HIP(hipStreamWaitEvent(stream, slab.ev[cur], 0));
+    // (behind the readers, and behind a copy on a caller's stream whose call failed to use it: late, it would
+    // write the old table over this one)
+    if ((rc = readers.order(cs)) || (rc = order_behind_copy(cs))) return rc;
+    DMM_HIP(hipMemcpyAsync(slab.dev, slab.pinned[next], bytes, hipMemcpyHostToDevice, cs));
+    DMM_HIP(hipEventRecord(slab.ev[next], cs));
+    cur = next;                            // (only now: a call that fails above leaves the last copy known)
     ev_used[cur] = true;
     copied_on = StreamKey::of(cs);
+    DMM_HIP(hipStreamWaitEvent(stream, slab.ev[cur], 0));
     resident.assign((const char *)src, (const char *)src + bytes);
     return DMM_OK;
   }

@@ -20,7 +20,7 @@ struct Op {
   std::string name;             // kernel, "copy", "event"
   void *stream;
   uint64_t arg, bytes;          // kernel: first eight bytes of its first argument; copy: destination and size
-  uint64_t more[3] = {0, 0, 0}; // pack_kernel: its other arguments
+  uint64_t more[3] = {0, 0, 0}; // pack_kernel: its other arguments; copy: 1 if table_kernel makes it
   unsigned blocks = 0;
   std::vector<int> behind;
   int done_at = -1;             // known on the host to have finished before operation number done_at was enqueued
@@ -40,6 +40,7 @@ std::map<const void *, void *> symbols;
 std::map<void *, size_t> memory;
 size_t live = 0, limit = ~(size_t)0;
 int wait_in = -1;                                   // waits for an event until one reports an error and does not wait
+bool launches_fail = false;                         // of all kernels but table_kernel
 int fail_in = -1, fail_n = 0;                       // allocations until some fail, and how many do
 uint64_t next_at = 0;                               // where the next large allocation goes
 hipError_t last_error = hipSuccess;
@@ -128,6 +129,7 @@ void rec_fail_allocations(int in, int n) {
   fail_n = n;
 }
 void rec_fail_wait(int in) { wait_in = in; }
+void rec_fail_launches(int on) { launches_fail = on != 0; }
 int rec_failed() { return fail_in < 0; }
 
 // ---- the runtime ------------------------------------------------------------------------------------
@@ -160,6 +162,14 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipSt
 }
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, hipStream_t stream) {
   stream = real(stream);
+  if (kernels[f] == "table_kernel") {               // (table, where to, words): a copy on the caller's stream
+    void *to = *(void **)args[1];
+    const size_t bytes = 8 * (size_t)*(int *)args[2];
+    memcpy(to, args[0], bytes);
+    ops[(size_t)enqueue("copy", stream, (uint64_t)to, bytes)].more[0] = 1;
+    return hipSuccess;
+  }
+  if (launches_fail) return fail(hipErrorLaunchFailure);
   uint64_t first;
   memcpy(&first, args[0], sizeof first);
   Op &o = ops[(size_t)enqueue(kernels[f], stream, first, 0)];
@@ -170,6 +180,13 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, 
     memcpy(&o.more[2], args[3], 8);
   }
   return hipSuccess;
+}
+// (the event is recorded by the launch; in a capture the runtime refuses)
+hipError_t hipExtLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t stream, hipEvent_t before, hipEvent_t behind, int) {
+  if (before || streams[real(stream)].capturing) return fail(hipErrorStreamCaptureUnsupported);
+  const hipError_t e = hipLaunchKernel(f, grid, block, args, lds, stream);
+  if (behind && e == hipSuccess) events[behind] = streams[real(stream)].last;
+  return e;
 }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) {

@@ -47,14 +47,17 @@ class Recorder:
 
     def check_tables(self):
         """No table is overwritten under a kernel that reads it: a copy onto memory that the first
-        argument of an earlier launch lies in is ordered behind that launch, and a launch is ordered
-        behind the last copy onto the memory its first argument lies in."""
+        argument of an earlier launch lies in is ordered behind that launch and behind earlier copies onto
+        that memory, and a launch is ordered behind the last copy onto the memory its first argument lies in.
+        (Small tables are written by a kernel on the caller's stream: a copy here.)"""
         ops = self.ops()
         for i, name, _, at, size in ops:
             if name == "copy":
-                for j, other, _, arg, _ in ops[:i]:
+                for j, other, _, arg, n in ops[:i]:
                     if other not in ("copy", "event") and at <= arg < at + size:
                         assert self.before(j, i), f"copy {i} overwrites the table of {other} {j}"
+                    elif other == "copy" and at < arg + n and arg < at + size:
+                        assert self.before(j, i), f"copy {i} may be overwritten by the earlier copy {j}"
             elif name != "event":
                 copies = [j for j, other, _, to, n in ops[:i] if other == "copy" and to <= at < to + n]
                 if copies:
@@ -627,6 +630,35 @@ def copies_do_not_lie_across_a_4gb_line(rec):
         rec.so.rec_set_limit(2 ** 63)
 
 
+def _small_tables(rec, start=0):
+    """The tables that a kernel on the caller's stream wrote."""
+    return [o for o in rec.ops(start) if o[1] == "copy" and rec.so.rec_more(o[0], 0) == 1]
+
+
+def a_table_whose_call_failed_is_not_written_late(rec):
+    """A table is written on the caller's stream, then the call's launch fails.  The next call's table, copied on the
+    library's own stream (its caller's is being captured), comes behind it."""
+    p = Product(tuple(workloads.block_desc(256, 256, 2, 2) for _ in range(3)), 4, dtype="f32")
+    s, other = rec.stream(), rec.stream()
+    for i, streams in enumerate(((s, s), (s, other), (other, s))):
+        at = len(rec.ops())
+        rec.so.rec_fail_launches(1)
+        try:
+            p.run(p.args(where=3 * i), 0, streams[0])
+            raise AssertionError("the call did not fail")
+        except p.b.DmmError:
+            rec.so.rec_fail_launches(0)
+        assert len(_small_tables(rec, at)) == 1 and not rec.launches(at)
+        rec.so.rec_set_capturing(streams[1], 1)
+        p.run(p.args(where=3 * i + 1), 0, streams[1])
+        rec.so.rec_set_capturing(streams[1], 0)
+        assert len(_small_tables(rec, at)) == 1 and len(rec.launches(at)) == 1
+        rec.check_tables()
+        p.run(p.args(where=3 * i + 2), 0, streams[0])
+        assert len(_small_tables(rec, at)) == 2
+        rec.check_tables()
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
              more_streams_than_the_plan_remembers, reports_say_what_ran,
              the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call,
@@ -635,7 +667,7 @@ SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stre
              free_memory_does_not_show_in_the_cut,
              an_error_on_one_stream_leaves_the_others_waited_for,
              a_copy_whose_product_failed_is_waited_for, what_was_slower_stays_as_it_is,
-             copies_do_not_lie_across_a_4gb_line]
+             copies_do_not_lie_across_a_4gb_line, a_table_whose_call_failed_is_not_written_late]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
