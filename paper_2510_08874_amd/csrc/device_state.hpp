@@ -63,10 +63,15 @@ class Uses {
     DMM_HIP(hipEventRecord(e->ev, stream));
     return DMM_OK;
   }
-  // The event that the call's last launch on `stream` is to record; none while the stream is being captured: mark() then.
+  // The event that the call's last launch on `stream` is to record; none: mark() then.  That is while the stream is being
+  // captured, and for one call of 32 in any case: of a stream of launches that record events themselves the runtime
+  // keeps what it had for each until the host waits or an event is recorded behind them, and then works that off beside
+  // the caller.  (256^3 fp32, after 20000 calls without a wait: the first calls of new plans took 60 to 130 us instead of 25, and
+  // each of the 20000 8.2 us instead of 6.)  Every 8th, 32nd or 128th call made no difference.
   int claim(hipStream_t stream, hipEvent_t *ev) {
+    static std::atomic<unsigned> calls{0};
     *ev = nullptr;
-    if (is_capturing(stream)) return DMM_OK;
+    if (calls.fetch_add(1, std::memory_order_relaxed) % 32 == 31 || is_capturing(stream)) return DMM_OK;
     Entry *e = nullptr;
     const int rc = entry(stream, &e);
     if (!rc) *ev = e->ev;

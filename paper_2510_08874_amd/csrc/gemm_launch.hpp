@@ -14,7 +14,8 @@
 namespace dmm {
 
 // A launch with the event (none: nullptr) that is to stand for its end.  Recorded by the launch itself an event costs the
-// stream 0.2 us, by a call behind it 3 us.  True: it has been recorded; false: the runtime would not (it
+// stream 0.2 us, by a call behind it 3 us (a host that waits for each call pays for it: 19 us instead of 17 for 256^3 fp32,
+// 24 instead of 20 with a new plan).  True: it has been recorded; false: the runtime would not (it
 // refuses such launches without saying so in a capture, where no event is given), or no event was given; the kernel
 // has been launched, and the event is the caller's to record.  (launch_behind_only: nothing has been launched then.)
 template <class... P, class... A>

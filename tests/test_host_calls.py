@@ -659,6 +659,27 @@ def a_table_whose_call_failed_is_not_written_late(rec):
         rec.check_tables()
 
 
+def events_are_recorded_between_launches(rec):
+    """Launches record the events that stand for their calls; in a long row of calls, on a plan that is kept or on new ones,
+    an event is recorded by a call of its own now and then, so that the runtime lets go of the launches before."""
+    d = tuple(workloads.block_desc(256, 256, 2, 2) for _ in range(3))
+    s = rec.stream()
+    p = Product(d, 4, dtype="f32")
+    args = p.args()
+    for new in (False, True):
+        at = len(rec.ops())
+        for _ in range(256):
+            q = Product(d, 4, dtype="f32") if new else p
+            q.run(args, 0, s)
+        row = [o[1] for o in rec.ops(at) if o[2] == s and o[1] in ("event", "small_gemm_kernel")]
+        assert row.count("small_gemm_kernel") == 256 and row.count("event") <= 16
+        while "event" in row:
+            assert row.index("event") <= 64
+            row = row[row.index("event") + 1:]
+        assert len(row) <= 64
+    rec.check_tables()
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
              more_streams_than_the_plan_remembers, reports_say_what_ran,
              the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call,
@@ -667,7 +688,8 @@ SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stre
              free_memory_does_not_show_in_the_cut,
              an_error_on_one_stream_leaves_the_others_waited_for,
              a_copy_whose_product_failed_is_waited_for, what_was_slower_stays_as_it_is,
-             copies_do_not_lie_across_a_4gb_line, a_table_whose_call_failed_is_not_written_late]
+             copies_do_not_lie_across_a_4gb_line, a_table_whose_call_failed_is_not_written_late,
+             events_are_recorded_between_launches]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
