@@ -977,7 +977,7 @@ int build_small_exec(dmm_plan_t *P, const ExecArgs &x, const SmallPlan &sp, hipS
   l.o_mc = l.o_starts + (size_t)sp.runs * sizeof(SmallStart);
   l.o_nc = l.o_mc + (MR + 1) * 4;
   l.o_klen = l.o_nc + (NR + 1) * 4;
-  const size_t total = l.o_klen + S * 4;
+  const size_t total = (l.o_klen + S * 4 + 7) & ~(size_t)7;   // (whole words: table_kernel)
   std::vector<char> &h = P->dev->host;
   h.assign(total, 0);
   auto tiles = [&](size_t at, const std::vector<Extent> &v, const std::vector<int64_t> &cuts) {

@@ -680,6 +680,28 @@ def events_are_recorded_between_launches(rec):
     rec.check_tables()
 
 
+def small_tables_travel_with_a_kernel(rec):
+    """Tables of up to 3584 bytes, whatever the number of cuts in them; larger ones, and under capture all, are copied."""
+    block, s = workloads.block_desc, rec.stream()
+    sizes = set()
+    for descs, ranks, dtype in ((row_col(256, 256, 256, 4), 4, "f32"), (row_col(2048, 1024, 2048, 8), 8, "bf16"),
+                                (tuple(block(300, 300, 1, 1) for _ in range(3)), 1, "bf16"), (tuple(block(300, 300, 2, 2) for _ in range(3)), 4, "f32"),
+                                ((block(300, 700, 1, 7), block(700, 300, 5, 1), block(300, 300, 2, 3)), 7, "f32"),
+                                ((block(300, 6000, 1, 50), block(6000, 300, 40, 1), block(300, 300, 2, 3)), 50, "f32")):
+        for capture in (0, 1):
+            p, at = Product(descs, ranks, dtype=dtype), len(rec.ops())
+            rec.so.rec_set_capturing(s, capture)
+            p.run(p.args(where=1 + capture), 0, s)
+            rec.so.rec_set_capturing(s, 0)
+            assert p.plan.small_tile()
+            written = [o for o in rec.ops(at) if o[1] == "copy"]
+            assert len(written) == 1 and written[0][4] % 8 == 0
+            assert len(_small_tables(rec, at)) == (0 if capture else int(written[0][4] <= 3584))
+            sizes.add(written[0][4] <= 3584)
+            rec.check_tables()
+    assert sizes == {True, False}
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
              more_streams_than_the_plan_remembers, reports_say_what_ran,
              the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call,
@@ -689,7 +711,7 @@ SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stre
              an_error_on_one_stream_leaves_the_others_waited_for,
              a_copy_whose_product_failed_is_waited_for, what_was_slower_stays_as_it_is,
              copies_do_not_lie_across_a_4gb_line, a_table_whose_call_failed_is_not_written_late,
-             events_are_recorded_between_launches]
+             events_are_recorded_between_launches, small_tables_travel_with_a_kernel]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
