@@ -118,6 +118,40 @@ def check_m0_private(asm_path: str) -> None:
                 raise RuntimeError(f"{asm_path}:{ln}: `{t}`: the compiler uses M0, which the assembly statements overwrite")
 
 
+# kernel (part of its mangled name) -> accumulator registers a0 .. that its assembly statements own by name
+OWNED = {"grouped_gemm_kernel": 256, "grouped_gemm_comp_kernel": 256, "small_gemm_kernelINS_9RingShape": 64}
+
+
+def check_accumulators_private(asm_path: str) -> None:
+    """The macro-tile and ring kernels keep their partial sums in accumulator registers by name, which their
+    assembly statements declare as clobbered.  That keeps the compiler from holding a value of its own there across a
+    statement, but not from using one between two of them, where the partial sums are just as much alive: fail the build
+    where an instruction outside the assembly statements names a register that they own."""
+    inside, kernel, owned = False, "", 0
+    with open(asm_path) as f:
+        for ln, line in enumerate(f, 1):
+            t = line.strip()
+            m = re.match(r"(_Z\w+):", t)
+            if m:
+                kernel = m.group(1)
+                owned = max((n for k, n in OWNED.items() if k in kernel), default=0)
+                continue
+            if t.startswith(".Lfunc_end"):
+                owned = 0
+            if t.startswith(";;#ASMSTART"):
+                inside = True
+                continue
+            if t.startswith(";;#ASMEND"):
+                inside = False
+                continue
+            t = t.split(";")[0].strip()
+            if inside or not owned or not t or t.startswith(".") or t.endswith(":"):
+                continue
+            for one, first in re.findall(r"\ba(?:(\d+)\b|\[(\d+):\d+\])", t):
+                if int(one or first) < owned:
+                    raise RuntimeError(f"{asm_path}:{ln}: `{t}`: the compiler uses a partial sum of {kernel}")
+
+
 def _device_asm(name: str) -> str:
     for f in os.listdir(os.path.join(OUT, name)):
         if "-hip-amdgcn" in f and f.endswith(".s"):
@@ -154,6 +188,7 @@ def build(verbose: bool = False, extra=()) -> str:
             check_resources(err, want_kernel=src == "gemm_instance.hip" and name[-1] in "0123")
             check_wait_states(_device_asm(name))
             check_m0_private(_device_asm(name))
+            check_accumulators_private(_device_asm(name))
 
     try:
         while todo or running:

@@ -88,6 +88,39 @@ def test_compiler_use_of_m0_fails_the_build(tmp_path):
             build.check_m0_private(str(bad))
 
 
+RING = """
+_ZN3dmm17small_gemm_kernelINS_9RingShapeILi32ELi1ELi2ELi1ELi3ELi12288EEEEEvNS_9SmallArgsE:
+	v_accvgpr_write_b32 a64, v3
+	ds_write_b128 v2, a[64:67] offset:12288
+	;;#ASMSTART
+	v_mfma_f32_32x32x16_bf16 a[0:15], v[2:5], v[6:9], a[0:15]
+	;;#ASMEND
+	%s
+.Lfunc_end0:
+_ZN3dmm17small_gemm_kernelINS_10SmallShapeILi4ELi32EEEEEvNS_9SmallArgsE:
+	v_accvgpr_write_b32 a0, v3
+.Lfunc_end1:
+"""
+
+
+# (the ring kernels own a0 .. a63, the macro-tile kernels all of a0 .. a255)
+@pytest.mark.parametrize("line,in_ring,in_macro_tile", [
+    ("v_add_u32_e32 v5, s18, v5", True, True), ("v_accvgpr_read_b32 v33, a65", True, False), ("v_accvgpr_write_b32 a63, v3", False, False),
+    ("v_accvgpr_read_b32 v1, a5 ; Reload Reuse", False, False), ("global_load_dwordx4 a[60:63], v[2:3], off", False, False),
+    ("ds_write_b64 v2, a[62:65]", False, False)])
+def test_compiler_use_of_partial_sums_fails_the_build(tmp_path, line, in_ring, in_macro_tile):
+    p = tmp_path / "unit.s"
+    macro = RING.replace("small_gemm_kernelINS_9RingShape", "grouped_gemm_kernelILi2").replace("a64", "v64").replace("a[64:67]", "v[64:67]")
+    for text, ok in ((RING, in_ring), (macro, in_macro_tile)):
+        p.write_text(text % line)
+        if ok:
+            build.check_accumulators_private(str(p))
+        else:
+            with pytest.raises(RuntimeError) as e:
+                build.check_accumulators_private(str(p))
+            assert "unit.s:8:" in str(e.value)
+
+
 def test_resource_check_rejects_scratch_and_lost_accumulators():
     ok = ("remark: k.hpp:1:0: Function Name: _ZN3dmm19grouped_gemm_kernelILi2ELb0EEEv [-Rpass]\n"
           "remark: k.hpp:1:0:     VGPRs: 152 [-Rpass]\nremark: k.hpp:1:0:     AGPRs: 256 [-Rpass]\n"
