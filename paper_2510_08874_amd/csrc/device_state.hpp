@@ -64,13 +64,15 @@ class Uses {
     return DMM_OK;
   }
   // The event that the call's last launch on `stream` is to record; none: mark() then.  That is while the stream is being
-  // captured, and for one call of 32 in any case: of a stream of launches that record events themselves the runtime
+  // captured, on hipStreamPerThread and hipStreamLegacy (launches that record events are documented for streams and for
+  // the null stream only), and for one call of 32 in any case: of a stream of launches that record events themselves the runtime
   // keeps what it had for each until the host waits or an event is recorded behind them, and then works that off beside
   // the caller.  (256^3 fp32, after 20000 calls without a wait: the first calls of new plans took 60 to 130 us instead of 25, and
   // each of the 20000 8.2 us instead of 6.)  Every 8th, 32nd or 128th call made no difference.
   int claim(hipStream_t stream, hipEvent_t *ev) {
     static std::atomic<unsigned> calls{0};
     *ev = nullptr;
+    if (stream == hipStreamPerThread || stream == hipStreamLegacy) return DMM_OK;
     if (calls.fetch_add(1, std::memory_order_relaxed) % 32 == 31 || is_capturing(stream)) return DMM_OK;
     Entry *e = nullptr;
     const int rc = entry(stream, &e);
@@ -414,7 +416,7 @@ struct Uploader {
       return order_behind_copy(stream);
     }
     resident.clear();                      // unknown contents until the copy below has been enqueued
-    if (bytes <= sizeof(TableArg) && bytes % 8 == 0 && !is_capturing(stream)) {
+    if (bytes <= sizeof(TableArg) && bytes % 8 == 0 && stream != hipStreamPerThread && stream != hipStreamLegacy && !is_capturing(stream)) {
       // (behind the readers on other streams, and behind a copy that a call made and failed to use)
       int rc = readers.order(stream);
       if (rc || (rc = order_behind_copy(stream))) return rc;

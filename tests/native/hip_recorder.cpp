@@ -57,6 +57,7 @@ void *fresh() {
 
 hipStream_t real(hipStream_t s) {                   // hipStreamPerThread: a stream of the calling thread's own
   static thread_local hipStream_t mine = nullptr;
+  if (s == hipStreamLegacy) return nullptr;
   if (s != hipStreamPerThread) return s;
   if (!mine) mine = (hipStream_t)fresh();
   return mine;
@@ -183,6 +184,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, 
 }
 // (the event is recorded by the launch; in a capture the runtime refuses)
 hipError_t hipExtLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t stream, hipEvent_t before, hipEvent_t behind, int) {
+  if (stream == hipStreamPerThread || stream == hipStreamLegacy) abort();   // (not documented for these)
   if (before || streams[real(stream)].capturing) return fail(hipErrorStreamCaptureUnsupported);
   const hipError_t e = hipLaunchKernel(f, grid, block, args, lds, stream);
   if (behind && e == hipSuccess) events[behind] = streams[real(stream)].last;

@@ -702,6 +702,23 @@ def small_tables_travel_with_a_kernel(rec):
     assert sizes == {True, False}
 
 
+def handles_that_name_a_stream(rec):
+    """hipStreamLegacy and hipStreamPerThread: launches that record events are not made on these; the null stream and the
+    former are one."""
+    d = tuple(workloads.block_desc(256, 256, 2, 2) for _ in range(3))
+    long = (workloads.block_desc(1024, 16384, 8, 1), workloads.block_desc(16384, 1024, 1, 8), workloads.block_desc(1024, 1024, 4, 2))
+    for descs, ranks, dtype in ((d, 4, "f32"), (long, 8, "bf16")):
+        p = Product(descs, ranks, dtype=dtype)
+        for i, stream in enumerate((0, 1, 2, 0, rec.stream(), 2, 1)):
+            for _ in range(2):
+                at = len(rec.ops())
+                p.run(p.args(where=i % 3), 0, stream)
+                own = [o[1] for o in rec.ops(at) if o[2] == rec.ops()[-1][2]]
+                assert stream not in (1, 2) or own[-1] == "event"
+        rec.check_tables()
+        p.plan.destroy()
+
+
 SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stream, scratch_is_not_shared_by_calls_that_overlap,
              more_streams_than_the_plan_remembers, reports_say_what_ran,
              the_copies_hold_the_k_steps_of_the_operands, copies_do_not_show_in_the_bits, a_failed_allocation_costs_no_call,
@@ -711,7 +728,8 @@ SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stre
              an_error_on_one_stream_leaves_the_others_waited_for,
              a_copy_whose_product_failed_is_waited_for, what_was_slower_stays_as_it_is,
              copies_do_not_lie_across_a_4gb_line, a_table_whose_call_failed_is_not_written_late,
-             events_are_recorded_between_launches, small_tables_travel_with_a_kernel]
+             events_are_recorded_between_launches, small_tables_travel_with_a_kernel,
+             handles_that_name_a_stream]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
