@@ -217,6 +217,15 @@ hipError_t hipMalloc(void **p, size_t n) {
   if (at) next_at = 0;
   void *m = mmap(at, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE | (at ? MAP_FIXED_NOREPLACE : 0), -1, 0);
   if (m == MAP_FAILED) return fail(hipErrorOutOfMemory);
+  // (not across a multiple of 2^32 unless the test wants it there: where the system puts it changes from run to run)
+  const uint64_t line = (((uint64_t)m >> 32) + 1) << 32;
+  for (uint64_t up = 0; !at && n < (size_t)1 << 32 && (uint64_t)m + n > line && up < 16; ++up) {
+    void *other = mmap((void *)(line - ((up + 1) << 32)), n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE | MAP_FIXED_NOREPLACE, -1, 0);
+    if (other == MAP_FAILED) continue;
+    munmap(m, n);
+    m = other;
+    break;
+  }
   memory[*p = m] = n;
   live += n;
   return hipSuccess;
