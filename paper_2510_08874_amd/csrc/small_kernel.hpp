@@ -260,7 +260,7 @@ typedef SmallShape<4, 64, 64, 32, 2, 2, 1, 2, 4> SmallF32;
 // fp32 kernels', of single products the same (see multiply).
 typedef SmallShape<4, 128, 128, 32, 2, 2, 1, 1, 2, true> SmallF32Split;
 typedef SmallShape<4, 64, 128, 32, 2, 2, 1, 1, 2, false, 2> SmallF32Whole;   // for its tiles that cannot be split (all of them,
-                                        // 2048 x 4096 x 2048: 505 us instead of 243; in 128 rows at once registers spill)
+                                        // 2048 x 4096 x 2048: 519 us instead of 284; in 128 rows at once registers spill)
 
 // An fp32 value as the sum of three bf16: the nearest one, the nearest one to what is left, and the rest, which has no
 // more than 8 significant bits.  (To nearest, so that the second and third parts have either sign: cut off, all parts have

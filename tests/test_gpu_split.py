@@ -65,11 +65,11 @@ def test_split(dims, ldm):
         assert np.linalg.norm((got - ref)[rows, cols]) <= np.linalg.norm(chain - ref[rows, cols])
 
 
-@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3e38, 1e-37, 1.5e-45])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3e38, 3.4028235e38, 1e-37, 1.5e-45])
 @pytest.mark.parametrize("dims", SHAPES[:1] + SHAPES[2:4])
 def test_values_that_cannot_be_split(dims, value):
     """One such element in A and one in B: everything they do not reach as before, and what they reach as
-    the macro-tiles give it.  (3e38 can be split; its products overflow, or do not.)"""
+    the macro-tiles give it.  (3e38 can be split; its products overflow, or do not.  The largest value rounds to infinity.)"""
     cfg = dict(_problem(*dims), dtype="f32")
     A, B = workloads.make_operands(cfg)
     M, K, N = dims[:3]
