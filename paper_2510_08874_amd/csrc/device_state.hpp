@@ -403,7 +403,7 @@ struct Uploader {
       if (slab.dev) {
         if ((rc = readers.wait())) return rc;
         DMM_HIP(hipStreamSynchronize(stream));
-        pool().release(&slab);
+        release();
       }
       if ((rc = pool().acquire(bytes, &slab))) return rc;
       ev_used[0] = ev_used[1] = false;

@@ -659,6 +659,27 @@ def a_table_whose_call_failed_is_not_written_late(rec):
         rec.check_tables()
 
 
+def a_buffer_given_up_for_a_larger_one_is_not_written_late(rec):
+    """A table is copied, then the call's launch fails; the next call needs a larger buffer.  The plan that takes the
+    smaller one over writes its table behind that copy."""
+    block, s = workloads.block_desc, [rec.stream() for _ in range(3)]
+    p = Product((block(512, 1024, 16, 16), block(1024, 512, 1, 8), block(512, 512, 1, 8)), 256)
+    rec.so.rec_fail_launches(1)
+    try:
+        p.run(p.args(), 0, s[0])
+        raise AssertionError("the call did not fail")
+    except p.b.DmmError:
+        rec.so.rec_fail_launches(0)
+    late = rec.ops()[-2]
+    assert late[1] == "copy" and late[4] < 65536 and not _small_tables(rec) and not rec.launches()
+    p.run(p.args(), p.b.DMM_NO_MERGE, s[1])
+    assert max(o[4] for o in rec.ops() if o[1] == "copy") > 65536
+    q = Product(tuple(block(256, 256, 2, 2) for _ in range(3)), 4, dtype="f32")
+    q.run(q.args(), 0, s[2])
+    assert [o[3] for o in _small_tables(rec)] == [late[3]]       # the same buffer
+    rec.check_tables()
+
+
 def events_are_recorded_between_launches(rec):
     """Launches record the events that stand for their calls; in a long row of calls, on a plan that is kept or on new ones,
     an event is recorded by a call of its own now and then, so that the runtime lets go of the launches before."""
@@ -728,8 +749,8 @@ SCENARIOS = [dense_calls_and_others_on_two_streams, destroy_waits_for_every_stre
              an_error_on_one_stream_leaves_the_others_waited_for,
              a_copy_whose_product_failed_is_waited_for, what_was_slower_stays_as_it_is,
              copies_do_not_lie_across_a_4gb_line, a_table_whose_call_failed_is_not_written_late,
-             events_are_recorded_between_launches, small_tables_travel_with_a_kernel,
-             handles_that_name_a_stream]
+             a_buffer_given_up_for_a_larger_one_is_not_written_late, events_are_recorded_between_launches,
+             small_tables_travel_with_a_kernel, handles_that_name_a_stream]
 
 
 # ---- the tests ----------------------------------------------------------------------------------------
