@@ -901,7 +901,8 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
   // These kernels: rounds of `occ` workgroups per CU, operands at no more than 5.6 TB/s, and a second
   // launch that adds the partial tiles up.
   const double bytes = (double)x.es * ((double)M * K + (double)K * N) + (double)x.c_es * (double)M * N;
-  const double odd = std::max(cut_misaligned(A, c.kc), cut_misaligned(B, c.nc)) > 0.1 ? 1.25 : 1.0;
+  // (long K at odd places: 4985 x 9842 x 3072 in uneven tiles, packed, 440 with macro-tiles and 550 with these)
+  const double odd = std::max(cut_misaligned(A, c.kc), cut_misaligned(B, c.nc)) > 0.1 ? (K >= 7680 ? 1.6 : 1.25) : 1.0;
   for (int k = 0; k < SMALL_SHAPES; ++k) {
     const SmallKind &s = kSmall[k];
     if (s.es != (int)x.es) continue;
@@ -939,8 +940,13 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
       } else {
         t += segs / (double)runs + (k == SMALL_F32_SPLIT ? 5 : 0);
       }
-      t = 4 + std::max(t, s.es == 2 ? mem * std::max(1.0, 187.0 / (double)std::min<int64_t>(cus, tiles * runs)) : mem);
-      if (runs > 1) t += (x.es == 2 ? 3 : 4) + 2.0 * (double)part_bytes / 12e6;
+      // Operands from memory take as long as on the CU that loads most of them, where 200 CUs (160 that hold more, smaller
+      // workgroups) keep memory busy: 40 x 10240 x 11088 in 176 workgroups 40, in 264 54; 43 x 13723 x 16385 in 272 136, in
+      // 408 108; 32-row tiles, 2 x 3328 x 34716 in 272 41, in 816 49; 8 x 14848 x 16652 in 272 122, in 680 96.
+      const double share = (s.tm == 32 ? 160.0 : 200.0) * (double)per_cu / (double)(tiles * runs);
+      t = 4 + std::max(t, s.es == 2 ? mem * std::max(1.0, share) : mem);
+      // (a second launch: 640 x 384 x 832 uncut 10, in two runs 14; 8 x 2496 x 18432 17, 23)
+      if (runs > 1) t += (x.es == 2 ? 6 : 4) + 2.0 * (double)part_bytes / 12e6;
       if (t < least) {
         least = t;
         best->shape = k;

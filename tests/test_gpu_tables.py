@@ -53,7 +53,7 @@ def test_buffers_change_on_two_streams(dtype, dims):
     ("bf16", (300, 250, 260), (2, 2), False, False),
     ("f32", (130, 100, 140), (2, 2), False, False),
     ("bf16", (300, 20000, 260), (2, 2), False, True),     # partial tiles in a buffer that all calls share
-    ("bf16", (700, 500, 600), (3, 6), True, True),        # ... a table of 2224 bytes, written, and one of 8064, copied
+    ("bf16", (700, 900, 600), (3, 6), True, True),        # ... a table of 2232 bytes, written, and one of 8064, copied
 ])
 def test_calls_that_overlap_on_two_streams(dtype, dims, cuts, alternate, runs):
     """A few milliseconds of other work lie ahead on both streams while the calls are enqueued, none of them waited for."""

@@ -105,6 +105,12 @@ def row_col(m, k, n, p=8):
     return block(m, k, p, 1), block(k, n, 1, p), block(m, n, 4, p // 4)
 
 
+def uneven(m, k, n, seed):
+    cuts, desc = workloads.jittered_cuts, workloads.desc
+    return (desc(m, k, cuts(m, 3, seed), cuts(k, 5, seed + 1), 3, 5), desc(k, n, cuts(k, 7, seed + 2), [0, n], 7, 1),
+            desc(m, n, cuts(m, 5, seed + 3), cuts(n, 3, seed + 4), 5, 3))
+
+
 def dense_calls_and_others_on_two_streams(rec):
     """One plan, its calls alternating between operands that are copied first and operands that are not,
     on two streams: a call's copies must not be made before the product that reads the copies of an
@@ -613,6 +619,22 @@ def what_was_slower_stays_as_it_is(rec):
         p = Product((block(m, k, 1, 1, replication=8), block(k, n, 1, 8), block(m, n, 1, 8)), 8)
         p.run(p.args(), 0, rec.stream())
         assert p.plan.small_tile() in (None, (64, 128)), (m, k, n, p.plan.small_tile())
+    # operands from memory in little more than one workgroup per CU; a second launch that takes longer than it saves; long K
+    # at odd places in 128 x 128 tiles
+    for m, k, n in ((43, 13723, 16385), (40, 10240, 11088), (8, 14848, 16652), (112, 13312, 33360)):
+        p = Product((block(m, k, 1, 1, replication=8), block(k, n, 1, 8), block(m, n, 1, 8)), 8)
+        at = len(rec.ops())
+        p.run(p.args(), p.b.DMM_C_BF16, rec.stream())
+        if p.plan.small_tile():
+            wgs = max(rec.so.rec_blocks(o[0]) for o in rec.launches(at) if o[1] == "small_gemm_kernel")
+            assert not (256 < wgs < 340 or 512 < wgs < 600), (m, k, n, wgs)
+    for d in (tuple(block(r, c, 4, 2) for r, c in ((640, 384), (384, 832), (640, 832))), row_col(256, 896, 321)):
+        p = Product(d, 8)
+        p.run(p.args(), 0, rec.stream())
+        assert p.plan.small_tile() and p.plan.last_kernels().small_runs == 1, (d, p.plan.last_kernels().small_runs)
+    p = Product(uneven(4985, 9842, 3072, 286), 15)
+    p.run(p.args(False), 0, rec.stream())
+    assert p.plan.small_tile() is None
 
 
 def copies_do_not_lie_across_a_4gb_line(rec):
