@@ -212,7 +212,12 @@ const dmm_merged_item *dmm_plan_merged_items(const dmm_plan_t *p);
  * badly run on kernels for small products instead, and large bf16 products whose rows are
  * not 16-byte aligned or whose K is finely cut run on dense copies of A and B made in
  * the call, where an estimate finds that faster (DMM_NO_MERGE keeps the macro-tiles;
- * dmm_plan_last_kernels tells).  The shape, the element types and the device decide
+ * dmm_plan_last_kernels tells).  One of the former multiplies fp32 operands as three bf16 parts
+ * each, without loss: sums of many terms are rounded less than by fp32 matrix instructions,
+ * single products as much.  A tile of 128 x 128 elements of C that cannot be had so (an operand of
+ * its rows or columns, or a sum, that is infinite or not a number, bits below 2^-133) is
+ * multiplied in fp32, so which of the two roundings an element gets may depend on the operands of
+ * the other elements of its tile.  The shape, the element types and the device decide
  * how the sums are cut along K: the copies, which a call takes or not by where its
  * operands lie and by what memory is free, leave the bits of the result as they are,
  * and a small product without room for all of its partial sums takes its tiles in several

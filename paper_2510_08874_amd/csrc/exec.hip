@@ -941,8 +941,8 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
         t += segs / (double)runs + (k == SMALL_F32_SPLIT ? 5 : 0);
       }
       // Operands from memory take as long as on the CU that loads most of them, where 200 CUs (160 that hold more, smaller
-      // workgroups) keep memory busy: 40 x 10240 x 11088 in 176 workgroups 40, in 264 54; 43 x 13723 x 16385 in 272 136, in
-      // 408 108; 32-row tiles, 2 x 3328 x 34716 in 272 41, in 816 49; 8 x 14848 x 16652 in 272 122, in 680 96.
+      // workgroups) keep memory busy: 40 x 10240 x 11088 in 176 workgroups 40, in 264 54; 43 x 13723 x 16385 in 270 136, in
+      // 405 104; 32-row tiles, 2 x 3328 x 34716 in 272 41, in 816 49; 8 x 14848 x 16652 in 272 122, in 680 96.
       const double share = (s.tm == 32 ? 160.0 : 200.0) * (double)per_cu / (double)(tiles * runs);
       t = 4 + std::max(t, s.es == 2 ? mem * std::max(1.0, share) : mem);
       // (a second launch: 640 x 384 x 832 uncut 10, in two runs 14; 8 x 2496 x 18432 17, 23)

@@ -16,8 +16,9 @@
 // to its place when it has landed.  (Loaded element by element, as rows shorter than a chunk still are, a tail cost 2.6 us.)
 //
 // Measured, kernel us, register-staged loop -> this one: 2048^3 38 -> 27 (a step 0.9 -> 0.5, of which the loads alone,
-// 45 bytes per CU and cycle from L2, take 0.4), 1024 x 16384 x 1024 in eight runs 49 -> 38; us per call 1536^3 30 -> 23,
-// 17 x 11429 x 13568 80 -> 61, 21 x 10368 x 31384 135 -> 109 (6.0 TB/s), 32 x 12288 x 49152 227 either way (5.4 TB/s).
+// 45 bytes per CU and cycle from L2, take 0.4), 1024 x 16384 x 1024 with the sum of its runs 59 (eight of them) -> 47 (four);
+// us per call 1536^3 29 -> 18, 17 x 11429 x 13568 77 -> 60, 21 x 10368 x 31384 134 -> 106 (6.1 TB/s), 32 x 12288 x 49152 226
+// either way (5.4 TB/s).
 #pragma once
 
 #include "small_kernel.hpp"

@@ -254,13 +254,13 @@ typedef SmallShape<4, 64, 64, 32, 2, 2, 1, 2, 4> SmallF32;
 // What bounds the fp32 shapes is the fp32 matrix instruction, 64 cycles for 2 k of 32 x 32.  Taken as three bf16 each
 // (exactly), eight bf16 products of 32 cycles do 16 k: 256 cycles instead of 512.  A 128 x 128 x 32 step is 2048 cycles
 // of the matrix pipes and some 1200 of taking apart and LDS writes, which the CU's other workgroup fills with its
-// matrix instructions: hence one LDS stage (60 KB; 68 KB with the finished tile), twice per CU.  Measured, us per call, the
+// matrix instructions (busy 54 % of the time): hence one LDS stage (60 KB; 68 KB with the finished tile), twice per CU.  Measured, us per call, the
 // other fp32 kernels -> this one: 4096^3 950 (macro-tiles, 145 TFLOP/s) -> 860 (160); 2048^3 177 -> 127; 2501 x 1999 x 1777
 // uneven 219 -> 172; 5612 x 1584 x 3264 597 -> 467.  Error against 64 bits: of sums of many terms 0.2 to 0.5 of the
 // fp32 kernels', of single products the same (see multiply).
 typedef SmallShape<4, 128, 128, 32, 2, 2, 1, 1, 2, true> SmallF32Split;
 typedef SmallShape<4, 64, 128, 32, 2, 2, 1, 1, 2, false, 2> SmallF32Whole;   // for its tiles that cannot be split (all of them,
-                                        // 2048 x 4096 x 2048: 519 us instead of 284; in 128 rows at once registers spill)
+                                        // 2048 x 4096 x 2048: 503 us instead of 230; in 128 rows at once registers spill)
 
 // An fp32 value as the sum of three bf16: the nearest one, the nearest one to what is left, and the rest, which has no
 // more than 8 significant bits.  (To nearest, so that the second and third parts have either sign: cut off, all parts have
