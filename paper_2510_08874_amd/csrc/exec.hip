@@ -898,8 +898,8 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
     if (big_runs > 1) least += 4 + 2.0 * (double)(tail * big_runs) * sizeof(float) * BM * BN / 12e6;
   }
   least *= x.es == 2 ? 0.93 : 0.97;                                            // (not for a tie)
-  // These kernels: rounds of `occ` workgroups per CU, operands at no more than 5.6 TB/s, and a second
-  // launch that adds the partial tiles up.
+  // These kernels: rounds of `occ` workgroups per CU, operands at no more than 5.6 TB/s (7.5 from the last-level cache:
+  // 82 x 2944 x 33024 in 264 workgroups 42, in 792 and their sum 56), and a second launch that adds the partial tiles up.
   const double bytes = (double)x.es * ((double)M * K + (double)K * N) + (double)x.c_es * (double)M * N;
   // (long K at odd places: 4985 x 9842 x 3072 in uneven tiles, packed, 440 with macro-tiles and 550 with these)
   const double odd = std::max(cut_misaligned(A, c.kc), cut_misaligned(B, c.nc)) > 0.1 ? (K >= 7680 ? 1.6 : 1.25) : 1.0;
@@ -914,7 +914,7 @@ void choose_small(dmm_plan_t *P, const ExecArgs &x, int cus, SmallPlan *best) {
     // B comes again for every tile row but the first: from memory (64 x 6615 x 45440 in 32 x 128 tiles 187 us, in
     // 64 x 128 tiles 161), or, where the last-level cache holds it, from there.
     const double b_bytes = (double)x.es * (double)K * N;
-    const double mem = bytes / 5.6e6 + (double)(c.rows.size() - 1) * b_bytes / (b_bytes > 128e6 ? 6.5e6 : 14e6);
+    const double mem = bytes / (x.es == 2 && bytes < 256e6 ? 7.5e6 : 5.6e6) + (double)(c.rows.size() - 1) * b_bytes / (b_bytes > 128e6 ? 6.5e6 : 14e6);
     // Rounding grows with the root of the number of terms in a chain of sums.  The split kernel rounds once where the others
     // round eight times: over drawn products it has 0.3 times their error (median; normal and uniform operands), and with at
     // least 0.15 times as many chains as there would be otherwise never more than it (0.91 at most, operands of one sign).

@@ -632,6 +632,9 @@ def what_was_slower_stays_as_it_is(rec):
         p = Product(d, 8)
         p.run(p.args(), 0, rec.stream())
         assert p.plan.small_tile() and p.plan.last_kernels().small_runs == 1, (d, p.plan.last_kernels().small_runs)
+    p = Product((block(82, 2944, 1, 1, replication=8), block(2944, 33024, 1, 8), block(82, 33024, 1, 8)), 8)
+    p.run(p.args(), p.b.DMM_C_BF16, rec.stream())
+    assert p.plan.small_tile() == (128, 128) and p.plan.last_kernels().small_runs == 1      # (B fits the last-level cache)
     p = Product(uneven(4985, 9842, 3072, 286), 15)
     p.run(p.args(False), 0, rec.stream())
     assert p.plan.small_tile() is None
